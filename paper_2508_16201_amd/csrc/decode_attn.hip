@@ -81,6 +81,7 @@ struct AttnParams {
     int rows_pad;            // rows per partial slot: n_rgroups * (row blocks per workgroup) * 16
     int n_rgroups;           // groups of at most 4 row blocks that share a (head, split): one workgroup each
     int n_work;
+    int n_main;              // attn_short_kernel without splits: workgroups that compute (the rest prefetch)
     const uint64_t* block_mask;  // [sum q_len] tree masks of the block's queries, or null (chain)
     int balanced;            // batch mode: balanced pieces (see attn_balance) instead of uniform splits
     int max_wg;              // workgroups launched in balanced mode
@@ -783,6 +784,237 @@ void attn_merge_rows_kernel(const AttnParams p)
         p.lse[(int64_t)(q0 + t) * p.n_q_heads + h] = (m + fast_log2(l)) * kLn2;
 }
 
+// Short key ranges (bound: launches and round trips).  No ring and no barrier in the sweep: every wave owns 32 * CH
+// keys of the workgroup's range and issues all its loads before it waits for the first.  K and V come through
+// registers (the bytes in flight are then not bound by the LDS) into a private LDS buffer, one 32-key chunk at a
+// time, and from there in operand layout: loaded in that layout directly a quad of lanes would touch four cache
+// lines, and the address path takes one line a cycle (10.3 against 7.6 us at 1511 keys).  All logits of a wave are
+// there before its maximum is taken, so nothing is rescaled; the waves meet once, at the end.
+//   COLS < D: a workgroup computes a slice of 16 VALUE COLUMNS over ALL keys of its rows and writes output.  The
+//     slices recompute the logits, and in return there are no partial results and no merge launch, which costs
+//     2.8 us behind a first kernel of 3.6.  Every workgroup pulls all of K and the cache lines of V through one CU,
+//     so this is for short caches only: attn_direct_chunks has the line and both sides' times.
+//   COLS = D: a workgroup computes a key split and writes a partial result for attn_merge_kernel (head size 64,
+//     one block of query rows: 7.15 -> 6.8 us at 1537 to 2000 keys against the ring kernel; at head size 128 the two
+//     are equal).
+//
+// Helper workgroups.  The few workgroups that compute bring in about 100 bytes/ns each, bound by their CU's
+// outstanding misses; helpers on the same XCD touch the head's rows at the same time, so that most of those misses
+// find the line in that XCD's L2 already (7.4 -> 6.3 us at 1511 keys of head size 64, 9.0 -> 7.4 us at 1024 keys of
+// head size 128; the caches of 80 to 120 layers in turn, so that they come from beyond the L2).
+template <int D, int THREADS>
+__device__ __forceinline__ void attn_prefetch_rows(const AttnParams& p, int id)
+{
+    // ids are dealt to the XCDs round-robin: helper `id` shares the XCD of workgroup id % kNumXcd and reads a share of
+    // that workgroup's head (with fewer workgroups than XCDs some XCDs compute nothing)
+    const int x = id % kNumXcd, n_help = (p.n_work - p.n_main) / kNumXcd, k = (id - p.n_main) / kNumXcd;
+    if (x >= p.n_main) return;
+    int kv0 = 0, kvl = p.kv_len;
+    if (p.cu_kv) { kv0 = p.cu_kv[0]; kvl = p.cu_kv[1] - kv0; }
+    const int g = x % p.n_kv_heads;
+    const int per = (kvl + n_help - 1) / n_help;
+    const int first = k * per, n = (min(kvl, first + per) - first) * (D / 8);
+    u32x4 acc = {0u, 0u, 0u, 0u};
+    for (int i = threadIdx.x; i < n; i += THREADS) {
+        const int64_t off = (int64_t)(kv0 + first + i / (D / 8)) * p.kv_tok + (int64_t)g * p.kv_head + (i % (D / 8)) * 8;
+        acc ^= *reinterpret_cast<const u32x4*>(p.k + off) ^ *reinterpret_cast<const u32x4*>(p.v + off);
+    }
+    __asm__ volatile("" :: "v"(acc));
+}
+
+template <int D, int NW, int CH, int COLS>
+__global__ __launch_bounds__(NW * kWave)
+void attn_short_kernel(const AttnParams p)
+{
+    constexpr bool DIRECT = COLS < D;
+    constexpr int KK = D / 32;                       // MFMA steps over the head dimension
+    constexpr int SLICES = D / COLS;
+    constexpr int DJ = COLS / 16;
+    constexpr int WAVE_KEYS = CH * kChunkKeys;
+    constexpr int KP = D / 8, VP = COLS / 8;         // 16-byte pieces per key row and per row of the value slice
+    constexpr int KPL = kWave / KP, VPL = kWave / VP;   // rows that one wave-wide load covers
+    constexpr int KL = kChunkKeys / KPL, VL = kChunkKeys / VPL;   // loads per chunk
+    constexpr int K_BYTES = kChunkKeys * D * 2;
+    constexpr int WAVE_LDS = K_BYTES + kChunkKeys * COLS * 2;
+    static_assert(16 * COLS * 4 <= WAVE_LDS, "a wave's result takes the place of its buffers");
+    // LDS: a private part per wave (its [row][column] fp32 result afterwards), then the waves' maxima and sums
+    extern __shared__ __align__(16) unsigned char smem[];
+    float (*s_m)[16] = reinterpret_cast<float (*)[16]>(smem + NW * WAVE_LDS);
+    float (*s_l)[16] = s_m + NW;
+
+    if (DIRECT && (int)blockIdx.x >= p.n_main) { attn_prefetch_rows<D, NW * kWave>(p, blockIdx.x); return; }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    // kv heads fastest, as in the split kernel: with 8 kv heads a head's workgroups share an XCD and its L2
+    const int g = blockIdx.x % p.n_kv_heads, rest = blockIdx.x / p.n_kv_heads;
+    const int part = rest % (DIRECT ? SLICES : p.num_splits);            // column slice or key split
+    const int rest2 = rest / (DIRECT ? SLICES : p.num_splits);
+    const int rb = rest2 % p.n_rgroups, b = rest2 / p.n_rgroups;         // block of 16 query rows, request
+    int q0 = 0, ql = p.q_len, kv0 = 0, kvl = p.kv_len;
+    if (p.cu_q) { q0 = p.cu_q[b]; ql = p.cu_q[b + 1] - q0; kv0 = p.cu_kv[b]; kvl = p.cu_kv[b + 1] - kv0; }
+    const int n_rows = p.group * ql;
+    if (ql <= 0 || kvl < ql || rb * 16 >= n_rows) return;
+    const int k_begin = DIRECT ? 0 : part * p.split_keys;
+    const int k_end = DIRECT ? kvl : min(kvl, k_begin + p.split_keys);
+    if (k_begin >= kvl) return;                      // (the merge reads only the live splits)
+
+    const int row = rb * 16 + r;
+    const bool live = row < n_rows;                  // padding rows read row 0: finite, never stored
+    const int t = live ? row / p.group : 0, h = g * p.group + (live ? row % p.group : 0);
+    const int k_wave = k_begin + wave * WAVE_KEYS;   // this wave's first key
+    const char* kbase = reinterpret_cast<const char*>(p.k + (int64_t)kv0 * p.kv_tok + (int64_t)g * p.kv_head);
+    const char* vbase = reinterpret_cast<const char*>(p.v + (int64_t)kv0 * p.kv_tok + (int64_t)g * p.kv_head +
+                                                      (DIRECT ? part * COLS : 0));
+    const uint32_t tok_bytes = (uint32_t)p.kv_tok * 2u;
+    unsigned char* const k_lds = smem + wave * WAVE_LDS;
+    unsigned char* const v_lds = k_lds + K_BYTES;
+
+    float m = -INFINITY, l = 0.f;
+    floatx4 o_acc[DJ];
+#pragma unroll
+    for (int j = 0; j < DJ; ++j) o_acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (k_wave < k_end) {
+        bf16x8 qf[KK];
+        u32x4 kraw[CH][KL], vraw[CH][VL];
+        const __bf16* qp = p.q + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + c * 8;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 32);
+        // (keys past the end are masked below: the last key is read again)
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+#pragma unroll
+            for (int n = 0; n < KL; ++n) {
+                const uint32_t key = (uint32_t)min(k_wave + ch * kChunkKeys + n * KPL + lane / KP, k_end - 1);
+                kraw[ch][n] = *reinterpret_cast<const u32x4*>(kbase + (key * tok_bytes + (uint32_t)(lane % KP) * 16u));
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+#pragma unroll
+            for (int n = 0; n < VL; ++n) {
+                const uint32_t key = (uint32_t)min(k_wave + ch * kChunkKeys + n * VPL + lane / VP, k_end - 1);
+                vraw[ch][n] = *reinterpret_cast<const u32x4*>(vbase + (key * tok_bytes + (uint32_t)(lane % VP) * 16u));
+            }
+        }
+        // ---- logits of all keys of the wave (S^T = K Q^T, as in the split kernel) ----
+        const float sc = fmaxf(p.scale_log2, 1e-30f);      // (see attn_split_kernel)
+        float s[CH][8];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            // (LDS executes a wave's accesses in order: the buffer is rewritten behind the reads of the last chunk)
+#pragma unroll
+            for (int n = 0; n < KL; ++n) {
+                const int kl = n * KPL + lane / KP;
+                const int swz = (D == 128) ? (kl & 15) : ((kl >> 1) & 7);
+                *reinterpret_cast<u32x4*>(k_lds + kl * (D * 2) + (((lane % KP) ^ swz) * 16)) = kraw[ch][n];
+            }
+            floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const int x = kk * 4 + c;
+                const int sw = (D == 128) ? (r & 15) : ((r >> 1) & 7);      // (the same for row r + 16)
+                const u32x4 k0 = *reinterpret_cast<const u32x4*>(k_lds + r * (D * 2) + ((x ^ sw) * 16));
+                const u32x4 k1 = *reinterpret_cast<const u32x4*>(k_lds + (r + 16) * (D * 2) + ((x ^ sw) * 16));
+                s0 = mfma16(__builtin_bit_cast(bf16x8, k0), qf[kk], s0);
+                s1 = mfma16(__builtin_bit_cast(bf16x8, k1), qf[kk], s1);
+            }
+            const int base = k_wave + ch * kChunkKeys;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s[ch][i] = s0[i]; s[ch][4 + i] = s1[i]; }
+            if (base + kChunkKeys > k_end || base + kChunkKeys > kvl - ql) {
+                const uint64_t row_mask = p.block_mask ? p.block_mask[q0 + t] : ((2ull << t) - 1ull);
+                const uint32_t mask_lo = (uint32_t)row_mask, mask_hi = (uint32_t)(row_mask >> 32);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int key = base + (i < 4 ? 4 * c + i : 16 + 4 * c + (i - 4));
+                    const int bk = key - (kvl - ql);
+                    const uint32_t word = (bk & 32) ? mask_hi : mask_lo;
+                    const bool in_block_hidden = bk >= 0 && ((word >> (bk & 31)) & 1u) == 0u;
+                    s[ch][i] = (key >= k_end || in_block_hidden) ? -INFINITY : s[ch][i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mx = fmaxf(mx, s[ch][i]);
+        }
+        m = quad_max(mx) * sc;
+        const float m_ref = (m == -INFINITY) ? 0.f : m;
+        bf16x8 pf[CH];
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            floatx8 pv;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { pv[i] = fast_exp2(fmaf(s[ch][i], sc, -m_ref)); l += pv[i]; }
+            pf[ch] = __builtin_convertvector(pv, bf16x8);
+        }
+        l = quad_sum(l);
+        // ---- O^T = V^T P^T ----
+        const int vk = 4 * c + (r >> 2);                             // (the second half of a chunk is 16 rows on)
+        const int pair_swz = DIRECT ? 0 : v_swizzle<D>(vk) >> 1;     // a 16-column slice needs none: 8 rows are 256 bytes
+        const uint32_t v_addr = (uint32_t)(uintptr_t)(SPECVLM_AS3 const void*)(v_lds + vk * (COLS * 2) + (r & 3) * 8);
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+#pragma unroll
+            for (int n = 0; n < VL; ++n) {
+                const int kl = n * VPL + lane / VP;
+                const int swz = DIRECT ? 0 : v_swizzle<D>(kl);
+                *reinterpret_cast<u32x4*>(v_lds + kl * (COLS * 2) + (((lane % VP) ^ swz) * 16)) = vraw[ch][n];
+            }
+            __asm__ volatile("" ::: "memory");
+            u32x2 lo[DJ], hi[DJ];
+#pragma unroll
+            for (int j = 0; j < DJ; ++j) {
+                const uint32_t src = v_addr + (uint32_t)((j ^ pair_swz) * 32);
+                lo[j] = lds_read_tr16<0>(src);
+                hi[j] = lds_read_tr16<16 * COLS * 2>(src);
+            }
+            __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < DJ; ++j) {
+                __asm__ volatile("" : "+v"(lo[j]), "+v"(hi[j]));     // (their uses stay behind the wait)
+                o_acc[j] = mfma16(__builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[j], hi[j], 0, 1, 2, 3)), pf[ch], o_acc[j]);
+            }
+        }
+    }
+    // ---- the waves meet: lane (r, c) holds columns 16j + 4c .. 16j + 4c + 3 of row r ----
+    // 16-byte piece q of a row goes to place q ^ r: the 16 rows of a store or a load fall on different banks
+    constexpr int PIECES = COLS / 4;
+#pragma unroll
+    for (int j = 0; j < DJ; ++j)
+        reinterpret_cast<floatx4*>(k_lds)[r * PIECES + ((4 * j + c) ^ (r & (PIECES - 1)))] = o_acc[j];
+    if (c == 0) { s_m[wave][r] = m; s_l[wave][r] = l; }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * PIECES; e += NW * kWave) {
+        const int orow = e / PIECES, piece = e % PIECES, grow = rb * 16 + orow;
+        if (grow >= n_rows) continue;
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][orow]);
+        const float ref = (m_all == -INFINITY) ? 0.f : m_all;
+        floatx4 tot = {0.f, 0.f, 0.f, 0.f};
+        float l_all = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = fast_exp2(s_m[w][orow] - ref);           // 0 for a wave without keys
+            tot += f * reinterpret_cast<const floatx4*>(smem + w * WAVE_LDS)[orow * PIECES + (piece ^ (orow & (PIECES - 1)))];
+            l_all += f * s_l[w][orow];
+        }
+        if (DIRECT) {
+            const int to = grow / p.group, ho = g * p.group + grow % p.group;
+            tot *= 1.f / l_all;
+            *reinterpret_cast<bf16x4*>(p.out + (int64_t)(q0 + to) * p.q_tok + (int64_t)ho * p.q_head + part * COLS + 4 * piece) =
+                __builtin_convertvector(tot, bf16x4);
+            if (p.lse && part == 0 && piece == 0)
+                p.lse[(int64_t)(q0 + to) * p.n_q_heads + ho] = (m_all + fast_log2(l_all)) * kLn2;
+        } else {
+            const int64_t slot = ((int64_t)(b * p.n_kv_heads + g) * p.num_splits + part) * p.rows_pad + grow;
+            *reinterpret_cast<bf16x4*>(p.part_o + slot * D + 4 * piece) = __builtin_convertvector(tot, bf16x4);
+            if (piece == 0) { p.part_ml[slot * 2] = m_all; p.part_ml[slot * 2 + 1] = l_all; }
+        }
+    }
+}
+
 // ---------------------------------------------------------------- host side ----
 // A batch whose split count is left to the library is cut into balanced pieces by the kernels
 // themselves (they know the request lengths; the host only knows their maximum).
@@ -798,6 +1030,22 @@ static void attn_row_groups(int rows, int* n_groups, int* mb)
     const int blocks = (rows + 15) / 16;
     *n_groups = (blocks + 3) / 4;
     *mb = (blocks + *n_groups - 1) / *n_groups;
+}
+
+// Launch shapes of attn_short_kernel.  Chunks per wave of a launch without splits; 0: the shape takes splits.
+// Where the line lies (us a layer, splits and merge against this, one to four row blocks per kv head, caches of 40 to
+// 160 layers in turn):  head size 64:  512 keys 6.5-7.9 / 3.9-4.3, 1024: 6.7-8.0 / 5.0-5.4, 1536: 6.7-8.1 / 6.1-6.5,
+// 1790: 6.9-8.3 / 6.7-7.1;  head size 128:  512 keys 7.5-9.6 / 5.1-5.9, 1024: 7.7-9.6 / 7.1-8.7, 1280: 7.7-9.8 / 8.0-10.1.
+// More workgroups than CUs would take a second round.
+constexpr int kDirectWaves = 8, kShortWaves = 4;
+constexpr int kPrefetchers = 15;       // helper workgroups per XCD, at most (1511 keys: 7: 6.5 us, 15: 6.3, 28: 6.4)
+static int attn_direct_chunks(int batch, int kv_len, int n_kv_heads, int head_dim, int rows, int num_splits)
+{
+    if (num_splits != 0) return 0;                            // (a caller that names a split count gets it)
+    const int64_t wgs = (int64_t)batch * n_kv_heads * ((rows + 15) / 16) * (head_dim / 16);
+    if (wgs > kNumCu) return 0;
+    const int ch = (kv_len + kDirectWaves * kChunkKeys - 1) / (kDirectWaves * kChunkKeys);
+    return ch <= (head_dim == 64 ? 6 : 4) ? ch : 0;
 }
 
 static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, int num_splits)
@@ -859,6 +1107,47 @@ static int launch_attn_s(const AttnParams& p, hipStream_t stream)
     return launch_status();
 }
 
+template <int D, int NW, int CH, int COLS>
+static int launch_short(const AttnParams& p, hipStream_t stream)
+{
+    constexpr size_t lds = (size_t)NW * (kChunkKeys * (D + COLS) * 2 + 2 * 16 * sizeof(float));
+    if (lds > 64 * 1024) {
+        static std::atomic<bool> raised[kMaxDevices];
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
+        if (!raised[dev].load(std::memory_order_acquire)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_short_kernel<D, NW, CH, COLS>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                return SPECVLM_ELAUNCH;
+            raised[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL((attn_short_kernel<D, NW, CH, COLS>), dim3(p.n_work), dim3(NW * kWave), lds, stream, p);
+    return launch_status();
+}
+
+static int launch_attn_direct(const AttnParams& p, int head_dim, int chunks, hipStream_t stream)
+{
+    if (head_dim == 64) {
+        switch (chunks) {
+            case 1: return launch_short<64, kDirectWaves, 1, 16>(p, stream);
+            case 2: return launch_short<64, kDirectWaves, 2, 16>(p, stream);
+            case 3: return launch_short<64, kDirectWaves, 3, 16>(p, stream);
+            case 4: return launch_short<64, kDirectWaves, 4, 16>(p, stream);
+            case 5: return launch_short<64, kDirectWaves, 5, 16>(p, stream);
+            case 6: return launch_short<64, kDirectWaves, 6, 16>(p, stream);
+        }
+    } else {
+        switch (chunks) {
+            case 1: return launch_short<128, kDirectWaves, 1, 16>(p, stream);
+            case 2: return launch_short<128, kDirectWaves, 2, 16>(p, stream);
+            case 3: return launch_short<128, kDirectWaves, 3, 16>(p, stream);
+            case 4: return launch_short<128, kDirectWaves, 4, 16>(p, stream);
+        }
+    }
+    return SPECVLM_EUNSUPPORTED;
+}
+
 // From this size per launch on, the cache is streamed with non-temporal loads: its lines would
 // only push the split partials (which the merge re-reads) and other reusable data out of the L2.
 // Smaller caches (a draft's pruned cache, re-read at every decode step) stay cacheable.
@@ -881,7 +1170,11 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
     // computing): on the draft's small cache the four extra waves cost more at workgroup start-up than
     // they save (6.7 against 6.4 us per layer).
     switch (mb) {
-        case 1: return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
+        case 1:
+            // (one chunk of 32 keys for each of four waves, results for the merge; longer splits need the ring, and a
+            // single split writes output instead of a partial result)
+            if (D == 64 && p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced) return launch_short<D, kShortWaves, 1, D>(p, stream);
+            return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
         case 2: return launch_attn<D, 2, 2, 64, 3, 4>(p, stream);
         case 3: return launch_attn<D, 3, 2, 64, 3, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)
         case 4: return launch_attn<D, 4, 2, 64, 3, 4>(p, stream);
@@ -902,6 +1195,7 @@ extern "C" size_t specvlm_decode_attn_workspace_bytes(int batch, int q_len, int 
         return 0;
     const int rows = (n_q_heads / n_kv_heads) * q_len;
     if (q_len > kMaxQueryBlock) return 0;
+    if (attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) return 256;
     int n_rgroups, mb;
     attn_row_groups(rows, &n_rgroups, &mb);
     const int rows_pad = n_rgroups * mb * 16;
@@ -956,6 +1250,13 @@ static int attn_impl(
     p.batch = batch; p.q_len = q_len; p.kv_len = kv_len;
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.group = group;
     p.scale_log2 = softmax_scale * kLog2e;
+    if (const int chunks = attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) {
+        p.n_rgroups = (rows + 15) / 16;
+        p.n_main = batch * n_kv_heads * p.n_rgroups * (head_dim / 16);
+        const int pieces = (kv_len * (head_dim / 8) + kDirectWaves * kWave - 1) / (kDirectWaves * kWave);
+        p.n_work = p.n_main + (batch == 1 ? kNumXcd * (pieces < kPrefetchers ? pieces : kPrefetchers) : 0);
+        return launch_attn_direct(p, head_dim, chunks, (hipStream_t)stream);
+    }
     p.balanced = attn_is_balanced(batch, num_splits, n_kv_heads, rows) ? 1 : 0;
     p.max_wg = kNumCu;
     p.tile_keys = mb == 1 ? 128 : 64;                 // TK of the launch shape chosen below

@@ -1,0 +1,65 @@
+"""GPU parity of the decode-attention launches for short caches (no splits, no merge) and of the short key splits,
+at the edges where their shapes change: chunk and wave ends, the last cache length of the launch and the first
+beyond it, one and several row blocks, ragged batches, a tree.  Bounds: those of every attention test (max-abs 2e-2,
+mean-abs 2e-3 for outputs of size one: bf16 in and out, fp32 sums)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2508_16201_amd import synth
+from gpu_util import dev_bf16, host_f64, rnd_bits, assert_attn_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2508_16201_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
+    (1, 2, 2, 2, 64, 0), (1, 33, 4, 1, 64, 0), (2, 255, 14, 2, 64, 0), (3, 256, 14, 2, 64, 0),   # 21 rows: two row blocks
+    (1, 257, 4, 1, 64, 0), (6, 1023, 12, 3, 64, 0),                   # 3 kv heads: helpers and heads out of step
+    (1, 1535, 14, 2, 64, 0), (2, 1536, 16, 2, 64, 0), (1, 1537, 14, 2, 64, 0),
+    (1, 16, 8, 8, 128, 0), (5, 289, 32, 2, 128, 0), (4, 768, 8, 2, 128, 0), (6, 1024, 16, 2, 128, 0),
+    (1, 1025, 7, 1, 128, 0), (8, 64, 64, 8, 128, 0),                  # 256 workgroups: the most without a second round
+    (8, 65, 72, 8, 128, 0),                                           # 72 rows per kv head: splits
+    (1, 500, 14, 2, 64, 4), (1, 500, 14, 2, 64, 5), (1, 2049, 4, 1, 64, 17),   # short splits, a ragged and a one-key last one
+])
+def test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, splits):
+    q, k, v = (rnd_bits((n, h, d), 5000 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    scale = 1.0 / np.sqrt(d)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"q{q_len} kv{kv_len} {hq}/{hkv} d{d} splits {splits}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+def test_ragged_batch_of_short_caches(B):
+    lens, q_lens, hq, hkv, d = [1500, 3, 257, 1024, 64], [1, 3, 2, 3, 1], 14, 2, 64
+    q, k, v = [], [], []
+    for i, (n, m) in enumerate(zip(lens, q_lens)):
+        q.append(rnd_bits((m, hq, d), 5600 + i)); k.append(rnd_bits((n, hkv, d), 5700 + i)); v.append(rnd_bits((n, hkv, d), 5800 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.125,
+                        cu_q=cu(q_lens), cu_kv=cu(lens), max_q_len=3, max_kv_len=1500)
+    torch.cuda.synchronize()
+    o = 0
+    for i, m in enumerate(q_lens):
+        assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.125)[0], f"request {i}")
+        o += m
+
+
+@pytest.mark.parametrize("n_nodes,kv_len,hq,hkv,d", [(26, 300, 8, 1, 128), (64, 700, 4, 2, 64), (40, 40, 4, 1, 64)])
+def test_tree_over_a_short_cache(B, n_nodes, kv_len, hq, hkv, d):
+    parent = synth.make_tree(n_nodes, 90 + n_nodes)
+    masks = synth.ancestor_masks(parent)
+    q, k, v = rnd_bits((n_nodes, hq, d), 5900), rnd_bits((kv_len, hkv, d), 5901), rnd_bits((kv_len, hkv, d), 5902)
+    want, _ = oracle.tree_attn(q, k, v, masks, 0.1)
+    out = B.tree_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), 0.1, torch.from_numpy(masks.view(np.int64)).cuda())
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"tree {n_nodes} over {kv_len}")
