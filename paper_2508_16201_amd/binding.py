@@ -111,11 +111,13 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_cuda:
         raise ValueError("tensors must live on the GPU")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()          # (an int: the argtypes make the pointer of it)
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """The hipStream_t of torch's current stream on the current device, without a Stream object around it: the
+    short calls (acceptance, pruning, the scores of one layer) are bound by the host, and every call asks."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(fn: str, rc: int):
@@ -128,17 +130,12 @@ def new_workspace(nbytes: int, device=None) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device or "cuda")
 
 
-def _ws(workspace: Optional[torch.Tensor], need: int, like: torch.Tensor) -> torch.Tensor:
-    if workspace is None:
-        workspace = new_workspace(need, like.device)
-    return workspace
-
-
 def _thd(t: torch.Tensor) -> Tuple[int, int]:
     """(token stride, head stride) in elements of a [tokens, heads, d] view."""
-    if t.dim() != 3 or t.stride(2) != 1:
+    st = t.stride()
+    if len(st) != 3 or st[2] != 1:
         raise ValueError("expected a [tokens, heads, d] view with contiguous d")
-    return t.stride(0), t.stride(1)
+    return st[0], st[1]
 
 
 # --------------------------------------------------------------------------- score
@@ -208,11 +205,11 @@ def score_layers(q_text: torch.Tensor, k_cache: torch.Tensor, video_start: int, 
         scores = torch.empty(total_video, dtype=torch.float32, device=q_text.device)
         if beta != 0.0:
             raise ValueError("beta != 0 needs an existing scores tensor")
-    need = score_layers_workspace_bytes(n_layers, n_text, n_keys, n_video, hq, hkv, d, row_lse is not None,
-                                        batch=max(batch, 1))
-    workspace = _ws(workspace, need, q_text)
-    rc = lib().specvlm_score_layers(_ptr(q_text), q_text.stride(0), q_text.stride(1), q_text.stride(2),
-                                    _ptr(k_cache), k_cache.stride(0), k_cache.stride(1), k_cache.stride(2), n_layers,
+    if workspace is None:
+        workspace = new_workspace(score_layers_workspace_bytes(n_layers, n_text, n_keys, n_video, hq, hkv, d,
+                                                               row_lse is not None, batch=max(batch, 1)), q_text.device)
+    qs, ks = q_text.stride(), k_cache.stride()
+    rc = lib().specvlm_score_layers(_ptr(q_text), qs[0], qs[1], qs[2], _ptr(k_cache), ks[0], ks[1], ks[2], n_layers,
                                     _ptr(ptrs[0]), _ptr(ptrs[1]), _ptr(ptrs[2]), batch, n_text, n_keys, video_start,
                                     n_video, text_pos0, hq, hkv, d,
                                     float(softmax_scale), norm_mode, _ptr(row_lse),
@@ -244,8 +241,9 @@ def score(q_text: torch.Tensor, k_cache: torch.Tensor, video_start: int, n_video
         scores = torch.empty(total_video, dtype=torch.float32, device=q_text.device)
         if beta != 0.0:
             raise ValueError("beta != 0 needs an existing scores tensor")
-    need = score_workspace_bytes(n_text, n_keys, n_video, hq, hkv, d, row_lse is not None, batch=max(batch, 1))
-    workspace = _ws(workspace, need, q_text)
+    if workspace is None:
+        workspace = new_workspace(score_workspace_bytes(n_text, n_keys, n_video, hq, hkv, d, row_lse is not None,
+                                                        batch=max(batch, 1)), q_text.device)
     qs, ks = _thd(q_text), _thd(k_cache)
     rc = lib().specvlm_score(_ptr(q_text), qs[0], qs[1], _ptr(k_cache), ks[0], ks[1],
                              _ptr(ptrs[0]), _ptr(ptrs[1]), _ptr(ptrs[2]), batch, n_text, n_keys, video_start,
@@ -321,9 +319,9 @@ def gather_kv(k_src: torch.Tensor, v_src: Optional[torch.Tensor], video_start: i
     if v_dst is not None and v_dst.stride() != k_dst.stride():
         raise ValueError("K and V destinations must share strides")
     status = torch.empty(1, dtype=torch.int32, device=k_src.device) if want_status else None
-    rc = lib().specvlm_gather_kv(_ptr(k_src), _ptr(v_src), k_src.stride(0), k_src.stride(1),
-                                 k_src.stride(2), _ptr(k_dst), _ptr(v_dst), k_dst.stride(0),
-                                 k_dst.stride(1), k_dst.stride(2), n_layers, n_keys, video_start,
+    src, dst = k_src.stride(), k_dst.stride()
+    rc = lib().specvlm_gather_kv(_ptr(k_src), _ptr(v_src), src[0], src[1], src[2], _ptr(k_dst), _ptr(v_dst),
+                                 dst[0], dst[1], dst[2], n_layers, n_keys, video_start,
                                  n_video, _ptr(keep_idx), n_keep, _ptr(cu_keys), _ptr(cu_video),
                                  _ptr(cu_keep), batch, _ptr(status), hkv, d, _stream())
     _check("specvlm_gather_kv", rc)
@@ -359,8 +357,8 @@ def decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, softmax_scale
     if v.stride() != k.stride():
         raise ValueError("K and V must share strides")
     lse = torch.empty((tq, hq), dtype=torch.float32, device=q.device) if want_lse else None
-    need = decode_attn_workspace_bytes(batch, q_len, kv_len, hq, hkv, d, num_splits)
-    workspace = _ws(workspace, need, q)
+    if workspace is None:
+        workspace = new_workspace(decode_attn_workspace_bytes(batch, q_len, kv_len, hq, hkv, d, num_splits), q.device)
     qs, ks = _thd(q), _thd(k)
     if ancestor_mask is None:
         rc = lib().specvlm_decode_attn(_ptr(q), qs[0], qs[1], _ptr(k), _ptr(v), ks[0], ks[1],
@@ -425,8 +423,8 @@ def accept(target_logits: torch.Tensor, draft_tokens: torch.Tensor, *,
     out = out_tokens if out_tokens is not None else \
         torch.empty((batch, gamma + 1), dtype=torch.int32, device=dev)
     sampling = uniforms is not None
-    need = accept_workspace_bytes(batch, gamma, vocab, sampling)
-    workspace = _ws(workspace, need, target_logits)
+    if workspace is None:
+        workspace = new_workspace(accept_workspace_bytes(batch, gamma, vocab, sampling), dev)
     for t in (target_logits, draft_logits, draft_tokens, uniforms):
         if t is not None and not t.is_contiguous():
             raise ValueError("accept inputs must be contiguous")
@@ -446,8 +444,8 @@ def accept_tree(target_logits: torch.Tensor, node_tokens: torch.Tensor, parent: 
     n_acc = torch.empty(batch, dtype=torch.int32, device=dev)
     nodes = torch.empty((batch, n_nodes), dtype=torch.int32, device=dev)
     out = torch.empty((batch, n_nodes), dtype=torch.int32, device=dev)
-    need = lib().specvlm_accept_tree_workspace_bytes(batch, n_nodes, vocab)
-    workspace = _ws(workspace, need, target_logits)
+    if workspace is None:
+        workspace = new_workspace(lib().specvlm_accept_tree_workspace_bytes(batch, n_nodes, vocab), dev)
     for t in (target_logits, node_tokens, parent):
         if not t.is_contiguous():
             raise ValueError("accept_tree inputs must be contiguous")
@@ -473,8 +471,8 @@ def baseline_keep(mode: str, n_video: int, keep_budget: int, *, n_frames: int = 
         raise SpecVLMError("specvlm_baseline_count", count)
     keep_idx = torch.empty(count, dtype=torch.int32, device=device or "cuda")
     need = lib().specvlm_baseline_workspace_bytes(m, n_video)
-    if need:
-        workspace = _ws(workspace, need, keep_idx)
+    if need and workspace is None:
+        workspace = new_workspace(need, keep_idx.device)
     rc = lib().specvlm_baseline_keep(m, n_video, n_frames, grid_h, grid_w, keep_budget, stride_h, stride_w,
                                      seed, _ptr(keep_idx), _ptr(workspace),
                                      workspace.numel() if workspace is not None else 0, _stream())
@@ -489,7 +487,7 @@ def probe_read(a: torch.Tensor, b: Optional[torch.Tensor] = None) -> None:
     def span(t):
         if t is None:
             return None, 0
-        return C.c_void_p(t.data_ptr()), t.numel() * t.element_size()
+        return t.data_ptr(), t.numel() * t.element_size()
     pa, na = span(a)
     pb, nb = span(b)
     _check("specvlm_probe_read", lib().specvlm_probe_read(pa, na, pb, nb, None, _stream()))
