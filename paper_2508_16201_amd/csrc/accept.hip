@@ -31,7 +31,7 @@ struct AcceptParams {
     int32_t* out_tokens;
     float* part_val;          // [batch][rows][n_chunks]   max
     float* part_aux;          // [batch][rows][n_chunks]   sum exp (sampling) / argmax index bits (greedy)
-    float* norm;              // sampling: [batch][rows][2] merged (max, sum exp) of every row
+    float* norm;              // sampling: [batch][rows][2], first pair (max, sum exp) of target row n, second of draft row n
     float* chunk_mass;        // sampling: [batch][n_chunks] residual (or target) mass of row n per chunk
     int32_t* n_rej;           // sampling: [batch] first rejected position n (gamma if none)
 };
@@ -81,32 +81,48 @@ void accept_argmax_partial(const AcceptParams p)
     }
 }
 
-__global__ __launch_bounds__(64)
+// Argmax of every row from the pass-1 partials, into LDS: 16 lanes per row, so that the partials of 16 rows are one
+// round trip (a lane per row took one for every eight chunks: three at a vocabulary of 152064; 4.1 -> 2.3 us).
+constexpr int kFinalThreads = 256;
+__device__ __forceinline__ void accept_merge_argmax(const AcceptParams& p, int b, int rows, int* s_t)
+{
+    const int l = threadIdx.x & 15;
+    for (int row = threadIdx.x >> 4; row < rows; row += kFinalThreads / 16) {
+        const int64_t slot = ((int64_t)b * rows + row) * p.n_chunks;
+        float bv = 0.f; int bi = -1;
+        for (int c0 = l; c0 < p.n_chunks; c0 += 64) {            // four chunks' loads in flight at a time
+            float pv[4]; int pi[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool in = c0 + 16 * j < p.n_chunks;
+                pv[j] = in ? p.part_val[slot + c0 + 16 * j] : 0.f;
+                pi[j] = in ? __float_as_int(p.part_aux[slot + c0 + 16 * j]) : -1;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) argmax_merge(bv, bi, pv[j], pi[j]);
+        }
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+            const float ov = __shfl_xor(bv, off);
+            const int oi = __shfl_xor(bi, off);
+            argmax_merge(bv, bi, ov, oi);
+        }
+        if (l == 0) s_t[row] = bi;
+    }
+}
+
+__global__ __launch_bounds__(kFinalThreads)
 void accept_greedy_final(const AcceptParams p)
 {
-    // one wave per request; lane i merges the partials of row i and holds drafted token i
-    // (gamma <= 64), the first mismatch is found by a ballot and every lane writes its own output
+    // one workgroup per request; lane i of its first wave holds drafted token i (gamma <= 64), the first mismatch is
+    // found by a ballot and every lane writes its own output
     const int b = blockIdx.x, lane = threadIdx.x;
     __shared__ int s_t[65];
     const int32_t* x = p.tokens + (int64_t)b * p.gamma;
     const int drafted = lane < p.gamma ? x[lane] : -1;           // (in flight while the partials are merged)
-    for (int row = lane; row <= p.gamma; row += 64) {
-        float bv = 0.f; int bi = -1;
-        const int64_t slot = ((int64_t)b * (p.gamma + 1) + row) * p.n_chunks;
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 8) {             // eight chunks' loads in flight at a time
-            float pv[8]; int pi[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool in = c0 + j < p.n_chunks;
-                pv[j] = in ? p.part_val[slot + c0 + j] : 0.f;
-                pi[j] = in ? __float_as_int(p.part_aux[slot + c0 + j]) : -1;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) argmax_merge(bv, bi, pv[j], pi[j]);
-        }
-        s_t[row] = bi;
-    }
+    accept_merge_argmax(p, b, p.gamma + 1, s_t);
     __syncthreads();
+    if (threadIdx.x >= kWave) return;
     const uint64_t mismatch = __ballot(lane < p.gamma && drafted != s_t[lane]);
     const int n = mismatch ? __ffsll((long long)mismatch) - 1 : p.gamma;
     int32_t* out = p.out_tokens + (int64_t)b * (p.gamma + 1);
@@ -156,19 +172,20 @@ void accept_softmax_partial(const AcceptParams p)
     }
 }
 
-// Merged (max, sum exp) of every row from the pass-1 partials, into LDS.
-__device__ __forceinline__ void accept_merge_rows(const AcceptParams& p, int b, int rows, float* s_m, float* s_z)
+// Merged (max, sum exp) of every row from its pass-1 partials, into LDS.
+__device__ __forceinline__ void accept_merge_rows(const AcceptParams& p, int rows, const float* val, const float* aux,
+                                                  float* s_m, float* s_z)
 {
     for (int row = threadIdx.x; row < rows; row += blockDim.x) {
-        const int64_t slot = ((int64_t)b * rows + row) * p.n_chunks;
+        const int slot = row * p.n_chunks;
         float m = -INFINITY, z = 0.f;
         for (int c0 = 0; c0 < p.n_chunks; c0 += 8) {         // eight chunks' loads in flight at a time
             float pm[8], pz[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool in = c0 + j < p.n_chunks;
-                pm[j] = in ? p.part_val[slot + c0 + j] : -INFINITY;
-                pz[j] = in ? p.part_aux[slot + c0 + j] : 0.f;
+                pm[j] = in ? val[slot + c0 + j] : -INFINITY;
+                pz[j] = in ? aux[slot + c0 + j] : 0.f;
             }
             float mc = m;
 #pragma unroll
@@ -187,12 +204,25 @@ struct AcceptWeight {
     const float* trow;
     const float* drow;        // null: no residual
     float inv_t_log2, mt, inv_zt, md, inv_zd;
-    __device__ __forceinline__ float operator()(int v) const
+    // Weights of tokens first, first + step, ... (0 from `end` on).  Both rows' logits are requested before the first is
+    // looked at: with the test for a residual inside, every token was a round trip or two of its own.
+    template <int N> __device__ __forceinline__ void operator()(float (&w)[N], int first, int step, int end) const
     {
-        const float pv = fast_exp2(trow[v] * inv_t_log2 - mt) * inv_zt;
-        if (!drow) return pv;
-        const float qv = fast_exp2(drow[v] * inv_t_log2 - md) * inv_zd;
-        return fmaxf(pv - qv, 0.f);
+        float t[N], d[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) { const int v = first + j * step; t[j] = v < end ? trow[v] : -INFINITY; }
+        if (drow) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) { const int v = first + j * step; d[j] = v < end ? drow[v] : -INFINITY; }
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) w[j] = fast_exp2(t[j] * inv_t_log2 - mt) * inv_zt;
+        if (drow) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) w[j] = fmaxf(w[j] - fast_exp2(d[j] * inv_t_log2 - md) * inv_zd, 0.f);
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) w[j] = first + j * step < end ? w[j] : 0.f;
     }
 };
 
@@ -208,50 +238,66 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
     return w;
 }
 
+// The chain of round trips is what this kernel costs (two for the accept tests' tokens and logits, one for the pass-1
+// partials, one for the rejected row), so the first three run beside each other: the partials of all rows are fetched
+// by all threads, into LDS, where they fit (a thread per row fetching eight chunks at a time took one trip per eight).
+// gamma 7, 152064 tokens: 8.5 -> 5.9 us with the loads of both rows batched (AcceptWeight); the final kernel 9.3 -> 5.6.
+constexpr int kMergeStage = 4096;           // pass-1 partials of a request that are staged (152064 tokens: 215 rows)
+
 __global__ __launch_bounds__(256)
 void accept_mass_partial(const AcceptParams p)
 {
+    __shared__ float s_val[kMergeStage], s_aux[kMergeStage];
     __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
     __shared__ float s_part[4];
     __shared__ int s_n;
     const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rows = 2 * p.gamma + 1;
-    accept_merge_rows(p, b, rows, s_m, s_z);
+    // The gamma accept tests, one per lane of the first wave (gamma <= 64): every test's loads are in flight together,
+    // beside the partials; the first failing test is found by a ballot.
+    bool ok = true;
+    float t_logit = 0.f, d_logit = 0.f, u = 0.f;
+    if (tid < p.gamma) {
+        const int tok = p.tokens[(int64_t)b * p.gamma + tid];
+        ok = tok >= 0 && tok < p.vocab;                          // not a token: cannot be accepted
+        if (ok) {
+            t_logit = p.target[((int64_t)b * (p.gamma + 1) + tid) * p.vocab + tok];
+            d_logit = p.draft[((int64_t)b * p.gamma + tid) * p.vocab + tok];
+            u = p.uniforms[(int64_t)b * (p.gamma + 1) + tid];
+        }
+    }
+    const float* val = p.part_val + (int64_t)b * rows * p.n_chunks;
+    const float* aux = p.part_aux + (int64_t)b * rows * p.n_chunks;
+    if (rows * (int64_t)p.n_chunks <= kMergeStage) {
+        for (int i = tid; i < rows * p.n_chunks; i += 256) { s_val[i] = val[i]; s_aux[i] = aux[i]; }
+        __syncthreads();
+        accept_merge_rows(p, rows, s_val, s_aux, s_m, s_z);
+    } else {
+        accept_merge_rows(p, rows, val, aux, s_m, s_z);
+    }
     __syncthreads();
-    // The gamma accept tests, one per lane of the first wave (gamma <= 64): every test's loads
-    // are in flight together; the first failing test is found by a ballot.
     if (wave == 0) {
-        const float* tgt = p.target + (int64_t)b * (p.gamma + 1) * p.vocab;
-        const float* drf = p.draft + (int64_t)b * p.gamma * p.vocab;
-        bool ok = true;
-        if (lane < p.gamma) {
-            const int tok = p.tokens[(int64_t)b * p.gamma + lane];
-            ok = tok >= 0 && tok < p.vocab;                      // not a token: cannot be accepted
-            if (ok) {
-                const float pt = fast_exp2(tgt[(int64_t)lane * p.vocab + tok] * p.inv_t_log2 - s_m[lane]) / s_z[lane];
-                const float qd = fast_exp2(drf[(int64_t)lane * p.vocab + tok] * p.inv_t_log2 - s_m[p.gamma + 1 + lane]) /
-                                 s_z[p.gamma + 1 + lane];
-                ok = p.uniforms[(int64_t)b * (p.gamma + 1) + lane] * qd < pt;
-            }
+        if (lane < p.gamma && ok) {
+            const float pt = fast_exp2(t_logit * p.inv_t_log2 - s_m[lane]) / s_z[lane];
+            const float qd = fast_exp2(d_logit * p.inv_t_log2 - s_m[p.gamma + 1 + lane]) / s_z[p.gamma + 1 + lane];
+            ok = u * qd < pt;
         }
         const uint64_t failed = __ballot(!ok);
         if (lane == 0) s_n = failed ? __ffsll((long long)failed) - 1 : p.gamma;
     }
     __syncthreads();
     const int n = s_n;
-    if (chunk == 0) {                                            // what pass 3 needs of the above
-        if (tid < rows) { p.norm[((int64_t)b * rows + tid) * 2] = s_m[tid]; p.norm[((int64_t)b * rows + tid) * 2 + 1] = s_z[tid]; }
-        if (tid == 0) p.n_rej[b] = n;
-    }
     const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
+    if (chunk == 0 && tid == 0) {                                // what pass 3 needs of the above
+        float* nm = p.norm + (int64_t)b * rows * 2;
+        nm[0] = s_m[n]; nm[1] = s_z[n];
+        if (n < p.gamma) { nm[2] = s_m[dn]; nm[3] = s_z[dn]; }
+        p.n_rej[b] = n;
+    }
     const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
     const int lo = chunk * kAccChunk, hi = min(p.vocab, lo + kAccChunk);
     float w[kAccPerThread];
-#pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
-        const int v = lo + j * 256 + tid;
-        w[j] = v < hi ? weight(v) : 0.f;
-    }
+    weight(w, lo + tid, 256, hi);
     float mine = 0.f;
 #pragma unroll
     for (int j = 0; j < kAccPerThread; ++j) mine += w[j];
@@ -268,14 +314,22 @@ void accept_sample_final(const AcceptParams p)
     __shared__ float s_w[kAccWaves];
     __shared__ int s_idx[kAccWaves];
     __shared__ int s_y;
+    __shared__ float s_cm[kAccThreads];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rows = 2 * p.gamma + 1;
-    const int n = p.n_rej[b];
-    const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
-    const float* nm = p.norm + (int64_t)b * rows * 2;
-    const AcceptWeight weight = accept_weight(p, b, n, nm[2 * n], nm[2 * n + 1], nm[2 * dn], nm[2 * dn + 1]);
+    // (everything that does not depend on the owning chunk is requested together: one round trip)
+    const int drafted = tid < p.gamma ? p.tokens[(int64_t)b * p.gamma + tid] : -1;
+    const float u_last = p.uniforms[(int64_t)b * (p.gamma + 1) + p.gamma];
     const float* cm = p.chunk_mass + (int64_t)b * p.n_chunks;
+    const float my_cm = tid < p.n_chunks ? cm[tid] : 0.f;
+    const int n = p.n_rej[b];
+    const float* nm = p.norm + (int64_t)b * rows * 2;
+    const int second = p.gamma > 0 ? 2 : 0;                      // (gamma = 0: one row, nothing to reject)
+    const AcceptWeight weight = accept_weight(p, b, n, nm[0], nm[1], nm[second], nm[second + 1]);
     if (tid == 0) s_y = -1;
+    s_cm[tid] = my_cm;
+    __syncthreads();
+    if (p.n_chunks <= kAccThreads) cm = s_cm;
     // total mass and the owner of the goal among the chunks: the LAST chunk with mass whose prefix
     // does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that
     // rounding put at or beyond the total lands on the last chunk with mass).  Every thread walks
@@ -305,7 +359,7 @@ void accept_sample_final(const AcceptParams p)
         }
         __syncthreads();
     } else {
-        const float goal = p.uniforms[(int64_t)b * (p.gamma + 1) + p.gamma] * W;
+        const float goal = u_last * W;
         int own1 = -1;
         float pre1 = 0.f, acc1 = 0.f;
         for (int c = 0; c < p.n_chunks; ++c) {
@@ -319,9 +373,11 @@ void accept_sample_final(const AcceptParams p)
         const int lo1 = own1 * kAccChunk, hi1 = min(p.vocab, lo1 + kAccChunk);
         const int seg2 = ((hi1 - lo1 + kAccWaves - 1) / kAccWaves + 63) & ~63;
         const int lo2 = min(hi1, lo1 + wave * seg2), hi2 = min(hi1, lo2 + seg2);
-        float mine2 = 0.f;
-#pragma unroll 8
-        for (int v = lo2 + lane; v < hi2; v += 64) mine2 += weight(v);
+        constexpr int STEPS = kAccChunk / kAccThreads;           // of 64 tokens of a wave's share
+        float w2[STEPS], mine2 = 0.f;
+        weight(w2, lo2 + lane, 64, hi2);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) mine2 += w2[i];
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) mine2 += __shfl_xor(mine2, off);
         if (lane == 0) s_w[wave] = mine2;
@@ -337,42 +393,44 @@ void accept_sample_final(const AcceptParams p)
         // first wave then reports the chunk's last token with mass, or its first token)
         if (own2 < 0) own2 = 0;
         if (wave == own2) {
+            // (the scans of the steps do not depend on each other: six shuffles deep, not six per step)
+            float incl[STEPS];
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) incl[i] = w2[i];
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) {
+                    const float t = __shfl_up(incl[i], off);
+                    if (lane >= off) incl[i] += t;
+                }
+            }
             float c = pre2;
             int y = -1, last = -1;
-            for (int base = lo2; base < hi2; base += 64) {       // (at most eight steps)
-                const int v = base + lane;
-                const float w = v < hi2 ? weight(v) : 0.f;
-                float incl = w;
 #pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const float t = __shfl_up(incl, off);
-                    if (lane >= off) incl += t;
-                }
-                const uint64_t massive = __ballot(w > 0.f);
-                const uint64_t passed = __ballot(w > 0.f && c + incl > goal);
+            for (int i = 0; i < STEPS; ++i) {
+                const int base = lo2 + 64 * i;
+                const uint64_t massive = __ballot(w2[i] > 0.f);
+                const uint64_t passed = __ballot(w2[i] > 0.f && c + incl[i] > goal);
                 if (massive) last = base + 63 - __builtin_clzll(massive);
                 if (passed && y < 0) y = base + __ffsll((long long)passed) - 1;
-                c += __shfl(incl, 63);
+                c += __shfl(incl[i], 63);
             }
             if (lane == 0) s_y = y >= 0 ? y : (last >= 0 ? last : lo1);
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        const int32_t* x = p.tokens + (int64_t)b * p.gamma;
-        int32_t* out = p.out_tokens + (int64_t)b * (p.gamma + 1);
-        for (int i = 0; i <= p.gamma; ++i) out[i] = i < n ? x[i] : (i == n ? s_y : -1);
-        p.n_accepted[b] = n;
-    }
+    if (tid <= p.gamma) p.out_tokens[(int64_t)b * (p.gamma + 1) + tid] = tid < n ? drafted : (tid == n ? s_y : -1);
+    if (tid == 0) p.n_accepted[b] = n;
 }
 
 // ------------------------------------------------------------------ tree ----
 // Greedy walk over a static draft tree (App. B): rows of target_logits are tree
-// nodes; node 0 is the last committed token, parent[i] < i.  One wave per
-// request: lane i merges the per-chunk argmax partials of node i and holds its
-// parent and drafted token; the wave walks from the root, moving to the
-// lowest-numbered child that drafted the target's token (found by a ballot).
-__global__ __launch_bounds__(64)
+// nodes; node 0 is the last committed token, parent[i] < i.  One workgroup per
+// request merges the per-chunk argmax partials of all nodes; lane i of its first
+// wave holds node i's parent and drafted token, and that wave walks from the root,
+// moving to the lowest-numbered child that drafted the target's token (found by a ballot).
+__global__ __launch_bounds__(kFinalThreads)
 void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* accepted_nodes)
 {
     const int b = blockIdx.x, lane = threadIdx.x;
@@ -381,23 +439,9 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
     const int32_t* x = p.tokens + (int64_t)b * n_nodes;
     const int my_tok = lane < n_nodes ? x[lane] : -1;            // (in flight while the partials are merged)
     const int my_par = lane < n_nodes ? parent[lane] : -1;       // parent[] is shared by the batch
-    if (lane < n_nodes) {
-        float bv = 0.f; int bi = -1;
-        const int64_t slot = ((int64_t)b * n_nodes + lane) * p.n_chunks;
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 8) {             // eight chunks' loads in flight at a time
-            float pv[8]; int pi[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool in = c0 + j < p.n_chunks;
-                pv[j] = in ? p.part_val[slot + c0 + j] : 0.f;
-                pi[j] = in ? __float_as_int(p.part_aux[slot + c0 + j]) : -1;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) argmax_merge(bv, bi, pv[j], pi[j]);
-        }
-        s_t[lane] = bi;
-    }
+    accept_merge_argmax(p, b, n_nodes, s_t);
     __syncthreads();
+    if (threadIdx.x >= kWave) return;
     int32_t* out = p.out_tokens + (int64_t)b * n_nodes;
     int32_t* nodes = accepted_nodes + (int64_t)b * n_nodes;
     // the walk: every lane follows it; the children of the current node that drafted the target's
@@ -470,7 +514,7 @@ extern "C" int specvlm_accept(
     hipStream_t s = (hipStream_t)stream;
     if (!sampling) {
         hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, gamma + 1, batch), dim3(256), 0, s, p);
-        hipLaunchKernelGGL(accept_greedy_final, dim3(batch), dim3(64), 0, s, p);
+        hipLaunchKernelGGL(accept_greedy_final, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
         hipLaunchKernelGGL(accept_softmax_partial, dim3(p.n_chunks, 2 * gamma + 1, batch), dim3(256), 0, s, p);
         hipLaunchKernelGGL(accept_mass_partial, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
@@ -508,6 +552,6 @@ extern "C" int specvlm_accept_tree(
     p.norm = nullptr; p.chunk_mass = nullptr; p.n_rej = nullptr;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, n_nodes, batch), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(accept_tree_final, dim3(batch), dim3(64), 0, s, p, parent, accepted_nodes);
+    hipLaunchKernelGGL(accept_tree_final, dim3(batch), dim3(kFinalThreads), 0, s, p, parent, accepted_nodes);
     return launch_status();
 }
