@@ -1,8 +1,7 @@
 // specvlm_select: the two-stage retention set of Sec. 3.2.
 //   Stage I  : V_R = the k highest-scoring video tokens (ties -> lower index),
 //              by a most-significant-digit radix select on order-preserving
-//              integer keys (4 passes of 8 bits, wave-ballot aggregated
-//              histograms in LDS).
+//              integer keys (4 passes of 8 bits, histograms in LDS).
 //   Stage II : V_U = tokens of V \ V_R at the fixed fractional interval
 //              I = R/U in raster order: remainder ranks floor(t*R/U), exact
 //              integer arithmetic (Eq. 7 with the budget as denominator).
@@ -10,7 +9,12 @@
 // One workgroup of 1024 threads per request; thread t owns the contiguous run
 // of tokens [t*per, (t+1)*per) and keeps their keys in registers, so every
 // "how many before me" question is one block-wide exclusive scan of popcounts.
-#include <atomic>
+//
+// Bound: latency and VALU issue of the one workgroup.  Sixteen waves share four SIMDs, so an instruction that all of
+// them execute takes about 20 cycles; a barrier 100, and a wave scan by __shfl six LDS round trips (600).  Hence the
+// scans by DPP, no test on a key that its position or the pass already decides, masks of 32 bits where a thread has at
+// most 32 keys, and one wave that sums and scans a pass's histograms between two barriers.
+#include <type_traits>
 
 #include "common.h"
 
@@ -18,9 +22,55 @@ namespace specvlm {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
-constexpr int kSelCopies = 64;            // copies of the digit histogram in LDS (summed after every pass)
-constexpr int kSelCopyWords = 257;        // a copy is 257 words long: the copies of one digit lie in different banks
-constexpr size_t kSelHistBytes = 2ull * kSelCopies * kSelCopyWords * sizeof(int);   // two sets: the passes alternate
+// Copies of the digit histogram, summed after a pass by one wave.  An LDS atomic serialises over the lanes that hit one
+// address, and digits do coincide (the leading one, sign and exponent, takes a handful of values; scores summed over many
+// rows share their upper 16 bits), but every copy is also cleared, summed and moves the pass's end: cycles of the select
+// kernel at 12544 tokens, long-tailed / clustered within 1e-3 / within 1e-5, by the copies of passes 1 to 3:  2: 20.0 /
+// 26.1 / 31.7 thousand, 4: 19.8 / 22.7 / 25.5, 8: 20.3 / 21.4 / 22.2, 16: 25.3, 32: 28.7; 16 or 64 in pass 0 are equal.
+constexpr int kSelCopies = 8;
+constexpr int kSelCopyWords = 260;        // 256 counters, 16-byte aligned; the copies of one digit lie in different banks
+
+// Wave-wide inclusive prefix sum by DPP: rows of 16 lanes, then the rows' totals.
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or_0(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+
+__device__ __forceinline__ int row_incl_scan(int x)
+{
+    x += dpp_or_0<0x111, 0xf>(x);         // row_shr 1, 2, 4, 8
+    x += dpp_or_0<0x112, 0xf>(x);
+    x += dpp_or_0<0x114, 0xf>(x);
+    return x + dpp_or_0<0x118, 0xf>(x);
+}
+
+__device__ __forceinline__ int wave_incl_scan(int x)
+{
+    x = row_incl_scan(x);
+    x += dpp_or_0<0x142, 0xa>(x);         // row_bcast 15, into rows 1 and 3
+    return x + dpp_or_0<0x143, 0xc>(x);   // row_bcast 31, into rows 2 and 3
+}
+
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned long long dpp_or_0(unsigned long long x)
+{
+    const unsigned lo = (unsigned)dpp_or_0<CTRL, ROWS>((int)(unsigned)x), hi = (unsigned)dpp_or_0<CTRL, ROWS>((int)(x >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long x)
+{
+    x += dpp_or_0<0x111, 0xf>(x);
+    x += dpp_or_0<0x112, 0xf>(x);
+    x += dpp_or_0<0x114, 0xf>(x);
+    x += dpp_or_0<0x118, 0xf>(x);
+    x += dpp_or_0<0x142, 0xa>(x);
+    return x + dpp_or_0<0x143, 0xc>(x);
+}
+
+__device__ __forceinline__ int count_bits(uint32_t m) { return __popc(m); }
+__device__ __forceinline__ int count_bits(uint64_t m) { return __popcll(m); }
+__device__ __forceinline__ int first_bit(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int first_bit(uint64_t m) { return __ffsll((long long)m) - 1; }
 
 struct SelectParams {
     const float* scores;
@@ -38,10 +88,9 @@ struct SelectParams {
 // smallest key of all.
 __device__ __forceinline__ uint32_t score_key(float x)
 {
-    if (x != x) return 0u;
-    uint32_t u = __float_as_uint(x);
-    if (x == 0.f) u = 0u;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    const uint32_t u = __float_as_uint(x + 0.f);                 // (-0 + 0 is +0)
+    const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+    return x != x ? 0u : key;
 }
 
 // A thread's run of scores [first, first + per) of a request of n scores, four at a time (dword-aligned
@@ -66,36 +115,29 @@ __device__ __forceinline__ void load_run(const float* sc, int first, int per, in
     }
 }
 
-// Exclusive prefix sums of two ints per thread in one round of barriers.
-__device__ __forceinline__ void block_excl_scan2(int a, int b, int (*s_wave2)[kSelWaves], int* a_before, int* b_before)
+// Exclusive prefix sums of two counts per thread (at most 64 each: a wave's sums fit 16 bits) behind one barrier.
+__device__ __forceinline__ void block_excl_scan2(int a, int b, int* s_wave, int* a_before, int* b_before)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int ia = a, ib = b;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int ya = __shfl_up(ia, off), yb = __shfl_up(ib, off);
-        if (lane >= off) { ia += ya; ib += yb; }
-    }
-    if (lane == 63) { s_wave2[0][wave] = ia; s_wave2[1][wave] = ib; }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mine = a | (b << 16);
+    const int incl = wave_incl_scan(mine);
+    if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    int wa = 0, wb = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        if (w < wave) { wa += s_wave2[0][w]; wb += s_wave2[1][w]; }
-    }
-    *a_before = wa + ia - a;
-    *b_before = wb + ib - b;
+    const int w = lane < kSelWaves ? s_wave[lane] : 0;
+    const int wa = row_incl_scan(w & 0xffff) - (w & 0xffff), wb = row_incl_scan(w >> 16) - (w >> 16);
+    const int excl = incl - mine;
+    *a_before = __builtin_amdgcn_readlane(wa, wave) + (excl & 0xffff);
+    *b_before = __builtin_amdgcn_readlane(wb, wave) + (excl >> 16);
 }
 
 template <int E>
 __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const SelectParams p)
 {
-    // kSelCopies copies of the digit histogram (padded: see below); the passes alternate between two sets
-    extern __shared__ int s_hist_dyn[];
-    int (*s_hist)[kSelCopies][kSelCopyWords] = reinterpret_cast<int (*)[kSelCopies][kSelCopyWords]>(s_hist_dyn);
-    __shared__ int s_part[4][256];
-    __shared__ int s_wave2[2][kSelWaves];
+    using mask_t = std::conditional_t<(E <= 32), uint32_t, uint64_t>;      // a bit per key of a thread
+    static_assert(kSelWaves == 16, "the waves' sums are one DPP row");
+    __shared__ __align__(16) int s_hist[2][kSelCopies * kSelCopyWords];    // the passes alternate between two sets
+    __shared__ int s_wave[kSelWaves];
     __shared__ int s_pick[3];
 
     const int b = blockIdx.x;
@@ -109,77 +151,67 @@ void select_kernel(const SelectParams p)
     const float* sc = p.scores + v0;
     float raw[E];
     load_run<E>(sc, first, per, n, raw);
-    // the first pass's histograms are cleared while the scores are on their way
-    for (int i = tid; i < kSelCopies * kSelCopyWords; i += kSelThreads) (&s_hist[0][0][0])[i] = 0;
+    // the first two passes' histograms are cleared while the scores are on their way
+    auto clear = [&](int* from, int words) __attribute__((always_inline)) {
+        for (int i = tid; i < words / 4; i += kSelThreads) reinterpret_cast<u32x4*>(from)[i] = u32x4{0u, 0u, 0u, 0u};
+    };
+    clear(s_hist[0], 2 * kSelCopies * kSelCopyWords);
     const int k = p.k_top[b], budget = p.keep_budget[b];
     const int out0 = p.cu_keep ? p.cu_keep[b] : 0;
     const bool bad = n < 0 || n > E * kSelThreads || n > p.max_n_video || k < 0 || k > budget || budget > n;
     if (p.status && tid == 0) p.status[b] = bad ? SPECVLM_EINVAL : SPECVLM_OK;
     if (bad || budget == 0) return;
 
+    // Slots past the last token hold the smallest key.  They come after every token of equal key, and never more keys
+    // are taken than there are tokens, so they need no test: none of them is ever among the first `need` equal keys.
+    const int mine = first < n ? min(per, n - first) : 0;
     uint32_t key[E];
-    uint64_t valid = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int idx = first + e;
-        const bool ok = e < per && idx < n;                     // (per <= E once the sizes are valid)
-        key[e] = ok ? score_key(raw[e]) : 0u;
-        if (ok) valid |= 1ull << e;
-    }
+    for (int e = 0; e < E; ++e) key[e] = e < mine ? score_key(raw[e]) : 0u;
 
     // ---- Stage I: radix select of the k-th largest key ----
     uint32_t prefix = 0, known = 0;
     int need = k;                       // how many still to take inside the current prefix
     if (k > 0) {
+        __syncthreads();                                // the cleared histograms are visible
         for (int pass = 0; pass < 4; ++pass) {
             const int shift = 24 - 8 * pass;
-            if (pass == 0) __syncthreads();             // the cleared histograms are visible
-            // The copies are summed afterwards, so a lane may add to any of them: every lane of an
-            // instruction has a copy of its own (an LDS atomic serialises over the lanes that hit one
-            // address, and the leading digit of attention scores, sign and exponent, takes only a handful
-            // of values), the waves start at different copies, and a copy is 257 words long, so the copies
-            // of a digit lie in different banks.  No aggregation over the wave or over a thread's keys:
-            // both were measured and cost more than the additions they save.
-            int* const my_hist = &s_hist[pass & 1][(4 * wave + lane) & (kSelCopies - 1)][0];
+            int* const hist = s_hist[pass & 1];
+            // A lane may add to any copy: the lanes of an instruction are spread over the copies, the waves start at
+            // different ones.  No aggregation over the wave or over a thread's keys: both were measured and cost more
+            // than the additions they save.
+            int* const my_hist = hist + ((4 * wave + lane) & (kSelCopies - 1)) * kSelCopyWords;
+            if (pass == 0) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const bool match = ((valid >> e) & 1) && ((key[e] & known) == prefix);
-                if (match) atomicAdd(&my_hist[(key[e] >> shift) & 255], 1);
-            }
-            // the other set (read for the last time two barriers ago) is cleared for the next pass
-            if (pass < 3)
-                for (int i = tid; i < kSelCopies * kSelCopyWords; i += kSelThreads) (&s_hist[(pass + 1) & 1][0][0])[i] = 0;
-            __syncthreads();
-            {
-                // thread (quarter, digit) sums a quarter of the digit's copies; the four quarters sit in
-                // the lanes of four different waves, so they meet in LDS
-                const int digit = tid & 255, quarter = tid >> 8;
-                int t = 0;
+                for (int e = 0; e < E; ++e)
+                    if (e < per) atomicAdd(&my_hist[key[e] >> 24], 1);
+            } else {
 #pragma unroll
-                for (int w = 0; w < kSelCopies / 4; ++w) t += s_hist[pass & 1][quarter * (kSelCopies / 4) + w][digit];
-                s_part[quarter][digit] = t;
+                for (int e = 0; e < E; ++e)
+                    if (e < per && (key[e] & known) == prefix) atomicAdd(&my_hist[(key[e] >> shift) & 255], 1);
+                // (the other set was read for the last time before the barrier above)
+                if (pass < 3) clear(s_hist[(pass + 1) & 1], kSelCopies * kSelCopyWords);
             }
             __syncthreads();
             if (wave == 0) {
-                // lane l owns digits 4l..4l+3; suffix sums from the top digit down
-                int c4[4], mine = 0;
+                // lane l sums digits 252 - 4l .. 255 - 4l over the copies; prefix sums over the lanes run down from the
+                // top digit
+                const int d0 = 252 - 4 * lane;
+                int c4[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    c4[i] = s_part[0][4 * lane + i] + s_part[1][4 * lane + i] + s_part[2][4 * lane + i] + s_part[3][4 * lane + i];
-                    mine += c4[i];
-                }
-                int incl = mine;                        // inclusive suffix sum over lanes >= lane
+                for (int w = 0; w < kSelCopies; ++w) {
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(hist + w * kSelCopyWords + d0);
 #pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int y = __shfl_down(incl, off);
-                    if (lane + off < 64) incl += y;
+                    for (int i = 0; i < 4; ++i) c4[i] += (int)v[i];
                 }
-                int above = incl - mine;                // keys in digits owned by higher lanes
+                const int sum = c4[0] + c4[1] + c4[2] + c4[3];
+                const int incl = wave_incl_scan(sum);
+                int above = incl - sum;                 // keys in higher digits
                 if (above < need && need <= incl) {
 #pragma unroll
                     for (int i = 3; i >= 0; --i) {
                         if (above < need && need <= above + c4[i]) {
-                            s_pick[0] = 4 * lane + i;
+                            s_pick[0] = d0 + i;
                             s_pick[1] = need - above;
                             s_pick[2] = (need - above == c4[i]);    // the whole bucket is taken: nothing left to rank
                         }
@@ -199,14 +231,14 @@ void select_kernel(const SelectParams p)
     }
     // now: prefix = the known digits of the k-th largest key (all four, or fewer when a whole bucket
     // is taken); take every key above it and the first `need` keys that share it, in index order.
-    uint64_t gt = 0, eq = 0;
+    mask_t gt = 0, eq = 0;
     if (k > 0) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (!((valid >> e) & 1)) continue;
+            if (e >= per) continue;
             const uint32_t kk = key[e] & known;
-            if (kk > prefix) gt |= 1ull << e;
-            else if (kk == prefix) eq |= 1ull << e;
+            gt |= kk > prefix ? (mask_t)1 << e : 0;
+            eq |= kk == prefix ? (mask_t)1 << e : 0;
         }
     }
     // One block scan gives every thread the numbers of larger and of equal keys before its
@@ -215,50 +247,45 @@ void select_kernel(const SelectParams p)
     // `need`, the rest is my first remainder rank, and the stride picks below that rank are counted
     // by the stride formula itself.
     int gt_before, eq_before;
-    block_excl_scan2(__popcll(gt), __popcll(eq), s_wave2, &gt_before, &eq_before);
+    block_excl_scan2(count_bits(gt), count_bits(eq), s_wave, &gt_before, &eq_before);
     int take = need - eq_before;
-    take = take < 0 ? 0 : take;
     const int top_before = gt_before + (eq_before < need ? eq_before : need);
-    uint64_t top = gt;
-    for (uint64_t m = eq; m && take > 0; --take) {
-        const uint64_t bit = m & (~m + 1);
+    mask_t top = gt;
+    for (mask_t m = eq; m && take > 0; --take) {
+        const mask_t bit = m & (~m + 1);
         top |= bit;
         m ^= bit;
     }
 
     // ---- Stage II: uniform stride over the remainder ----
-    const uint64_t rem_mask = valid & ~top;
-    const int rho_before = (first < n ? first : n) - top_before;
-    // n <= 65536, so every product below (rank x U, index x R, each factor <= 65536 and one of them
-    // < 65536) fits 32 bits: unsigned 32-bit divisions, exact
+    const mask_t valid = mine > 0 ? (mask_t)(~(mask_t)0 >> (sizeof(mask_t) * 8 - mine)) : 0;
+    const mask_t rem_mask = valid & ~top;
+    const uint32_t rho_before = (uint32_t)((first < n ? first : n) - top_before);
+    // Stride picks are the ranks floor(t*R/U), t < U.  t(rho) = ceil(rho*U/R) of them lie below rank rho, and with
+    // slack(rho) = t(rho)*R - rho*U (in [0, R), at least U where t(rho) = U) rank rho is a pick exactly if slack < U;
+    // then slack moves by R - U, else by -U.  n <= 65536: for rho < R, rho*U + R - 1 <= (R-1)*(R+1) < 2^32.
     const uint32_t R = (uint32_t)(n - k), U = (uint32_t)(budget - k);
-    uint64_t uni = 0;
-    int uni_before = 0;                                           // stride picks with a rank below mine
-    if (U > 0) {
-        uint32_t t = (uint32_t)(((uint64_t)rho_before * U + R - 1) / R);   // first stride index at or after my ranks
-        uni_before = (int)(t < U ? t : U);
-        if (t < U && rem_mask) {
-            const uint32_t tr = t * R;                            // t <= U - 1: the product fits
-            uint32_t q = tr / U, frac = tr % U;                   // rank floor(t*R/U)
-            const uint32_t step_q = R / U, step_f = R % U;
-            uint32_t rho = (uint32_t)rho_before;
-            for (uint64_t m = rem_mask; m && t < U; ++rho) {
-                const uint64_t bit = m & (~m + 1);
-                m ^= bit;
-                if (rho == q) {
-                    uni |= bit;
-                    ++t; q += step_q; frac += step_f;
-                    if (frac >= U) { frac -= U; ++q; }
-                }
+    mask_t uni = 0;
+    uint32_t uni_before = U;                                      // stride picks with a rank below mine
+    if (U > 0 && rho_before < R) {
+        uni_before = (rho_before * U + R - 1) / R;
+        uint32_t slack = uni_before * R - rho_before * U;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (e >= per) continue;
+            if ((rem_mask >> e) & 1) {
+                const bool pick = slack < U;
+                uni |= pick ? (mask_t)1 << e : 0;
+                slack += pick ? R - U : 0u - U;
             }
         }
     }
 
     // ---- stable compaction of V_R u V_U: my first output position is what was kept before me ----
-    const uint64_t keep = top | uni;
-    int pos = out0 + top_before + uni_before;
-    for (uint64_t m = keep; m;) {
-        const int e = __ffsll((long long)m) - 1;
+    const mask_t keep = top | uni;
+    int pos = out0 + top_before + (int)uni_before;
+    for (mask_t m = keep; m;) {
+        const int e = first_bit(m);
         m &= m - 1;
         p.keep_idx[pos] = first + e;
         if (p.from_topk) p.from_topk[pos] = (uint8_t)((top >> e) & 1);
@@ -286,17 +313,15 @@ struct TopPParams {
     int32_t* count;
 };
 
-constexpr size_t kTopPHistBytes = (size_t)kSelCopies * kSelCopyWords * sizeof(unsigned long long);   // one set
+constexpr int kTopPCopyWords = 258;       // 256 sums, 16-byte aligned; the copies of one digit lie in different banks
 
 template <int E>
 __global__ __launch_bounds__(kSelThreads)
 void top_p_kernel(const TopPParams p)
 {
-    // 64 copies of the 256 per-digit mass sums, one copy per lane of an instruction as in the selection
-    // (dynamic LDS); counts are not kept per digit: only the threshold key's are needed, at the end
-    extern __shared__ unsigned long long s_mass_dyn[];
-    unsigned long long (*s_mass)[kSelCopyWords] = reinterpret_cast<unsigned long long (*)[kSelCopyWords]>(s_mass_dyn);
-    __shared__ unsigned long long s_part[4][256];
+    // copies of the 256 per-digit mass sums, two sets as in the selection; counts are not kept per digit: only the
+    // threshold key's are needed, at the end
+    __shared__ __align__(16) unsigned long long s_mass[2][kSelCopies * kTopPCopyWords];
     __shared__ float s_redf[kSelWaves];
     __shared__ int s_redc[2][kSelWaves];
     __shared__ unsigned long long s_pick_sum, s_goal;
@@ -316,14 +341,16 @@ void top_p_kernel(const TopPParams p)
     float val[E];
     load_run<E>(sc, first, per, n, val);
     // the sums are cleared while the scores are on their way
-    for (int i = tid; i < kSelCopies * kSelCopyWords; i += kSelThreads) (&s_mass[0][0])[i] = 0ull;
-    uint64_t valid = 0;
+    auto clear = [&](unsigned long long* from, int words) __attribute__((always_inline)) {
+        for (int i = tid; i < words / 2; i += kSelThreads) reinterpret_cast<u32x4*>(from)[i] = u32x4{0u, 0u, 0u, 0u};
+    };
+    clear(s_mass[0], 2 * kSelCopies * kTopPCopyWords);
+    // (slots past the last token hold a NaN: the lowest key, without mass, so they need no test)
+    const int mine = first < n ? min(per, n - first) : 0;
     float mx = 0.f;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int idx = first + e;
-        const bool ok = e < per && idx < n;
-        if (ok) valid |= 1ull << e;
+        if (e >= mine) val[e] = NAN;
         mx = fmaxf(mx, mass_of(val[e]));
     }
 #pragma unroll
@@ -346,46 +373,40 @@ void top_p_kernel(const TopPParams p)
     unsigned long long goal = 0;               // ceil(lambda * total), known once the first pass has the total
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
-        unsigned long long* const my_mass = &s_mass[(4 * wave + lane) & (kSelCopies - 1)][0];
+        unsigned long long* const mass = s_mass[pass & 1];
+        unsigned long long* const my_mass = mass + ((4 * wave + lane) & (kSelCopies - 1)) * kTopPCopyWords;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
+            if (e >= per) continue;
             float x = val[e];
             __asm__ volatile("" : "+v"(x));          // recompute key and mass per pass: keeps them out of registers
             const uint32_t key = score_key(x);
-            if (((valid >> e) & 1) && ((key & known) == prefix)) {
+            if ((key & known) == prefix) {
                 const unsigned long long m = to_fix(x);
                 if (m) atomicAdd(&my_mass[(key >> shift) & 255], m);
             }
         }
-        __syncthreads();
-        {
-            // thread (quarter, digit) sums a quarter of the digit's copies
-            const int digit = tid & 255, quarter = tid >> 8;
-            unsigned long long t = 0;
-#pragma unroll
-            for (int w = 0; w < kSelCopies / 4; ++w) t += s_mass[quarter * (kSelCopies / 4) + w][digit];
-            s_part[quarter][digit] = t;
-        }
+        // (the other set was read for the last time before the barrier above)
+        if (pass == 1 || pass == 2) clear(s_mass[(pass + 1) & 1], kSelCopies * kTopPCopyWords);
         __syncthreads();
         if (wave == 0) {
-            // lane l owns digits 4l..4l+3; inclusive suffix sums from the top digit down
-            unsigned long long m4[4], mmine = 0;
+            // lane l sums digits 252 - 4l .. 255 - 4l over the copies; prefix sums run down from the top digit
+            const int d0 = 252 - 4 * lane;
+            unsigned long long m4[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                m4[i] = s_part[0][4 * lane + i] + s_part[1][4 * lane + i] + s_part[2][4 * lane + i] + s_part[3][4 * lane + i];
-                mmine += m4[i];
+            for (int w = 0; w < kSelCopies; ++w) {
+                typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+                const u64x2* src = reinterpret_cast<const u64x2*>(mass + w * kTopPCopyWords + d0);
+                const u64x2 v0 = src[0], v1 = src[1];
+                m4[0] += v0[0]; m4[1] += v0[1]; m4[2] += v1[0]; m4[3] += v1[1];
             }
-            unsigned long long mincl = mmine;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const unsigned long long ym = __shfl_down(mincl, off);
-                if (lane + off < 64) mincl += ym;
-            }
+            const unsigned long long mmine = m4[0] + m4[1] + m4[2] + m4[3];
+            const unsigned long long mincl = wave_incl_scan(mmine);
             if (pass == 0) {
-                // the first pass sees every key: lane 0's suffix sum is the total mass.
+                // the first pass sees every key: the last lane's sum is the total mass.
                 // goal = ceil(lambda * total); lambda is an fp32 in [0,1] and total < 2^56, so the double
                 // product is within a few units of 2^-40 of the largest score: far below the parity margin
-                const unsigned long long total = __shfl(mincl, 0);
+                const unsigned long long total = __shfl(mincl, 63);
                 const double goal_d = ceil((double)p.lambda * (double)total);
                 goal = goal_d <= 0.0 ? 0ull : (unsigned long long)goal_d;
                 if (goal > total) goal = total;
@@ -396,13 +417,10 @@ void top_p_kernel(const TopPParams p)
             if (goal > 0 && m_above < goal && goal <= above_sum + mincl) {
 #pragma unroll
                 for (int i = 3; i >= 0; --i) {
-                    if (m_above < goal && goal <= m_above + m4[i]) { s_pick = 4 * lane + i; s_pick_sum = m_above; }
+                    if (m_above < goal && goal <= m_above + m4[i]) { s_pick = d0 + i; s_pick_sum = m_above; }
                     m_above += m4[i];
                 }
             }
-        } else if (pass < 3) {
-            // (the sums were read for the last time before the barrier above: cleared for the next pass)
-            for (int i = tid - kWave; i < kSelCopies * kSelCopyWords; i += kSelThreads - kWave) (&s_mass[0][0])[i] = 0ull;
         }
         __syncthreads();
         if (pass == 0) {
@@ -418,7 +436,7 @@ void top_p_kernel(const TopPParams p)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const uint32_t key = score_key(val[e]);
-        if ((valid >> e) & 1) { gt += key > prefix; eq += key == prefix; }
+        if (e < per) { gt += key > prefix; eq += key == prefix; }      // (prefix has mass, so no NaN equals it)
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) { gt += __shfl_xor(gt, off); eq += __shfl_xor(eq, off); }
@@ -440,42 +458,6 @@ void top_p_kernel(const TopPParams p)
         if (p.max_count && c > p.max_count[b]) c = p.max_count[b];
         p.count[b] = c;
     }
-}
-
-// The histogram copies take more LDS than a kernel gets by default: the limit is raised once per
-// device (the attribute belongs to the kernel as loaded on one device).
-template <int E>
-static int launch_select(int batch, const SelectParams& p, hipStream_t stream)
-{
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<E>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelHistBytes) != hipSuccess)
-            return SPECVLM_ELAUNCH;
-        raised[dev].store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL(select_kernel<E>, dim3(batch), dim3(kSelThreads), kSelHistBytes, stream, p);
-    return SPECVLM_OK;
-}
-
-template <int E>
-static int launch_top_p(int batch, const TopPParams& p, hipStream_t stream)
-{
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&top_p_kernel<E>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTopPHistBytes) != hipSuccess)
-            return SPECVLM_ELAUNCH;
-        raised[dev].store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL(top_p_kernel<E>, dim3(batch), dim3(kSelThreads), kTopPHistBytes, stream, p);
-    return SPECVLM_OK;
 }
 
 }  // namespace specvlm
@@ -514,12 +496,10 @@ extern "C" int specvlm_select(
     p.keep_idx = keep_idx; p.from_topk = from_topk; p.status = status;
     hipStream_t s = (hipStream_t)stream;
     const int per = (max_n_video + kSelThreads - 1) / kSelThreads;
-    int rc;
-    if (per <= 4)       rc = launch_select<4>(batch, p, s);
-    else if (per <= 16) rc = launch_select<16>(batch, p, s);
-    else if (per <= 32) rc = launch_select<32>(batch, p, s);
-    else                rc = launch_select<64>(batch, p, s);
-    if (rc != SPECVLM_OK) return rc;
+    if (per <= 4)       hipLaunchKernelGGL(select_kernel<4>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else if (per <= 16) hipLaunchKernelGGL(select_kernel<16>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else if (per <= 32) hipLaunchKernelGGL(select_kernel<32>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else                hipLaunchKernelGGL(select_kernel<64>, dim3(batch), dim3(kSelThreads), 0, s, p);
     return launch_status();
 }
 
@@ -546,11 +526,9 @@ extern "C" int specvlm_top_p_count(
     p.lambda = lambda; p.max_count = max_count; p.count = count;
     hipStream_t s = (hipStream_t)stream;
     const int per = (max_n_video + kSelThreads - 1) / kSelThreads;
-    int rc;
-    if (per <= 4)       rc = launch_top_p<4>(batch, p, s);
-    else if (per <= 16) rc = launch_top_p<16>(batch, p, s);
-    else if (per <= 32) rc = launch_top_p<32>(batch, p, s);
-    else                rc = launch_top_p<64>(batch, p, s);
-    if (rc != SPECVLM_OK) return rc;
+    if (per <= 4)       hipLaunchKernelGGL(top_p_kernel<4>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else if (per <= 16) hipLaunchKernelGGL(top_p_kernel<16>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else if (per <= 32) hipLaunchKernelGGL(top_p_kernel<32>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    else                hipLaunchKernelGGL(top_p_kernel<64>, dim3(batch), dim3(kSelThreads), 0, s, p);
     return launch_status();
 }

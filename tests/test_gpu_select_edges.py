@@ -1,0 +1,66 @@
+"""GPU parity of specvlm_select and specvlm_top_p_count at the edges of what their kernels assume: tokens that fill the
+threads' runs exactly, by one less and one more, the first and last size of every kernel (4, 16, 32 and 64 tokens a
+thread), k and budget at both ends, keys that all coincide in one digit or in all, and a selection that reaches the NaN
+keys, which the slots past the last token share.  Exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2508_16201_amd import binding
+    binding.lib()
+    return binding
+
+
+def i32(x):
+    return torch.tensor([x], dtype=torch.int32).cuda()
+
+
+def scores(kind, n, seed):
+    r = np.random.default_rng(seed)
+    s = np.exp(r.standard_normal(n)).astype(np.float32)
+    if kind == "equal":
+        s[:] = 0.25
+    elif kind == "tight":                      # three equal leading digits
+        s = (1.0 + 1e-5 * r.standard_normal(n)).astype(np.float32)
+    elif kind == "nan":                        # fewer numbers than are taken
+        s[r.random(n) < 0.9] = np.nan
+        s[r.random(n) < 0.05] = -0.0
+    return s
+
+
+SIZES = [1, 2, 63, 1023, 1024, 1025, 4095, 4096, 4097, 12544, 16383, 16384, 16385, 32768, 32769, 65535, 65536]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("kind", ["spread", "equal", "tight", "nan"])
+def test_select(B, n, kind):
+    s = scores(kind, n, n)
+    dev = torch.from_numpy(s).cuda()
+    for k, budget in {(0, n), (0, 1), (1, 1), (n, n), (n - 1, n), (n // 20, n // 10), (n // 2, n // 2 + n // 3), (n // 5, n)}:
+        if not 0 <= k <= budget <= n or budget == 0:
+            continue
+        want, want_flags = oracle.select(s, k, budget)
+        keep, flags = B.select(dev, i32(k), i32(budget), budget)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(keep.cpu().numpy(), want, err_msg=f"n {n} k {k} budget {budget} {kind}")
+        np.testing.assert_array_equal(flags.cpu().numpy(), want_flags)
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("kind", ["spread", "equal", "nan"])
+def test_top_p_count(B, n, kind):
+    s = scores(kind, n, n + 1)
+    dev = torch.from_numpy(s).cuda()
+    for lam in (0.0, 0.25, 0.4, 1.0):
+        lam = float(np.float32(lam))
+        got = B.top_p_count(dev, lam).item()
+        want, margin = oracle.top_p_count(s, lam, want_margin=True)
+        if margin > 1e-6 or lam == 1.0:
+            assert got == want, (n, kind, lam)
