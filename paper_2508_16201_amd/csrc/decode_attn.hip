@@ -728,8 +728,8 @@ void attn_merge_kernel(const AttnParams p)
         p.lse[(int64_t)(q0 + t) * p.n_q_heads + h] = (m + fast_log2(l)) * kLn2;
 }
 
-// Merge for the balanced decomposition, where a (request, head) has only a handful of pieces: each
-// group of D/4 threads merges one query row on its own, with the loads of up to PRE pieces in
+// Merge where a (request, head) has only a handful of pieces (the balanced decomposition, and uniform splits by
+// attn_merges_by_row): each group of D/4 threads merges one query row on its own, with the loads of up to PRE pieces in
 // flight together, so a workgroup finishes 256 / (D/4) rows and no cross-thread combine is needed.
 template <int D, int PRE>
 __global__ __launch_bounds__(256)
@@ -746,8 +746,17 @@ void attn_merge_rows_kernel(const AttnParams p)
     if (p.cu_q) { q0 = p.cu_q[b]; ql = p.cu_q[b + 1] - q0; }
     if (p.cu_kv) { kvl = p.cu_kv[b + 1] - p.cu_kv[b]; }
     if (ql <= 0 || kvl < ql || row >= p.group * ql) return;
-    const int live = p.seg_table[2 * bh + 1];
-    const int64_t slot0 = (int64_t)p.seg_table[2 * bh] * p.rows_pad + row;
+    int live;
+    int64_t slot0, step;                             // pieces, the row's slot in the first one, slots from one to the next
+    if (p.balanced) {
+        live = p.seg_table[2 * bh + 1];
+        slot0 = (int64_t)p.seg_table[2 * bh] * p.rows_pad + row;
+        step = (int64_t)p.n_kv_heads * p.rows_pad;   // the next group's piece
+    } else {
+        live = min(p.num_splits, (kvl + p.split_keys - 1) / p.split_keys);
+        slot0 = (int64_t)bh * p.num_splits * p.rows_pad + row;
+        step = p.rows_pad;
+    }
     float m = -INFINITY, l = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < live; s0 += PRE) {
@@ -757,7 +766,7 @@ void attn_merge_rows_kernel(const AttnParams p)
         for (int i = 0; i < PRE; ++i) {
             m_i[i] = -INFINITY; l_i[i] = 0.f; ov[i] = floatx4{0.f, 0.f, 0.f, 0.f};
             if (s0 + i < live) {
-                const int64_t slot = slot0 + (int64_t)(s0 + i) * p.n_kv_heads * p.rows_pad;   // the next group's piece
+                const int64_t slot = slot0 + (s0 + i) * step;
                 m_i[i] = p.part_ml[slot * 2]; l_i[i] = p.part_ml[slot * 2 + 1];
                 ov[i] = __builtin_convertvector(*reinterpret_cast<const bf16x4*>(p.part_o + slot * D + col), floatx4);
             }
@@ -1083,6 +1092,18 @@ static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, i
     return s;
 }
 
+// Which merge uniform splits take.  A workgroup of attn_merge_kernel finishes one row with twelve groups of threads, so
+// with eight splits or fewer a third of it has nothing to do, and with more rows than CUs there are several to a CU; a
+// group per row has all its loads in flight as well and an eighth of the workgroups.  Us a layer, one row per workgroup
+// against this (64/8 heads, d 128):  8 splits, 208 rows a head over 12826 keys 26.7 / 25.2;  4 splits, 512 rows over
+// 12826 keys 44.3 / 40.7, over 3000 22.4 / 18.2;  3 splits, 208 rows over 400 keys 11.7 / 10.1.  With more splits the
+// second trip costs more (16 splits 18.7 / 20.1), with few rows the missing parallelism (8 splits, 14 rows 8.7 / 10.1).
+constexpr int kMergeRowPieces = 8;
+static bool attn_merges_by_row(int64_t total_rows, int num_splits)
+{
+    return num_splits <= kMergeRowPieces && total_rows > kNumCu;
+}
+
 template <int D, int MB, int KS, int TK, int NS, int NLD, bool STREAM>
 static int launch_attn_s(const AttnParams& p, hipStream_t stream)
 {
@@ -1279,11 +1300,11 @@ static int attn_impl(
     hipStream_t s = (hipStream_t)stream;
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);
     if (rc != SPECVLM_OK) return rc;
-    if (p.balanced) {
+    if (p.balanced || (p.num_splits > 1 && attn_merges_by_row(batch * n_kv_heads * (int64_t)rows, p.num_splits))) {
         const int per_wg = 256 / (head_dim / 4);
         dim3 grid((rows + per_wg - 1) / per_wg * batch * n_kv_heads);
-        if (head_dim == 128) hipLaunchKernelGGL((attn_merge_rows_kernel<128, 8>), grid, dim3(256), 0, s, p);
-        else                 hipLaunchKernelGGL((attn_merge_rows_kernel<64, 8>), grid, dim3(256), 0, s, p);
+        if (head_dim == 128) hipLaunchKernelGGL((attn_merge_rows_kernel<128, kMergeRowPieces>), grid, dim3(256), 0, s, p);
+        else                 hipLaunchKernelGGL((attn_merge_rows_kernel<64, kMergeRowPieces>), grid, dim3(256), 0, s, p);
         rc = launch_status();
     } else if (p.num_splits > 1) {
         dim3 grid(rows * batch * n_kv_heads);

@@ -1,0 +1,48 @@
+"""GPU parity of the decode-attention merge where its launch changes: eight splits and nine, as many query rows as CUs and
+one group of rows more, rows that do not fill the last workgroup, and a ragged batch in which requests have fewer live
+splits than the launch.  Bounds: those of every attention test."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev_bf16, host_f64, rnd_bits, assert_attn_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2508_16201_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
+    (8, 1300, 32, 4, 128, 8), (8, 1300, 36, 4, 128, 8), (8, 1300, 36, 4, 128, 9),      # 256 and 288 rows
+    (11, 900, 24, 1, 64, 8), (11, 900, 24, 1, 64, 2),                                  # 264 rows, 16 to a workgroup: half a one
+    (13, 300, 63, 3, 128, 3), (13, 1025, 63, 3, 128, 8),                               # 273 rows a head, the last workgroup short
+])
+def test_uniform_splits(B, q_len, kv_len, hq, hkv, d, splits):
+    q, k, v = (rnd_bits((n, h, d), 6000 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    scale = 1.0 / np.sqrt(d)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"q{q_len} kv{kv_len} {hq}/{hkv} d{d} splits {splits}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+def test_ragged_batch_with_named_splits(B):
+    lens, q_lens, hq, hkv, d = [1500, 3, 257, 1024], [6, 3, 2, 6], 64, 4, 128
+    q, k, v = [], [], []
+    for i, (n, m) in enumerate(zip(lens, q_lens)):
+        q.append(rnd_bits((m, hq, d), 6600 + i)); k.append(rnd_bits((n, hkv, d), 6700 + i)); v.append(rnd_bits((n, hkv, d), 6800 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.088,
+                        cu_q=cu(q_lens), cu_kv=cu(lens), max_q_len=6, max_kv_len=1500, num_splits=6)
+    torch.cuda.synchronize()
+    o = 0
+    for i, m in enumerate(q_lens):
+        assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.088)[0], f"request {i}")
+        o += m
