@@ -1,7 +1,9 @@
-"""GPU parity of specvlm_score where the merge of the key splits changes shape: one block of rows is cut into one split per
+"""GPU parity of specvlm_score where its merges change shape.  Key splits: one block of rows is cut into one split per
 64 keys, so 512 / 513 keys are the last launch with one lane per row and the first with eight, 4096 keys have the most
 splits a row can have, 4097 half as many; with prefix rows, hidden text keys and keyless splits.  Bounds: those of
-every score test."""
+every score test.  Partial columns: up to eight of them (layers x kv heads x row splits) one thread sums a column, then
+eight; one layer of 5, 8, 9 and 16 heads with one row split each, 2 and 17 layers of one head, columns that do not fill the last
+workgroup."""
 import pytest
 
 import test_gpu_prune as base
@@ -16,3 +18,11 @@ B = base.B
 ])
 def test_key_splits(B, V, L, P, hq, hkv, d, mode):
     base.test_score_matches_oracle(B, V, L, P, hq, hkv, d, mode)
+
+
+@pytest.mark.parametrize("layers,V,L,P,hq,hkv,d,mode", [
+    (1, 4100, 5, 0, 5, 5, 64, 0), (1, 300, 5, 0, 8, 8, 64, 0), (1, 300, 5, 0, 9, 9, 64, 0), (1, 2049, 3, 0, 16, 16, 64, 0), (2, 33, 3, 0, 1, 1, 64, 0), (17, 257, 4, 2, 1, 1, 64, 1),
+    (3, 1, 2, 0, 8, 2, 128, 0),
+])
+def test_partial_columns(B, layers, V, L, P, hq, hkv, d, mode):
+    base.test_score_layers_is_the_sum_over_layers(B, layers, V, L, P, hq, hkv, d, mode)
