@@ -38,7 +38,7 @@ struct AcceptParams {
 
 __device__ __forceinline__ void argmax_merge(float& bv, int& bi, float v, int i)
 {
-    // larger value wins; equal values: lower index wins.  (i < 0 = empty)
+    // larger value wins; equal values: lower index wins.  (i < 0 = empty; no NaN gets here)
     if (i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
 }
 
@@ -56,14 +56,16 @@ void accept_argmax_partial(const AcceptParams p)
 #pragma unroll
     for (int j = 0; j < kAccPerThread; ++j) {
         const int v = lo + j * 256 + threadIdx.x;
-        y[j] = v < hi ? x[v] : 0.f;
+        y[j] = v < hi ? x[v] : -INFINITY;
     }
-    float bv = 0.f; int bi = -1;
+    // A NaN is greater than nothing: it must not become a share's maximum, or it would hide the tokens that a merge
+    // compares with it, so the search starts at -inf.  It starts at token 0, and a NaN there stays: nothing is greater.
+    if (lo == 0 && threadIdx.x == 0 && y[0] != y[0]) y[0] = INFINITY;
+    float bv = -INFINITY;
+    int bi = lo + (int)threadIdx.x < hi ? lo + (int)threadIdx.x : -1;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
-        const int v = lo + j * 256 + threadIdx.x;
-        if (v < hi && (bi < 0 || y[j] > bv)) { bv = y[j]; bi = v; }     // ascending v: first maximum is kept
-    }
+    for (int j = 0; j < kAccPerThread; ++j)
+        if (y[j] > bv) { bv = y[j]; bi = lo + j * 256 + threadIdx.x; }     // ascending tokens: the first maximum is kept
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const float ov = __shfl_xor(bv, off);

@@ -2,8 +2,11 @@
 fit the staging area and that do not (129 rows x 31 / 32 chunks), more chunks than the final kernel has threads, more
 rows and chunks than one round of the argmax merge takes.  Bounds: those of the acceptance tests (greedy bit-exact,
 sampling equal outside a margin of 1e-4)."""
+import numpy as np
 import pytest
+import torch
 
+import oracle
 import test_gpu_accept as base
 
 pytestmark = pytest.mark.gpu
@@ -20,3 +23,33 @@ def test_sampling(B, batch, gamma, vocab, temp):
 @pytest.mark.parametrize("batch,gamma,vocab,sigma", [(2, 15, 524288, 0.3), (1, 16, 532481, 0.3), (3, 33, 8193, 0.1)])
 def test_greedy(B, batch, gamma, vocab, sigma):
     base.test_greedy_bit_exact(B, batch, gamma, vocab, sigma)
+
+
+def nan_rows():
+    """Logits with NaN where a merge could keep one: at the first token of a chunk, of a thread's and of a wave's share,
+    at token 0 (which then wins: nothing is greater), everywhere but in one place, and strewn about."""
+    r = np.random.default_rng(77)
+    x = r.standard_normal((8, 40000)).astype(np.float32)
+    x[0, 8192], x[0, 25000] = np.nan, 9.0
+    x[1, 0], x[1, 30000] = np.nan, 9.0
+    x[2, :39999] = np.nan
+    x[2, 0] = -np.inf
+    x[3, ::8192], x[3, 9], x[3, 8192] = np.nan, 9.0, np.nan
+    x[3, 0] = 0.0
+    x[4, r.random(40000) < 0.3] = np.nan
+    x[5, 64:8192:64], x[5, 8192 + 64], x[5, 64 + 256] = np.nan, np.nan, 9.0
+    x[6, :] = np.nan
+    x[7, 16384:], x[7, 0] = np.nan, -1.0
+    return x
+
+
+def test_a_nan_logit_is_never_the_largest(B):
+    x = nan_rows()
+    tokens = np.array([oracle.accept_greedy(row[None], np.zeros(0, np.int32))[1][0] for row in x], np.int32)
+    n, out = B.accept(base.cuda(x[None]), base.cuda(tokens[None, :7]))
+    parent = np.arange(-1, 7, dtype=np.int32)                          # a tree of one path drafts the same tokens
+    nodes = np.concatenate([[0], tokens[:7]]).astype(np.int32)
+    tn, _, tout = B.accept_tree(base.cuda(x[None]), base.cuda(nodes[None]), base.cuda(parent))
+    torch.cuda.synchronize()
+    assert out[0].cpu().tolist() == tokens.tolist() and n.item() == 7
+    assert tout[0].cpu().tolist() == tokens.tolist() and tn.item() == 7
