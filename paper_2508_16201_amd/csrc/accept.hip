@@ -5,7 +5,7 @@
 // Pass 1 (many workgroups): per (request, row, vocab chunk) partial statistics
 //   -- argmax with lowest-index ties for greedy; running (max, sum exp) of
 //   logit/T for the target rows and the draft rows for sampling.
-// Pass 2, greedy (one wave per request): merge the partials and walk the gamma tests in order.
+// Pass 2, greedy (one workgroup per request): merge the partials and walk the gamma tests in order.
 // Pass 2, sampling (many workgroups): every workgroup merges the partials and repeats the gamma
 //   accept tests (a few loads), so all agree on the first rejected position n; each then sums the
 //   mass of the residual max(p - q, 0) at row n (of p when every draft survived) over its chunk.
@@ -64,8 +64,10 @@ void accept_argmax_partial(const AcceptParams p)
     float bv = -INFINITY;
     int bi = lo + (int)threadIdx.x < hi ? lo + (int)threadIdx.x : -1;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j)
+    for (int j = 0; j < kAccPerThread; ++j) {
+        if (j % 4 == 0 && lo + j * 256 >= hi) break;                       // (a short chunk: 1024 tokens are four steps)
         if (y[j] > bv) { bv = y[j]; bi = lo + j * 256 + threadIdx.x; }     // ascending tokens: the first maximum is kept
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const float ov = __shfl_xor(bv, off);
@@ -83,28 +85,30 @@ void accept_argmax_partial(const AcceptParams p)
     }
 }
 
-// Argmax of every row from the pass-1 partials, into LDS: 16 lanes per row, so that the partials of 16 rows are one
-// round trip (a lane per row took one for every eight chunks: three at a vocabulary of 152064; 4.1 -> 2.3 us).
-constexpr int kFinalThreads = 256;
-__device__ __forceinline__ void accept_merge_argmax(const AcceptParams& p, int b, int rows, int* s_t)
+// Argmax of every row from the pass-1 partials, into LDS.  Bound: round trips.  One lane per row takes eight chunks a
+// trip and all rows at once (one wave); 16 lanes per row take 64 chunks a trip and 16 rows at once (four waves, and an
+// exchange): accept_final_lanes takes the fewer trips.
+constexpr int kFinalLanes = 16, kFinalThreads = 256;
+template <int LANES> __device__ __forceinline__ void accept_merge_argmax(const AcceptParams& p, int b, int rows, int* s_t)
 {
-    const int l = threadIdx.x & 15;
-    for (int row = threadIdx.x >> 4; row < rows; row += kFinalThreads / 16) {
+    constexpr int LOADS = LANES == 1 ? 8 : 4;                    // chunks in flight per lane
+    const int l = threadIdx.x % LANES;
+    for (int row = threadIdx.x / LANES; row < rows; row += blockDim.x / LANES) {
         const int64_t slot = ((int64_t)b * rows + row) * p.n_chunks;
         float bv = 0.f; int bi = -1;
-        for (int c0 = l; c0 < p.n_chunks; c0 += 64) {            // four chunks' loads in flight at a time
-            float pv[4]; int pi[4];
+        for (int c0 = l; c0 < p.n_chunks; c0 += LANES * LOADS) {
+            float pv[LOADS]; int pi[LOADS];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool in = c0 + 16 * j < p.n_chunks;
-                pv[j] = in ? p.part_val[slot + c0 + 16 * j] : 0.f;
-                pi[j] = in ? __float_as_int(p.part_aux[slot + c0 + 16 * j]) : -1;
+            for (int j = 0; j < LOADS; ++j) {
+                const bool in = c0 + LANES * j < p.n_chunks;
+                pv[j] = in ? p.part_val[slot + c0 + LANES * j] : 0.f;
+                pi[j] = in ? __float_as_int(p.part_aux[slot + c0 + LANES * j]) : -1;
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) argmax_merge(bv, bi, pv[j], pi[j]);
+            for (int j = 0; j < LOADS; ++j) argmax_merge(bv, bi, pv[j], pi[j]);
         }
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
+        for (int off = LANES / 2; off >= 1; off >>= 1) {
             const float ov = __shfl_xor(bv, off);
             const int oi = __shfl_xor(bi, off);
             argmax_merge(bv, bi, ov, oi);
@@ -113,7 +117,8 @@ __device__ __forceinline__ void accept_merge_argmax(const AcceptParams& p, int b
     }
 }
 
-__global__ __launch_bounds__(kFinalThreads)
+template <int LANES>
+__global__ __launch_bounds__(LANES == 1 ? kWave : kFinalThreads)
 void accept_greedy_final(const AcceptParams p)
 {
     // one workgroup per request; lane i of its first wave holds drafted token i (gamma <= 64), the first mismatch is
@@ -122,7 +127,7 @@ void accept_greedy_final(const AcceptParams p)
     __shared__ int s_t[65];
     const int32_t* x = p.tokens + (int64_t)b * p.gamma;
     const int drafted = lane < p.gamma ? x[lane] : -1;           // (in flight while the partials are merged)
-    accept_merge_argmax(p, b, p.gamma + 1, s_t);
+    accept_merge_argmax<LANES>(p, b, p.gamma + 1, s_t);
     __syncthreads();
     if (threadIdx.x >= kWave) return;
     const uint64_t mismatch = __ballot(lane < p.gamma && drafted != s_t[lane]);
@@ -432,7 +437,8 @@ void accept_sample_final(const AcceptParams p)
 // request merges the per-chunk argmax partials of all nodes; lane i of its first
 // wave holds node i's parent and drafted token, and that wave walks from the root,
 // moving to the lowest-numbered child that drafted the target's token (found by a ballot).
-__global__ __launch_bounds__(kFinalThreads)
+template <int LANES>
+__global__ __launch_bounds__(LANES == 1 ? kWave : kFinalThreads)
 void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* accepted_nodes)
 {
     const int b = blockIdx.x, lane = threadIdx.x;
@@ -441,7 +447,7 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
     const int32_t* x = p.tokens + (int64_t)b * n_nodes;
     const int my_tok = lane < n_nodes ? x[lane] : -1;            // (in flight while the partials are merged)
     const int my_par = lane < n_nodes ? parent[lane] : -1;       // parent[] is shared by the batch
-    accept_merge_argmax(p, b, n_nodes, s_t);
+    accept_merge_argmax<LANES>(p, b, n_nodes, s_t);
     __syncthreads();
     if (threadIdx.x >= kWave) return;
     int32_t* out = p.out_tokens + (int64_t)b * n_nodes;
@@ -464,6 +470,16 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
 }
 
 static int accept_chunks(int vocab) { return (vocab + kAccChunk - 1) / kAccChunk; }
+
+// Lanes per row of the greedy final kernels: 16 where that is fewer trips.  The whole call from a graph, us, one lane /
+// 16 lanes:  152064 tokens (19 chunks): 6 rows 8.4 / 6.7, 21 rows 9.0 / 8.5, 65 rows 13.4 / 14.4;  65537 (9 chunks): 16 rows
+// 7.8 / 7.0, 21 rows 7.8 / 8.0;  32000 (4 chunks): 6 rows 6.7 / 7.0, 21 rows 6.9 / 8.0, 65 rows 7.5 / 10.7.
+static int accept_final_lanes(int rows, int n_chunks)
+{
+    const int rounds = (rows * kFinalLanes + kFinalThreads - 1) / kFinalThreads;
+    const int trips = rounds * ((n_chunks + 4 * kFinalLanes - 1) / (4 * kFinalLanes));
+    return trips < (n_chunks + 7) / 8 ? kFinalLanes : 1;
+}
 
 }  // namespace specvlm
 
@@ -516,7 +532,10 @@ extern "C" int specvlm_accept(
     hipStream_t s = (hipStream_t)stream;
     if (!sampling) {
         hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, gamma + 1, batch), dim3(256), 0, s, p);
-        hipLaunchKernelGGL(accept_greedy_final, dim3(batch), dim3(kFinalThreads), 0, s, p);
+        if (accept_final_lanes(gamma + 1, p.n_chunks) == 1)
+            hipLaunchKernelGGL(accept_greedy_final<1>, dim3(batch), dim3(kWave), 0, s, p);
+        else
+            hipLaunchKernelGGL(accept_greedy_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
         hipLaunchKernelGGL(accept_softmax_partial, dim3(p.n_chunks, 2 * gamma + 1, batch), dim3(256), 0, s, p);
         hipLaunchKernelGGL(accept_mass_partial, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
@@ -554,6 +573,9 @@ extern "C" int specvlm_accept_tree(
     p.norm = nullptr; p.chunk_mass = nullptr; p.n_rej = nullptr;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, n_nodes, batch), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(accept_tree_final, dim3(batch), dim3(kFinalThreads), 0, s, p, parent, accepted_nodes);
+    if (accept_final_lanes(n_nodes, p.n_chunks) == 1)
+        hipLaunchKernelGGL(accept_tree_final<1>, dim3(batch), dim3(kWave), 0, s, p, parent, accepted_nodes);
+    else
+        hipLaunchKernelGGL(accept_tree_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p, parent, accepted_nodes);
     return launch_status();
 }

@@ -8,6 +8,7 @@ import torch
 
 import oracle
 import test_gpu_accept as base
+import test_gpu_tree as tree
 
 pytestmark = pytest.mark.gpu
 B = base.B
@@ -23,6 +24,18 @@ def test_sampling(B, batch, gamma, vocab, temp):
 @pytest.mark.parametrize("batch,gamma,vocab,sigma", [(2, 15, 524288, 0.3), (1, 16, 532481, 0.3), (3, 33, 8193, 0.1)])
 def test_greedy(B, batch, gamma, vocab, sigma):
     base.test_greedy_bit_exact(B, batch, gamma, vocab, sigma)
+
+
+# where the merge goes from one lane a row to 16 and back: 8 and 9 chunks, 16 and 17 rows, 65 rows of 15 to 49 chunks
+@pytest.mark.parametrize("batch,gamma,vocab", [(2, 15, 65536), (2, 15, 65537), (2, 16, 65537), (1, 64, 122880),
+                                               (1, 64, 401408), (3, 0, 70000)])
+def test_greedy_at_the_merge_s_edges(B, batch, gamma, vocab):
+    base.test_greedy_bit_exact(B, batch, gamma, vocab, 0.3)
+
+
+@pytest.mark.parametrize("batch,n_nodes,vocab", [(4, 16, 65537), (4, 17, 65537), (4, 64, 65537), (4, 33, 140000)])
+def test_tree_at_the_merge_s_edges(B, batch, n_nodes, vocab):
+    tree.test_accept_tree_bit_exact_on_random_trees(B, batch, n_nodes, vocab)
 
 
 def nan_rows():
