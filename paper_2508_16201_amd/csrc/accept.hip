@@ -19,6 +19,7 @@ constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / kWave;
 constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup
 constexpr int kAccPerThread = kAccChunk / 256;   // of which each of the 256 threads takes this many
+constexpr int kAccShort = kAccThreads;           // vocabularies of at most so many have sampling kernels of their own
 
 struct AcceptParams {
     const float* target;      // [batch, gamma+1, vocab]
@@ -249,12 +250,16 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
 // partials, one for the rejected row), so the first three run beside each other: the partials of all rows are fetched
 // by all threads, into LDS, where they fit (a thread per row fetching eight chunks at a time took one trip per eight).
 // gamma 7, 152064 tokens: 8.5 -> 5.9 us with the loads of both rows batched (AcceptWeight); the final kernel 9.3 -> 5.6.
+// SHORT: one chunk, of which a thread here has four tokens and a wave of the final kernel 64.  There is nothing to stage,
+// and going through a whole chunk cost more than it fetched (1024 tokens, gamma 5, the whole call: 13.5 us, now 10.6; with
+// a branch inside instead of kernels of their own the large vocabularies lost 0.5 us).
 constexpr int kMergeStage = 4096;           // pass-1 partials of a request that are staged (152064 tokens: 215 rows)
 
+template <bool SHORT>
 __global__ __launch_bounds__(256)
 void accept_mass_partial(const AcceptParams p)
 {
-    __shared__ float s_val[kMergeStage], s_aux[kMergeStage];
+    __shared__ float s_val[SHORT ? 1 : kMergeStage], s_aux[SHORT ? 1 : kMergeStage];
     __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
     __shared__ float s_part[4];
     __shared__ int s_n;
@@ -275,7 +280,7 @@ void accept_mass_partial(const AcceptParams p)
     }
     const float* val = p.part_val + (int64_t)b * rows * p.n_chunks;
     const float* aux = p.part_aux + (int64_t)b * rows * p.n_chunks;
-    if (rows * (int64_t)p.n_chunks <= kMergeStage) {
+    if (!SHORT && rows * (int64_t)p.n_chunks <= kMergeStage) {
         for (int i = tid; i < rows * p.n_chunks; i += 256) { s_val[i] = val[i]; s_aux[i] = aux[i]; }
         __syncthreads();
         accept_merge_rows(p, rows, s_val, s_aux, s_m, s_z);
@@ -303,11 +308,11 @@ void accept_mass_partial(const AcceptParams p)
     }
     const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
     const int lo = chunk * kAccChunk, hi = min(p.vocab, lo + kAccChunk);
-    float w[kAccPerThread];
+    float w[SHORT ? kAccShort / 256 : kAccPerThread];
     weight(w, lo + tid, 256, hi);
     float mine = 0.f;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) mine += w[j];
+    for (const float x : w) mine += x;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
     if (lane == 0) s_part[wave] = mine;
@@ -315,6 +320,7 @@ void accept_mass_partial(const AcceptParams p)
     if (tid == 0) p.chunk_mass[(int64_t)b * p.n_chunks + chunk] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
 }
 
+template <bool SHORT>
 __global__ __launch_bounds__(kAccThreads)
 void accept_sample_final(const AcceptParams p)
 {
@@ -334,9 +340,11 @@ void accept_sample_final(const AcceptParams p)
     const int second = p.gamma > 0 ? 2 : 0;                      // (gamma = 0: one row, nothing to reject)
     const AcceptWeight weight = accept_weight(p, b, n, nm[0], nm[1], nm[second], nm[second + 1]);
     if (tid == 0) s_y = -1;
-    s_cm[tid] = my_cm;
-    __syncthreads();
-    if (p.n_chunks <= kAccThreads) cm = s_cm;
+    if (!SHORT) {
+        s_cm[tid] = my_cm;
+        __syncthreads();
+        if (p.n_chunks <= kAccThreads) cm = s_cm;
+    }
     // total mass and the owner of the goal among the chunks: the LAST chunk with mass whose prefix
     // does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that
     // rounding put at or beyond the total lands on the last chunk with mass).  Every thread walks
@@ -380,7 +388,7 @@ void accept_sample_final(const AcceptParams p)
         const int lo1 = own1 * kAccChunk, hi1 = min(p.vocab, lo1 + kAccChunk);
         const int seg2 = ((hi1 - lo1 + kAccWaves - 1) / kAccWaves + 63) & ~63;
         const int lo2 = min(hi1, lo1 + wave * seg2), hi2 = min(hi1, lo2 + seg2);
-        constexpr int STEPS = kAccChunk / kAccThreads;           // of 64 tokens of a wave's share
+        constexpr int STEPS = SHORT ? 1 : kAccChunk / kAccThreads;   // of 64 tokens of a wave's share
         float w2[STEPS], mine2 = 0.f;
         weight(w2, lo2 + lane, 64, hi2);
 #pragma unroll
@@ -538,8 +546,13 @@ extern "C" int specvlm_accept(
             hipLaunchKernelGGL(accept_greedy_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
         hipLaunchKernelGGL(accept_softmax_partial, dim3(p.n_chunks, 2 * gamma + 1, batch), dim3(256), 0, s, p);
-        hipLaunchKernelGGL(accept_mass_partial, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
-        hipLaunchKernelGGL(accept_sample_final, dim3(batch), dim3(kAccThreads), 0, s, p);
+        if (vocab <= kAccShort) {
+            hipLaunchKernelGGL(accept_mass_partial<true>, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
+            hipLaunchKernelGGL(accept_sample_final<true>, dim3(batch), dim3(kAccThreads), 0, s, p);
+        } else {
+            hipLaunchKernelGGL(accept_mass_partial<false>, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
+            hipLaunchKernelGGL(accept_sample_final<false>, dim3(batch), dim3(kAccThreads), 0, s, p);
+        }
     }
     return launch_status();
 }

@@ -26,6 +26,14 @@ def test_greedy(B, batch, gamma, vocab, sigma):
     base.test_greedy_bit_exact(B, batch, gamma, vocab, sigma)
 
 
+# short chunks (every wave has one step of 64 tokens up to 1024, two from 1025), eight chunks and nine (staged from there)
+@pytest.mark.parametrize("batch,gamma,vocab,temp", [
+    (8, 3, 63, 1.0), (8, 3, 1024, 1.0), (8, 3, 1025, 1.0), (4, 2, 8192 + 1024, 0.8), (4, 2, 8192 + 1, 1.0), (2, 5, 65536, 1.0), (2, 5, 65537, 1.0),
+])
+def test_sampling_at_the_ends_of_chunks(B, batch, gamma, vocab, temp):
+    base.test_sampling_matches_oracle_outside_margin(B, batch, gamma, vocab, temp)
+
+
 # where the merge goes from one lane a row to 16 and back: 8 and 9 chunks, 16 and 17 rows, 65 rows of 15 to 49 chunks
 @pytest.mark.parametrize("batch,gamma,vocab", [(2, 15, 65536), (2, 15, 65537), (2, 16, 65537), (1, 64, 122880),
                                                (1, 64, 401408), (3, 0, 70000)])
