@@ -355,10 +355,11 @@ void accept_sample_final(const AcceptParams p)
         // no residual mass (p == q): fall back to the target's most likely token
         const int seg = ((p.vocab + kAccWaves - 1) / kAccWaves + 63) & ~63;
         const int lo = min(p.vocab, wave * seg), hi = min(p.vocab, lo + seg);
-        float bv = 0.f; int bi = -1;
+        float bv = -INFINITY;
+        int bi = lo + lane < hi ? lo + lane : -1;
         for (int v = lo + lane; v < hi; v += 64) {
             const float y = weight.trow[v];
-            if (bi < 0 || y > bv) { bv = y; bi = v; }
+            if (y > bv) { bv = y; bi = v; }                      // (never a NaN, as in accept_argmax_partial)
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
@@ -375,7 +376,7 @@ void accept_sample_final(const AcceptParams p)
         __syncthreads();
     } else {
         const float goal = u_last * W;
-        int own1 = -1;
+        int own1 = 0;                                            // (no chunk qualifies for a uniform below 0 or NaN)
         float pre1 = 0.f, acc1 = 0.f;
         for (int c = 0; c < p.n_chunks; ++c) {
             const float m = cm[c];

@@ -74,3 +74,17 @@ def test_a_nan_logit_is_never_the_largest(B):
     torch.cuda.synchronize()
     assert out[0].cpu().tolist() == tokens.tolist() and n.item() == 7
     assert tout[0].cpu().tolist() == tokens.tolist() and tn.item() == 7
+
+
+@pytest.mark.parametrize("vocab", [700, 8192, 20000])
+def test_a_final_uniform_outside_its_range_stays_inside_the_row(B, vocab):
+    """Outside [0, 1) nothing is promised but a token of the row; at 1 and above it is the last one with mass."""
+    r = np.random.default_rng(vocab)
+    x = r.standard_normal((5, 1, vocab)).astype(np.float32)
+    x[:, 0, vocab - 40:] = -np.inf
+    u = np.array([[-0.25], [-np.inf], [np.nan], [1.0], [2.0]], np.float32)
+    n, out = B.accept(base.cuda(x), base.cuda(np.zeros((5, 0), np.int32)), uniforms=base.cuda(u))
+    torch.cuda.synchronize()
+    out = out.cpu().numpy().ravel()
+    assert n.cpu().tolist() == [0] * 5
+    assert ((0 <= out) & (out < vocab)).all() and out[3] == out[4] == vocab - 41
