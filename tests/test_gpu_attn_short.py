@@ -63,3 +63,12 @@ def test_tree_over_a_short_cache(B, n_nodes, kv_len, hq, hkv, d):
     out = B.tree_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), 0.1, torch.from_numpy(masks.view(np.int64)).cuda())
     torch.cuda.synchronize()
     assert_attn_close(out, want, f"tree {n_nodes} over {kv_len}")
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d", [
+    (1, 1345, 14, 2, 64), (2, 1376, 14, 2, 64), (3, 1377, 4, 1, 64), (1, 961, 4, 1, 64),      # a last wave of 1, 32, 33, 1 keys
+    (1, 897, 8, 2, 128), (6, 929, 16, 2, 128), (2, 769, 8, 1, 128), (8, 513, 32, 4, 128),
+    (40, 1346, 4, 1, 64), (40, 898, 4, 1, 128),          # a block that lies across waves: the last one has 1 or 2 of its keys
+])
+def test_a_last_wave_of_few_keys(B, q_len, kv_len, hq, hkv, d):
+    test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, 0)
