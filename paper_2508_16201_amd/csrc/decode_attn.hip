@@ -1223,7 +1223,8 @@ extern "C" size_t specvlm_decode_attn_workspace_bytes(int batch, int q_len, int 
         return 0;
     const int rows = (n_q_heads / n_kv_heads) * q_len;
     if (q_len > kMaxQueryBlock) return 0;
-    if (attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) return 256;
+    // (a launch without splits uses none of it, but asks for it all the same: what is enough for a shape stays enough for
+    // every smaller one, whichever launch that takes)
     int n_rgroups, mb;
     attn_row_groups(rows, &n_rgroups, &mb);
     const int rows_pad = n_rgroups * mb * 16;
@@ -1278,13 +1279,6 @@ static int attn_impl(
     p.batch = batch; p.q_len = q_len; p.kv_len = kv_len;
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.group = group;
     p.scale_log2 = softmax_scale * kLog2e;
-    if (const int chunks = attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) {
-        p.n_rgroups = (rows + 15) / 16;
-        p.n_main = batch * n_kv_heads * p.n_rgroups * (head_dim / 16);
-        const int pieces = (kv_len * (head_dim / 8) + kDirectWaves * kWave - 1) / (kDirectWaves * kWave);
-        p.n_work = p.n_main + (batch == 1 ? kNumXcd * (pieces < kPrefetchers ? pieces : kPrefetchers) : 0);
-        return launch_attn_direct(p, head_dim, chunks, (hipStream_t)stream);
-    }
     p.balanced = attn_is_balanced(batch, num_splits, n_kv_heads, rows) ? 1 : 0;
     p.max_wg = kNumCu;
     p.tile_keys = mb == 1 ? 128 : 64;                 // TK of the launch shape chosen below
@@ -1305,6 +1299,13 @@ static int attn_impl(
         p.seg_table = (int32_t*)((char*)p.part_ml + align256(slots * 2 * sizeof(float)));   // (used in balanced mode)
     }
     hipStream_t s = (hipStream_t)stream;
+    if (const int chunks = attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) {
+        p.n_rgroups = (rows + 15) / 16;
+        p.n_main = batch * n_kv_heads * p.n_rgroups * (head_dim / 16);
+        const int pieces = (kv_len * (head_dim / 8) + kDirectWaves * kWave - 1) / (kDirectWaves * kWave);
+        p.n_work = p.n_main + (batch == 1 ? kNumXcd * (pieces < kPrefetchers ? pieces : kPrefetchers) : 0);
+        return launch_attn_direct(p, head_dim, chunks, s);
+    }
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);
     if (rc != SPECVLM_OK) return rc;
     if (p.balanced || (p.num_splits > 1 && attn_merges_by_row(batch * n_kv_heads * (int64_t)rows, p.num_splits))) {

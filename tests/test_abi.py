@@ -94,3 +94,23 @@ def test_bad_arguments_are_rejected_before_any_launch(B):
     assert rc == -1
     rc = lib.specvlm_select(null, null, C.c_void_p(8), C.c_void_p(8), null, 2, 10, 1, null, null, null, null, 0, null)
     assert rc == -1
+
+
+def test_short_caches_keep_their_workspace(B):
+    """A cache that one launch serves without splits asks for the workspace of its splits and is refused without it, as a
+    longer one is: a program that was sized for its largest shape may meet either."""
+    lib = B.lib()
+    at = C.c_void_p(4096)                                       # (never read: every call below is refused)
+    for batch, q_len, kv_len, hq, hkv, d in ((1, 1, 1511, 14, 2, 64), (1, 6, 1000, 64, 8, 128), (4, 1, 500, 28, 4, 128)):
+        need = B.decode_attn_workspace_bytes(batch, q_len, kv_len, hq, hkv, d)
+        assert need > 256
+        cu = at if batch > 1 else None
+        for ws, size in ((None, 0), (C.c_void_p(4096 + 16), need), (at, need - 1)):
+            rc = lib.specvlm_decode_attn(at, hq * d, d, at, at, hkv * d, d, cu, cu, batch, q_len, kv_len, hq, hkv, d, 0.1,
+                                         at, None, 0, ws, size, None)
+            assert rc == -3, (kv_len, size, rc)
+    for hq, hkv, d in ((6, 3, 64), (10, 5, 64), (14, 2, 64), (64, 8, 128), (20, 10, 128)):
+        sizes = [B.decode_attn_workspace_bytes(b, 1, 1536, hq, hkv, d) for b in (1, 2, 3, 4)]
+        for n in (100, 700, 1000, 1300, 1535):
+            assert all(B.decode_attn_workspace_bytes(b, 1, n, hq, hkv, d) <= s for b, s in zip((1, 2, 3, 4), sizes))
+        assert sizes[0] <= min(sizes)
