@@ -1052,7 +1052,20 @@ static void attn_row_groups(int rows, int* n_groups, int* mb)
 // Where the line lies (us a layer, splits and merge against this, one to four row blocks per kv head, caches of 40 to
 // 160 layers in turn):  head size 64:  512 keys 6.5-7.9 / 3.9-4.3, 1024: 6.7-8.0 / 5.0-5.4, 1536: 6.7-8.1 / 6.1-6.5,
 // 1790: 6.9-8.3 / 6.7-7.1;  head size 128:  512 keys 7.5-9.6 / 5.1-5.9, 1024: 7.7-9.6 / 7.1-8.7, 1280: 7.7-9.8 / 8.0-10.1.
-// More workgroups than CUs would take a second round.
+// With five row blocks and more (up to 64) the splits' side grows faster: 1536 keys of size 64 8.3-8.8 / 6.6-8.0, 1024 of
+// size 128 9.6-10.1 / 7.9-9.3.  More workgroups than CUs would take a second round.
+// Less than that where the helpers miss heads or there are none:
+//   one request whose heads do not divide the XCDs (a helper reads one head an XCD): 3, 5 or 6 heads, size 64, 1400 keys,
+//     token-major 6.9-7.2 / 7.6-8.1, 1280 keys 0 to 10 % faster than splits; 10 and more heads lose from 1100 keys on (32 heads,
+//     1200 keys 8.5 / 9.3) and win 8 % at 1000; size 128, 16 heads, 1024 keys 8.5 / 9.7, 768 keys 8.5 / 7.5;
+//   a batch of more than 16 heads in all with more than four each, size 64: 4 requests of 8 heads, token-major, 1536 keys
+//     10.7 / 12.0, 1280 keys 10.6 / 9.3; more than 16 heads each, 2 requests of 24 heads, 1280 keys 10.7 / 11.1;
+//   a batch that fetches too much.  A head's slices lie on as many XCDs as its ids are dealt to, and each of these fetches
+//     the head's rows (MB over all XCDs; the balanced pieces cost more with more requests):  32 requests of 2 heads, size
+//     64, 1500 keys, 98 MB 16.8 / 18.2, 1280 keys, 84 MB 16.6 / 15.9;  size 128:  8 of 3 heads, 900 keys, 88 MB 12.5 / 14.8;
+//     6 of 5, 768 keys, 94 MB 12.0 / 13.5;  5 of 6, 900 keys, 55 MB 12.4 / 13.1;  16 of 2, 900 keys, 59 MB 14.0 / 13.5.
+// Other batches (2 to 64 requests, against the balanced pieces and their merge): size 64, 14/2 heads, 2 requests of 1536
+// keys 10.7 / 7.5, 8 requests 12.5 / 8.1; size 128, 64/8 heads, 2 requests of 1024 keys 10.1 / 8.7, 4 requests 11.6 / 10.2.
 constexpr int kDirectWaves = 8, kShortWaves = 4;
 constexpr int kPrefetchers = 15;       // helper workgroups per XCD, at most (1511 keys: 7: 6.5 us, 15: 6.3, 28: 6.4)
 static int attn_direct_chunks(int batch, int kv_len, int n_kv_heads, int head_dim, int rows, int num_splits)
@@ -1060,8 +1073,18 @@ static int attn_direct_chunks(int batch, int kv_len, int n_kv_heads, int head_di
     if (num_splits != 0) return 0;                            // (a caller that names a split count gets it)
     const int64_t wgs = (int64_t)batch * n_kv_heads * ((rows + 15) / 16) * (head_dim / 16);
     if (wgs > kNumCu) return 0;
+    int most = head_dim == 64 ? 6 : 4;
+    if (batch == 1) {
+        if (kNumXcd % n_kv_heads != 0) most = head_dim == 64 && n_kv_heads < kNumXcd ? 5 : head_dim == 64 ? 4 : 3;
+    } else {
+        const int shared = n_kv_heads & -n_kv_heads;          // (ids run over the heads first: a head's step by n_kv_heads)
+        int spread = shared < kNumXcd ? kNumXcd / shared : 1;
+        if (spread > head_dim / 16) spread = head_dim / 16;
+        if (4ll * batch * n_kv_heads * kv_len * head_dim * spread > ((44ll + batch) << 20)) return 0;
+        if (head_dim == 64 && n_kv_heads > 4 && batch * n_kv_heads > 16) most = n_kv_heads > 16 ? 4 : 5;
+    }
     const int ch = (kv_len + kDirectWaves * kChunkKeys - 1) / (kDirectWaves * kChunkKeys);
-    return ch <= (head_dim == 64 ? 6 : 4) ? ch : 0;
+    return ch <= most ? ch : 0;
 }
 
 static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, int num_splits)

@@ -39,6 +39,20 @@ def test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, splits):
     np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
 
 
+def ragged_case(B, lens, q_lens, hq, hkv, d, **more):
+    q, k, v = [], [], []
+    for i, (n, m) in enumerate(zip(lens, q_lens)):
+        q.append(rnd_bits((m, hq, d), 5600 + i)); k.append(rnd_bits((n, hkv, d), 5700 + i)); v.append(rnd_bits((n, hkv, d), 5800 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.125,
+                        cu_q=cu(q_lens), cu_kv=cu(lens), max_q_len=max(q_lens), max_kv_len=max(lens), **more)
+    torch.cuda.synchronize()
+    o = 0
+    for i, m in enumerate(q_lens):
+        assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.125)[0], f"request {i}")
+        o += m
+
+
 def test_ragged_batch_of_short_caches(B):
     lens, q_lens, hq, hkv, d = [1500, 3, 257, 1024, 64], [1, 3, 2, 3, 1], 14, 2, 64
     q, k, v = [], [], []
@@ -52,6 +66,23 @@ def test_ragged_batch_of_short_caches(B):
     for i, m in enumerate(q_lens):
         assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.125)[0], f"request {i}")
         o += m
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [
+    ([1281, 40], 12, 6, 64), ([1024, 1025, 3], 10, 5, 64), ([1281] * 3, 12, 6, 64),       # more than 16 heads: five chunks
+    ([1300, 70, 900], 8, 4, 64), ([1281] + [33 + i for i in range(31)], 4, 2, 64),         # every CU, two heads: five chunks
+    ([769, 5], 16, 8, 128), ([770, 300, 129, 768], 10, 5, 128), ([769, 100, 200], 10, 5, 128),
+    ([1000] + [40 + 9 * i for i in range(31)], 4, 1, 128),
+])
+def test_ragged_batch_at_the_last_chunk_count(B, lens, hq, hkv, d):
+    ragged_case(B, lens, [1] * len(lens), hq, hkv, d)
+
+
+@pytest.mark.parametrize("kv_len,hq,hkv,d", [
+    (1280, 6, 3, 64), (1281, 6, 3, 64), (1024, 20, 10, 64), (1025, 20, 10, 64), (768, 32, 16, 128), (769, 32, 16, 128), (769, 16, 8, 128),
+])
+def test_heads_that_do_not_divide_the_xcds(B, kv_len, hq, hkv, d):
+    test_edges_match_oracle(B, 2, kv_len, hq, hkv, d, 0)
 
 
 @pytest.mark.parametrize("n_nodes,kv_len,hq,hkv,d", [(26, 300, 8, 1, 128), (64, 700, 4, 2, 64), (40, 40, 4, 1, 64)])
