@@ -1123,15 +1123,20 @@ static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, i
 }
 
 // Which merge uniform splits take.  A workgroup of attn_merge_kernel finishes one row with twelve groups of threads, so
-// with eight splits or fewer a third of it has nothing to do, and with more rows than CUs there are several to a CU; a
-// group per row has all its loads in flight as well and an eighth of the workgroups.  Us a layer, one row per workgroup
-// against this (64/8 heads, d 128):  8 splits, 208 rows a head over 12826 keys 26.7 / 25.2;  4 splits, 512 rows over
-// 12826 keys 44.3 / 40.7, over 3000 22.4 / 18.2;  3 splits, 208 rows over 400 keys 11.7 / 10.1.  With more splits the
-// second trip costs more (16 splits 18.7 / 20.1), with few rows the missing parallelism (8 splits, 14 rows 8.7 / 10.1).
+// with eight splits or fewer a third of it has nothing to do, and when there are several such workgroups to a CU a group
+// per row, which has all its loads in flight as well, does it in an eighth (head size 64: a sixteenth) of the workgroups.
+// Us a layer, one row per workgroup against this (2 to 8 splits; keys in brackets):
+//   size 128, 8 heads:  512 rows [1600] 11.0-15.6 / 11.6-15.6, 768 [3000] 0 to 3 % faster, 1664 [12826] 28.9-66.0 / 27.6-64.0,
+//     4096 [3000] 22.4 / 18.2;  10 heads:  800 [3000] 13.2-15.2 / 14.3-15.6;  1 or 2 heads:  1280 [3000] 7 % slower to 3 % faster,
+//     1536 3 % slower to 6 % faster, 2048 2 to 9 % faster;
+//   size 64, 8 heads:  1024 [1600] 9.8-12.8 / 10.4-12.9, 1536 [3000] 1 % slower to 2 % faster, 4096 [1600] 13.6-17.8 / 11.6-16.1;
+//     10 heads:  2560 [3000], 8 splits 18.3 / 19.0;  2 heads:  2048 [3000] 7 % slower to 3 % faster, 3072 0 to 9 % faster.
+// Where the kv heads are a multiple of the XCDs a head's partials lie in the L2 of the XCD that merges them; elsewhere more
+// rows are needed to hide the way.  With more splits the second trip costs more (16 splits 18.7 / 20.1).
 constexpr int kMergeRowPieces = 8;
-static bool attn_merges_by_row(int64_t total_rows, int num_splits)
+static bool attn_merges_by_row(int n_kv_heads, int64_t total_rows, int head_dim, int num_splits)
 {
-    return num_splits <= kMergeRowPieces && total_rows > kNumCu;
+    return num_splits <= kMergeRowPieces && total_rows * head_dim >= (n_kv_heads % kNumXcd == 0 ? 3 : 7) * kNumCu * 128ll;
 }
 
 template <int D, int MB, int KS, int TK, int NS, int NLD, bool STREAM>
@@ -1331,7 +1336,8 @@ static int attn_impl(
     }
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);
     if (rc != SPECVLM_OK) return rc;
-    if (p.balanced || (p.num_splits > 1 && attn_merges_by_row(batch * n_kv_heads * (int64_t)rows, p.num_splits))) {
+    if (p.balanced || (p.num_splits > 1 &&
+                       attn_merges_by_row(n_kv_heads, batch * n_kv_heads * (int64_t)rows, head_dim, p.num_splits))) {
         const int per_wg = 256 / (head_dim / 4);
         dim3 grid((rows + per_wg - 1) / per_wg * batch * n_kv_heads);
         if (head_dim == 128) hipLaunchKernelGGL((attn_merge_rows_kernel<128, kMergeRowPieces>), grid, dim3(256), 0, s, p);

@@ -46,3 +46,28 @@ def test_ragged_batch_with_named_splits(B):
     for i, m in enumerate(q_lens):
         assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.088)[0], f"request {i}")
         o += m
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
+    (12, 700, 64, 8, 128, 4), (11, 700, 64, 8, 128, 4),                    # 768 and 704 rows, a head per XCD
+    (24, 1025, 64, 8, 64, 8), (24, 1100, 64, 8, 64, 9), (23, 300, 64, 8, 64, 2),      # 1536 and 1472 at head size 64
+    (28, 600, 64, 2, 128, 3), (27, 600, 64, 2, 128, 3), (56, 500, 64, 2, 64, 4),      # 1792, 1728 and 3584 rows, fewer heads
+    (37, 400, 49, 7, 128, 2), (64, 300, 57, 3, 64, 2),                     # 1813 and 3648: rows that do not fill the last workgroup
+])
+def test_uniform_splits_of_many_rows(B, q_len, kv_len, hq, hkv, d, splits):
+    test_uniform_splits(B, q_len, kv_len, hq, hkv, d, splits)
+
+
+def test_ragged_batch_of_many_rows(B):
+    lens, q_lens, hq, hkv, d = [900, 20, 257, 640], [9, 9, 2, 4], 64, 8, 128     # 2304 rows at most, 1 to 6 live splits
+    q, k, v = [], [], []
+    for i, (n, m) in enumerate(zip(lens, q_lens)):
+        q.append(rnd_bits((m, hq, d), 6900 + i)); k.append(rnd_bits((n, hkv, d), 7000 + i)); v.append(rnd_bits((n, hkv, d), 7100 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.088,
+                        cu_q=cu(q_lens), cu_kv=cu(lens), max_q_len=9, max_kv_len=900, num_splits=6)
+    torch.cuda.synchronize()
+    o = 0
+    for i, m in enumerate(q_lens):
+        assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.088)[0], f"request {i}")
+        o += m
