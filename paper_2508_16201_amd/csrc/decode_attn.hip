@@ -803,9 +803,8 @@ void attn_merge_rows_kernel(const AttnParams p)
 //     slices recompute the logits, and in return there are no partial results and no merge launch, which costs
 //     2.8 us behind a first kernel of 3.6.  Every workgroup pulls all of K and the cache lines of V through one CU,
 //     so this is for short caches only: attn_direct_chunks has the line and both sides' times.
-//   COLS = D: a workgroup computes a key split and writes a partial result for attn_merge_kernel (head size 64,
-//     one block of query rows: 7.15 -> 6.8 us at 1537 to 2000 keys against the ring kernel; at head size 128 the two
-//     are equal).
+//   COLS = D: a workgroup computes a key split and writes a partial result for the merge (head size 64, one block of
+//     query rows: launch_attn_d has both sides' times; at head size 128 it equals the ring kernel).
 //
 // Helper workgroups.  The few workgroups that compute bring in about 100 bytes/ns each, bound by their CU's
 // outstanding misses; helpers on the same XCD touch the head's rows at the same time, so that most of those misses
@@ -1227,9 +1226,16 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
     // they save (6.7 against 6.4 us per layer).
     switch (mb) {
         case 1:
-            // (one chunk of 32 keys for each of four waves, results for the merge; longer splits need the ring, and a
-            // single split writes output instead of a partial result)
-            if (D == 64 && p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced) return launch_short<D, kShortWaves, 1, D>(p, stream);
+            // Splits of at most 128 keys: one chunk of 32 keys for each of four waves, results for the merge (a single split
+            // writes output).  Us a layer, ring / this:  14/2 heads 2000 keys 7.2 / 6.9, 12000 10.0 / 9.6;  7/1 heads 24000 keys
+            // 12.8 / 12.5;  named splits 12/4 heads, 256 of 32768 keys 20.2 / 18.6, 4 requests of 14/2 heads, 128 splits of 16384
+            // keys 18.2 / 15.5.  Left out is what loses: one request of eight heads, a head an XCD, with 128 splits and more
+            // (16384 keys token-major 15.0 / 15.5, 24000 in 256 splits 19.1 / 19.9; 96 splits of 12288 keys win 10 %).
+            if constexpr (D == 64) {
+                const bool loses = p.batch == 1 && p.n_kv_heads == kNumXcd && p.num_splits >= 128;
+                if (p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced && !loses)
+                    return launch_short<D, kShortWaves, 1, D>(p, stream);
+            }
             return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
         case 2: return launch_attn<D, 2, 2, 64, 3, 4>(p, stream);
         case 3: return launch_attn<D, 3, 2, 64, 3, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)

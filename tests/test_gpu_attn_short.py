@@ -103,3 +103,17 @@ def test_tree_over_a_short_cache(B, n_nodes, kv_len, hq, hkv, d):
 ])
 def test_a_last_wave_of_few_keys(B, q_len, kv_len, hq, hkv, d):
     test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, 0)
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
+    (1, 16257, 4, 1, 64, 128), (2, 2080, 8, 2, 64, 17),       # 128 keys a split and a last one of 1; 123 and 112
+    (1, 2081, 4, 1, 64, 17), (4, 2049, 4, 4, 64, 16),         # 123 and 113; 129: one key too many for the four waves
+    (1, 16384, 8, 8, 64, 128), (1, 16256, 8, 8, 64, 127),     # a head per XCD: the ring kernel from 128 splits on
+])
+def test_short_splits(B, q_len, kv_len, hq, hkv, d, splits):
+    test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, splits)
+
+
+def test_ragged_batch_of_short_splits(B):
+    """128 keys a split; last splits of 1, 32, 33 and 128 keys, requests with fewer live splits than the launch, waves without keys."""
+    ragged_case(B, [1280, 129, 160, 161, 3, 1024], [2, 1, 2, 1, 2, 2], 14, 2, 64, num_splits=10)
