@@ -27,6 +27,11 @@ constexpr int kSelWaves = kSelThreads / kWave;
 // rows share their upper 16 bits), but every copy is also cleared, summed and moves the pass's end: cycles of the select
 // kernel at 12544 tokens, long-tailed / clustered within 1e-3 / within 1e-5, by the copies of passes 1 to 3:  2: 20.0 /
 // 26.1 / 31.7 thousand, 4: 19.8 / 22.7 / 25.5, 8: 20.3 / 21.4 / 22.2, 16: 25.3, 32: 28.7; 16 or 64 in pass 0 are equal.
+// More keys to a thread mean more additions to every sum: the selection with 33 to 64 of them takes sixteen copies
+// (65536 tokens, a twentieth kept, us with 8 / 16, the 64 copies of before in brackets: long-tailed 31.7 / 30.9 [38.5], within
+// 1e-5 46.0 / 41.2 [45.3], all equal 55.1 / 44.8 [46.5]).  With 17 to 32 the eight stay the better ones wherever scores differ
+// (32768 tokens: long-tailed 17.6 / 18.7 [24.6], within 1e-5 23.7 / 22.7 [26.2]); only where nearly all are equal they are not
+// (28.0 / 23.4 [25.9]).  Copies chosen pass by pass, by the keys still in play, cost more than they save (19.2 and 25.1).
 constexpr int kSelCopies = 8;
 constexpr int kSelCopyWords = 260;        // 256 counters, 16-byte aligned; the copies of one digit lie in different banks
 
@@ -134,9 +139,10 @@ template <int E>
 __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const SelectParams p)
 {
+    constexpr int COPIES = E <= 32 ? kSelCopies : 2 * kSelCopies;
     using mask_t = std::conditional_t<(E <= 32), uint32_t, uint64_t>;      // a bit per key of a thread
     static_assert(kSelWaves == 16, "the waves' sums are one DPP row");
-    __shared__ __align__(16) int s_hist[2][kSelCopies * kSelCopyWords];    // the passes alternate between two sets
+    __shared__ __align__(16) int s_hist[2][COPIES * kSelCopyWords];    // the passes alternate between two sets
     __shared__ int s_wave[kSelWaves];
     __shared__ int s_pick[3];
 
@@ -155,7 +161,7 @@ void select_kernel(const SelectParams p)
     auto clear = [&](int* from, int words) __attribute__((always_inline)) {
         for (int i = tid; i < words / 4; i += kSelThreads) reinterpret_cast<u32x4*>(from)[i] = u32x4{0u, 0u, 0u, 0u};
     };
-    clear(s_hist[0], 2 * kSelCopies * kSelCopyWords);
+    clear(s_hist[0], 2 * COPIES * kSelCopyWords);
     const int k = p.k_top[b], budget = p.keep_budget[b];
     const int out0 = p.cu_keep ? p.cu_keep[b] : 0;
     const bool bad = n < 0 || n > E * kSelThreads || n > p.max_n_video || k < 0 || k > budget || budget > n;
@@ -180,7 +186,7 @@ void select_kernel(const SelectParams p)
             // A lane may add to any copy: the lanes of an instruction are spread over the copies, the waves start at
             // different ones.  No aggregation over the wave or over a thread's keys: both were measured and cost more
             // than the additions they save.
-            int* const my_hist = hist + ((4 * wave + lane) & (kSelCopies - 1)) * kSelCopyWords;
+            int* const my_hist = hist + ((4 * wave + lane) & (COPIES - 1)) * kSelCopyWords;
             if (pass == 0) {
 #pragma unroll
                 for (int e = 0; e < E; ++e)
@@ -190,7 +196,7 @@ void select_kernel(const SelectParams p)
                 for (int e = 0; e < E; ++e)
                     if (e < per && (key[e] & known) == prefix) atomicAdd(&my_hist[(key[e] >> shift) & 255], 1);
                 // (the other set was read for the last time before the barrier above)
-                if (pass < 3) clear(s_hist[(pass + 1) & 1], kSelCopies * kSelCopyWords);
+                if (pass < 3) clear(s_hist[(pass + 1) & 1], COPIES * kSelCopyWords);
             }
             __syncthreads();
             if (wave == 0) {
@@ -199,7 +205,7 @@ void select_kernel(const SelectParams p)
                 const int d0 = 252 - 4 * lane;
                 int c4[4] = {0, 0, 0, 0};
 #pragma unroll
-                for (int w = 0; w < kSelCopies; ++w) {
+                for (int w = 0; w < COPIES; ++w) {
                     const u32x4 v = *reinterpret_cast<const u32x4*>(hist + w * kSelCopyWords + d0);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) c4[i] += (int)v[i];
