@@ -528,17 +528,19 @@ void score_lse_kernel(const ScoreParams p_launch)
 // The partial columns of all layers, kv heads and row splits, summed in a fixed order.  Bound: round trips.  One thread per
 // column walked 640 partials of the 80-layer shape eight at a time, in 49 workgroups: 55 us; with RUNS = 8 threads per
 // column, each with an equal run of the partials (in the order layer, head and split) and sixteen loads in flight: 9 us.
-// Up to eight partials are one trip for one thread, which then needs no exchange (a small layer: 2.5 us against 2.8).
-constexpr int kFinalRuns = 8, kFinalOneTrip = 8;
-template <int RUNS>
+// Up to sixteen partials are one trip for one thread, which then needs no exchange: eight loads up to eight (a small layer:
+// 2.5 us, with sixteen 2.7, with eight threads 2.8), else sixteen (the call with given normalisers, sixteen partials of 33000
+// columns: 24.7 us, with eight threads 25.5; fourteen of 800: 9.7, 10.2).
+constexpr int kFinalRuns = 8, kFinalLoads = 16;
+template <int RUNS, int LOADS>
 __global__ __launch_bounds__(256)
 void score_final_kernel(const ScoreParams p_launch)
 {
-    constexpr int COLS = 256 / RUNS, LOADS = RUNS > 1 ? 16 : kFinalOneTrip;
+    constexpr int COLS = 256 / RUNS;
     __shared__ float s_run[RUNS][COLS];
     ScoreParams p = p_launch;
     if (!score_select_request(p, blockIdx.y)) return;           // (layer 0 of request blockIdx.y)
-    const int c = threadIdx.x % COLS, run = threadIdx.x / COLS;
+    const int c = threadIdx.x % COLS, run = RUNS > 1 ? threadIdx.x / COLS : 0;     // (0: no division below)
     const int j = blockIdx.x * COLS + c;
     const int parts = p.n_kv_heads * p.b_splits;
     const int64_t layer_step = (int64_t)p.batch * p.ws_cols;
@@ -748,11 +750,14 @@ static int score_impl(
     } else {
         p.b_splits = 0;          // no language queries in the whole batch: the mean is empty, only beta applies
     }
-    if ((int64_t)n_layers * n_kv_heads * p.b_splits <= kFinalOneTrip)
-        hipLaunchKernelGGL(score_final_kernel<1>, dim3((n_video + 255) / 256, batch), dim3(256), 0, s, p);
+    const int64_t partials = (int64_t)n_layers * n_kv_heads * p.b_splits;
+    if (partials <= 8)
+        hipLaunchKernelGGL((score_final_kernel<1, 8>), dim3((n_video + 255) / 256, batch), dim3(256), 0, s, p);
+    else if (partials <= kFinalLoads)
+        hipLaunchKernelGGL((score_final_kernel<1, kFinalLoads>), dim3((n_video + 255) / 256, batch), dim3(256), 0, s, p);
     else
-        hipLaunchKernelGGL(score_final_kernel<kFinalRuns>, dim3((n_video + 256 / kFinalRuns - 1) / (256 / kFinalRuns), batch),
-                           dim3(256), 0, s, p);
+        hipLaunchKernelGGL((score_final_kernel<kFinalRuns, kFinalLoads>),
+                           dim3((n_video + 256 / kFinalRuns - 1) / (256 / kFinalRuns), batch), dim3(256), 0, s, p);
     return launch_status();
 }
 

@@ -26,3 +26,12 @@ def test_key_splits(B, V, L, P, hq, hkv, d, mode):
 ])
 def test_partial_columns(B, layers, V, L, P, hq, hkv, d, mode):
     base.test_score_layers_is_the_sum_over_layers(B, layers, V, L, P, hq, hkv, d, mode)
+
+
+# sixteen partial columns are the last that one thread sums: one row split each, layers x heads on both sides of the line
+@pytest.mark.parametrize("layers,V,L,P,hq,hkv,d,mode", [
+    (2, 300, 5, 0, 8, 8, 64, 0), (1, 2049, 3, 0, 17, 17, 64, 0), (16, 257, 4, 0, 1, 1, 64, 1), (3, 4100, 3, 2, 5, 5, 64, 0),
+    (2, 270, 40, 0, 14, 2, 64, 0), (5, 255, 3, 0, 6, 3, 128, 0),
+])
+def test_partial_columns_of_one_thread(B, layers, V, L, P, hq, hkv, d, mode):
+    base.test_score_layers_is_the_sum_over_layers(B, layers, V, L, P, hq, hkv, d, mode)
