@@ -276,7 +276,7 @@ def _batch_case(B, lens, q_lens, hq, hkv, d, seed, scale=0.09):
 
 
 @pytest.mark.parametrize("lens,q_lens,hq,hkv,d", [
-    # fewer tiles than workgroups: every workgroup holds one tile
+    # short requests: one launch without pieces
     ([70, 5, 129], [3, 3, 3], 8, 2, 128),
     # a request without queries in the middle, one key only, one long request that spans many workgroups
     ([300, 64, 1, 9000, 17], [6, 0, 1, 6, 2], 16, 2, 128),

@@ -1,6 +1,6 @@
-"""GPU parity of the decode-attention merge where its launch changes: eight splits and nine, as many query rows as CUs and
-one group of rows more, rows that do not fill the last workgroup, and a ragged batch in which requests have fewer live
-splits than the launch.  Bounds: those of every attention test."""
+"""GPU parity of the decode-attention merges where their launch changes: eight splits and nine, row counts on both sides of
+the lines from which a group of threads takes a row, rows that do not fill the last workgroup, and ragged batches in which
+requests have fewer live splits than the launch.  Bounds: those of every attention test."""
 import numpy as np
 import pytest
 import torch
@@ -19,9 +19,9 @@ def B():
 
 
 @pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
-    (8, 1300, 32, 4, 128, 8), (8, 1300, 36, 4, 128, 8), (8, 1300, 36, 4, 128, 9),      # 256 and 288 rows
-    (11, 900, 24, 1, 64, 8), (11, 900, 24, 1, 64, 2),                                  # 264 rows, 16 to a workgroup: half a one
-    (13, 300, 63, 3, 128, 3), (13, 1025, 63, 3, 128, 8),                               # 273 rows a head, the last workgroup short
+    (8, 1300, 32, 4, 128, 8), (8, 1300, 36, 4, 128, 8), (8, 1300, 36, 4, 128, 9),      # 256 and 288 rows: a workgroup each
+    (11, 900, 24, 1, 64, 8), (11, 900, 24, 1, 64, 2),                                  # 264 rows
+    (13, 300, 63, 3, 128, 3), (13, 1025, 63, 3, 128, 8),                               # 273 rows a head
 ])
 def test_uniform_splits(B, q_len, kv_len, hq, hkv, d, splits):
     q, k, v = (rnd_bits((n, h, d), 6000 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))

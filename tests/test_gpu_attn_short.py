@@ -1,6 +1,6 @@
 """GPU parity of the decode-attention launches for short caches (no splits, no merge) and of the short key splits,
 at the edges where their shapes change: chunk and wave ends, the last cache length of the launch and the first
-beyond it, one and several row blocks, ragged batches, a tree.  Bounds: those of every attention test (max-abs 2e-2,
+beyond it, one and several row blocks, ragged batches, a tree, both layouts, keys that tower over all others.  Bounds: those of every attention test (max-abs 2e-2,
 mean-abs 2e-3 for outputs of size one: bf16 in and out, fp32 sums)."""
 import numpy as np
 import pytest
@@ -27,7 +27,7 @@ def B():
     (1, 16, 8, 8, 128, 0), (5, 289, 32, 2, 128, 0), (4, 768, 8, 2, 128, 0), (6, 1024, 16, 2, 128, 0),
     (1, 1025, 7, 1, 128, 0), (8, 64, 64, 8, 128, 0),                  # 256 workgroups: the most without a second round
     (8, 65, 72, 8, 128, 0),                                           # 72 rows per kv head: splits
-    (1, 500, 14, 2, 64, 4), (1, 500, 14, 2, 64, 5), (1, 2049, 4, 1, 64, 17),   # short splits, a ragged and a one-key last one
+    (1, 500, 14, 2, 64, 4), (1, 500, 14, 2, 64, 5), (1, 2049, 4, 1, 64, 17),   # short splits: four of 125 keys (five are clamped), a last one of 113
 ])
 def test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, splits):
     q, k, v = (rnd_bits((n, h, d), 5000 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
@@ -117,3 +117,39 @@ def test_short_splits(B, q_len, kv_len, hq, hkv, d, splits):
 def test_ragged_batch_of_short_splits(B):
     """128 keys a split; last splits of 1, 32, 33 and 128 keys, requests with fewer live splits than the launch, waves without keys."""
     ragged_case(B, [1280, 129, 160, 161, 3, 1024], [2, 1, 2, 1, 2, 2], 14, 2, 64, num_splits=10)
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [(2, 1345, 14, 2, 64, 0), (6, 1000, 64, 8, 128, 0), (1, 1000, 12, 3, 64, 0),
+                                                          (1, 2080, 14, 2, 64, 17)])
+def test_head_major_caches(B, q_len, kv_len, hq, hkv, d, splits):
+    q, k, v = (rnd_bits((n, h, d), 7200 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    want, want_lse = oracle.decode_attn(q, k, v, 0.11)
+    kd, vd = (dev_bf16(x).permute(1, 0, 2).contiguous().permute(1, 0, 2) for x in (k, v))
+    out, lse = B.decode_attn(dev_bf16(q), kd, vd, 0.11, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"head-major q{q_len} kv{kv_len} {hq}/{hkv} d{d}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [(6, 1000, 16, 2, 128, 0), (1, 1500, 14, 2, 64, 0), (2, 2080, 8, 2, 64, 17)])
+@pytest.mark.parametrize("bumps", [((3, 120.0),), ((700, 60.0),), ((40, 60.0), (500, 150.0), (930, 40.0))])
+def test_dominant_keys(B, q_len, kv_len, hq, hkv, d, splits, bumps):
+    """Keys whose logits tower over the others by 2^40 .. 2^150: each wave has its own maximum, and the waves' parts meet."""
+    scale, r = 0.088, np.random.default_rng(7300 + kv_len + int(bumps[0][1]))
+    base = r.standard_normal(d).astype(np.float32)
+    q = synth.f32_to_bf16_bits(base[None, None, :] + 0.3 * r.standard_normal((q_len, hq, d)).astype(np.float32))
+    k = 0.2 * r.standard_normal((kv_len, hkv, d)).astype(np.float32)
+    for pos, log2_units in bumps:
+        k[pos] = (log2_units / (scale * np.log2(np.e) * float(base @ base))) * base[None, :]
+    k, v = synth.f32_to_bf16_bits(k), rnd_bits((kv_len, hkv, d), 7301)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"bumps {bumps} kv{kv_len}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+def test_balanced_pieces_of_few_tiles(B):
+    """Fewer tiles than workgroups, one request just too long for the launch without splits."""
+    ragged_case(B, [70, 5, 1100], [3, 3, 3], 8, 2, 128)
+    ragged_case(B, [1537, 90], [1, 2], 14, 2, 64)
