@@ -90,11 +90,12 @@ void accept_argmax_partial(const AcceptParams p)
 // trip and all rows at once (one wave); 16 lanes per row take 64 chunks a trip and 16 rows at once (four waves, and an
 // exchange): accept_final_lanes takes the fewer trips.
 constexpr int kFinalLanes = 16, kFinalThreads = 256;
+constexpr int final_threads(int lanes) { return lanes == 1 ? kWave : kFinalThreads; }
 template <int LANES> __device__ __forceinline__ void accept_merge_argmax(const AcceptParams& p, int b, int rows, int* s_t)
 {
     constexpr int LOADS = LANES == 1 ? 8 : 4;                    // chunks in flight per lane
     const int l = threadIdx.x % LANES;
-    for (int row = threadIdx.x / LANES; row < rows; row += blockDim.x / LANES) {
+    for (int row = threadIdx.x / LANES; row < rows; row += final_threads(LANES) / LANES) {
         const int64_t slot = ((int64_t)b * rows + row) * p.n_chunks;
         float bv = 0.f; int bi = -1;
         for (int c0 = l; c0 < p.n_chunks; c0 += LANES * LOADS) {
@@ -119,7 +120,7 @@ template <int LANES> __device__ __forceinline__ void accept_merge_argmax(const A
 }
 
 template <int LANES>
-__global__ __launch_bounds__(LANES == 1 ? kWave : kFinalThreads)
+__global__ __launch_bounds__(final_threads(LANES))
 void accept_greedy_final(const AcceptParams p)
 {
     // one workgroup per request; lane i of its first wave holds drafted token i (gamma <= 64), the first mismatch is
@@ -447,7 +448,7 @@ void accept_sample_final(const AcceptParams p)
 // wave holds node i's parent and drafted token, and that wave walks from the root,
 // moving to the lowest-numbered child that drafted the target's token (found by a ballot).
 template <int LANES>
-__global__ __launch_bounds__(LANES == 1 ? kWave : kFinalThreads)
+__global__ __launch_bounds__(final_threads(LANES))
 void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* accepted_nodes)
 {
     const int b = blockIdx.x, lane = threadIdx.x;
