@@ -131,8 +131,9 @@ int specvlm_score(
  * and every launch has n_layers times the workgroups to fill the chip with).
  * n_layers = 0 only applies beta.  n_layers * batch <= 65535.
  * The workspace query takes n_layers as well; the result is deterministic (the
- * layers are added in the order 0, 1, ...), and equals what the per-layer calls
- * give up to the rounding of one fp32 sum taken in a different order.
+ * parts of all layers and kv heads are added in a fixed order that the shape
+ * alone decides), and equals what the per-layer calls give up to the rounding
+ * of one fp32 sum taken in a different order.
  * -------------------------------------------------------------------------- */
 size_t specvlm_score_layers_workspace_bytes(int n_layers, int batch, int n_text, int n_keys, int n_video,
                                             int n_q_heads, int n_kv_heads, int head_dim,
@@ -258,18 +259,29 @@ int specvlm_gather_kv(
  *   lse  optional fp32 [sum q_len_b, H_q]: natural log of each row's softmax sum
  *   q head h reads kv head h / (H_q / H_kv)
  *   num_splits: key-range splits per (request, kv head) (flash-decode);
- *               0 lets the library choose for the shape.  For a batch of 2..64
- *               requests the choice is made on the device from the request
- *               lengths: the key tiles of the requests are dealt in equal
- *               contiguous runs to groups of n_kv_heads workgroups (one per
- *               head, one workgroup per CU), so requests of very different
+ *               0 lets the library choose for the shape.  Short caches (at most
+ *               1536 keys at d = 64, 1024 at d = 128, and no more work than one
+ *               round of the CUs) are then served by one launch without splits.
+ *               Otherwise, for a batch of 2..64 requests of at most 64 query
+ *               rows per kv head, the choice is made on the device from the
+ *               request lengths: the key tiles of the requests are dealt in
+ *               equal contiguous runs to groups of n_kv_heads workgroups (one
+ *               per head, one workgroup per CU), so requests of very different
  *               lengths finish together.
+ *   q_len and kv_len must not be understated for a batch: they are the maxima
+ *               over the requests, and what lies beyond them may be left out
+ *               without an error (the launch without splits has room for kv_len
+ *               keys, uniform splits end at kv_len).
  *   Workspace: the query takes the same batch, maxima, head counts and
- *               num_splits as the call (it is pure: it depends on nothing else).
+ *               num_splits as the call (it is pure: it depends on nothing else),
+ *               and the call is refused without it, also where the launch that
+ *               serves the shape uses none.
  * Limits: q_len <= 64.  Up to 64 query rows per kv head ((H_q/H_kv) * q_len)
  *   read K and V from memory exactly once; beyond that the rows are processed in
  *   groups of at most 64 (one workgroup per group, head and key range) and each
  *   group reads the key range again, its neighbours' copy mostly still cached.
+ *   The launch without splits reads K once per block of 16 rows and 16 value
+ *   columns, mostly from the L2.
  * -------------------------------------------------------------------------- */
 size_t specvlm_decode_attn_workspace_bytes(int batch, int q_len, int kv_len,
                                            int n_q_heads, int n_kv_heads, int head_dim,

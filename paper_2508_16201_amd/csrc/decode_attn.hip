@@ -1,6 +1,8 @@
 // specvlm_decode_attn: grouped-query softmax attention of a short query block
 // (1 query for plain decode, gamma+1 for parallel verification; Sec. 2.1 of the
-// paper) over a long bf16 KV cache, in split-K (flash-decode) form for gfx950.
+// paper) over a bf16 KV cache, for gfx950: long caches in split-K (flash-decode)
+// form, which the rest of this comment describes, short ones in one launch
+// without splits (attn_short_kernel; attn_direct_chunks has the line).
 //
 // Work decomposition
 //   One workgroup owns one (request, kv head, key split).  All G*q_len query
@@ -1221,9 +1223,9 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
 {
 
     // (key-split waves, tile keys, ring depth, loader waves) per row-block count; the ring
-    // holds NS * 2 * TK * D * 2 bytes of LDS.  The single-query decode keeps its four waves (loading and
-    // computing): on the draft's small cache the four extra waves cost more at workgroup start-up than
-    // they save (6.7 against 6.4 us per layer).
+    // holds NS * 2 * TK * D * 2 bytes of LDS.  One row block (the single-query decode beyond the short
+    // caches) keeps its four waves, loading and computing: on a small cache the four extra waves cost more
+    // at workgroup start-up than they save (6.7 against 6.4 us per layer at 1511 keys).
     switch (mb) {
         case 1:
             // Splits of at most 128 keys: one chunk of 32 keys for each of four waves, results for the merge (a single split
