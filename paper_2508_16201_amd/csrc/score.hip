@@ -33,6 +33,8 @@
 // exponential per logit: away from the causal mask it does not track maxima at
 // all, and where it does it rescales its running sum only when a tile's maximum
 // exceeds the reference by more than 2^8.
+#include <atomic>
+
 #include "common.h"
 
 namespace specvlm {
@@ -576,6 +578,203 @@ void score_final_kernel(const ScoreParams p_launch)
     p.scores[j] = (p.beta != 0.f ? p.beta * p.scores[j] : 0.f) + a;
 }
 
+// ---- one small layer: two launches instead of four (one instead of three with the caller's normalisers) ----
+// Bound: launches, chains of round trips and the first execution of every instruction, not arithmetic.  Hence lean
+// parameters, no division, as little code as it takes.  The row statistics are taken by workgroups of 64 rows and one key
+// range each; then every workgroup of 64 keys merges all rows' statistics itself and sums its columns over all rows and
+// heads: neither normalisers nor partial columns go through memory.  64 queries over 1568 + 64 keys, 4 heads of size 64: from a
+// graph 14.1 -> 8.5 us, called from Python 15.5 -> 9.7 (rows 3.3, columns 5); with the caller's normalisers 8.1 -> 3.7.
+constexpr int kSmallLds = 144 * 1024;  // of the column sums' workgroup, at most
+constexpr int kScoreMaxDevices = 64;
+constexpr int kSmallTiles = 8;         // row tiles (64 text queries of a q head), at most
+constexpr int kSmallSplits = 32;       // key ranges of the row statistics, at most (eight lanes of four)
+
+struct ScoreSmallParams {
+    const __bf16* q;
+    const __bf16* k;
+    int64_t q_tok, q_head, k_tok, k_head;
+    int n_text, text_pos0, n_q_heads, n_kv_heads, n_tiles;
+    int tile_mul, head_mul;                // row tile -> q head -> kv head: (x * mul) >> 16, exact for the few there are
+    int tiles_per_head;
+    int key_lo, key_hi, splits, split_keys;
+    int video_start, n_video;
+    float scale_log2, beta, inv_count;
+    float2* part;                          // [row tile][64][splits] (max, sum)
+    const float* row_lse;
+    float* scores;
+};
+
+// Logits of the 64 streamed vectors of an LDS tile (chunk-swizzled) against the wave's 16 stationary ones.
+template <int D>
+__device__ __forceinline__ void score_small_logits(const unsigned char* tile, int r, int c, const bf16x8 (&sf)[D / 32], floatx4 (&acc)[4])
+{
+#pragma unroll
+    for (int sub = 0; sub < 4; ++sub) {
+        bf16x8 af[D / 32];
+        score_load_a<D>(tile, sub, r, c, af);
+        acc[sub] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < D / 32; ++kk) acc[sub] = mfma16(af[kk], sf[kk], acc[sub]);
+    }
+}
+
+// Direct-to-LDS loads of a 64-vector tile by WAVES waves; vectors from `limit` on are the last one.
+template <int D, int WAVES>
+__device__ __forceinline__ void score_small_load(unsigned char* tile, const __bf16* base, int64_t tok, int idx0, int limit, int wave, int lane)
+{
+    constexpr int CH = D / 8, VEC = kWave / CH;
+#pragma unroll
+    for (int n = 0; n < kScoreTile / VEC / WAVES; ++n) {
+        const int at = wave + n * WAVES, it = at * VEC + lane / CH;
+        const int swz = (D == 128) ? (it & 15) : ((it >> 1) & 7);
+        const __bf16* src = base + (uint64_t)(uint32_t)min(idx0 + it, limit - 1) * (uint32_t)tok + ((lane % CH) ^ swz) * 8;
+        __builtin_amdgcn_global_load_lds((const SPECVLM_AS1 void*)src, (SPECVLM_AS3 void*)(tile + at * 1024), 16, 0, 0);
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(256)
+void score_small_rows_kernel(const ScoreSmallParams p)
+{
+    constexpr int KK = D / 32, TILE_BYTES = kScoreTile * D * 2;
+    __shared__ __align__(16) unsigned char s_tile[2][TILE_BYTES];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    const int tile = blockIdx.x, split = blockIdx.y;
+    const int h = (tile * p.tile_mul) >> 16, g = (h * p.head_mul) >> 16;
+    const int i = (tile - h * p.tiles_per_head) * kScoreTile + wave * 16 + r;
+    const int s_begin = p.key_lo + split * p.split_keys, s_end = min(p.key_hi, s_begin + p.split_keys);     // (never empty)
+    const __bf16* const keys = p.k + g * p.k_head;
+    score_small_load<D, 4>(s_tile[0], keys, p.k_tok, s_begin, s_end, wave, lane);
+    bf16x8 sf[KK];
+    const __bf16* q = p.q + (uint64_t)(uint32_t)min(i, p.n_text - 1) * (uint32_t)p.q_tok + h * p.q_head + c * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) sf[kk] = *reinterpret_cast<const bf16x8*>(q + kk * 32);
+    const int lim = i < p.n_text ? p.text_pos0 + i : -1;         // last visible key of the lane's row
+    const float sc = fmaxf(p.scale_log2, 1e-30f);                // (see score_sweep_kernel)
+    float m = kNegBig, l = 0.f;
+    int at = 0;
+    for (int k0 = s_begin; k0 < s_end; k0 += kScoreTile, at ^= 1) {
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                                         // this tile landed; everyone is done with the one before
+        if (k0 + kScoreTile < s_end) score_small_load<D, 4>(s_tile[at ^ 1], keys, p.k_tok, k0 + kScoreTile, s_end, wave, lane);
+        floatx4 acc[4];
+        score_small_logits<D>(s_tile[at], r, c, sf, acc);
+        const int hidden = min(s_end - 1, lim) - k0 - 4 * c;     // (of the lane's keys 16 x + e, those beyond this)
+        float m_new = m;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            if (e / 4 * 16 + e % 4 > hidden) acc[e / 4][e % 4] = -INFINITY;
+            m_new = fmaxf(m_new, acc[e / 4][e % 4] * sc);
+        }
+        l *= fast_exp2(m - m_new);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) l += fast_exp2(fmaf(acc[e / 4][e % 4], sc, -m_new));
+        m = m_new;
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+        const float om = __shfl_xor(m, off), ol = __shfl_xor(l, off);
+        const float mm = fmaxf(m, om);
+        l = l * fast_exp2(m - mm) + ol * fast_exp2(om - mm);
+        m = mm;
+    }
+    if (c == 0) p.part[(tile * kScoreTile + wave * 16 + r) * p.splits + split] = float2{m, l};
+}
+
+// Another lane's value by DPP (0xB1: lane ^ 1, 0x4E: lane ^ 2, 0x141: lane ^ 7): a VALU move, where a shuffle goes through LDS.
+template <int CTRL> __device__ __forceinline__ float lane_move(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+
+template <int D>
+__global__ __launch_bounds__(512)
+void score_small_cols_kernel(const ScoreSmallParams p)
+{
+    constexpr int KK = D / 32, TILE_BYTES = kScoreTile * D * 2;
+    extern __shared__ __align__(16) unsigned char s_mem[];       // the workgroup's keys of every kv head, then the row tiles
+    __shared__ __align__(16) float s_lse[kSmallTiles * kScoreTile];
+    __shared__ float s_col[kScoreTile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    const int kw = wave & 3, half = wave >> 2;                   // the wave's 16 keys; it takes every other row tile
+    const int j0 = blockIdx.x * kScoreTile, key0 = p.video_start + j0;
+    unsigned char* const s_rows = s_mem + p.n_kv_heads * TILE_BYTES;
+    for (int g = 0; g < p.n_kv_heads; ++g)
+        score_small_load<D, 8>(s_mem + g * TILE_BYTES, p.k + g * p.k_head, p.k_tok, key0, p.video_start + p.n_video, wave, lane);
+    for (int t = 0; t < p.n_tiles; ++t) {
+        const int h = (t * p.tile_mul) >> 16;
+        score_small_load<D, 8>(s_rows + t * TILE_BYTES, p.q + h * p.q_head, p.q_tok, (t - h * p.tiles_per_head) * kScoreTile, p.n_text,
+                               wave, lane);
+    }
+    // all rows' normalisers; padded rows contribute nothing (see score_lse_kernel)
+    if (p.row_lse) {
+        for (int x = tid; x < p.n_tiles * kScoreTile; x += 512) {
+            const int t = x / kScoreTile, h = (t * p.tile_mul) >> 16, i = (t - h * p.tiles_per_head) * kScoreTile + x % kScoreTile;
+            const float v = i < p.n_text ? p.row_lse[i * p.n_q_heads + h] * kLog2e : INFINITY;
+            s_lse[x] = v > -INFINITY ? v : INFINITY;
+        }
+    } else {
+        // eight lanes a row; past the last range a lane reads it again and leaves it out
+        const int sub = tid & 7, row_in = tid >> 3;
+        for (int t = 0; t < p.n_tiles; t += 2) {
+            float2 ml[2][kSmallSplits / 8];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int u = 0; u < kSmallSplits / 8; ++u)
+                    if (8 * u < p.splits)
+                        ml[x][u] = p.part[(min(t + x, p.n_tiles - 1) * kScoreTile + row_in) * p.splits + min(sub + 8 * u, p.splits - 1)];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                float m = kNegBig, l = 0.f;
+#pragma unroll
+                for (int u = 0; u < kSmallSplits / 8; ++u) if (8 * u < p.splits) m = fmaxf(m, ml[x][u].x);
+                m = fmaxf(m, lane_move<0xB1>(m)); m = fmaxf(m, lane_move<0x4E>(m)); m = fmaxf(m, lane_move<0x141>(m));
+#pragma unroll
+                for (int u = 0; u < kSmallSplits / 8; ++u)
+                    if (8 * u < p.splits) l += sub + 8 * u < p.splits ? ml[x][u].y * fast_exp2(ml[x][u].x - m) : 0.f;
+                l += lane_move<0xB1>(l); l += lane_move<0x4E>(l); l += lane_move<0x141>(l);
+                const int tt = t + x, h = (tt * p.tile_mul) >> 16, i = (tt - h * p.tiles_per_head) * kScoreTile + row_in;
+                if (sub == 0 && tt < p.n_tiles) s_lse[tt * kScoreTile + row_in] = i < p.n_text && l > 0.f ? m + fast_log2(l) : INFINITY;
+            }
+        }
+    }
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const float sc = p.scale_log2;
+    float v = 0.f;
+    bf16x8 sf[KK];
+    int g_have = -1;
+    for (int t = half; t < p.n_tiles; t += 2) {
+        const int h = (t * p.tile_mul) >> 16, g = (h * p.head_mul) >> 16;
+        if (g != g_have) { score_load_a<D>(s_mem + g * TILE_BYTES, kw, r, c, sf); g_have = g; }
+        floatx4 acc[4];
+        score_small_logits<D>(s_rows + t * TILE_BYTES, r, c, sf, acc);
+        // text query i sees key k iff k <= text_pos0 + i: of the lane's rows 16 x + e, those from `from` on
+        const int from = key0 + kw * 16 + r - p.text_pos0 - (t - h * p.tiles_per_head) * kScoreTile - 4 * c;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const floatx4 lse = *reinterpret_cast<const floatx4*>(s_lse + t * kScoreTile + x * 16 + 4 * c);
+            float part = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float y = fast_exp2(fmaf(acc[x][e], sc, -lse[e]));
+                part += x * 16 + e < from ? 0.f : y;
+            }
+            v += part;
+        }
+    }
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (half == 1 && c == 0) s_col[kw * 16 + r] = v;
+    __syncthreads();
+    const int j = j0 + kw * 16 + r;
+    if (half == 0 && c == 0 && j < p.n_video)
+        p.scores[j] = (p.beta != 0.f ? p.beta * p.scores[j] : 0.f) + (v + s_col[kw * 16 + r]) * p.inv_count;
+}
+
 struct ScorePlan {
     int l_pad, rows, rows_pad, video_pad, key_lo, key_hi, a_splits, a_split_keys, b_splits, b_split_rows;
     size_t off_ml, off_lse, off_cols, total;
@@ -629,6 +828,53 @@ static ScorePlan score_plan(int batch, int n_text, int n_keys, int video_start, 
     return s;
 }
 
+// Where the two-launch form is the better one: one layer of one request, up to eight row tiles (they all lie in LDS, and every
+// workgroup walks all of them) over up to as many keys as there are CUs for its workgroups.  Us from a graph, sweeps / this:
+// 1632 keys, size 64: 4 tiles 14.1 / 8.5, 8 tiles 14.2 / 11.4, 16 tiles 14.8 / over 20;  size 128: 8 tiles 16.9 / 12.8;  16000 keys,
+// size 64: 4 tiles 16.9 / 12.6, 8 tiles 20.2 / 15.6;  size 128, 8 tiles 24.0 / 18.5;  33000 keys (two rounds of workgroups):
+// 4 tiles 24.3 / 21.3, 8 tiles 28.4 / 29.4, size 128 35.2 / 39.4.
+// Key ranges, 1632 keys: at most 8 9.1, 16 8.2, 32 8.5, 64 8.8;  16000 keys: 25.0, 16.6, 12.6, 11.7 (8 tiles 27.8, 19.1, 15.6, 16.4).
+constexpr int kSmallKeys = kNumCu * 68;
+static bool score_is_small(int n_layers, int batch, int n_text, int n_keys, int n_q_heads, int n_kv_heads, int head_dim)
+{
+    const int64_t tiles = (int64_t)n_q_heads * ((n_text + kScoreTile - 1) / kScoreTile);
+    return n_layers == 1 && batch == 1 && n_text > 0 && tiles <= kSmallTiles && (tiles + n_kv_heads) * kScoreTile * head_dim * 2 <= kSmallLds &&
+           n_keys <= kSmallKeys;
+}
+
+// Key ranges of its row statistics: about a workgroup per CU.  `bytes` is enough for every smaller domain, too.
+struct ScoreSmallPlan { int splits, split_keys; size_t bytes; };
+static ScoreSmallPlan score_small_plan(int n_text, int domain, int n_q_heads)
+{
+    const int tiles = n_q_heads * ((n_text + kScoreTile - 1) / kScoreTile);
+    int splits = kNumCu / tiles, most = (domain + kScoreTile - 1) / kScoreTile;
+    if (most > kSmallSplits) most = kSmallSplits;
+    if (splits > most) splits = most;
+    const int per = round_up((domain + splits - 1) / splits, kScoreTile);
+    return {(domain + per - 1) / per, per, (size_t)tiles * kScoreTile * splits * sizeof(float2)};
+}
+
+template <int D>
+static int launch_small(const ScoreSmallParams& p, hipStream_t stream)
+{
+    if (!p.row_lse) hipLaunchKernelGGL((score_small_rows_kernel<D>), dim3(p.n_tiles, p.splits), dim3(256), 0, stream, p);
+    // (more than 64 KB of LDS wants the attribute, which belongs to the kernel as loaded on one device)
+    const size_t lds = (size_t)(p.n_tiles + p.n_kv_heads) * kScoreTile * D * 2;
+    static std::atomic<bool> raised[kScoreMaxDevices];
+    if (lds > 48 * 1024) {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScoreMaxDevices) return SPECVLM_ELAUNCH;
+        if (!raised[dev].load(std::memory_order_acquire)) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_small_cols_kernel<D>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds) != hipSuccess)
+                return SPECVLM_ELAUNCH;
+            raised[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL((score_small_cols_kernel<D>), dim3((p.n_video + kScoreTile - 1) / kScoreTile), dim3(512), lds, stream, p);
+    return launch_status();
+}
+
 }  // namespace specvlm
 
 using namespace specvlm;
@@ -645,7 +891,10 @@ extern "C" size_t specvlm_score_layers_workspace_bytes(int n_layers, int batch, 
     const int units = n_layers * batch;
     const ScorePlan a = score_plan(units, n_text, n_keys, 0, n_video, n_q_heads, n_kv_heads, head_dim, 0, have_row_lse);
     const ScorePlan b = score_plan(units, n_text, n_keys, 0, n_video, n_q_heads, n_kv_heads, head_dim, 1, have_row_lse);
-    return (size_t)units * (a.total > b.total ? a.total : b.total);
+    const size_t sweeps = (size_t)units * (a.total > b.total ? a.total : b.total);
+    const size_t small = have_row_lse || !score_is_small(n_layers, batch, n_text, n_keys, n_q_heads, n_kv_heads, head_dim) ? 0 :
+        score_small_plan(n_text, n_keys, n_q_heads).bytes;
+    return sweeps > small ? sweeps : small;
 }
 
 extern "C" size_t specvlm_score_workspace_bytes(int batch, int n_text, int n_keys, int n_video,
@@ -731,6 +980,15 @@ static int score_impl(
     p.n_layers = n_layers; p.q_layer = q_layer_stride; p.k_layer = k_layer_stride; p.lse_layer = lse_layer_stride;
     hipStream_t s = (hipStream_t)stream;
 
+    if (!ragged && score_is_small(n_layers, 1, n_text, n_keys, n_q_heads, n_kv_heads, head_dim)) {
+        const ScoreSmallPlan sp = score_small_plan(n_text, p.key_hi - p.key_lo, n_q_heads);
+        if (!row_lse && workspace_bytes < sp.bytes) return SPECVLM_EWORKSPACE;
+        const int per_head = plan.l_pad / kScoreTile;
+        const ScoreSmallParams sm = {p.q, p.k, p.q_tok, p.q_head, p.k_tok, p.k_head, n_text, text_pos0, n_q_heads, n_kv_heads,
+                                     n_q_heads * per_head, 65536 / per_head + 1, 65536 / p.group + 1, per_head, p.key_lo, p.key_hi, sp.splits,
+                                     sp.split_keys, video_start, n_video, p.scale_log2, beta, p.inv_count, (float2*)workspace, row_lse, scores};
+        return head_dim == 128 ? launch_small<128>(sm, s) : launch_small<64>(sm, s);
+    }
     if (n_text > 0 && n_layers > 0) {
         if ((int64_t)(plan.rows_pad / kScoreBlock) * n_kv_heads * plan.a_splits * units > 0x7fffff00ll ||
             (int64_t)(plan.video_pad / kScoreBlock) * n_kv_heads * plan.b_splits * units > 0x7fffff00ll)
