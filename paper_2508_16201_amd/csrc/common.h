@@ -40,6 +40,18 @@ __device__ __forceinline__ int xcd_logical_id(int hw_id, int padded)
     return (hw_id % kNumXcd) * per_xcd + hw_id / kNumXcd;
 }
 
+// Division by a launch's own divisor d, with inv = reciprocal(d) from the host: exact for every x >= 0.  (The compiler's
+// sequence for a divisor that it does not know is a chain of about 25 instructions, and the kernels here that take a few
+// microseconds had four to six of them in front of their first load.)
+struct QuotRem { int q, r; };
+__device__ __forceinline__ QuotRem divide(int x, int d, uint32_t inv)
+{
+    // inv <= 2^32 / d < inv + 1 (or inv = 2^32 - 1 for d = 1): the estimate is the quotient or one less
+    const int q = (int)__umulhi((uint32_t)x, inv), r = x - q * d;
+    return r >= d ? QuotRem{q + 1, r - d} : QuotRem{q, r};
+}
+inline uint32_t reciprocal(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d) : 0xffffffffu; }
+
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 

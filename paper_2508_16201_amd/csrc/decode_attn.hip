@@ -76,6 +76,7 @@ struct AttnParams {
     const int32_t* cu_q;
     const int32_t* cu_kv;
     int batch, q_len, kv_len, n_q_heads, n_kv_heads, group;
+    uint32_t inv_heads, inv_all_heads, inv_group, inv_splits, inv_rgroups, inv_split_keys, inv_help;   // reciprocal() of n_kv_heads, batch * n_kv_heads, ...
     float scale_log2;        // softmax_scale * log2(e)
     int num_splits, split_keys;
     __bf16* part_o;          // [batch*H_kv][num_splits][rows_pad][D] unnormalised partial outputs (bf16: see the merge kernel)
@@ -93,6 +94,18 @@ struct AttnParams {
 
 constexpr int kChunkKeys = 32;       // keys per PV contraction step
 constexpr int kMaxBalancedBatch = 64;   // (every workgroup walks the request lengths once)
+
+// Brings in what a kernel is about to need of its parameters, together: left alone, the compiler fetches each one where it
+// is first used, and every such place is a wait of its own in front of the first load of a key.  With this and divide() for
+// the ids (us a layer, before / with divide() / both): 14/2 heads of size 64, 5000 keys 7.7 / 7.45 / 7.2, 28/4 heads, 4 queries, 3000
+// keys 9.9 / 9.7 / 9.3, the 72B verify 15.9 / 15.6 / 15.4, 1511 keys in one launch 6.46 / 6.36 / 6.36.
+__device__ __forceinline__ void attn_fetch_params(const AttnParams& p)
+{
+    __asm__ volatile("" :: "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.q_tok), "s"(p.q_head), "s"(p.kv_tok), "s"(p.kv_head), "s"(p.cu_q), "s"(p.cu_kv),
+                     "s"(p.q_len), "s"(p.kv_len), "s"(p.n_kv_heads), "s"(p.group), "s"(p.inv_heads), "s"(p.inv_group), "s"(p.inv_splits),
+                     "s"(p.inv_rgroups), "s"(p.num_splits), "s"(p.split_keys), "s"(p.n_rgroups), "s"(p.n_main), "s"(p.scale_log2),
+                     "s"(p.balanced), "s"(p.rows_pad));
+}
 
 // Tiles of request b in balanced mode; a request with nothing to do (no queries, or fewer keys
 // than queries) has none.
@@ -116,7 +129,7 @@ __device__ __forceinline__ AttnBalance attn_balance(const AttnParams& p, int til
     for (int b = 0; b < p.batch; ++b) n += attn_request_tiles(p, b, tile_keys);
     AttnBalance r;
     r.n_units = n;
-    r.n_groups = (int)min((int64_t)(p.max_wg / p.n_kv_heads), n);
+    r.n_groups = (int)min((int64_t)divide(p.max_wg, p.n_kv_heads, p.inv_heads).q, n);
     return r;
 }
 constexpr int kMaxSplits = 256;
@@ -212,6 +225,7 @@ template <int D, int MB, int KS, int TK, int NS, int NLD, bool STREAM>
 __global__ __launch_bounds__((MB * KS + NLD) * kWave)
 void attn_split_kernel(const AttnParams p)
 {
+    attn_fetch_params(p);
     constexpr int NW = MB * KS;                  // compute waves per workgroup (the loader waves come after them)
     constexpr bool SPLIT_ROLES = NLD > 0;
     constexpr int DJ = D / 16;                   // value columns per lane (8 or 4)
@@ -261,8 +275,8 @@ void attn_split_kernel(const AttnParams p)
     if (computes) {
         const int row = row0 + mb * 16 + r;
         const bool live = row < n_rows;             // padding rows read row 0: finite, never stored
-        const int t = live ? row / p.group : 0;
-        const int h = g * p.group + (live ? row % p.group : 0);
+        const QuotRem at = divide(live ? row : 0, p.group, p.inv_group);
+        const int t = at.q, h = g * p.group + at.r;
         t_blk = t;
         const __bf16* qp = p.q + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + c * 8;
 #pragma unroll
@@ -487,7 +501,8 @@ void attn_split_kernel(const AttnParams p)
     if constexpr (KS == 1) { if (!computes) return; }
     l_run = quad_sum(l_run);
     const int row = row0 + mb * 16 + r;
-    const int t_row = row / p.group, h_row = g * p.group + row % p.group;
+    const QuotRem out_at = divide(row, p.group, p.inv_group);
+    const int t_row = out_at.q, h_row = g * p.group + out_at.r;
     const int64_t slot = slot0 + row;
     if constexpr (KS == 1) {
         // lane (r, c) holds columns 16j + 4c .. 16j + 4c + 3 of its row in o_acc[j]: write them out directly
@@ -568,13 +583,12 @@ void attn_split_kernel(const AttnParams p)
         // g runs on XCD g: its partial results stay near that XCD, where the merge kernel (same
         // head-to-XCD order) finds them.  Token-major caches interleave the heads inside every token
         // row, so neighbours also walk the same DRAM pages at the same time.
-        const int vid = blockIdx.x;
-        const int g = vid % p.n_kv_heads, rest = vid / p.n_kv_heads;
-        const int split = rest % p.num_splits;
+        const QuotRem head = divide(blockIdx.x, p.n_kv_heads, p.inv_heads), part = divide(head.q, p.num_splits, p.inv_splits);
+        const int g = head.r, split = part.r;
         // more than 64 query rows per kv head: groups of MB row blocks, one workgroup each; the groups of
         // a (head, split) re-read its keys, as neighbours in time on one XCD (mostly from its L2)
-        const int rg = (rest / p.num_splits) % p.n_rgroups;
-        const int b = rest / (p.num_splits * p.n_rgroups);
+        const QuotRem group = divide(part.q, p.n_rgroups, p.inv_rgroups);
+        const int rg = group.r, b = group.q;
         int ql = p.q_len, kvl = p.kv_len;
         if (p.cu_q) ql = p.cu_q[b + 1] - p.cu_q[b];
         if (p.cu_kv) kvl = p.cu_kv[b + 1] - p.cu_kv[b];
@@ -614,7 +628,8 @@ void attn_split_kernel(const AttnParams p)
             p.seg_table[2 * seg + 1] = live;
         }
     }
-    const int j = w / H, g = w % H;
+    const QuotRem run = divide(w, H, p.inv_heads);
+    const int j = run.q, g = run.r;
     if (j >= bal.n_groups) return;
     int64_t x = (int64_t)j * bal.n_units / bal.n_groups;
     const int64_t x_end = (int64_t)(j + 1) * bal.n_units / bal.n_groups;
@@ -652,20 +667,23 @@ template <int D, int PRE, int THREADS>
 __global__ __launch_bounds__(THREADS)
 void attn_merge_kernel(const AttnParams p)
 {
+    __asm__ volatile("" :: "s"(p.part_o), "s"(p.part_ml), "s"(p.cu_q), "s"(p.cu_kv), "s"(p.q_len), "s"(p.kv_len), "s"(p.batch), "s"(p.n_kv_heads),
+                     "s"(p.group), "s"(p.inv_all_heads), "s"(p.inv_heads), "s"(p.inv_group), "s"(p.inv_split_keys), "s"(p.num_splits),
+                     "s"(p.split_keys), "s"(p.rows_pad), "s"(p.out), "s"(p.lse), "s"(p.q_tok), "s"(p.q_head), "s"(p.n_q_heads));   // (see attn_fetch_params)
     constexpr int TPR = D / 4;                       // threads that cover one row of D columns
     constexpr int GROUPS = THREADS / TPR;            // split groups working in parallel
     __shared__ float s_m[GROUPS], s_l[GROUPS];
     __shared__ __align__(16) float s_acc[GROUPS][D];
     // (request, kv head) fastest: workgroup id modulo the XCD count follows the kv head, as in the split kernel
     const int nbh = p.batch * p.n_kv_heads;
-    const int bh = blockIdx.x % nbh, row = blockIdx.x / nbh;
-    const int b = bh / p.n_kv_heads, g = bh % p.n_kv_heads;
+    const QuotRem at = divide(blockIdx.x, nbh, p.inv_all_heads), head = divide(at.r, p.n_kv_heads, p.inv_heads);
+    const int bh = at.r, row = at.q, b = head.q, g = head.r;
     int q0 = 0, ql = p.q_len, kvl = p.kv_len;
     if (p.cu_q) { q0 = p.cu_q[b]; ql = p.cu_q[b + 1] - q0; }
     if (p.cu_kv) { kvl = p.cu_kv[b + 1] - p.cu_kv[b]; }
     if (ql <= 0 || kvl < ql || row >= p.group * ql) return;
     // the partial slots of this (request, head) are consecutive: splits 0..live-1
-    const int live = min(p.num_splits, (kvl + p.split_keys - 1) / p.split_keys);
+    const int live = min(p.num_splits, divide(kvl + p.split_keys - 1, p.split_keys, p.inv_split_keys).q);
     const int64_t slot0 = (int64_t)bh * p.num_splits * p.rows_pad + row;
     const int tid = threadIdx.x;
     const int grp = tid / TPR, col = (tid % TPR) * 4;
@@ -723,7 +741,8 @@ void attn_merge_kernel(const AttnParams p)
         l += f * s_l[gg];
     }
     tot *= 1.f / l;
-    const int t = row / p.group, h = g * p.group + row % p.group;
+    const QuotRem out_at = divide(row, p.group, p.inv_group);
+    const int t = out_at.q, h = g * p.group + out_at.r;
     __bf16* op = p.out + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + col;
     *reinterpret_cast<bf16x4*>(op) = __builtin_convertvector(tot, bf16x4);
     if (p.lse && col == 0)
@@ -737,13 +756,16 @@ template <int D, int PRE>
 __global__ __launch_bounds__(256)
 void attn_merge_rows_kernel(const AttnParams p)
 {
+    __asm__ volatile("" :: "s"(p.part_o), "s"(p.part_ml), "s"(p.cu_q), "s"(p.cu_kv), "s"(p.q_len), "s"(p.kv_len), "s"(p.batch), "s"(p.n_kv_heads),
+                     "s"(p.group), "s"(p.inv_all_heads), "s"(p.inv_heads), "s"(p.inv_group), "s"(p.inv_split_keys), "s"(p.num_splits),
+                     "s"(p.split_keys), "s"(p.rows_pad), "s"(p.out), "s"(p.lse), "s"(p.q_tok), "s"(p.q_head), "s"(p.n_q_heads));   // (see attn_fetch_params)
     constexpr int TPR = D / 4;
     constexpr int GROUPS = 256 / TPR;
     const int nbh = p.batch * p.n_kv_heads;
-    const int bh = blockIdx.x % nbh;
-    const int b = bh / p.n_kv_heads, g = bh % p.n_kv_heads;
+    const QuotRem at = divide(blockIdx.x, nbh, p.inv_all_heads), head = divide(at.r, p.n_kv_heads, p.inv_heads);
+    const int bh = at.r, b = head.q, g = head.r;
     const int tid = threadIdx.x;
-    const int row = (blockIdx.x / nbh) * GROUPS + tid / TPR, col = (tid % TPR) * 4;
+    const int row = at.q * GROUPS + tid / TPR, col = (tid % TPR) * 4;
     int q0 = 0, ql = p.q_len, kvl = p.kv_len;
     if (p.cu_q) { q0 = p.cu_q[b]; ql = p.cu_q[b + 1] - q0; }
     if (p.cu_kv) { kvl = p.cu_kv[b + 1] - p.cu_kv[b]; }
@@ -755,7 +777,7 @@ void attn_merge_rows_kernel(const AttnParams p)
         slot0 = (int64_t)p.seg_table[2 * bh] * p.rows_pad + row;
         step = (int64_t)p.n_kv_heads * p.rows_pad;   // the next group's piece
     } else {
-        live = min(p.num_splits, (kvl + p.split_keys - 1) / p.split_keys);
+        live = min(p.num_splits, divide(kvl + p.split_keys - 1, p.split_keys, p.inv_split_keys).q);
         slot0 = (int64_t)bh * p.num_splits * p.rows_pad + row;
         step = p.rows_pad;
     }
@@ -788,7 +810,8 @@ void attn_merge_rows_kernel(const AttnParams p)
         m = m_new;
     }
     acc *= 1.f / l;
-    const int t = row / p.group, h = g * p.group + row % p.group;
+    const QuotRem out_at = divide(row, p.group, p.inv_group);
+    const int t = out_at.q, h = g * p.group + out_at.r;
     __bf16* op = p.out + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + col;
     *reinterpret_cast<bf16x4*>(op) = __builtin_convertvector(acc, bf16x4);
     if (p.lse && col == 0)
@@ -821,8 +844,8 @@ __device__ __forceinline__ void attn_prefetch_rows(const AttnParams& p, int id)
     if (x >= p.n_main) return;
     int kv0 = 0, kvl = p.kv_len;
     if (p.cu_kv) { kv0 = p.cu_kv[0]; kvl = p.cu_kv[1] - kv0; }
-    const int g = x % p.n_kv_heads;
-    const int per = (kvl + n_help - 1) / n_help;
+    const int g = divide(x, p.n_kv_heads, p.inv_heads).r;
+    const int per = divide(kvl + n_help - 1, n_help, p.inv_help).q;
     const int first = k * per, n = (min(kvl, first + per) - first) * (D / 8);
     u32x4 acc = {0u, 0u, 0u, 0u};
     for (int i = threadIdx.x; i < n; i += THREADS) {
@@ -836,6 +859,7 @@ template <int D, int NW, int CH, int COLS>
 __global__ __launch_bounds__(NW * kWave)
 void attn_short_kernel(const AttnParams p)
 {
+    attn_fetch_params(p);
     constexpr bool DIRECT = COLS < D;
     constexpr int KK = D / 32;                       // MFMA steps over the head dimension
     constexpr int SLICES = D / COLS;
@@ -857,10 +881,11 @@ void attn_short_kernel(const AttnParams p)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, c = lane >> 4;
     // kv heads fastest, as in the split kernel: with 8 kv heads a head's workgroups share an XCD and its L2
-    const int g = blockIdx.x % p.n_kv_heads, rest = blockIdx.x / p.n_kv_heads;
-    const int part = rest % (DIRECT ? SLICES : p.num_splits);            // column slice or key split
-    const int rest2 = rest / (DIRECT ? SLICES : p.num_splits);
-    const int rb = rest2 % p.n_rgroups, b = rest2 / p.n_rgroups;         // block of 16 query rows, request
+    const QuotRem head = divide(blockIdx.x, p.n_kv_heads, p.inv_heads);
+    const QuotRem cut = DIRECT ? QuotRem{head.q / SLICES, head.q % SLICES} : divide(head.q, p.num_splits, p.inv_splits);
+    const QuotRem block = divide(cut.q, p.n_rgroups, p.inv_rgroups);
+    const int g = head.r, part = cut.r;              // (part: column slice or key split)
+    const int rb = block.r, b = block.q;             // block of 16 query rows, request
     int q0 = 0, ql = p.q_len, kv0 = 0, kvl = p.kv_len;
     if (p.cu_q) { q0 = p.cu_q[b]; ql = p.cu_q[b + 1] - q0; kv0 = p.cu_kv[b]; kvl = p.cu_kv[b + 1] - kv0; }
     const int n_rows = p.group * ql;
@@ -871,7 +896,8 @@ void attn_short_kernel(const AttnParams p)
 
     const int row = rb * 16 + r;
     const bool live = row < n_rows;                  // padding rows read row 0: finite, never stored
-    const int t = live ? row / p.group : 0, h = g * p.group + (live ? row % p.group : 0);
+    const QuotRem at = divide(live ? row : 0, p.group, p.inv_group);
+    const int t = at.q, h = g * p.group + at.r;
     const int k_wave = k_begin + wave * WAVE_KEYS;   // this wave's first key
     const char* kbase = reinterpret_cast<const char*>(p.k + (int64_t)kv0 * p.kv_tok + (int64_t)g * p.kv_head);
     const char* vbase = reinterpret_cast<const char*>(p.v + (int64_t)kv0 * p.kv_tok + (int64_t)g * p.kv_head +
@@ -1018,7 +1044,8 @@ void attn_short_kernel(const AttnParams p)
             l_all += f * s_l[w][orow];
         }
         if (DIRECT) {
-            const int to = grow / p.group, ho = g * p.group + grow % p.group;
+            const QuotRem out_at = divide(grow, p.group, p.inv_group);
+            const int to = out_at.q, ho = g * p.group + out_at.r;
             tot *= 1.f / l_all;
             *reinterpret_cast<bf16x4*>(p.out + (int64_t)(q0 + to) * p.q_tok + (int64_t)ho * p.q_head + part * COLS + 4 * piece) =
                 __builtin_convertvector(tot, bf16x4);
@@ -1315,6 +1342,7 @@ static int attn_impl(
     p.batch = batch; p.q_len = q_len; p.kv_len = kv_len;
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.group = group;
     p.scale_log2 = softmax_scale * kLog2e;
+    p.inv_heads = reciprocal(n_kv_heads); p.inv_all_heads = reciprocal(batch * n_kv_heads); p.inv_group = reciprocal(group);
     p.balanced = attn_is_balanced(batch, num_splits, n_kv_heads, rows) ? 1 : 0;
     p.max_wg = kNumCu;
     p.tile_keys = mb == 1 ? 128 : 64;                 // TK of the launch shape chosen below
@@ -1323,6 +1351,7 @@ static int attn_impl(
     p.rows_pad = n_rgroups * mb * 16;
     p.n_rgroups = n_rgroups;
     p.n_work = p.balanced ? p.max_wg : batch * n_kv_heads * p.num_splits * n_rgroups;
+    p.inv_splits = reciprocal(p.num_splits); p.inv_split_keys = reciprocal(p.split_keys); p.inv_help = 0; p.inv_rgroups = reciprocal(n_rgroups);
     p.part_o = nullptr; p.part_ml = nullptr; p.seg_table = nullptr;
     if (p.num_splits > 1) {
         const size_t need = specvlm_decode_attn_workspace_bytes(batch, q_len, kv_len, n_q_heads,
@@ -1337,9 +1366,11 @@ static int attn_impl(
     hipStream_t s = (hipStream_t)stream;
     if (const int chunks = attn_direct_chunks(batch, kv_len, n_kv_heads, head_dim, rows, num_splits)) {
         p.n_rgroups = (rows + 15) / 16;
+        p.inv_rgroups = reciprocal(p.n_rgroups);
         p.n_main = batch * n_kv_heads * p.n_rgroups * (head_dim / 16);
         const int pieces = (kv_len * (head_dim / 8) + kDirectWaves * kWave - 1) / (kDirectWaves * kWave);
         p.n_work = p.n_main + (batch == 1 ? kNumXcd * (pieces < kPrefetchers ? pieces : kPrefetchers) : 0);
+        if (batch == 1) p.inv_help = reciprocal((p.n_work - p.n_main) / kNumXcd);
         return launch_attn_direct(p, head_dim, chunks, s);
     }
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);
