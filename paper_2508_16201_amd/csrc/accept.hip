@@ -8,9 +8,9 @@
 // Pass 2, greedy (one workgroup per request): merge the partials and walk the gamma tests in order.
 // Pass 2, sampling (many workgroups): every workgroup merges the partials and repeats the gamma
 //   accept tests (a few loads), so all agree on the first rejected position n; each then sums the
-//   mass of the residual max(p - q, 0) at row n (of p when every draft survived) over its chunk.
-// Pass 3, sampling (one workgroup per request): inverse CDF over the chunk masses, then inside
-//   the owning chunk over its waves, then inside the owning wave's tokens.
+//   mass of the residual max(p - q, 0) at row n (of p when every draft survived) over its chunk, in
+//   segments.  The workgroup of a request that finishes last goes on: inverse CDF over the chunks,
+//   then over the owning chunk's segments, then over the owning segment's tokens.
 #include "common.h"
 
 namespace specvlm {
@@ -19,6 +19,7 @@ constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / kWave;
 constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup
 constexpr int kAccPerThread = kAccChunk / 256;   // of which each of the 256 threads takes this many
+constexpr int kAccSegs = kAccWaves;              // segments of a chunk, one per wave of the second sampling pass
 constexpr int kAccShort = kAccThreads;           // vocabularies of at most so many have sampling kernels of their own
 
 struct AcceptParams {
@@ -32,15 +33,56 @@ struct AcceptParams {
     int32_t* out_tokens;
     float* part_val;          // [batch][rows][n_chunks]   max
     float* part_aux;          // [batch][rows][n_chunks]   sum exp (sampling) / argmax index bits (greedy)
-    float* norm;              // sampling: [batch][rows][2], first pair (max, sum exp) of target row n, second of draft row n
-    float* chunk_mass;        // sampling: [batch][n_chunks] residual (or target) mass of row n per chunk
-    int32_t* n_rej;           // sampling: [batch] first rejected position n (gamma if none)
+    float* tok_logit;         // sampling: [batch][2 * gamma + 1] logit / T (log2 units) of the drafted token in target and draft rows
+    float* seg_mass;          // sampling: [batch][n_chunks][kAccSegs] residual (or target) mass of row n per segment
+    uint32_t* arrived;        // sampling: [batch] chunks that are done, cleared by pass 1
 };
 
 __device__ __forceinline__ void argmax_merge(float& bv, int& bi, float v, int i)
 {
     // larger value wins; equal values: lower index wins.  (i < 0 = empty; no NaN gets here)
     if (i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
+}
+
+// Wave-wide float reductions and prefix sums by DPP (rows of 16 lanes, then the rows' totals): a shuffle is an LDS round trip.
+template <int CTRL, int ROWS> __device__ __forceinline__ float lane_move(float x, float other)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(other), (int)__float_as_uint(x), CTRL, ROWS, 0xf, false));
+}
+
+__device__ __forceinline__ float wave_prefix(float x)                // lane i: the sum of lanes 0 .. i
+{
+    x += lane_move<0x111, 0xf>(x, 0.f);      // row_shr 1, 2, 4, 8
+    x += lane_move<0x112, 0xf>(x, 0.f);
+    x += lane_move<0x114, 0xf>(x, 0.f);
+    x += lane_move<0x118, 0xf>(x, 0.f);
+    x += lane_move<0x142, 0xa>(x, 0.f);      // row_bcast 15, into rows 1 and 3
+    return x + lane_move<0x143, 0xc>(x, 0.f);   // row_bcast 31, into rows 2 and 3
+}
+
+__device__ __forceinline__ float from_lane(float x, int lane) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane)); }
+__device__ __forceinline__ float wave_sum(float x) { return from_lane(wave_prefix(x), 63); }
+
+__device__ __forceinline__ float row_max(float x)                    // over the lane's row of 16
+{
+    x = fmaxf(x, lane_move<0xB1, 0xf>(x, x));    // lane ^ 1, lane ^ 2, then the other four (mirrored) and the other eight
+    x = fmaxf(x, lane_move<0x4E, 0xf>(x, x));
+    x = fmaxf(x, lane_move<0x141, 0xf>(x, x));
+    return fmaxf(x, lane_move<0x140, 0xf>(x, x));
+}
+
+__device__ __forceinline__ float row_sum(float x)
+{
+    x += lane_move<0xB1, 0xf>(x, 0.f);
+    x += lane_move<0x4E, 0xf>(x, 0.f);
+    x += lane_move<0x141, 0xf>(x, 0.f);
+    return x + lane_move<0x140, 0xf>(x, 0.f);
+}
+
+__device__ __forceinline__ float wave_max(float x)
+{
+    x = row_max(x);
+    return fmaxf(fmaxf(from_lane(x, 0), from_lane(x, 16)), fmaxf(from_lane(x, 32), from_lane(x, 48)));
 }
 
 // ---------------------------------------------------------------- greedy ----
@@ -147,6 +189,10 @@ void accept_softmax_partial(const AcceptParams p)
 {
     __shared__ float s_m[4], s_z[4];
     const int chunk = blockIdx.x, row = blockIdx.y, b = blockIdx.z;
+    // (pass 2 would look the drafted token's logits up behind its tokens, two round trips that nothing there covers)
+    const int draft = row <= p.gamma ? row : row - p.gamma - 1;
+    const int tok = draft < p.gamma ? p.tokens[(int64_t)b * p.gamma + draft] : -1;
+    if (chunk == 0 && row == 0 && threadIdx.x == 0) p.arrived[b] = 0u;
     const float* x = row <= p.gamma
         ? p.target + ((int64_t)b * (p.gamma + 1) + row) * p.vocab
         : p.draft + ((int64_t)b * p.gamma + (row - p.gamma - 1)) * p.vocab;
@@ -158,11 +204,11 @@ void accept_softmax_partial(const AcceptParams p)
         const int v = lo + j * 256 + threadIdx.x;
         y[j] = v < hi ? x[v] * p.inv_t_log2 : -INFINITY;
     }
+    if (threadIdx.x == 0 && tok >= lo && tok < hi) p.tok_logit[(int64_t)b * (2 * p.gamma + 1) + row] = x[tok] * p.inv_t_log2;
     float m = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kAccPerThread; ++j) m = fmaxf(m, y[j]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    m = wave_max(m);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) s_m[wave] = m;
     __syncthreads();
@@ -170,8 +216,7 @@ void accept_softmax_partial(const AcceptParams p)
     float z = 0.f;
 #pragma unroll
     for (int j = 0; j < kAccPerThread; ++j) z += fast_exp2(y[j] - m);       // (-inf padding adds 0)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) z += __shfl_xor(z, off);
+    z = wave_sum(z);
     if (lane == 0) s_z[wave] = z;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -181,30 +226,31 @@ void accept_softmax_partial(const AcceptParams p)
     }
 }
 
-// Merged (max, sum exp) of every row from its pass-1 partials, into LDS.
+// Merged (max, sum exp) of every row from its pass-1 partials, into LDS: sixteen lanes a row, four chunks each a trip.
 __device__ __forceinline__ void accept_merge_rows(const AcceptParams& p, int rows, const float* val, const float* aux,
                                                   float* s_m, float* s_z)
 {
-    for (int row = threadIdx.x; row < rows; row += blockDim.x) {
-        const int slot = row * p.n_chunks;
+    const int l = threadIdx.x & 15;
+    for (int row = threadIdx.x >> 4; row < rows; row += kAccThreads / 16) {
         float m = -INFINITY, z = 0.f;
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 8) {         // eight chunks' loads in flight at a time
-            float pm[8], pz[8];
+        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
+            float pm[4], pz[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool in = c0 + j < p.n_chunks;
-                pm[j] = in ? val[slot + c0 + j] : -INFINITY;
-                pz[j] = in ? aux[slot + c0 + j] : 0.f;
+            for (int j = 0; j < 4; ++j) {
+                if (c0 + 16 * j >= p.n_chunks) { pm[j] = -INFINITY; pz[j] = 0.f; continue; }
+                const int c = min(c0 + 16 * j + l, p.n_chunks - 1);
+                const bool in = c0 + 16 * j + l < p.n_chunks;
+                pm[j] = val[(int64_t)row * p.n_chunks + c]; pz[j] = aux[(int64_t)row * p.n_chunks + c];
+                pm[j] = in ? pm[j] : -INFINITY; pz[j] = in ? pz[j] : 0.f;
             }
-            float mc = m;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) mc = fmaxf(mc, pm[j]);
+            const float mc = row_max(fmaxf(fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])), m));
             z *= (mc == -INFINITY) ? 0.f : fast_exp2(m - mc);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) z += (pz[j] > 0.f) ? pz[j] * fast_exp2(pm[j] - mc) : 0.f;
+            for (int j = 0; j < 4; ++j) z += (pz[j] > 0.f) ? pz[j] * fast_exp2(pm[j] - mc) : 0.f;
             m = mc;
         }
-        s_m[row] = m; s_z[row] = z;
+        z = row_sum(z);
+        if (l == 0) { s_m[row] = m; s_z[row] = z; }
     }
 }
 
@@ -247,120 +293,116 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
     return w;
 }
 
-// The chain of round trips is what this kernel costs (two for the accept tests' tokens and logits, one for the pass-1
-// partials, one for the rejected row), so the first three run beside each other: the partials of all rows are fetched
-// by all threads, into LDS, where they fit (a thread per row fetching eight chunks at a time took one trip per eight).
-// gamma 7, 152064 tokens: 8.5 -> 5.9 us with the loads of both rows batched (AcceptWeight); the final kernel 9.3 -> 5.6.
-// SHORT: one chunk, of which a thread here has four tokens and a wave of the final kernel 64.  There is nothing to stage,
-// and going through a whole chunk cost more than it fetched (1024 tokens, gamma 5, the whole call: 13.5 us, now 10.6; with
-// a branch inside instead of kernels of their own the large vocabularies lost 0.5 us).
-constexpr int kMergeStage = 4096;           // pass-1 partials of a request that are staged (152064 tokens: 215 rows)
+// Bound: its chain of round trips -- the partials beside the accept tests' inputs, the rejected row, the masses beside the
+// arrival, the owning segment -- and the launches.  As a launch of its own the inverse CDF cost another start, the
+// statistics' way through memory and a gap between launches.
+//
+// The last workgroup of a request goes on.  Pass 1 has cleared the arrival counter, so nothing is asked of the workspace's
+// earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release), the one
+// that finds all others counted (acquire) reads them.  With an acquire alone or neither, behind a wait for the stores, the
+// call takes the same time.  gamma 7, 152064 tokens, from a graph: 19.7 us with a third launch and the tests' logits looked up
+// here, now 13.7; 32000 tokens 16.9 / 12.9, 8 requests 38.6 / 33.0, 1024 tokens, gamma 3, 4 requests 10.6 / 7.8.
+// SHORT: one chunk, of which a wave has 64 tokens: nothing to exchange.
+constexpr int kAccSegSteps = kAccChunk / kAccThreads;        // of 64 tokens each
 
-template <bool SHORT>
-__global__ __launch_bounds__(256)
-void accept_mass_partial(const AcceptParams p)
-{
-    __shared__ float s_val[SHORT ? 1 : kMergeStage], s_aux[SHORT ? 1 : kMergeStage];
-    __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
-    __shared__ float s_part[4];
-    __shared__ int s_n;
-    const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rows = 2 * p.gamma + 1;
-    // The gamma accept tests, one per lane of the first wave (gamma <= 64): every test's loads are in flight together,
-    // beside the partials; the first failing test is found by a ballot.
-    bool ok = true;
-    float t_logit = 0.f, d_logit = 0.f, u = 0.f;
-    if (tid < p.gamma) {
-        const int tok = p.tokens[(int64_t)b * p.gamma + tid];
-        ok = tok >= 0 && tok < p.vocab;                          // not a token: cannot be accepted
-        if (ok) {
-            t_logit = p.target[((int64_t)b * (p.gamma + 1) + tid) * p.vocab + tok];
-            d_logit = p.draft[((int64_t)b * p.gamma + tid) * p.vocab + tok];
-            u = p.uniforms[(int64_t)b * (p.gamma + 1) + tid];
-        }
-    }
-    const float* val = p.part_val + (int64_t)b * rows * p.n_chunks;
-    const float* aux = p.part_aux + (int64_t)b * rows * p.n_chunks;
-    if (!SHORT && rows * (int64_t)p.n_chunks <= kMergeStage) {
-        for (int i = tid; i < rows * p.n_chunks; i += 256) { s_val[i] = val[i]; s_aux[i] = aux[i]; }
-        __syncthreads();
-        accept_merge_rows(p, rows, s_val, s_aux, s_m, s_z);
-    } else {
-        accept_merge_rows(p, rows, val, aux, s_m, s_z);
-    }
-    __syncthreads();
-    if (wave == 0) {
-        if (lane < p.gamma && ok) {
-            const float pt = fast_exp2(t_logit * p.inv_t_log2 - s_m[lane]) / s_z[lane];
-            const float qd = fast_exp2(d_logit * p.inv_t_log2 - s_m[p.gamma + 1 + lane]) / s_z[p.gamma + 1 + lane];
-            ok = u * qd < pt;
-        }
-        const uint64_t failed = __ballot(!ok);
-        if (lane == 0) s_n = failed ? __ffsll((long long)failed) - 1 : p.gamma;
-    }
-    __syncthreads();
-    const int n = s_n;
-    const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
-    if (chunk == 0 && tid == 0) {                                // what pass 3 needs of the above
-        float* nm = p.norm + (int64_t)b * rows * 2;
-        nm[0] = s_m[n]; nm[1] = s_z[n];
-        if (n < p.gamma) { nm[2] = s_m[dn]; nm[3] = s_z[dn]; }
-        p.n_rej[b] = n;
-    }
-    const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
-    const int lo = chunk * kAccChunk, hi = min(p.vocab, lo + kAccChunk);
-    float w[SHORT ? kAccShort / 256 : kAccPerThread];
-    weight(w, lo + tid, 256, hi);
-    float mine = 0.f;
-#pragma unroll
-    for (const float x : w) mine += x;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
-    if (lane == 0) s_part[wave] = mine;
-    __syncthreads();
-    if (tid == 0) p.chunk_mass[(int64_t)b * p.n_chunks + chunk] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
-}
+__device__ __forceinline__ void store_device(float* at, float x) { __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_device(const float* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 template <bool SHORT>
 __global__ __launch_bounds__(kAccThreads)
-void accept_sample_final(const AcceptParams p)
+void accept_sample_kernel(const AcceptParams p)
 {
+    __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
+    __shared__ float s_seg[kAccSegs];
     __shared__ float s_w[kAccWaves];
     __shared__ int s_idx[kAccWaves];
-    __shared__ int s_y;
-    __shared__ float s_cm[kAccThreads];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float s_mass;
+    __shared__ int s_last;
+    const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = 2 * p.gamma + 1;
-    // (everything that does not depend on the owning chunk is requested together: one round trip)
-    const int drafted = tid < p.gamma ? p.tokens[(int64_t)b * p.gamma + tid] : -1;
-    const float u_last = p.uniforms[(int64_t)b * (p.gamma + 1) + p.gamma];
-    const float* cm = p.chunk_mass + (int64_t)b * p.n_chunks;
-    const float my_cm = tid < p.n_chunks ? cm[tid] : 0.f;
-    const int n = p.n_rej[b];
-    const float* nm = p.norm + (int64_t)b * rows * 2;
-    const int second = p.gamma > 0 ? 2 : 0;                      // (gamma = 0: one row, nothing to reject)
-    const AcceptWeight weight = accept_weight(p, b, n, nm[0], nm[1], nm[second], nm[second + 1]);
-    if (tid == 0) s_y = -1;
-    if (!SHORT) {
-        s_cm[tid] = my_cm;
-        __syncthreads();
-        if (p.n_chunks <= kAccThreads) cm = s_cm;
+    // The gamma accept tests, one per lane (gamma <= 64) and again in every wave, which saves a barrier: their inputs are
+    // in flight beside the partials, the first failing test is found by a ballot.
+    int tok = -1;
+    float t_logit = 0.f, d_logit = 0.f, u = 0.f;
+    if (lane < p.gamma) {
+        tok = p.tokens[(int64_t)b * p.gamma + lane];
+        t_logit = p.tok_logit[(int64_t)b * rows + lane];
+        d_logit = p.tok_logit[(int64_t)b * rows + p.gamma + 1 + lane];
+        u = p.uniforms[(int64_t)b * (p.gamma + 1) + lane];
     }
-    // total mass and the owner of the goal among the chunks: the LAST chunk with mass whose prefix
-    // does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that
-    // rounding put at or beyond the total lands on the last chunk with mass).  Every thread walks
-    // the same few numbers in the same order.
-    float W = 0.f;
-    for (int c = 0; c < p.n_chunks; ++c) W += cm[c];
+    const float u_last = p.uniforms[(int64_t)b * (p.gamma + 1) + p.gamma];
+    accept_merge_rows(p, rows, p.part_val + (int64_t)b * rows * p.n_chunks, p.part_aux + (int64_t)b * rows * p.n_chunks, s_m, s_z);
+    __syncthreads();
+    bool ok = true;
+    if (lane < p.gamma) {
+        const float pt = fast_exp2(t_logit - s_m[lane]) / s_z[lane];
+        const float qd = fast_exp2(d_logit - s_m[p.gamma + 1 + lane]) / s_z[p.gamma + 1 + lane];
+        ok = tok >= 0 && tok < p.vocab && u * qd < pt;           // (not a token: cannot be accepted, and has no logits)
+    }
+    const uint64_t failed = __ballot(!ok);
+    const int n = failed ? __ffsll((long long)failed) - 1 : p.gamma;
+    const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
+    const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
+    constexpr int STEPS = SHORT ? 1 : kAccSegSteps;
+    // a chunk's segments are as wide as it takes to deal it to the waves in token order
+    auto segment = [&](int c, int w, int& lo, int& hi) __attribute__((always_inline)) {
+        const int from = c * kAccChunk, to = min(p.vocab, from + kAccChunk);
+        const int width = ((to - from + kAccSegs - 1) / kAccSegs + 63) & ~63;
+        lo = min(to, from + w * width); hi = min(to, lo + width);
+    };
+    int lo, hi;
+    segment(chunk, wave, lo, hi);
+    float w2[STEPS], mine = 0.f;
+    weight(w2, lo + lane, 64, hi);
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) mine += w2[i];
+    mine = wave_sum(mine);
+    if (lane == 0) s_seg[wave] = mine;
+    float* const masses = p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs;
+    __syncthreads();
+    if (!SHORT) {
+        if (wave == 0) {
+            if (lane < kAccSegs) store_device(masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
+            if (lane == 0) s_last = __hip_atomic_fetch_add(p.arrived + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.n_chunks - 1u;
+        }
+        __syncthreads();
+        if (!s_last) return;
+    }
+    // ---- the last workgroup: total mass and the owner of the goal among the chunks: the LAST chunk with mass whose prefix
+    // does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that rounding put at or
+    // beyond the total lands on the last chunk with mass).  A lane per chunk, 64 at a time.
+    float seg[kAccSegs];                                         // the lane's chunk's segments
+    auto chunk_mass = [&](int c) __attribute__((always_inline)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < kAccSegs; ++i) seg[i] = c < p.n_chunks ? (SHORT ? s_seg[i] : load_device(masses + (int64_t)c * kAccSegs + i)) : 0.f;
+#pragma unroll
+        for (int i = 0; i < kAccSegs; ++i) sum += seg[i];
+        return sum;
+    };
+    float W = 0.f, m1 = 0.f, incl1 = 0.f;
+    if (wave == 0) {
+        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
+            m1 = chunk_mass(c0 + lane);
+            incl1 = wave_prefix(m1);
+            W += from_lane(incl1, 63);
+        }
+        if (lane == 0) s_mass = W;
+    }
+    __syncthreads();
+    W = s_mass;
+    const int drafted = tid < p.gamma ? tok : -1;                // (lane = tid in the first wave, gamma <= 64)
+    int y = -1;
     if (!(W > 0.f)) {
         // no residual mass (p == q): fall back to the target's most likely token
-        const int seg = ((p.vocab + kAccWaves - 1) / kAccWaves + 63) & ~63;
-        const int lo = min(p.vocab, wave * seg), hi = min(p.vocab, lo + seg);
+        const int share = ((p.vocab + kAccWaves - 1) / kAccWaves + 63) & ~63;
+        const int from = min(p.vocab, wave * share), to = min(p.vocab, from + share);
         float bv = -INFINITY;
-        int bi = lo + lane < hi ? lo + lane : -1;
-        for (int v = lo + lane; v < hi; v += 64) {
-            const float y = weight.trow[v];
-            if (y > bv) { bv = y; bi = v; }                      // (never a NaN, as in accept_argmax_partial)
+        int bi = from + lane < to ? from + lane : -1;
+        for (int v = from + lane; v < to; v += 64) {
+            const float x = weight.trow[v];
+            if (x > bv) { bv = x; bi = v; }                      // (never a NaN, as in accept_argmax_partial)
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
@@ -370,75 +412,59 @@ void accept_sample_final(const AcceptParams p)
         }
         if (lane == 0) { s_w[wave] = bv; s_idx[wave] = bi; }
         __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < kAccWaves; ++w) argmax_merge(bv, bi, s_w[w], s_idx[w]);
-            s_y = bi;
-        }
-        __syncthreads();
+        if (wave != 0) return;
+        for (int w = 1; w < kAccWaves; ++w) argmax_merge(bv, bi, s_w[w], s_idx[w]);
+        y = __builtin_amdgcn_readfirstlane(bi);
     } else {
+        if (wave != 0) return;
         const float goal = u_last * W;
         int own1 = 0;                                            // (no chunk qualifies for a uniform below 0 or NaN)
-        float pre1 = 0.f, acc1 = 0.f;
-        for (int c = 0; c < p.n_chunks; ++c) {
-            const float m = cm[c];
-            if (m > 0.f && acc1 <= goal) { own1 = c; pre1 = acc1; }
-            acc1 += m;
+        float pre1 = 0.f, before = 0.f, own_seg[kAccSegs];
+        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
+            if (p.n_chunks > 64) { m1 = chunk_mass(c0 + lane); incl1 = wave_prefix(m1); }
+            const float below = __shfl_up(incl1, 1);             // (by all lanes: one that is switched off gives 0)
+            const float excl = before + (lane == 0 ? 0.f : below);
+            const uint64_t fits = __ballot(m1 > 0.f && excl <= goal);
+            const int l = fits ? 63 - __builtin_clzll(fits) : 0;
+            if (fits || c0 == 0) {
+                own1 = c0 + l;
+                pre1 = fits ? from_lane(excl, l) : 0.f;
+#pragma unroll
+                for (int i = 0; i < kAccSegs; ++i) own_seg[i] = from_lane(seg[i], l);
+            }
+            before += from_lane(incl1, 63);
         }
-        // Inside the owning chunk the same rule picks a wave's share (the chunk is dealt to the
-        // waves in token order), and the owning wave walks its few hundred tokens 64 at a time for
-        // the first token whose cumulative mass passes the goal, else takes its last token with mass.
-        const int lo1 = own1 * kAccChunk, hi1 = min(p.vocab, lo1 + kAccChunk);
-        const int seg2 = ((hi1 - lo1 + kAccWaves - 1) / kAccWaves + 63) & ~63;
-        const int lo2 = min(hi1, lo1 + wave * seg2), hi2 = min(hi1, lo2 + seg2);
-        constexpr int STEPS = SHORT ? 1 : kAccChunk / kAccThreads;   // of 64 tokens of a wave's share
-        float w2[STEPS], mine2 = 0.f;
-        weight(w2, lo2 + lane, 64, hi2);
-#pragma unroll
-        for (int i = 0; i < STEPS; ++i) mine2 += w2[i];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) mine2 += __shfl_xor(mine2, off);
-        if (lane == 0) s_w[wave] = mine2;
-        __syncthreads();
-        int own2 = -1;
+        // the same rule picks a segment of the owning chunk, whose few hundred tokens are then walked 64 at a time for
+        // the first one whose cumulative mass passes the goal, else its last token with mass (rounding can leave no segment
+        // that fits although the chunk had mass: the first one then)
+        int own2 = 0;
         float pre2 = pre1, acc2 = pre1;
 #pragma unroll
-        for (int w = 0; w < kAccWaves; ++w) {
-            if (s_w[w] > 0.f && acc2 <= goal) { own2 = w; pre2 = acc2; }
-            acc2 += s_w[w];
+        for (int w = 0; w < kAccSegs; ++w) {
+            if (own_seg[w] > 0.f && acc2 <= goal) { own2 = w; pre2 = acc2; }
+            acc2 += own_seg[w];
         }
-        // (rounding can leave the chunk's own waves without mass although the chunk had some: the
-        // first wave then reports the chunk's last token with mass, or its first token)
-        if (own2 < 0) own2 = 0;
-        if (wave == own2) {
-            // (the scans of the steps do not depend on each other: six shuffles deep, not six per step)
-            float incl[STEPS];
+        own2 = __builtin_amdgcn_readfirstlane(own2);
+        segment(own1, own2, lo, hi);
+        weight(w2, lo + lane, 64, hi);
+        float c = pre2;
+        int last = -1;
 #pragma unroll
-            for (int i = 0; i < STEPS; ++i) incl[i] = w2[i];
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-                for (int i = 0; i < STEPS; ++i) {
-                    const float t = __shfl_up(incl[i], off);
-                    if (lane >= off) incl[i] += t;
-                }
-            }
-            float c = pre2;
-            int y = -1, last = -1;
-#pragma unroll
-            for (int i = 0; i < STEPS; ++i) {
-                const int base = lo2 + 64 * i;
-                const uint64_t massive = __ballot(w2[i] > 0.f);
-                const uint64_t passed = __ballot(w2[i] > 0.f && c + incl[i] > goal);
-                if (massive) last = base + 63 - __builtin_clzll(massive);
-                if (passed && y < 0) y = base + __ffsll((long long)passed) - 1;
-                c += __shfl(incl[i], 63);
-            }
-            if (lane == 0) s_y = y >= 0 ? y : (last >= 0 ? last : lo1);
+        for (int i = 0; i < STEPS; ++i) {
+            const float incl = wave_prefix(w2[i]);
+            const int base = lo + 64 * i;
+            const uint64_t massive = __ballot(w2[i] > 0.f);
+            const uint64_t passed = __ballot(w2[i] > 0.f && c + incl > goal);
+            if (massive) last = base + 63 - __builtin_clzll(massive);
+            if (passed && y < 0) y = base + __ffsll((long long)passed) - 1;
+            c += from_lane(incl, 63);
         }
-        __syncthreads();
+        if (y < 0) y = last >= 0 ? last : own1 * kAccChunk;
     }
-    if (tid <= p.gamma) p.out_tokens[(int64_t)b * (p.gamma + 1) + tid] = tid < n ? drafted : (tid == n ? s_y : -1);
-    if (tid == 0) p.n_accepted[b] = n;
+    // (the first wave only from here on)
+    for (int i = lane; i <= p.gamma; i += 64)
+        p.out_tokens[(int64_t)b * (p.gamma + 1) + i] = i < n ? drafted : (i == n ? y : -1);      // (i < n implies i = lane < gamma)
+    if (lane == 0) p.n_accepted[b] = n;
 }
 
 // ------------------------------------------------------------------ tree ----
@@ -500,10 +526,10 @@ extern "C" size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab
     if (batch <= 0 || gamma < 0 || vocab < 1) return 0;
     const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
     size_t bytes = 2 * align256((size_t)batch * rows * accept_chunks(vocab) * sizeof(float));
-    if (sampling)       // merged row statistics, chunk masses of the rejected row, rejected positions
-        bytes += align256((size_t)batch * rows * 2 * sizeof(float)) +
-                 align256((size_t)batch * accept_chunks(vocab) * sizeof(float)) +
-                 align256((size_t)batch * sizeof(int32_t));
+    if (sampling)       // the drafted tokens' logits, segment masses of the rejected row, arrivals
+        bytes += align256((size_t)batch * rows * sizeof(float)) +
+                 align256((size_t)batch * accept_chunks(vocab) * kAccSegs * sizeof(float)) +
+                 align256((size_t)batch * sizeof(uint32_t));
     return bytes;
 }
 
@@ -536,9 +562,9 @@ extern "C" int specvlm_accept(
     char* ws = (char*)workspace;
     p.part_val = (float*)ws;
     p.part_aux = (float*)(ws + part_bytes);
-    p.norm = (float*)(ws + 2 * part_bytes);
-    p.chunk_mass = (float*)((char*)p.norm + align256((size_t)batch * rows * 2 * sizeof(float)));
-    p.n_rej = (int32_t*)((char*)p.chunk_mass + align256((size_t)batch * p.n_chunks * sizeof(float)));
+    p.tok_logit = (float*)(ws + 2 * part_bytes);                 // (sampling only, from here on)
+    p.seg_mass = (float*)((char*)p.tok_logit + align256((size_t)batch * rows * sizeof(float)));
+    p.arrived = (uint32_t*)((char*)p.seg_mass + align256((size_t)batch * p.n_chunks * kAccSegs * sizeof(float)));
     hipStream_t s = (hipStream_t)stream;
     if (!sampling) {
         hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, gamma + 1, batch), dim3(256), 0, s, p);
@@ -548,13 +574,8 @@ extern "C" int specvlm_accept(
             hipLaunchKernelGGL(accept_greedy_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
         hipLaunchKernelGGL(accept_softmax_partial, dim3(p.n_chunks, 2 * gamma + 1, batch), dim3(256), 0, s, p);
-        if (vocab <= kAccShort) {
-            hipLaunchKernelGGL(accept_mass_partial<true>, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
-            hipLaunchKernelGGL(accept_sample_final<true>, dim3(batch), dim3(kAccThreads), 0, s, p);
-        } else {
-            hipLaunchKernelGGL(accept_mass_partial<false>, dim3(p.n_chunks, batch), dim3(256), 0, s, p);
-            hipLaunchKernelGGL(accept_sample_final<false>, dim3(batch), dim3(kAccThreads), 0, s, p);
-        }
+        if (vocab <= kAccShort) hipLaunchKernelGGL(accept_sample_kernel<true>, dim3(1, batch), dim3(kAccThreads), 0, s, p);
+        else hipLaunchKernelGGL(accept_sample_kernel<false>, dim3(p.n_chunks, batch), dim3(kAccThreads), 0, s, p);
     }
     return launch_status();
 }
@@ -585,7 +606,7 @@ extern "C" int specvlm_accept_tree(
     p.n_accepted = n_accepted; p.out_tokens = out_tokens;
     p.part_val = (float*)workspace;
     p.part_aux = (float*)((char*)workspace + need / 2);
-    p.norm = nullptr; p.chunk_mass = nullptr; p.n_rej = nullptr;
+    p.tok_logit = nullptr; p.seg_mass = nullptr; p.arrived = nullptr;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, n_nodes, batch), dim3(256), 0, s, p);
     if (accept_final_lanes(n_nodes, p.n_chunks) == 1)
