@@ -1230,8 +1230,17 @@ static int launch_short(const AttnParams& p, hipStream_t stream)
     return launch_status();
 }
 
+// Waves of a workgroup without splits: eight, or sixteen with half the keys each where a wave of eight would have many.  The
+// loads take as long either way, but less is left to do behind the last of them (us a layer, eight / sixteen): size 64, 14/2
+// heads, 1511 keys 6.36 / 6.27, 1400 keys, 26 nodes 7.13 / 6.96, but 1200 keys 5.69 / 5.99 (half a wave's keys are past the end), 1000
+// keys 5.27 / 5.40;  size 128, 64/8 heads, 6 queries, 700 keys 6.53 / 6.34, 1000 keys 8.65 / 8.24, 40/8, 4 queries, 900 keys 8.37 / 7.91,
+// 6 queries, 600 keys 6.04 / 6.14, 28/4, 1000 keys 7.09 / 7.14, 8 queries 7.99 / 7.73, 400 keys 4.85 / 5.27.
+static bool attn_direct_16_waves(int head_dim, int kv_len) { return kv_len > (head_dim == 64 ? 1280 : 640); }
+
 static int launch_attn_direct(const AttnParams& p, int head_dim, int chunks, hipStream_t stream)
 {
+    if (attn_direct_16_waves(head_dim, p.kv_len))
+        return head_dim == 64 ? launch_short<64, 2 * kDirectWaves, 3, 16>(p, stream) : launch_short<128, 2 * kDirectWaves, 2, 16>(p, stream);
     if (head_dim == 64) {
         switch (chunks) {
             case 1: return launch_short<64, kDirectWaves, 1, 16>(p, stream);
@@ -1239,14 +1248,12 @@ static int launch_attn_direct(const AttnParams& p, int head_dim, int chunks, hip
             case 3: return launch_short<64, kDirectWaves, 3, 16>(p, stream);
             case 4: return launch_short<64, kDirectWaves, 4, 16>(p, stream);
             case 5: return launch_short<64, kDirectWaves, 5, 16>(p, stream);
-            case 6: return launch_short<64, kDirectWaves, 6, 16>(p, stream);
         }
     } else {
         switch (chunks) {
             case 1: return launch_short<128, kDirectWaves, 1, 16>(p, stream);
             case 2: return launch_short<128, kDirectWaves, 2, 16>(p, stream);
             case 3: return launch_short<128, kDirectWaves, 3, 16>(p, stream);
-            case 4: return launch_short<128, kDirectWaves, 4, 16>(p, stream);
         }
     }
     return SPECVLM_EUNSUPPORTED;
@@ -1388,9 +1395,14 @@ static int attn_impl(
         p.n_rgroups = (rows + 15) / 16;
         p.inv_rgroups = reciprocal(p.n_rgroups);
         p.n_main = batch * n_kv_heads * p.n_rgroups * (head_dim / 16);
-        const int pieces = (kv_len * (head_dim / 8) + kDirectWaves * kWave - 1) / (kDirectWaves * kWave);
-        p.n_work = p.n_main + (batch == 1 ? kNumXcd * (pieces < kPrefetchers ? pieces : kPrefetchers) : 0);
-        if (batch == 1) p.inv_help = reciprocal((p.n_work - p.n_main) / kNumXcd);
+        const int threads = (attn_direct_16_waves(head_dim, kv_len) ? 2 : 1) * kDirectWaves * kWave;
+        int helpers = (kv_len * (head_dim / 8) + threads - 1) / threads;
+        if (helpers > kPrefetchers) helpers = kPrefetchers;
+        // (sixteen waves' LDS leaves a CU no second workgroup: a helper that finds none free would run when all is over; 64/8 heads, 8
+        // queries, 700 keys 7.43 us a layer with all 120 of them, 6.93 with none, 7.02 with eight waves and 120)
+        if (threads > kDirectWaves * kWave && helpers > (kNumCu - p.n_main) / kNumXcd) helpers = (kNumCu - p.n_main) / kNumXcd;
+        p.n_work = p.n_main + (batch == 1 ? kNumXcd * helpers : 0);
+        if (p.n_work > p.n_main) p.inv_help = reciprocal((p.n_work - p.n_main) / kNumXcd);
         return launch_attn_direct(p, head_dim, chunks, s);
     }
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);

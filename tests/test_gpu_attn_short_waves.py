@@ -1,0 +1,27 @@
+"""GPU parity of the decode attention over short caches where its workgroups go from eight waves to sixteen: the last cache
+length of one and the first of the other, waves without keys and with a single one, launches that leave some, one or no CU
+for helper workgroups, a ragged batch and a tree.  Bounds: those of every attention test."""
+import pytest
+
+import test_gpu_attn_short as base
+
+pytestmark = pytest.mark.gpu
+B = base.B
+
+
+@pytest.mark.parametrize("q_len,kv_len,hq,hkv,d", [
+    (1, 1280, 14, 2, 64), (1, 1281, 14, 2, 64), (3, 1344, 14, 2, 64), (2, 1345, 8, 8, 64), (16, 1441, 32, 8, 64),
+    (1, 640, 8, 2, 128), (1, 641, 8, 2, 128), (8, 641, 64, 8, 128), (6, 705, 64, 8, 128), (4, 961, 32, 4, 128), (31, 700, 8, 4, 128),
+])
+def test_edges(B, q_len, kv_len, hq, hkv, d):
+    base.test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, 0)
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d", [([1281, 1400, 33, 1536], 8, 2, 64), ([641, 3, 900], 8, 2, 128)])
+def test_ragged_batch(B, lens, hq, hkv, d):
+    base.ragged_case(B, lens, [2] * len(lens), hq, hkv, d)
+
+
+@pytest.mark.parametrize("n_nodes,kv_len,hq,hkv,d", [(26, 1400, 14, 2, 64), (40, 800, 4, 1, 128)])
+def test_tree(B, n_nodes, kv_len, hq, hkv, d):
+    base.test_tree_over_a_short_cache(B, n_nodes, kv_len, hq, hkv, d)
