@@ -228,12 +228,13 @@ void score_sweep_kernel(const ScoreParams p_launch)
     // ---- stationary fragments (B operand) ----
     bf16x8 sf[4][KK];
     int lim[4];                                 // pass A: last visible key of the lane's row
-    int key_abs[4];                             // pass B: absolute key index of the lane's key
+    const int key_abs = p.video_start + stat0 + r;   // pass B: absolute key index of the lane's first key, the others 16 on each
+    const bool live = stat0 < (MODE == 0 ? p.rows : p.n_video);  // (a wave of padding only loads)
 #pragma unroll
     for (int sb = 0; sb < 4; ++sb) {
         const int item = stat0 + sb * 16 + r;
         const __bf16* src = nullptr;
-        lim[sb] = -1; key_abs[sb] = 0x7fffffff;
+        lim[sb] = -1;
         if (MODE == 0) {
             const int gl = item / p.l_pad, i = item % p.l_pad;
             if (item < p.rows && i < p.n_text) {
@@ -242,8 +243,7 @@ void score_sweep_kernel(const ScoreParams p_launch)
             }
         } else {
             if (item < p.n_video) {
-                key_abs[sb] = p.video_start + item;
-                src = p.k + (int64_t)key_abs[sb] * p.k_tok + (int64_t)g * p.k_head;
+                src = p.k + (int64_t)(p.video_start + item) * p.k_tok + (int64_t)g * p.k_head;
             }
         }
 #pragma unroll
@@ -377,7 +377,7 @@ void score_sweep_kernel(const ScoreParams p_launch)
                 const int sb = (i - 1) / 4, e = (i - 1) % 4;
                 y_prev = fast_exp2(x_prev);
                 // text query (lim0 + sub*16 + e) - text_pos0 of this tile sees keys <= lim0 + sub*16 + e
-                if (MODE == 1 && mask) y_prev = (key_abs[sb] > lim0 + sub * 16 + e) ? 0.f : y_prev;
+                if (MODE == 1 && mask) y_prev = (key_abs + 16 * sb > lim0 + sub * 16 + e) ? 0.f : y_prev;
             }
             if (i < 16) {                                   // exponent of logit i
                 const int sb = i / 4, e = i % 4;
@@ -452,7 +452,7 @@ void score_sweep_kernel(const ScoreParams p_launch)
             __builtin_amdgcn_s_barrier();
             __asm__ volatile("" ::: "memory");
             issue_next(st_fill);
-            compute(st_use, s_begin + t * kScoreTile, use_i0, t == 0);
+            if (live) compute(st_use, s_begin + t * kScoreTile, use_i0, t == 0);
             if (MODE == 1) { use_i0 += kScoreTile; if (use_i0 >= p.l_pad) use_i0 = 0; }
             st_use = (st_use + 1 == NS) ? 0 : st_use + 1;
             st_fill = (st_fill + 1 == NS) ? 0 : st_fill + 1;
