@@ -114,15 +114,26 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()          # (an int: the argtypes make the pointer of it)
 
 
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream() -> int:
     """The hipStream_t of torch's current stream on the current device, without a Stream object around it: the
     short calls (acceptance, pruning, the scores of one layer) are bound by the host, and every call asks."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_current_device())
 
 
 def _check(fn: str, rc: int):
     if rc != 0:
         raise SpecVLMError(fn, rc)
+
+
+def _contiguous_ptrs(what: str, *tensors: Optional[torch.Tensor]):
+    """The device addresses of tensors (None stays None) that have to be contiguous."""
+    for t in tensors:
+        if t is not None and not t.is_contiguous():
+            raise ValueError(what + " inputs must be contiguous")
+    return [None if t is None else _ptr(t) for t in tensors]
 
 
 def new_workspace(nbytes: int, device=None) -> torch.Tensor:
@@ -234,22 +245,29 @@ def score(q_text: torch.Tensor, k_cache: torch.Tensor, video_start: int, n_video
     maxima over the batch and the total number of video tokens must be given."""
     n_text, hq, d = q_text.shape
     n_keys, hkv, _ = k_cache.shape
-    batch, ptrs, n_text, n_keys, n_video, total_video = _batch_sizes(
-        q_text.device, cu_text, cu_keys, cu_video, n_text, n_keys, n_video, max_n_text, max_n_keys, max_n_video,
-        total_video)
+    if cu_text is None:
+        batch, p_text, p_keys, p_video, total_video = 1, None, None, None, n_video
+    else:
+        batch, cu, n_text, n_keys, n_video, total_video = _batch_sizes(
+            q_text.device, cu_text, cu_keys, cu_video, n_text, n_keys, n_video, max_n_text, max_n_keys, max_n_video,
+            total_video)
+        p_text, p_keys, p_video = _ptr(cu[0]), _ptr(cu[1]), _ptr(cu[2])
     if scores is None:
-        scores = torch.empty(total_video, dtype=torch.float32, device=q_text.device)
         if beta != 0.0:
             raise ValueError("beta != 0 needs an existing scores tensor")
+        scores = q_text.new_empty(total_video, dtype=torch.float32)
     if workspace is None:
         workspace = new_workspace(score_workspace_bytes(n_text, n_keys, n_video, hq, hkv, d, row_lse is not None,
                                                         batch=max(batch, 1)), q_text.device)
-    qs, ks = _thd(q_text), _thd(k_cache)
-    rc = lib().specvlm_score(_ptr(q_text), qs[0], qs[1], _ptr(k_cache), ks[0], ks[1],
-                             _ptr(ptrs[0]), _ptr(ptrs[1]), _ptr(ptrs[2]), batch, n_text, n_keys, video_start,
-                             n_video, text_pos0, hq, hkv, d, float(softmax_scale), norm_mode, _ptr(row_lse),
-                             float(beta), _ptr(scores), _ptr(workspace), workspace.numel(), _stream())
-    _check("specvlm_score", rc)
+    (q_tok, q_head, q_one), (k_tok, k_head, k_one) = q_text.stride(), k_cache.stride()
+    if q_one != 1 or k_one != 1:
+        raise ValueError("expected a [tokens, heads, d] view with contiguous d")
+    rc = lib().specvlm_score(_ptr(q_text), q_tok, q_head, _ptr(k_cache), k_tok, k_head, p_text, p_keys, p_video,
+                             batch, n_text, n_keys, video_start, n_video, text_pos0, hq, hkv, d, softmax_scale, norm_mode,
+                             None if row_lse is None else _ptr(row_lse), beta, _ptr(scores), _ptr(workspace),
+                             workspace.numel(), _raw_stream(_current_device()))
+    if rc:
+        _check("specvlm_score", rc)
     return scores
 
 
@@ -418,21 +436,18 @@ def accept(target_logits: torch.Tensor, draft_tokens: torch.Tensor, *,
     """target_logits fp32 [batch, gamma+1, vocab] -> (n_accepted int32 [batch], out_tokens int32 [batch, gamma+1])."""
     batch, g1, vocab = target_logits.shape
     gamma = g1 - 1
-    dev = target_logits.device
-    n_acc = n_accepted if n_accepted is not None else torch.empty(batch, dtype=torch.int32, device=dev)
-    out = out_tokens if out_tokens is not None else \
-        torch.empty((batch, gamma + 1), dtype=torch.int32, device=dev)
-    sampling = uniforms is not None
+    if n_accepted is None:
+        n_accepted = torch.empty(batch, dtype=torch.int32, device=target_logits.device)
+    if out_tokens is None:
+        out_tokens = torch.empty((batch, g1), dtype=torch.int32, device=target_logits.device)
     if workspace is None:
-        workspace = new_workspace(accept_workspace_bytes(batch, gamma, vocab, sampling), dev)
-    for t in (target_logits, draft_logits, draft_tokens, uniforms):
-        if t is not None and not t.is_contiguous():
-            raise ValueError("accept inputs must be contiguous")
-    rc = lib().specvlm_accept(_ptr(target_logits), _ptr(draft_logits), _ptr(draft_tokens),
-                              _ptr(uniforms), batch, gamma, vocab, float(temperature),
-                              _ptr(n_acc), _ptr(out), _ptr(workspace), workspace.numel(), _stream())
-    _check("specvlm_accept", rc)
-    return n_acc, out
+        workspace = new_workspace(accept_workspace_bytes(batch, gamma, vocab, uniforms is not None), target_logits.device)
+    target, draft, tokens, u = _contiguous_ptrs("accept", target_logits, draft_logits, draft_tokens, uniforms)
+    rc = lib().specvlm_accept(target, draft, tokens, u, batch, gamma, vocab, temperature, _ptr(n_accepted),
+                              _ptr(out_tokens), _ptr(workspace), workspace.numel(), _raw_stream(_current_device()))
+    if rc:
+        _check("specvlm_accept", rc)
+    return n_accepted, out_tokens
 
 
 def accept_tree(target_logits: torch.Tensor, node_tokens: torch.Tensor, parent: torch.Tensor, *,
