@@ -17,10 +17,9 @@ namespace specvlm {
 
 constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / kWave;
-constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup
-constexpr int kAccPerThread = kAccChunk / 256;   // of which each of the 256 threads takes this many
+constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup (sampling has smaller ones as well)
 constexpr int kAccSegs = kAccWaves;              // segments of a chunk, one per wave of the second sampling pass
-constexpr int kAccShort = kAccThreads;           // vocabularies of at most so many have sampling kernels of their own
+constexpr int kAccSmallChunk = 4096, kAccShort = kAccThreads;    // (see accept_chunk)
 
 struct AcceptParams {
     const float* target;      // [batch, gamma+1, vocab]
@@ -85,6 +84,17 @@ __device__ __forceinline__ float wave_max(float x)
     return fmaxf(fmaxf(from_lane(x, 0), from_lane(x, 16)), fmaxf(from_lane(x, 32), from_lane(x, 48)));
 }
 
+// A thread's share of a chunk [lo, hi): logits lo + thread + 256 j, all requested before the first is looked at; past the end
+// it reads the last one again, which the caller leaves out.  (With a test around each load, and anything to do with its
+// value behind it, the compiler waits for every load in turn: the sampling call over rows from HBM was 24.3 us, now 13.1, 32000
+// tokens 23 / 11.7, 8 requests 45 / 25.8; greedy, which had nothing behind the tests, 7.5 / 7.35.)
+template <int N>
+__device__ __forceinline__ void load_share(const float* x, int lo, int hi, float (&y)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) y[j] = x[min(lo + j * 256 + (int)threadIdx.x, hi - 1)];
+}
+
 // ---------------------------------------------------------------- greedy ----
 __global__ __launch_bounds__(256)
 void accept_argmax_partial(const AcceptParams p)
@@ -94,20 +104,18 @@ void accept_argmax_partial(const AcceptParams p)
     const int chunk = blockIdx.x, row = blockIdx.y, b = blockIdx.z;
     const float* x = p.target + ((int64_t)b * (p.gamma + 1) + row) * p.vocab;
     const int lo = chunk * kAccChunk, hi = min(p.vocab, lo + kAccChunk);
-    // the thread's whole share is requested before the first value is looked at: one round trip
-    float y[kAccPerThread];
+    constexpr int N = kAccChunk / 256;                           // tokens of a thread
+    float y[N];
+    load_share(x, lo, hi, y);
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
-        const int v = lo + j * 256 + threadIdx.x;
-        y[j] = v < hi ? x[v] : -INFINITY;
-    }
+    for (int j = 0; j < N; ++j) y[j] = lo + j * 256 + (int)threadIdx.x < hi ? y[j] : -INFINITY;
     // A NaN is greater than nothing: it must not become a share's maximum, or it would hide the tokens that a merge
     // compares with it, so the search starts at -inf.  It starts at token 0, and a NaN there stays: nothing is greater.
     if (lo == 0 && threadIdx.x == 0 && y[0] != y[0]) y[0] = INFINITY;
     float bv = -INFINITY;
     int bi = lo + (int)threadIdx.x < hi ? lo + (int)threadIdx.x : -1;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
+    for (int j = 0; j < N; ++j) {
         if (j % 4 == 0 && lo + j * 256 >= hi) break;                       // (a short chunk: 1024 tokens are four steps)
         if (y[j] > bv) { bv = y[j]; bi = lo + j * 256 + threadIdx.x; }     // ascending tokens: the first maximum is kept
     }
@@ -184,6 +192,7 @@ void accept_greedy_final(const AcceptParams p)
 
 // -------------------------------------------------------------- sampling ----
 // rows 0..gamma: target rows; rows gamma+1..2*gamma: draft rows 0..gamma-1
+template <int CHUNK>
 __global__ __launch_bounds__(256)
 void accept_softmax_partial(const AcceptParams p)
 {
@@ -196,18 +205,16 @@ void accept_softmax_partial(const AcceptParams p)
     const float* x = row <= p.gamma
         ? p.target + ((int64_t)b * (p.gamma + 1) + row) * p.vocab
         : p.draft + ((int64_t)b * p.gamma + (row - p.gamma - 1)) * p.vocab;
-    const int lo = chunk * kAccChunk, hi = min(p.vocab, lo + kAccChunk);
-    // the thread's whole share is requested up front and kept for the second pass
-    float y[kAccPerThread];
+    const int lo = chunk * CHUNK, hi = min(p.vocab, lo + CHUNK);
+    constexpr int N = CHUNK / 256;                               // tokens of a thread
+    float y[N];                                      // (kept for the second pass over them)
+    load_share(x, lo, hi, y);
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) {
-        const int v = lo + j * 256 + threadIdx.x;
-        y[j] = v < hi ? x[v] * p.inv_t_log2 : -INFINITY;
-    }
+    for (int j = 0; j < N; ++j) y[j] = lo + j * 256 + (int)threadIdx.x < hi ? y[j] * p.inv_t_log2 : -INFINITY;
     if (threadIdx.x == 0 && tok >= lo && tok < hi) p.tok_logit[(int64_t)b * (2 * p.gamma + 1) + row] = x[tok] * p.inv_t_log2;
     float m = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) m = fmaxf(m, y[j]);
+    for (int j = 0; j < N; ++j) m = fmaxf(m, y[j]);
     m = wave_max(m);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) s_m[wave] = m;
@@ -215,7 +222,7 @@ void accept_softmax_partial(const AcceptParams p)
     m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
     float z = 0.f;
 #pragma unroll
-    for (int j = 0; j < kAccPerThread; ++j) z += fast_exp2(y[j] - m);       // (-inf padding adds 0)
+    for (int j = 0; j < N; ++j) z += fast_exp2(y[j] - m);       // (-inf padding adds 0)
     z = wave_sum(z);
     if (lane == 0) s_z[wave] = z;
     __syncthreads();
@@ -265,10 +272,10 @@ struct AcceptWeight {
     {
         float t[N], d[N];
 #pragma unroll
-        for (int j = 0; j < N; ++j) { const int v = first + j * step; t[j] = v < end ? trow[v] : -INFINITY; }
+        for (int j = 0; j < N; ++j) t[j] = trow[min(first + j * step, end - 1)];     // (as in load_share; end >= 1)
         if (drow) {
 #pragma unroll
-            for (int j = 0; j < N; ++j) { const int v = first + j * step; d[j] = v < end ? drow[v] : -INFINITY; }
+            for (int j = 0; j < N; ++j) d[j] = drow[min(first + j * step, end - 1)];
         }
 #pragma unroll
         for (int j = 0; j < N; ++j) w[j] = fast_exp2(t[j] * inv_t_log2 - mt) * inv_zt;
@@ -300,18 +307,18 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
 // The last workgroup of a request goes on.  Pass 1 has cleared the arrival counter, so nothing is asked of the workspace's
 // earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release), the one
 // that finds all others counted (acquire) reads them.  With an acquire alone or neither, behind a wait for the stores, the
-// call takes the same time.  gamma 7, 152064 tokens, from a graph: 19.7 us with a third launch and the tests' logits looked up
-// here, now 13.7; 32000 tokens 16.9 / 12.9, 8 requests 38.6 / 33.0, 1024 tokens, gamma 3, 4 requests 10.6 / 7.8.
-// SHORT: one chunk, of which a wave has 64 tokens: nothing to exchange.
-constexpr int kAccSegSteps = kAccChunk / kAccThreads;        // of 64 tokens each
+// call takes the same time.  gamma 7, 152064 tokens, rows from HBM: 30.2 us with a third launch and the tests' logits looked up
+// here, 24.3 without, 12.3 with load_share and smaller chunks (see there); 8 requests 50 / 45 / 25.
+// CHUNK = kAccShort: the only chunk, nothing to exchange.
 
 __device__ __forceinline__ void store_device(float* at, float x) { __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_device(const float* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <bool SHORT>
+template <int CHUNK>
 __global__ __launch_bounds__(kAccThreads)
 void accept_sample_kernel(const AcceptParams p)
 {
+    constexpr bool SHORT = CHUNK == kAccShort;
     __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
     __shared__ float s_seg[kAccSegs];
     __shared__ float s_w[kAccWaves];
@@ -344,10 +351,10 @@ void accept_sample_kernel(const AcceptParams p)
     const int n = failed ? __ffsll((long long)failed) - 1 : p.gamma;
     const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
     const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
-    constexpr int STEPS = SHORT ? 1 : kAccSegSteps;
+    constexpr int STEPS = CHUNK / kAccThreads;   // of 64 tokens, a wave's segment
     // a chunk's segments are as wide as it takes to deal it to the waves in token order
     auto segment = [&](int c, int w, int& lo, int& hi) __attribute__((always_inline)) {
-        const int from = c * kAccChunk, to = min(p.vocab, from + kAccChunk);
+        const int from = c * CHUNK, to = min(p.vocab, from + CHUNK);
         const int width = ((to - from + kAccSegs - 1) / kAccSegs + 63) & ~63;
         lo = min(to, from + w * width); hi = min(to, lo + width);
     };
@@ -459,7 +466,7 @@ void accept_sample_kernel(const AcceptParams p)
             if (passed && y < 0) y = base + __ffsll((long long)passed) - 1;
             c += from_lane(incl, 63);
         }
-        if (y < 0) y = last >= 0 ? last : own1 * kAccChunk;
+        if (y < 0) y = last >= 0 ? last : own1 * CHUNK;
     }
     // (the first wave only from here on)
     for (int i = lane; i <= p.gamma; i += 64)
@@ -505,7 +512,18 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
     if (lane == 0) p.n_accepted[b] = n;
 }
 
-static int accept_chunks(int vocab) { return (vocab + kAccChunk - 1) / kAccChunk; }
+static int accept_chunks(int vocab, int chunk = kAccChunk) { return (vocab + chunk - 1) / chunk; }
+
+// Vocabulary entries of a chunk in the sampling passes.  Smaller chunks are more workgroups with less to do one after the
+// other, as long as those of the second pass, of 1024 threads each, find a CU of their own (us a call from a graph, rows from
+// HBM, chunks of 4096 / 8192; in brackets the requests' chunks of 8192):  152064 tokens, gamma 7, 1 request [19] 12.3 / 13.1, 2
+// 14.0 / 14.2, 3 [57] 15.8 / 16.3, 4 [76] 18.7 / 18.2, gamma 1, 8 requests [152] 18.7 / 15.4;  65537 tokens, gamma 7, 4 [36] 13.0 / 14.2, 8 [72]
+// 17.5 / 17.5;  32000 tokens, 8 [32] 12.7 / 13.8.  Up to kAccShort tokens there is one chunk.
+static int accept_chunk(int batch, int vocab)
+{
+    if (vocab <= kAccShort) return kAccShort;
+    return (int64_t)batch * accept_chunks(vocab) <= 64 ? kAccSmallChunk : kAccChunk;
+}
 
 // Lanes per row of the greedy final kernels: 16 where that is fewer trips.  The whole call from a graph, us, one lane /
 // 16 lanes:  152064 tokens (19 chunks): 6 rows 8.4 / 6.7, 21 rows 9.0 / 8.5, 65 rows 13.4 / 14.4;  65537 (9 chunks): 16 rows
@@ -525,10 +543,12 @@ extern "C" size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab
 {
     if (batch <= 0 || gamma < 0 || vocab < 1) return 0;
     const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
-    size_t bytes = 2 * align256((size_t)batch * rows * accept_chunks(vocab) * sizeof(float));
+    // (sampling: of the smaller chunks, whichever are taken, so that what is enough for a batch is enough for a smaller one)
+    const int chunks = accept_chunks(vocab, sampling ? kAccSmallChunk : kAccChunk);
+    size_t bytes = 2 * align256((size_t)batch * rows * chunks * sizeof(float));
     if (sampling)       // the drafted tokens' logits, segment masses of the rejected row, arrivals
         bytes += align256((size_t)batch * rows * sizeof(float)) +
-                 align256((size_t)batch * accept_chunks(vocab) * kAccSegs * sizeof(float)) +
+                 align256((size_t)batch * chunks * kAccSegs * sizeof(float)) +
                  align256((size_t)batch * sizeof(uint32_t));
     return bytes;
 }
@@ -554,7 +574,9 @@ extern "C" int specvlm_accept(
 
     AcceptParams p;
     p.target = target_logits; p.draft = draft_logits; p.tokens = draft_tokens; p.uniforms = uniforms;
-    p.batch = batch; p.gamma = gamma; p.vocab = vocab; p.n_chunks = accept_chunks(vocab);
+    p.batch = batch; p.gamma = gamma; p.vocab = vocab;
+    const int chunk = sampling ? accept_chunk(batch, vocab) : kAccChunk;
+    p.n_chunks = accept_chunks(vocab, chunk);
     p.inv_t_log2 = sampling ? kLog2e / temperature : kLog2e;
     p.n_accepted = n_accepted; p.out_tokens = out_tokens;
     const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
@@ -573,9 +595,17 @@ extern "C" int specvlm_accept(
         else
             hipLaunchKernelGGL(accept_greedy_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
-        hipLaunchKernelGGL(accept_softmax_partial, dim3(p.n_chunks, 2 * gamma + 1, batch), dim3(256), 0, s, p);
-        if (vocab <= kAccShort) hipLaunchKernelGGL(accept_sample_kernel<true>, dim3(1, batch), dim3(kAccThreads), 0, s, p);
-        else hipLaunchKernelGGL(accept_sample_kernel<false>, dim3(p.n_chunks, batch), dim3(kAccThreads), 0, s, p);
+        const dim3 rows_grid(p.n_chunks, 2 * gamma + 1, batch), grid(p.n_chunks, batch);
+        if (chunk == kAccShort) {
+            hipLaunchKernelGGL(accept_softmax_partial<kAccShort>, rows_grid, dim3(256), 0, s, p);
+            hipLaunchKernelGGL(accept_sample_kernel<kAccShort>, grid, dim3(kAccThreads), 0, s, p);
+        } else if (chunk == kAccSmallChunk) {
+            hipLaunchKernelGGL(accept_softmax_partial<kAccSmallChunk>, rows_grid, dim3(256), 0, s, p);
+            hipLaunchKernelGGL(accept_sample_kernel<kAccSmallChunk>, grid, dim3(kAccThreads), 0, s, p);
+        } else {
+            hipLaunchKernelGGL(accept_softmax_partial<kAccChunk>, rows_grid, dim3(256), 0, s, p);
+            hipLaunchKernelGGL(accept_sample_kernel<kAccChunk>, grid, dim3(kAccThreads), 0, s, p);
+        }
     }
     return launch_status();
 }

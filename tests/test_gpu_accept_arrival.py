@@ -63,3 +63,10 @@ def test_replays_between_eager_calls_on_one_workspace(B):
         call(other, workspace=ws)
         ws.fill_(0xff)
         torch.cuda.synchronize()
+
+
+# the requests' chunks of 8192 on both sides of 64 (chunks of 4096 and of 8192), last chunks of one token, one request alone
+@pytest.mark.parametrize("batch,gamma,vocab", [(7, 2, 73728), (7, 2, 73729), (64, 1, 4097), (65, 1, 4097), (32, 1, 8193), (33, 1, 8193),
+                                               (1, 3, 4096), (2, 3, 1025)])
+def test_chunk_sizes(B, batch, gamma, vocab):
+    base.test_sampling_matches_oracle_outside_margin(B, batch, gamma, vocab, 1.0)
