@@ -1,7 +1,7 @@
 // specvlm_select: the two-stage retention set of Sec. 3.2.
 //   Stage I  : V_R = the k highest-scoring video tokens (ties -> lower index),
 //              by a most-significant-digit radix select on order-preserving
-//              integer keys (4 passes of 8 bits, histograms in LDS).
+//              integer keys (digits of 11, 11 and 10 bits, histograms in LDS).
 //   Stage II : V_U = tokens of V \ V_R at the fixed fractional interval
 //              I = R/U in raster order: remainder ranks floor(t*R/U), exact
 //              integer arithmetic (Eq. 7 with the budget as denominator).
@@ -13,7 +13,7 @@
 // Bound: latency and VALU issue of the one workgroup.  Sixteen waves share four SIMDs, so an instruction that all of
 // them execute takes about 20 cycles; a barrier 100, and a wave scan by __shfl six LDS round trips (600).  Hence the
 // scans by DPP, no test on a key that its position or the pass already decides, masks of 32 bits where a thread has at
-// most 32 keys, and one wave that sums and scans a pass's histograms between two barriers.
+// most 32 keys, and few, wide digits.
 #include <type_traits>
 
 #include "common.h"
@@ -22,18 +22,27 @@ namespace specvlm {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
-// Copies of the digit histogram, summed after a pass by one wave.  An LDS atomic serialises over the lanes that hit one
-// address, and digits do coincide (the leading one, sign and exponent, takes a handful of values; scores summed over many
-// rows share their upper 16 bits), but every copy is also cleared, summed and moves the pass's end: cycles of the select
-// kernel at 12544 tokens, long-tailed / clustered within 1e-3 / within 1e-5, by the copies of passes 1 to 3:  2: 20.0 /
-// 26.1 / 31.7 thousand, 4: 19.8 / 22.7 / 25.5, 8: 20.3 / 21.4 / 22.2, 16: 25.3, 32: 28.7; 16 or 64 in pass 0 are equal.
-// More keys to a thread mean more additions to every sum: the selection with 33 to 64 of them takes sixteen copies
-// (65536 tokens, a twentieth kept, us with 8 / 16, the 64 copies of before in brackets: long-tailed 31.7 / 30.9 [38.5], within
-// 1e-5 46.0 / 41.2 [45.3], all equal 55.1 / 44.8 [46.5]).  With 17 to 32 the eight stay the better ones wherever scores differ
-// (32768 tokens: long-tailed 17.6 / 18.7 [24.6], within 1e-5 23.7 / 22.7 [26.2]); only where nearly all are equal they are not
-// (28.0 / 23.4 [25.9]).  Copies chosen pass by pass, by the keys still in play, cost more than they save (19.2 and 25.1).
-constexpr int kSelCopies = 8;
-constexpr int kSelCopyWords = 260;        // 256 counters, 16-byte aligned; the copies of one digit lie in different banks
+// The key is read in digits of 11, 11 and 10 bits, each with a histogram of its own, cleared while the scores are on their way.
+// With four digits of 8 bits 24 bits took three passes and scores that share their upper bits the fourth; two passes of 11
+// usually decide, the third ends it: 12544 tokens, a tenth kept, half of it by score, us in a graph, 8 bits / now: long-tailed
+// 10.5 / 9.6, within 1e-3 11.8 / 10.4, within 1e-5 12.4 / 11.0, all equal 13.8 / 13.4; 32768 tokens 19.3 / 17.8, 22.2 / 18.7,
+// 24.0 / 20.3, 28.2 / 27.7; 1568 tokens 5.76 / 5.55 and 6.33 / 6.13.  10 and 12 bits in front: 9.7 and 10.7 for the first two.
+// Copies of a histogram, summed after its pass by all waves: an LDS atomic serialises over the lanes that hit one address, and
+// digits do coincide (the leading one takes a handful of values), but every copy is also cleared and summed.  12544 tokens,
+// long-tailed / within 1e-5 / all equal, by the copies of the three digits:  4, 4, 1: 10.6 / 12.5 / 23.8;  4, 4, 4: 10.6 / 12.4 /
+// 16.0;  8, 8, 4: 9.7 / 11.1 / 13.6.  With up to 4 tokens a thread four are enough (1568 tokens 5.55 / 6.28 / 6.79; eight 5.74 /
+// 6.43 / 6.75; two 5.68 / 6.48 / 7.66); with more than 32 the last digit, where equal scores meet, takes sixteen, in the
+// place of the first one's (65536 tokens, all equal: 43.9, with four 53.7, before 45.2).
+constexpr int kSelBits[3] = {11, 11, 10}, kSelShift[3] = {21, 10, 0};
+template <int E> struct SelHist {
+    static constexpr int copies(int pass) { return E <= 4 ? 4 : pass < 2 ? 8 : E <= 32 ? 4 : 16; }
+    static constexpr int stride(int pass) { return (1 << kSelBits[pass]) + (pass < 2 ? 4 : 2); }   // (copies of a digit lie in different banks)
+    static constexpr int words(int pass) { return copies(pass) * stride(pass); }
+    static constexpr bool kReuse = E > 32;                       // the last pass takes the first one's place
+    static constexpr int at(int pass) { return pass == 0 || (pass == 2 && kReuse) ? 0 : at(pass - 1) + words(pass - 1); }
+    static constexpr int kWords = words(0) + words(1) + (kReuse ? 0 : words(2));
+    static_assert(!kReuse || words(2) <= words(0));
+};
 
 // Wave-wide inclusive prefix sum by DPP: rows of 16 lanes, then the rows' totals.
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or_0(int x)
@@ -90,12 +99,13 @@ struct SelectParams {
 };
 
 // Order-preserving key: larger score <=> larger key.  -0.0 is +0.0; NaN is the
-// smallest key of all.
-__device__ __forceinline__ uint32_t score_key(float x)
+// smallest key of all, and so is a slot without a token.  (Without branches: with the test around the
+// conversion every key had two of its own.)
+__device__ __forceinline__ uint32_t score_key(float x, bool token = true)
 {
     const uint32_t u = __float_as_uint(x + 0.f);                 // (-0 + 0 is +0)
     const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-    return x != x ? 0u : key;
+    return ((x == x) & token) ? key : 0u;
 }
 
 // A thread's run of scores [first, first + per) of a request of n scores, four at a time (dword-aligned
@@ -139,10 +149,10 @@ template <int E>
 __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const SelectParams p)
 {
-    constexpr int COPIES = E <= 32 ? kSelCopies : 2 * kSelCopies;
     using mask_t = std::conditional_t<(E <= 32), uint32_t, uint64_t>;      // a bit per key of a thread
     static_assert(kSelWaves == 16, "the waves' sums are one DPP row");
-    __shared__ __align__(16) int s_hist[2][COPIES * kSelCopyWords];    // the passes alternate between two sets
+    using H = SelHist<E>;
+    __shared__ __align__(16) int s_hist[H::kWords];         // a histogram for each digit
     __shared__ int s_wave[kSelWaves];
     __shared__ int s_pick[3];
 
@@ -157,11 +167,11 @@ void select_kernel(const SelectParams p)
     const float* sc = p.scores + v0;
     float raw[E];
     load_run<E>(sc, first, per, n, raw);
-    // the first two passes' histograms are cleared while the scores are on their way
-    auto clear = [&](int* from, int words) __attribute__((always_inline)) {
-        for (int i = tid; i < words / 4; i += kSelThreads) reinterpret_cast<u32x4*>(from)[i] = u32x4{0u, 0u, 0u, 0u};
+    // the histograms are cleared while the scores are on their way
+    auto clear = [&](int words) __attribute__((always_inline)) {
+        for (int i = tid; i < words / 4; i += kSelThreads) reinterpret_cast<u32x4*>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
     };
-    clear(s_hist[0], 2 * COPIES * kSelCopyWords);
+    clear(H::kWords);
     const int k = p.k_top[b], budget = p.keep_budget[b];
     const int out0 = p.cu_keep ? p.cu_keep[b] : 0;
     const bool bad = n < 0 || n > E * kSelThreads || n > p.max_n_video || k < 0 || k > budget || budget > n;
@@ -173,69 +183,66 @@ void select_kernel(const SelectParams p)
     const int mine = first < n ? min(per, n - first) : 0;
     uint32_t key[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) key[e] = e < mine ? score_key(raw[e]) : 0u;
+    for (int e = 0; e < E; ++e) key[e] = score_key(raw[e], e < mine);
 
     // ---- Stage I: radix select of the k-th largest key ----
     uint32_t prefix = 0, known = 0;
     int need = k;                       // how many still to take inside the current prefix
+    // One digit: its histogram, and the digit of the k-th key.  False when the rest of the key decides nothing.
+    auto digit = [&](auto pass_) __attribute__((always_inline)) {
+        constexpr int PASS = decltype(pass_)::value;
+        constexpr int SHIFT = kSelShift[PASS], BITS = kSelBits[PASS], BINS = 1 << BITS, COPIES = H::copies(PASS);
+        constexpr int PER = BINS / kSelThreads, STRIDE = H::stride(PASS);
+        int* const hist = s_hist + H::at(PASS);
+        // A lane may add to any copy: the lanes of an instruction are spread over the copies, the waves start at
+        // different ones.  No aggregation over the wave or over a thread's keys: both were measured and cost more
+        // than the additions they save.
+        int* const my_hist = hist + ((4 * wave + lane) & (COPIES - 1)) * STRIDE;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e < per && (PASS == 0 || (key[e] & known) == prefix)) atomicAdd(&my_hist[(key[e] >> SHIFT) & (BINS - 1)], 1);
+        // (the first histogram was read for the last time before the barrier above)
+        if (PASS == 1 && H::kReuse) clear(H::words(2));
+        __syncthreads();
+        // thread t sums PER digits from the top over the copies; prefix sums over the threads run down from the top digit
+        const int d0 = BINS - PER - PER * tid;
+        int c[PER] = {};
+#pragma unroll
+        for (int w = 0; w < COPIES; ++w)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) c[i] += hist[w * STRIDE + d0 + i];
+        int sum = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) sum += c[i];
+        const int incl = wave_incl_scan(sum);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        const int total = lane < kSelWaves ? s_wave[lane] : 0;
+        int above = __builtin_amdgcn_readlane(row_incl_scan(total) - total, __builtin_amdgcn_readfirstlane(wave)) + incl - sum;   // keys in higher digits
+        if (above < need && need <= above + sum) {
+#pragma unroll
+            for (int i = PER - 1; i >= 0; --i) {
+                if (above < need && need <= above + c[i]) {
+                    s_pick[0] = d0 + i;
+                    s_pick[1] = need - above;
+                    s_pick[2] = (need - above == c[i]);     // the whole bucket is taken: nothing left to rank
+                }
+                above += c[i];
+            }
+        }
+        __syncthreads();
+        prefix |= (uint32_t)s_pick[0] << SHIFT;
+        known |= (uint32_t)(BINS - 1) << SHIFT;
+        need = s_pick[1];
+        // When the keys that share the digits known so far are exactly as many as are still needed,
+        // all of them are taken and the lower digits decide nothing: the remaining passes are skipped.
+        return s_pick[2] == 0;
+    };
     if (k > 0) {
         __syncthreads();                                // the cleared histograms are visible
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
-            int* const hist = s_hist[pass & 1];
-            // A lane may add to any copy: the lanes of an instruction are spread over the copies, the waves start at
-            // different ones.  No aggregation over the wave or over a thread's keys: both were measured and cost more
-            // than the additions they save.
-            int* const my_hist = hist + ((4 * wave + lane) & (COPIES - 1)) * kSelCopyWords;
-            if (pass == 0) {
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (e < per) atomicAdd(&my_hist[key[e] >> 24], 1);
-            } else {
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (e < per && (key[e] & known) == prefix) atomicAdd(&my_hist[(key[e] >> shift) & 255], 1);
-                // (the other set was read for the last time before the barrier above)
-                if (pass < 3) clear(s_hist[(pass + 1) & 1], COPIES * kSelCopyWords);
-            }
-            __syncthreads();
-            if (wave == 0) {
-                // lane l sums digits 252 - 4l .. 255 - 4l over the copies; prefix sums over the lanes run down from the
-                // top digit
-                const int d0 = 252 - 4 * lane;
-                int c4[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int w = 0; w < COPIES; ++w) {
-                    const u32x4 v = *reinterpret_cast<const u32x4*>(hist + w * kSelCopyWords + d0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) c4[i] += (int)v[i];
-                }
-                const int sum = c4[0] + c4[1] + c4[2] + c4[3];
-                const int incl = wave_incl_scan(sum);
-                int above = incl - sum;                 // keys in higher digits
-                if (above < need && need <= incl) {
-#pragma unroll
-                    for (int i = 3; i >= 0; --i) {
-                        if (above < need && need <= above + c4[i]) {
-                            s_pick[0] = d0 + i;
-                            s_pick[1] = need - above;
-                            s_pick[2] = (need - above == c4[i]);    // the whole bucket is taken: nothing left to rank
-                        }
-                        above += c4[i];
-                    }
-                }
-            }
-            __syncthreads();
-            prefix |= (uint32_t)s_pick[0] << shift;
-            known |= 255u << shift;
-            need = s_pick[1];
-            // When the keys that share the digits known so far are exactly as many as are still needed,
-            // all of them are taken and the lower digits decide nothing: the remaining passes are skipped
-            // (with distinct scores this is the usual case after three passes).
-            if (s_pick[2]) break;
-        }
+        if (digit(std::integral_constant<int, 0>{}) && digit(std::integral_constant<int, 1>{})) digit(std::integral_constant<int, 2>{});
     }
-    // now: prefix = the known digits of the k-th largest key (all four, or fewer when a whole bucket
+    // now: prefix = the known digits of the k-th largest key (all of them, or fewer when a whole bucket
     // is taken); take every key above it and the first `need` keys that share it, in index order.
     mask_t gt = 0, eq = 0;
     if (k > 0) {
@@ -302,8 +309,8 @@ void select_kernel(const SelectParams p)
 
 // ---------------------------------------------------------------------------
 // Stage I's own size rule (Sec. 3.2, Eq. 6): the smallest c such that the c
-// largest scores reach lambda of the total score mass.  Same radix descent as
-// the selection, but the per-digit histograms carry the MASS of the keys, not
+// largest scores reach lambda of the total score mass.  A radix descent as the
+// selection's, in four digits of 8 bits, whose histograms carry the MASS of the keys, not
 // their number (the first pass's sums also give the total); the numbers of keys
 // above and at the threshold are counted once, at the end.
 // Sums are 64-bit fixed point (score * 2^40 / max score): integer adds commute,
@@ -319,15 +326,16 @@ struct TopPParams {
     int32_t* count;
 };
 
+constexpr int kTopPCopies = 8;
 constexpr int kTopPCopyWords = 258;       // 256 sums, 16-byte aligned; the copies of one digit lie in different banks
 
 template <int E>
 __global__ __launch_bounds__(kSelThreads)
 void top_p_kernel(const TopPParams p)
 {
-    // copies of the 256 per-digit mass sums, two sets as in the selection; counts are not kept per digit: only the
+    // copies of the 256 per-digit mass sums, two sets in turn; counts are not kept per digit: only the
     // threshold key's are needed, at the end
-    __shared__ __align__(16) unsigned long long s_mass[2][kSelCopies * kTopPCopyWords];
+    __shared__ __align__(16) unsigned long long s_mass[2][kTopPCopies * kTopPCopyWords];
     __shared__ float s_redf[kSelWaves];
     __shared__ int s_redc[2][kSelWaves];
     __shared__ unsigned long long s_pick_sum, s_goal;
@@ -350,7 +358,7 @@ void top_p_kernel(const TopPParams p)
     auto clear = [&](unsigned long long* from, int words) __attribute__((always_inline)) {
         for (int i = tid; i < words / 2; i += kSelThreads) reinterpret_cast<u32x4*>(from)[i] = u32x4{0u, 0u, 0u, 0u};
     };
-    clear(s_mass[0], 2 * kSelCopies * kTopPCopyWords);
+    clear(s_mass[0], 2 * kTopPCopies * kTopPCopyWords);
     // (slots past the last token hold a NaN: the lowest key, without mass, so they need no test)
     const int mine = first < n ? min(per, n - first) : 0;
     float mx = 0.f;
@@ -380,7 +388,7 @@ void top_p_kernel(const TopPParams p)
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
         unsigned long long* const mass = s_mass[pass & 1];
-        unsigned long long* const my_mass = mass + ((4 * wave + lane) & (kSelCopies - 1)) * kTopPCopyWords;
+        unsigned long long* const my_mass = mass + ((4 * wave + lane) & (kTopPCopies - 1)) * kTopPCopyWords;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             if (e >= per) continue;
@@ -393,14 +401,14 @@ void top_p_kernel(const TopPParams p)
             }
         }
         // (the other set was read for the last time before the barrier above)
-        if (pass == 1 || pass == 2) clear(s_mass[(pass + 1) & 1], kSelCopies * kTopPCopyWords);
+        if (pass == 1 || pass == 2) clear(s_mass[(pass + 1) & 1], kTopPCopies * kTopPCopyWords);
         __syncthreads();
         if (wave == 0) {
             // lane l sums digits 252 - 4l .. 255 - 4l over the copies; prefix sums run down from the top digit
             const int d0 = 252 - 4 * lane;
             unsigned long long m4[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
-            for (int w = 0; w < kSelCopies; ++w) {
+            for (int w = 0; w < kTopPCopies; ++w) {
                 typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
                 const u64x2* src = reinterpret_cast<const u64x2*>(mass + w * kTopPCopyWords + d0);
                 const u64x2 v0 = src[0], v1 = src[1];

@@ -64,3 +64,21 @@ def test_top_p_count(B, n, kind):
         want, margin = oracle.top_p_count(s, lam, want_margin=True)
         if margin > 1e-6 or lam == 1.0:
             assert got == want, (n, kind, lam)
+
+
+# keys that part in one digit of the descent (11, 11 and 10 bits) alone, its lowest and highest values among them, negative
+# scores included: the thread that owns a digit, and the digits on both sides of a thread's and of a wave's share
+@pytest.mark.parametrize("n", [2048, 4097, 16385, 32769, 65536])
+@pytest.mark.parametrize("shift,bits", [(21, 11), (10, 11), (0, 10)])
+def test_select_one_digit(B, n, shift, bits):
+    r = np.random.default_rng(n + shift)
+    digit = r.permutation(np.arange(n) % (1 << bits)).astype(np.uint32)
+    key = (np.uint32(0xBF812345) & ~np.uint32(((1 << bits) - 1) << shift)) | (digit << np.uint32(shift))
+    s = np.where(key >> 31 != 0, key & np.uint32(0x7FFFFFFF), ~key).astype(np.uint32).view(np.float32)
+    dev = torch.from_numpy(s).cuda()
+    for k in (1, n >> bits, (n >> bits) + 1, n // 16, n // 2 + 1, n - 1, n):
+        want, want_flags = oracle.select(s, k, n)
+        keep, flags = B.select(dev, i32(k), i32(n), n)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(keep.cpu().numpy(), want, err_msg=f"n {n} k {k} digit at {shift}")
+        np.testing.assert_array_equal(flags.cpu().numpy(), want_flags, err_msg=f"n {n} k {k} digit at {shift}")
