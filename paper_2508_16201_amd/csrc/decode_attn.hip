@@ -1231,11 +1231,12 @@ static int launch_short(const AttnParams& p, hipStream_t stream)
 }
 
 // Waves of a workgroup without splits: eight, or sixteen with half the keys each where a wave of eight would have many.  The
-// loads take as long either way, but less is left to do behind the last of them (us a layer, eight / sixteen): size 64, 14/2
-// heads, 1511 keys 6.36 / 6.27, 1400 keys, 26 nodes 7.13 / 6.96, but 1200 keys 5.69 / 5.99 (half a wave's keys are past the end), 1000
-// keys 5.27 / 5.40;  size 128, 64/8 heads, 6 queries, 700 keys 6.53 / 6.34, 1000 keys 8.65 / 8.24, 40/8, 4 queries, 900 keys 8.37 / 7.91,
-// 6 queries, 600 keys 6.04 / 6.14, 28/4, 1000 keys 7.09 / 7.14, 8 queries 7.99 / 7.73, 400 keys 4.85 / 5.27.
-static bool attn_direct_16_waves(int head_dim, int kv_len) { return kv_len > (head_dim == 64 ? 1280 : 640); }
+// loads take as long either way, but less is left to do behind the last of them (us a layer, eight / sixteen).  Size 64: 14/2
+// heads, 1400 keys 6.34 / 6.12, 26 nodes 7.07 / 6.82, 1500 keys 6.35 / 6.23, 26 nodes 6.60 / 6.65, 1281 keys 6.07 / 6.04, but 1200
+// keys 5.69 / 5.99 (half a wave's keys are past the end), 1000 keys 5.27 / 5.40;  size 128, 64/8 heads, 6 queries: 672 keys
+// 6.14 / 6.49, 700 6.68 / 6.56, 768 6.65 / 6.69, 800 7.25 / 7.16, 850 7.13 / 7.29, 900 8.03 / 7.54, 1024 8.16 / 7.71;  40/8, 1 query:
+// 641 keys 5.65 / 6.01, 768 6.04 / 6.12, 800 6.68 / 6.56, 900 7.01 / 6.76;  28/4, 16 queries: 672 6.40 / 6.57, 800 7.55 / 7.23.
+static bool attn_direct_16_waves(int head_dim, int kv_len) { return kv_len > (head_dim == 64 ? 1280 : 768); }
 
 static int launch_attn_direct(const AttnParams& p, int head_dim, int chunks, hipStream_t stream)
 {

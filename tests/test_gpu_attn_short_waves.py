@@ -12,12 +12,13 @@ B = base.B
 @pytest.mark.parametrize("q_len,kv_len,hq,hkv,d", [
     (1, 1280, 14, 2, 64), (1, 1281, 14, 2, 64), (3, 1344, 14, 2, 64), (2, 1345, 8, 8, 64), (16, 1441, 32, 8, 64),
     (1, 640, 8, 2, 128), (1, 641, 8, 2, 128), (8, 641, 64, 8, 128), (6, 705, 64, 8, 128), (4, 961, 32, 4, 128), (31, 700, 8, 4, 128),
+    (1, 768, 8, 2, 128), (1, 769, 8, 2, 128), (8, 769, 64, 8, 128), (31, 800, 8, 4, 128),
 ])
 def test_edges(B, q_len, kv_len, hq, hkv, d):
     base.test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, 0)
 
 
-@pytest.mark.parametrize("lens,hq,hkv,d", [([1281, 1400, 33, 1536], 8, 2, 64), ([641, 3, 900], 8, 2, 128)])
+@pytest.mark.parametrize("lens,hq,hkv,d", [([1281, 1400, 33, 1536], 8, 2, 64), ([641, 3, 900], 8, 2, 128), ([641, 3, 768], 8, 2, 128)])
 def test_ragged_batch(B, lens, hq, hkv, d):
     base.ragged_case(B, lens, [2] * len(lens), hq, hkv, d)
 
