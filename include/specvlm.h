@@ -358,6 +358,11 @@ int specvlm_tree_attn(
  *   target_logits fp32 [batch, gamma+1, vocab]   draft_logits fp32 [batch, gamma, vocab]
  *   draft_tokens  int32 [batch, gamma]           uniforms     fp32 [batch, gamma+1] in [0,1)
  *   n_accepted    int32 [batch] (0..gamma)       out_tokens   int32 [batch, gamma+1]
+ * Probabilities and their sums are fp32, summed in an order that the vocabulary
+ * alone decides: a request's tokens do not depend on the other requests of its
+ * batch, on the run or on the workspace, and the final token is the inverse
+ * CDF's up to the rounding of those sums (a uniform within about 1e-6 of a step
+ * of the CDF may fall on either side of it).
  * -------------------------------------------------------------------------- */
 size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab, int sampling);
 

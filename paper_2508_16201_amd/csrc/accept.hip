@@ -8,18 +8,21 @@
 // Pass 2, greedy (one workgroup per request): merge the partials and walk the gamma tests in order.
 // Pass 2, sampling (many workgroups): every workgroup merges the partials and repeats the gamma
 //   accept tests (a few loads), so all agree on the first rejected position n; each then sums the
-//   mass of the residual max(p - q, 0) at row n (of p when every draft survived) over its chunk, in
-//   segments.  The workgroup of a request that finishes last goes on: inverse CDF over the chunks,
-//   then over the owning chunk's segments, then over the owning segment's tokens.
+//   mass of the residual max(p - q, 0) at row n (of p when every draft survived) over its chunk.
+//   The workgroup of a request that finishes last goes on: inverse CDF over the chunks, then over
+//   the owning chunk's segments, then over the owning segment's tokens.
+// The drawn token lies where fp32 sums put the uniform, so it depends on their order wherever the uniform
+// is within rounding of a step of the CDF.  The order is therefore fixed by the vocabulary alone -- never by
+// the batch, the grid or who arrives when (tests/sampling_order.py has it in full).
 #include "common.h"
 
 namespace specvlm {
 
 constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / kWave;
-constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup (sampling has smaller ones as well)
-constexpr int kAccSegs = kAccWaves;              // segments of a chunk, one per wave of the second sampling pass
-constexpr int kAccSmallChunk = 4096, kAccShort = kAccThreads;    // (see accept_chunk)
+constexpr int kAccChunk = 8192;        // vocab entries per pass-1 workgroup
+constexpr int kAccSegs = kAccWaves;    // segments of a chunk, in token order, one per wave of the second sampling pass
+constexpr int kAccShort = kAccThreads; // vocabularies of at most so many have sampling kernels of their own
 
 struct AcceptParams {
     const float* target;      // [batch, gamma+1, vocab]
@@ -32,8 +35,9 @@ struct AcceptParams {
     int32_t* out_tokens;
     float* part_val;          // [batch][rows][n_chunks]   max
     float* part_aux;          // [batch][rows][n_chunks]   sum exp (sampling) / argmax index bits (greedy)
-    float* tok_logit;         // sampling: [batch][2 * gamma + 1] logit / T (log2 units) of the drafted token in target and draft rows
-    float* seg_mass;          // sampling: [batch][n_chunks][kAccSegs] residual (or target) mass of row n per segment
+    float* tok_logit;         // sampling: [batch][2 * gamma + 1] logit of the drafted token in target and draft rows
+    float* chunk_mass;        // sampling: [batch][n_chunks] residual (or target) mass of row n per chunk
+    float* seg_mass;          // sampling: [batch][n_chunks][kAccSegs] the same per segment
     uint32_t* arrived;        // sampling: [batch] chunks that are done, cleared by pass 1
 };
 
@@ -43,51 +47,33 @@ __device__ __forceinline__ void argmax_merge(float& bv, int& bi, float v, int i)
     if (i >= 0 && (bi < 0 || v > bv || (v == bv && i < bi))) { bv = v; bi = i; }
 }
 
-// Wave-wide float reductions and prefix sums by DPP (rows of 16 lanes, then the rows' totals): a shuffle is an LDS round trip.
-template <int CTRL, int ROWS> __device__ __forceinline__ float lane_move(float x, float other)
+// Wave-wide reductions over lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2 and ^ 1, in this order: swaps of half waves and of rows, then DPP in
+// rows of 16 (rotations by 8 and 4, which reach the partner once the higher bits no longer matter).  The same bits
+// as six shuffles, each of which is an LDS round trip.
+template <int CTRL> __device__ __forceinline__ float row_move(float x)
 {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(other), (int)__float_as_uint(x), CTRL, ROWS, 0xf, false));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
 }
 
-__device__ __forceinline__ float wave_prefix(float x)                // lane i: the sum of lanes 0 .. i
+template <typename OP> __device__ __forceinline__ float wave_reduce(float x, OP op)
 {
-    x += lane_move<0x111, 0xf>(x, 0.f);      // row_shr 1, 2, 4, 8
-    x += lane_move<0x112, 0xf>(x, 0.f);
-    x += lane_move<0x114, 0xf>(x, 0.f);
-    x += lane_move<0x118, 0xf>(x, 0.f);
-    x += lane_move<0x142, 0xa>(x, 0.f);      // row_bcast 15, into rows 1 and 3
-    return x + lane_move<0x143, 0xc>(x, 0.f);   // row_bcast 31, into rows 2 and 3
+    auto half = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(half[0]), __uint_as_float(half[1]));
+    auto row = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(row[0]), __uint_as_float(row[1]));
+    x = op(x, row_move<0x128>(x));
+    x = op(x, row_move<0x124>(x));
+    x = op(x, row_move<0x4E>(x));
+    return op(x, row_move<0xB1>(x));
 }
 
+__device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float x) { return wave_reduce(x, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float from_lane(float x, int lane) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane)); }
-__device__ __forceinline__ float wave_sum(float x) { return from_lane(wave_prefix(x), 63); }
-
-__device__ __forceinline__ float row_max(float x)                    // over the lane's row of 16
-{
-    x = fmaxf(x, lane_move<0xB1, 0xf>(x, x));    // lane ^ 1, lane ^ 2, then the other four (mirrored) and the other eight
-    x = fmaxf(x, lane_move<0x4E, 0xf>(x, x));
-    x = fmaxf(x, lane_move<0x141, 0xf>(x, x));
-    return fmaxf(x, lane_move<0x140, 0xf>(x, x));
-}
-
-__device__ __forceinline__ float row_sum(float x)
-{
-    x += lane_move<0xB1, 0xf>(x, 0.f);
-    x += lane_move<0x4E, 0xf>(x, 0.f);
-    x += lane_move<0x141, 0xf>(x, 0.f);
-    return x + lane_move<0x140, 0xf>(x, 0.f);
-}
-
-__device__ __forceinline__ float wave_max(float x)
-{
-    x = row_max(x);
-    return fmaxf(fmaxf(from_lane(x, 0), from_lane(x, 16)), fmaxf(from_lane(x, 32), from_lane(x, 48)));
-}
 
 // A thread's share of a chunk [lo, hi): logits lo + thread + 256 j, all requested before the first is looked at; past the end
-// it reads the last one again, which the caller leaves out.  (With a test around each load, and anything to do with its
-// value behind it, the compiler waits for every load in turn: the sampling call over rows from HBM was 24.3 us, now 13.1, 32000
-// tokens 23 / 11.7, 8 requests 45 / 25.8; greedy, which had nothing behind the tests, 7.5 / 7.35.)
+// it reads the last one again, which the caller leaves out.  (With a test around each load sampling takes up to 3 % longer:
+// 152064 tokens, gamma 7, 2 requests 17.1 instead of 16.7 us, 4 requests 20.9 instead of 20.2;  greedy 7.5 instead of 7.35.)
 template <int N>
 __device__ __forceinline__ void load_share(const float* x, int lo, int hi, float (&y)[N])
 {
@@ -211,7 +197,7 @@ void accept_softmax_partial(const AcceptParams p)
     load_share(x, lo, hi, y);
 #pragma unroll
     for (int j = 0; j < N; ++j) y[j] = lo + j * 256 + (int)threadIdx.x < hi ? y[j] * p.inv_t_log2 : -INFINITY;
-    if (threadIdx.x == 0 && tok >= lo && tok < hi) p.tok_logit[(int64_t)b * (2 * p.gamma + 1) + row] = x[tok] * p.inv_t_log2;
+    if (threadIdx.x == 0 && tok >= lo && tok < hi) p.tok_logit[(int64_t)b * (2 * p.gamma + 1) + row] = x[tok];
     float m = -INFINITY;
 #pragma unroll
     for (int j = 0; j < N; ++j) m = fmaxf(m, y[j]);
@@ -233,31 +219,40 @@ void accept_softmax_partial(const AcceptParams p)
     }
 }
 
-// Merged (max, sum exp) of every row from its pass-1 partials, into LDS: sixteen lanes a row, four chunks each a trip.
+// Merged (max, sum exp) of every row from its pass-1 partials, into LDS.  The sum runs over the chunks in ascending order, rescaled
+// to the maximum so far at every eighth, so eight lanes share a row, a chunk each, and only the additions are one after
+// the other (done in the first four lanes, which see the other four mirrored).  kMergeAhead groups of eight are requested together.
+constexpr int kMergeAhead = 4;
 __device__ __forceinline__ void accept_merge_rows(const AcceptParams& p, int rows, const float* val, const float* aux,
                                                   float* s_m, float* s_z)
 {
-    const int l = threadIdx.x & 15;
-    for (int row = threadIdx.x >> 4; row < rows; row += kAccThreads / 16) {
+    const int j = threadIdx.x & 7;
+    for (int row = threadIdx.x >> 3; row < rows; row += kAccThreads / 8) {
+        const int64_t slot = (int64_t)row * p.n_chunks;
         float m = -INFINITY, z = 0.f;
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
-            float pm[4], pz[4];
+        for (int c0 = 0; c0 < p.n_chunks; c0 += 8 * kMergeAhead) {
+            float pm[kMergeAhead], pz[kMergeAhead];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (c0 + 16 * j >= p.n_chunks) { pm[j] = -INFINITY; pz[j] = 0.f; continue; }
-                const int c = min(c0 + 16 * j + l, p.n_chunks - 1);
-                const bool in = c0 + 16 * j + l < p.n_chunks;
-                pm[j] = val[(int64_t)row * p.n_chunks + c]; pz[j] = aux[(int64_t)row * p.n_chunks + c];
-                pm[j] = in ? pm[j] : -INFINITY; pz[j] = in ? pz[j] : 0.f;
+            for (int g = 0; g < kMergeAhead; ++g) {
+                const int c = min(c0 + 8 * g + j, p.n_chunks - 1);           // (as in load_share)
+                pm[g] = val[slot + c]; pz[g] = aux[slot + c];
             }
-            const float mc = row_max(fmaxf(fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])), m));
-            z *= (mc == -INFINITY) ? 0.f : fast_exp2(m - mc);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) z += (pz[j] > 0.f) ? pz[j] * fast_exp2(pm[j] - mc) : 0.f;
-            m = mc;
+            for (int g = 0; g < kMergeAhead; ++g) {
+                if (c0 + 8 * g >= p.n_chunks) break;
+                const bool in = c0 + 8 * g + j < p.n_chunks;
+                const float top = in ? pm[g] : -INFINITY;
+                float mc = fmaxf(top, row_move<0xB1>(top));
+                mc = fmaxf(mc, row_move<0x4E>(mc));
+                mc = fmaxf(fmaxf(mc, row_move<0x141>(mc)), m);
+                const float a = in && pz[g] > 0.f ? pz[g] * fast_exp2(top - mc) : 0.f, b = row_move<0x141>(a);
+                z = fmaf(z, mc == -INFINITY ? 0.f : fast_exp2(m - mc), row_move<0x00>(a));
+                z += row_move<0x55>(a); z += row_move<0xAA>(a); z += row_move<0xFF>(a);
+                z += row_move<0xFF>(b); z += row_move<0xAA>(b); z += row_move<0x55>(b); z += row_move<0x00>(b);
+                m = mc;
+            }
         }
-        z = row_sum(z);
-        if (l == 0) { s_m[row] = m; s_z[row] = z; }
+        if (j == 0) { s_m[row] = m; s_z[row] = z; }
     }
 }
 
@@ -266,16 +261,26 @@ struct AcceptWeight {
     const float* trow;
     const float* drow;        // null: no residual
     float inv_t_log2, mt, inv_zt, md, inv_zd;
-    // Weights of tokens first, first + step, ... (0 from `end` on).  Both rows' logits are requested before the first is
-    // looked at: with the test for a residual inside, every token was a round trip or two of its own.
-    template <int N> __device__ __forceinline__ void operator()(float (&w)[N], int first, int step, int end) const
+    // Weights of the lane's tokens lo + lane + 64 j below hi (0 from there on).  Both rows' logits are requested before the
+    // first is looked at: with the test for a residual inside, every token was a round trip or two of its own.
+    template <int N> __device__ __forceinline__ void operator()(float (&w)[N], int lo, int hi) const
     {
+        const int lane = threadIdx.x & 63;
         float t[N], d[N];
+        if (lo + 64 * N <= hi) {
+            const float* const tl = trow + lo;
+            const float* const dl = (drow ? drow : trow) + lo;
 #pragma unroll
-        for (int j = 0; j < N; ++j) t[j] = trow[min(first + j * step, end - 1)];     // (as in load_share; end >= 1)
-        if (drow) {
+            for (int j = 0; j < N; ++j) t[j] = tl[lane + 64 * j];
 #pragma unroll
-            for (int j = 0; j < N; ++j) d[j] = drow[min(first + j * step, end - 1)];
+            for (int j = 0; j < N; ++j) d[j] = dl[lane + 64 * j];
+        } else {                                                 // (as in load_share; hi >= 1)
+#pragma unroll
+            for (int j = 0; j < N; ++j) t[j] = trow[min(lo + lane + 64 * j, hi - 1)];
+            if (drow) {
+#pragma unroll
+                for (int j = 0; j < N; ++j) d[j] = drow[min(lo + lane + 64 * j, hi - 1)];
+            }
         }
 #pragma unroll
         for (int j = 0; j < N; ++j) w[j] = fast_exp2(t[j] * inv_t_log2 - mt) * inv_zt;
@@ -284,7 +289,7 @@ struct AcceptWeight {
             for (int j = 0; j < N; ++j) w[j] = fmaxf(w[j] - fast_exp2(d[j] * inv_t_log2 - md) * inv_zd, 0.f);
         }
 #pragma unroll
-        for (int j = 0; j < N; ++j) w[j] = first + j * step < end ? w[j] : 0.f;
+        for (int j = 0; j < N; ++j) w[j] = lo + lane + 64 * j < hi ? w[j] : 0.f;
     }
 };
 
@@ -304,11 +309,14 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
 // arrival, the owning segment -- and the launches.  As a launch of its own the inverse CDF cost another start, the
 // statistics' way through memory and a gap between launches.
 //
+// gamma 7, 152064 tokens, rows from HBM, us a call from a graph: 1 request 14.9, 8 requests 27.4 (three launches, with the tests'
+// logits looked up behind their tokens: 29.9 and 49.5).  Of that the chunk's mass in the order of pass 1 takes 0.7, its weights'
+// way through LDS; the last scan by shuffles 0.3.  Chunks of 4096 for few requests and sums in whatever order is the
+// shortest were 12.0, but a uniform within rounding of a step then drew another token, and not the same in every batch.
+//
 // The last workgroup of a request goes on.  Pass 1 has cleared the arrival counter, so nothing is asked of the workspace's
-// earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release), the one
-// that finds all others counted (acquire) reads them.  With an acquire alone or neither, behind a wait for the stores, the
-// call takes the same time.  gamma 7, 152064 tokens, rows from HBM: 30.2 us with a third launch and the tests' logits looked up
-// here, 24.3 without, 12.3 with load_share and smaller chunks (see there); 8 requests 50 / 45 / 25.
+// earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release), the
+// one that finds all others counted (acquire) reads them, at device scope.
 // CHUNK = kAccShort: the only chunk, nothing to exchange.
 
 __device__ __forceinline__ void store_device(float* at, float x) { __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -319,9 +327,12 @@ __global__ __launch_bounds__(kAccThreads)
 void accept_sample_kernel(const AcceptParams p)
 {
     constexpr bool SHORT = CHUNK == kAccShort;
+    constexpr int STEPS = CHUNK / kAccThreads;  // of 64 tokens, a wave's segment
+    constexpr int COLS = 256, COL_TOKENS = CHUNK / COLS;         // running sums of a chunk's mass, as in pass 1
+    __shared__ float s_w[CHUNK];                // the chunk's weights
     __shared__ float s_m[129], s_z[129];        // merged (max, sum) of up to 2*gamma+1 rows
-    __shared__ float s_seg[kAccSegs];
-    __shared__ float s_w[kAccWaves];
+    __shared__ float s_seg[kAccSegs], s_part[COLS / kWave];
+    __shared__ float s_top[kAccWaves];
     __shared__ int s_idx[kAccWaves];
     __shared__ float s_mass;
     __shared__ int s_last;
@@ -339,67 +350,110 @@ void accept_sample_kernel(const AcceptParams p)
         u = p.uniforms[(int64_t)b * (p.gamma + 1) + lane];
     }
     const float u_last = p.uniforms[(int64_t)b * (p.gamma + 1) + p.gamma];
-    accept_merge_rows(p, rows, p.part_val + (int64_t)b * rows * p.n_chunks, p.part_aux + (int64_t)b * rows * p.n_chunks, s_m, s_z);
+    const float* val = p.part_val + (int64_t)b * rows * p.n_chunks;
+    const float* aux = p.part_aux + (int64_t)b * rows * p.n_chunks;
+    accept_merge_rows(p, rows, val, aux, s_m, s_z);
     __syncthreads();
     bool ok = true;
     if (lane < p.gamma) {
-        const float pt = fast_exp2(t_logit - s_m[lane]) / s_z[lane];
-        const float qd = fast_exp2(d_logit - s_m[p.gamma + 1 + lane]) / s_z[p.gamma + 1 + lane];
+        const float pt = fast_exp2(t_logit * p.inv_t_log2 - s_m[lane]) / s_z[lane];
+        const float qd = fast_exp2(d_logit * p.inv_t_log2 - s_m[p.gamma + 1 + lane]) / s_z[p.gamma + 1 + lane];
         ok = tok >= 0 && tok < p.vocab && u * qd < pt;           // (not a token: cannot be accepted, and has no logits)
     }
     const uint64_t failed = __ballot(!ok);
     const int n = failed ? __ffsll((long long)failed) - 1 : p.gamma;
     const int dn = n < p.gamma ? p.gamma + 1 + n : 0;
     const AcceptWeight weight = accept_weight(p, b, n, s_m[n], s_z[n], s_m[dn], s_z[dn]);
-    constexpr int STEPS = CHUNK / kAccThreads;   // of 64 tokens, a wave's segment
     // a chunk's segments are as wide as it takes to deal it to the waves in token order
-    auto segment = [&](int c, int w, int& lo, int& hi) __attribute__((always_inline)) {
+    auto segment = [&](int c, int s, int& lo, int& hi) __attribute__((always_inline)) {
         const int from = c * CHUNK, to = min(p.vocab, from + CHUNK);
         const int width = ((to - from + kAccSegs - 1) / kAccSegs + 63) & ~63;
-        lo = min(to, from + w * width); hi = min(to, lo + width);
+        lo = min(to, from + s * width); hi = min(to, lo + width);
     };
     int lo, hi;
-    segment(chunk, wave, lo, hi);
-    float w2[STEPS], mine = 0.f;
-    weight(w2, lo + lane, 64, hi);
+    float w[STEPS];
+    // masses of the wave's segment of a chunk: every lane's running sum, then the lanes
+    auto segment_mass = [&](int c) __attribute__((always_inline)) {
+        segment(c, wave, lo, hi);
+        weight(w, lo, hi);
+        float mine = 0.f;
 #pragma unroll
-    for (int i = 0; i < STEPS; ++i) mine += w2[i];
-    mine = wave_sum(mine);
-    if (lane == 0) s_seg[wave] = mine;
-    float* const masses = p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs;
-    __syncthreads();
-    if (!SHORT) {
-        if (wave == 0) {
-            if (lane < kAccSegs) store_device(masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
-            if (lane == 0) s_last = __hip_atomic_fetch_add(p.arrived + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.n_chunks - 1u;
+        for (int i = 0; i < STEPS; ++i) mine += w[i];
+        mine = wave_sum(mine);
+        if (lane == 0) s_seg[wave] = mine;
+    };
+    float* const masses = p.chunk_mass + (int64_t)b * p.n_chunks;
+    float* const seg_masses = p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs;
+    float mass = 0.f;
+    {
+        segment_mass(chunk);
+        const int from = chunk * CHUNK, size = min(p.vocab - from, CHUNK);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) if (lo + 64 * i + lane < hi) s_w[lo - from + 64 * i + lane] = w[i];
+        __syncthreads();
+        if (tid < COLS) {
+            float col[COL_TOKENS], mine = 0.f;
+#pragma unroll
+            for (int j = 0; j < COL_TOKENS; ++j) col[j] = s_w[min(tid + COLS * j, size - 1)];
+#pragma unroll
+            for (int j = 0; j < COL_TOKENS; ++j) mine += tid + COLS * j < size ? col[j] : 0.f;
+            mine = wave_sum(mine);
+            if (lane == 0) s_part[wave] = mine;
         }
         __syncthreads();
-        if (!s_last) return;
+        mass = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
+        if (!SHORT && wave == 0) {
+            if (lane < kAccSegs) store_device(seg_masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
+            if (lane == 0) {
+                store_device(masses + chunk, mass);
+                s_last = __hip_atomic_fetch_add(p.arrived + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.n_chunks - 1u;
+            }
+        }
+        if (!SHORT) {
+            __syncthreads();
+            if (!s_last) return;
+        }
     }
-    // ---- the last workgroup: total mass and the owner of the goal among the chunks: the LAST chunk with mass whose prefix
-    // does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that rounding put at or
-    // beyond the total lands on the last chunk with mass).  A lane per chunk, 64 at a time.
-    float seg[kAccSegs];                                         // the lane's chunk's segments
-    auto chunk_mass = [&](int c) __attribute__((always_inline)) {
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < kAccSegs; ++i) seg[i] = c < p.n_chunks ? (SHORT ? s_seg[i] : load_device(masses + (int64_t)c * kAccSegs + i)) : 0.f;
-#pragma unroll
-        for (int i = 0; i < kAccSegs; ++i) sum += seg[i];
-        return sum;
-    };
-    float W = 0.f, m1 = 0.f, incl1 = 0.f;
+    // ---- one workgroup of the request: total mass and the owner of the goal among the chunks: the LAST chunk with mass whose
+    // prefix does not exceed the goal -- exactly one chunk, whatever rounding did to the sums (a goal that rounding put at or
+    // beyond the total lands on the last chunk with mass).  A lane per chunk, 64 at a time; the prefixes are running sums.
+    float W = 0.f, goal = 0.f, pre1 = 0.f, own_seg[kAccSegs];
+    int own1 = 0;                                                // (no chunk qualifies for a uniform below 0 or NaN)
     if (wave == 0) {
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
-            m1 = chunk_mass(c0 + lane);
-            incl1 = wave_prefix(m1);
-            W += from_lane(incl1, 63);
+        float m = 0.f, before = 0.f, seg[kAccSegs];              // the lane's chunk, the sum in front of it, its segments
+        auto walk = [&](int c0, float& sum) __attribute__((always_inline)) {
+            const int c = min(c0 + lane, p.n_chunks - 1);
+            m = SHORT ? mass : load_device(masses + c);
+            if (!SHORT) {
+#pragma unroll
+                for (int i = 0; i < kAccSegs; ++i) seg[i] = load_device(seg_masses + (int64_t)c * kAccSegs + i);
+            }
+            const int chunks = SHORT ? 1 : min(kWave, p.n_chunks - c0);
+            m = lane < chunks ? m : 0.f;
+            before = sum;
+            for (int i = 0; i < chunks; i += 8) {                // (chunks from `chunks` on add 0)
+#pragma unroll
+                for (int x = 0; x < 8; ++x) before += lane > i + x ? from_lane(m, i + x) : 0.f;
+            }
+            sum = from_lane(before + m, chunks - 1);
+        };
+        for (int c0 = 0; c0 < p.n_chunks; c0 += kWave) walk(c0, W);
+        goal = u_last * W;
+        float sum = 0.f;
+        for (int c0 = 0; c0 < p.n_chunks; c0 += kWave) {
+            if (p.n_chunks > kWave) walk(c0, sum);
+            const uint64_t fits = __ballot(m > 0.f && before <= goal);
+            const int l = fits ? 63 - __builtin_clzll(fits) : 0;
+            if (fits) { own1 = c0 + l; pre1 = from_lane(before, l); }
+            if (!SHORT && (fits || c0 == 0)) {
+#pragma unroll
+                for (int i = 0; i < kAccSegs; ++i) own_seg[i] = from_lane(seg[i], l);
+            }
         }
         if (lane == 0) s_mass = W;
     }
     __syncthreads();
     W = s_mass;
-    const int drafted = tid < p.gamma ? tok : -1;                // (lane = tid in the first wave, gamma <= 64)
     int y = -1;
     if (!(W > 0.f)) {
         // no residual mass (p == q): fall back to the target's most likely token
@@ -417,29 +471,16 @@ void accept_sample_kernel(const AcceptParams p)
             const int oi = __shfl_xor(bi, off);
             argmax_merge(bv, bi, ov, oi);
         }
-        if (lane == 0) { s_w[wave] = bv; s_idx[wave] = bi; }
+        if (lane == 0) { s_top[wave] = bv; s_idx[wave] = bi; }
         __syncthreads();
         if (wave != 0) return;
-        for (int w = 1; w < kAccWaves; ++w) argmax_merge(bv, bi, s_w[w], s_idx[w]);
+        for (int x = 1; x < kAccWaves; ++x) argmax_merge(bv, bi, s_top[x], s_idx[x]);
         y = __builtin_amdgcn_readfirstlane(bi);
     } else {
         if (wave != 0) return;
-        const float goal = u_last * W;
-        int own1 = 0;                                            // (no chunk qualifies for a uniform below 0 or NaN)
-        float pre1 = 0.f, before = 0.f, own_seg[kAccSegs];
-        for (int c0 = 0; c0 < p.n_chunks; c0 += 64) {
-            if (p.n_chunks > 64) { m1 = chunk_mass(c0 + lane); incl1 = wave_prefix(m1); }
-            const float below = __shfl_up(incl1, 1);             // (by all lanes: one that is switched off gives 0)
-            const float excl = before + (lane == 0 ? 0.f : below);
-            const uint64_t fits = __ballot(m1 > 0.f && excl <= goal);
-            const int l = fits ? 63 - __builtin_clzll(fits) : 0;
-            if (fits || c0 == 0) {
-                own1 = c0 + l;
-                pre1 = fits ? from_lane(excl, l) : 0.f;
+        if (SHORT) {
 #pragma unroll
-                for (int i = 0; i < kAccSegs; ++i) own_seg[i] = from_lane(seg[i], l);
-            }
-            before += from_lane(incl1, 63);
+            for (int i = 0; i < kAccSegs; ++i) own_seg[i] = s_seg[i];
         }
         // the same rule picks a segment of the owning chunk, whose few hundred tokens are then walked 64 at a time for
         // the first one whose cumulative mass passes the goal, else its last token with mass (rounding can leave no segment
@@ -447,30 +488,41 @@ void accept_sample_kernel(const AcceptParams p)
         int own2 = 0;
         float pre2 = pre1, acc2 = pre1;
 #pragma unroll
-        for (int w = 0; w < kAccSegs; ++w) {
-            if (own_seg[w] > 0.f && acc2 <= goal) { own2 = w; pre2 = acc2; }
-            acc2 += own_seg[w];
+        for (int s = 0; s < kAccSegs; ++s) {
+            if (own_seg[s] > 0.f && acc2 <= goal) { own2 = s; pre2 = acc2; }
+            acc2 += own_seg[s];
         }
         own2 = __builtin_amdgcn_readfirstlane(own2);
         segment(own1, own2, lo, hi);
-        weight(w2, lo + lane, 64, hi);
+        weight(w, lo, hi);
+        // (the scans of the steps do not depend on each other: six shuffles deep, not six per step)
+        float incl[STEPS];
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) incl[i] = w[i];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+            for (int i = 0; i < STEPS; ++i) {
+                const float t = __shfl_up(incl[i], off);
+                if (lane >= off) incl[i] += t;
+            }
+        }
         float c = pre2;
         int last = -1;
 #pragma unroll
         for (int i = 0; i < STEPS; ++i) {
-            const float incl = wave_prefix(w2[i]);
             const int base = lo + 64 * i;
-            const uint64_t massive = __ballot(w2[i] > 0.f);
-            const uint64_t passed = __ballot(w2[i] > 0.f && c + incl > goal);
+            const uint64_t massive = __ballot(w[i] > 0.f);
+            const uint64_t passed = __ballot(w[i] > 0.f && c + incl[i] > goal);
             if (massive) last = base + 63 - __builtin_clzll(massive);
             if (passed && y < 0) y = base + __ffsll((long long)passed) - 1;
-            c += from_lane(incl, 63);
+            c += from_lane(incl[i], 63);
         }
         if (y < 0) y = last >= 0 ? last : own1 * CHUNK;
     }
     // (the first wave only from here on)
     for (int i = lane; i <= p.gamma; i += 64)
-        p.out_tokens[(int64_t)b * (p.gamma + 1) + i] = i < n ? drafted : (i == n ? y : -1);      // (i < n implies i = lane < gamma)
+        p.out_tokens[(int64_t)b * (p.gamma + 1) + i] = i < n ? tok : (i == n ? y : -1);      // (i < n implies i = lane < gamma)
     if (lane == 0) p.n_accepted[b] = n;
 }
 
@@ -512,18 +564,7 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
     if (lane == 0) p.n_accepted[b] = n;
 }
 
-static int accept_chunks(int vocab, int chunk = kAccChunk) { return (vocab + chunk - 1) / chunk; }
-
-// Vocabulary entries of a chunk in the sampling passes.  Smaller chunks are more workgroups with less to do one after the
-// other, as long as those of the second pass, of 1024 threads each, find a CU of their own (us a call from a graph, rows from
-// HBM, chunks of 4096 / 8192; in brackets the requests' chunks of 8192):  152064 tokens, gamma 7, 1 request [19] 12.3 / 13.1, 2
-// 14.0 / 14.2, 3 [57] 15.8 / 16.3, 4 [76] 18.7 / 18.2, gamma 1, 8 requests [152] 18.7 / 15.4;  65537 tokens, gamma 7, 4 [36] 13.0 / 14.2, 8 [72]
-// 17.5 / 17.5;  32000 tokens, 8 [32] 12.7 / 13.8.  Up to kAccShort tokens there is one chunk.
-static int accept_chunk(int batch, int vocab)
-{
-    if (vocab <= kAccShort) return kAccShort;
-    return (int64_t)batch * accept_chunks(vocab) <= 64 ? kAccSmallChunk : kAccChunk;
-}
+static int accept_chunks(int vocab) { return (vocab + kAccChunk - 1) / kAccChunk; }
 
 // Lanes per row of the greedy final kernels: 16 where that is fewer trips.  The whole call from a graph, us, one lane /
 // 16 lanes:  152064 tokens (19 chunks): 6 rows 8.4 / 6.7, 21 rows 9.0 / 8.5, 65 rows 13.4 / 14.4;  65537 (9 chunks): 16 rows
@@ -543,12 +584,11 @@ extern "C" size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab
 {
     if (batch <= 0 || gamma < 0 || vocab < 1) return 0;
     const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
-    // (sampling: of the smaller chunks, whichever are taken, so that what is enough for a batch is enough for a smaller one)
-    const int chunks = accept_chunks(vocab, sampling ? kAccSmallChunk : kAccChunk);
-    size_t bytes = 2 * align256((size_t)batch * rows * chunks * sizeof(float));
-    if (sampling)       // the drafted tokens' logits, segment masses of the rejected row, arrivals
+    size_t bytes = 2 * align256((size_t)batch * rows * accept_chunks(vocab) * sizeof(float));
+    if (sampling)       // the drafted tokens' logits, chunk and segment masses of the rejected row, arrivals
         bytes += align256((size_t)batch * rows * sizeof(float)) +
-                 align256((size_t)batch * chunks * kAccSegs * sizeof(float)) +
+                 align256((size_t)batch * accept_chunks(vocab) * sizeof(float)) +
+                 align256((size_t)batch * accept_chunks(vocab) * kAccSegs * sizeof(float)) +
                  align256((size_t)batch * sizeof(uint32_t));
     return bytes;
 }
@@ -574,9 +614,7 @@ extern "C" int specvlm_accept(
 
     AcceptParams p;
     p.target = target_logits; p.draft = draft_logits; p.tokens = draft_tokens; p.uniforms = uniforms;
-    p.batch = batch; p.gamma = gamma; p.vocab = vocab;
-    const int chunk = sampling ? accept_chunk(batch, vocab) : kAccChunk;
-    p.n_chunks = accept_chunks(vocab, chunk);
+    p.batch = batch; p.gamma = gamma; p.vocab = vocab; p.n_chunks = accept_chunks(vocab);
     p.inv_t_log2 = sampling ? kLog2e / temperature : kLog2e;
     p.n_accepted = n_accepted; p.out_tokens = out_tokens;
     const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
@@ -585,7 +623,8 @@ extern "C" int specvlm_accept(
     p.part_val = (float*)ws;
     p.part_aux = (float*)(ws + part_bytes);
     p.tok_logit = (float*)(ws + 2 * part_bytes);                 // (sampling only, from here on)
-    p.seg_mass = (float*)((char*)p.tok_logit + align256((size_t)batch * rows * sizeof(float)));
+    p.chunk_mass = (float*)((char*)p.tok_logit + align256((size_t)batch * rows * sizeof(float)));
+    p.seg_mass = (float*)((char*)p.chunk_mass + align256((size_t)batch * p.n_chunks * sizeof(float)));
     p.arrived = (uint32_t*)((char*)p.seg_mass + align256((size_t)batch * p.n_chunks * kAccSegs * sizeof(float)));
     hipStream_t s = (hipStream_t)stream;
     if (!sampling) {
@@ -596,12 +635,9 @@ extern "C" int specvlm_accept(
             hipLaunchKernelGGL(accept_greedy_final<kFinalLanes>, dim3(batch), dim3(kFinalThreads), 0, s, p);
     } else {
         const dim3 rows_grid(p.n_chunks, 2 * gamma + 1, batch), grid(p.n_chunks, batch);
-        if (chunk == kAccShort) {
+        if (vocab <= kAccShort) {
             hipLaunchKernelGGL(accept_softmax_partial<kAccShort>, rows_grid, dim3(256), 0, s, p);
             hipLaunchKernelGGL(accept_sample_kernel<kAccShort>, grid, dim3(kAccThreads), 0, s, p);
-        } else if (chunk == kAccSmallChunk) {
-            hipLaunchKernelGGL(accept_softmax_partial<kAccSmallChunk>, rows_grid, dim3(256), 0, s, p);
-            hipLaunchKernelGGL(accept_sample_kernel<kAccSmallChunk>, grid, dim3(kAccThreads), 0, s, p);
         } else {
             hipLaunchKernelGGL(accept_softmax_partial<kAccChunk>, rows_grid, dim3(256), 0, s, p);
             hipLaunchKernelGGL(accept_sample_kernel<kAccChunk>, grid, dim3(kAccThreads), 0, s, p);
@@ -636,7 +672,7 @@ extern "C" int specvlm_accept_tree(
     p.n_accepted = n_accepted; p.out_tokens = out_tokens;
     p.part_val = (float*)workspace;
     p.part_aux = (float*)((char*)workspace + need / 2);
-    p.tok_logit = nullptr; p.seg_mass = nullptr; p.arrived = nullptr;
+    p.tok_logit = nullptr; p.chunk_mass = nullptr; p.seg_mass = nullptr; p.arrived = nullptr;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, n_nodes, batch), dim3(256), 0, s, p);
     if (accept_final_lanes(n_nodes, p.n_chunks) == 1)

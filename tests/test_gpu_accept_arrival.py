@@ -1,7 +1,7 @@
 """GPU parity of the sampling acceptance whose last workgroup of a request finishes the call: 64 and 65 chunks (one and two
 trips of a lane per chunk), final uniforms on both sides of every segment's and chunk's end, a workspace full of other
 contents, and replays of a captured call with eager calls on the same workspace between them.  The bound of every sampling
-test (equal outside a margin of 1e-4); replays are equal bit for bit."""
+test (equal outside a margin of 1e-4; test_gpu_accept_order.py has none); replays are equal bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -21,8 +21,11 @@ def test_sampling(B, batch, gamma, vocab, temp):
 def test_goals_around_the_ends_of_segments_and_chunks(B, vocab):
     """One row of equal logits: token v owns [v / vocab, (v + 1) / vocab), so a uniform in the middle of that interval
     names v whatever the rounding of 40000 fp32 sums (2^-24 * 40000 / 2 < 1e-2 of an interval's share of the total)."""
-    width = ((min(vocab, 8192) + 15) // 16 + 63) & ~63
-    tokens = sorted({t for e in [*range(0, vocab, width), *range(0, vocab, 8192), vocab] for t in (e - 1, e, e + 1) if 0 <= t < vocab})
+    ends = {vocab}
+    for lo in range(0, vocab, 8192):                     # (a short chunk has narrower segments)
+        size = min(vocab - lo, 8192)
+        ends |= set(range(lo, lo + size, ((size + 15) // 16 + 63) & ~63))
+    tokens = sorted({t for e in ends for t in (e - 1, e, e + 1) if 0 <= t < vocab})
     u = ((np.array(tokens, np.float64) + 0.5) / vocab).astype(np.float32)[:, None]
     x = np.zeros((len(tokens), 1, vocab), np.float32)
     n, out = B.accept(base.cuda(x), base.cuda(np.zeros((len(tokens), 0), np.int32)), uniforms=base.cuda(u))
@@ -65,7 +68,7 @@ def test_replays_between_eager_calls_on_one_workspace(B):
         torch.cuda.synchronize()
 
 
-# the requests' chunks of 8192 on both sides of 64 (chunks of 4096 and of 8192), last chunks of one token, one request alone
+# last chunks of one token, one chunk that is not full, many requests and one alone
 @pytest.mark.parametrize("batch,gamma,vocab", [(7, 2, 73728), (7, 2, 73729), (64, 1, 4097), (65, 1, 4097), (32, 1, 8193), (33, 1, 8193),
                                                (1, 3, 4096), (2, 3, 1025)])
 def test_chunk_sizes(B, batch, gamma, vocab):

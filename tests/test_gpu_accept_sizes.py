@@ -1,5 +1,5 @@
-"""GPU parity of specvlm_accept at the sizes where its kernels change what they do: pass-1 partials of a request that just
-fit the staging area and that do not (129 rows x 31 / 32 chunks), more chunks than the final kernel has threads, more
+"""GPU parity of specvlm_accept at the sizes where its kernels change what they do: as many rows as there
+can be (129 with 31 and 32 chunks, more rows than one round of the merge takes), more chunks than a workgroup has threads, more
 rows and chunks than one round of the argmax merge takes.  Bounds: those of the acceptance tests (greedy bit-exact,
 sampling equal outside a margin of 1e-4)."""
 import numpy as np
@@ -26,7 +26,7 @@ def test_greedy(B, batch, gamma, vocab, sigma):
     base.test_greedy_bit_exact(B, batch, gamma, vocab, sigma)
 
 
-# short chunks (every wave has one step of 64 tokens up to 1024, two from 1025), eight chunks and nine (staged from there)
+# short chunks (every wave has one step of 64 tokens up to 1024, two from 1025), eight chunks and nine (one and two groups of the merge)
 @pytest.mark.parametrize("batch,gamma,vocab,temp", [
     (8, 3, 63, 1.0), (8, 3, 1024, 1.0), (8, 3, 1025, 1.0), (4, 2, 8192 + 1024, 0.8), (4, 2, 8192 + 1, 1.0), (2, 5, 65536, 1.0), (2, 5, 65537, 1.0),
 ])
