@@ -44,11 +44,21 @@ __device__ __forceinline__ int xcd_logical_id(int hw_id, int padded)
 // sequence for a divisor that it does not know is a chain of about 25 instructions, and the kernels here that take a few
 // microseconds had four to six of them in front of their first load.)
 struct QuotRem { int q, r; };
-__device__ __forceinline__ QuotRem divide(int x, int d, uint32_t inv)
+__host__ __device__ __forceinline__ QuotRem divide(int x, int d, uint32_t inv)
 {
     // inv <= 2^32 / d < inv + 1 (or inv = 2^32 - 1 for d = 1): the estimate is the quotient or one less
-    const int q = (int)__umulhi((uint32_t)x, inv), r = x - q * d;
+    const int q = (int)(((uint64_t)(uint32_t)x * inv) >> 32), r = x - q * d;
     return r >= d ? QuotRem{q + 1, r - d} : QuotRem{q, r};
+}
+// Share k of n_help equal ones of a request's rows, with inv = reciprocal(n_help).  Empty where the request has nothing to
+// compute (no queries, or fewer keys than queries), whatever its offsets say: divide() is exact from 0 on only.
+struct RowRange { int first, n; };
+__host__ __device__ __forceinline__ RowRange helper_rows(int n_queries, int n_keys, int k, int n_help, uint32_t inv)
+{
+    if (n_queries <= 0 || n_keys < n_queries) return {0, 0};
+    const int per = divide(n_keys + n_help - 1, n_help, inv).q, first = k * per;
+    const int n = (n_keys < first + per ? n_keys : first + per) - first;
+    return {first, n > 0 ? n : 0};
 }
 inline uint32_t reciprocal(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d) : 0xffffffffu; }
 

@@ -862,11 +862,11 @@ __device__ __forceinline__ void attn_prefetch_rows(const AttnParams& p, int id)
     // that workgroup's head (with fewer workgroups than XCDs some XCDs compute nothing)
     const int x = id % kNumXcd, n_help = (p.n_work - p.n_main) / kNumXcd, k = (id - p.n_main) / kNumXcd;
     if (x >= p.n_main) return;
-    int kv0 = 0, kvl = p.kv_len;
-    if (p.cu_kv) { kv0 = p.cu_kv[0]; kvl = p.cu_kv[1] - kv0; }
+    int ql = p.q_len, kv0 = 0, kvl = p.kv_len;
+    if (p.cu_q) { ql = p.cu_q[1] - p.cu_q[0]; kv0 = p.cu_kv[0]; kvl = p.cu_kv[1] - kv0; }
     const int g = divide(x, p.n_kv_heads, p.inv_heads).r;
-    const int per = divide(kvl + n_help - 1, n_help, p.inv_help).q;
-    const int first = k * per, n = (min(kvl, first + per) - first) * (D / 8);
+    const RowRange rows = helper_rows(ql, kvl, k, n_help, p.inv_help);
+    const int first = rows.first, n = rows.n * (D / 8);
     u32x4 acc = {0u, 0u, 0u, 0u};
     for (int i = threadIdx.x; i < n; i += THREADS) {
         const int64_t off = (int64_t)(kv0 + first + i / (D / 8)) * p.kv_tok + (int64_t)g * p.kv_head + (i % (D / 8)) * 8;
