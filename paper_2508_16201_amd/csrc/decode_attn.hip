@@ -685,7 +685,7 @@ void attn_merge_kernel(const AttnParams p)
     // the partial slots of this (request, head) are consecutive: splits 0..live-1
     const int live = min(p.num_splits, divide(kvl + p.split_keys - 1, p.split_keys, p.inv_split_keys).q);
     const int64_t slot0 = (int64_t)bh * p.num_splits * p.rows_pad + row;
-    // (a scalar base and 32-bit offsets: a (request, head) has at most 256 splits of 64 times its q heads' rows)
+    // (a scalar base and 32-bit offsets: attn_merges_by_row leaves no larger (request, head) to this kernel)
     const char* const ml_base = reinterpret_cast<const char*>(p.part_ml + slot0 * 2);
     const char* const o_base = reinterpret_cast<const char*>(p.part_o + slot0 * D);
     const int tid = threadIdx.x;
@@ -1181,9 +1181,13 @@ static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, i
 //     10 heads:  2560 [3000], 8 splits 18.3 / 19.0;  2 heads:  2048 [3000] 7 % slower to 3 % faster, 3072 0 to 9 % faster.
 // Where the kv heads are a multiple of the XCDs a head's partials lie in the L2 of the XCD that merges them; elsewhere more
 // rows are needed to hide the way.  With more splits the second trip costs more (16 splits 18.7 / 20.1).
-constexpr int kMergeRowPieces = 8;
-static bool attn_merges_by_row(int n_kv_heads, int64_t total_rows, int head_dim, int num_splits)
+// The kernel of one row per workgroup reaches its first 36 splits, which it requests together, by 32-bit byte offsets.  Where those do
+// not get that far (480000 rows of size 128: 64 queries of a kv head's 7500 q heads) a group per row, with 64 bits, does it.
+constexpr int kMergeRowPieces = 8, kMergeGroups = 12, kMergeAhead = 3;
+static bool attn_merges_by_row(int n_kv_heads, int64_t total_rows, int rows_pad, int head_dim, int num_splits)
 {
+    const int ahead = num_splits < kMergeGroups * kMergeAhead ? num_splits : kMergeGroups * kMergeAhead;
+    if ((int64_t)ahead * rows_pad * head_dim * 2 > 0xffffffffll) return true;
     return num_splits <= kMergeRowPieces && total_rows * head_dim >= (n_kv_heads % kNumXcd == 0 ? 3 : 7) * kNumCu * 128ll;
 }
 
@@ -1409,7 +1413,7 @@ static int attn_impl(
     int rc = head_dim == 128 ? launch_attn_d<128>(p, mb, s) : launch_attn_d<64>(p, mb, s);
     if (rc != SPECVLM_OK) return rc;
     if (p.balanced || (p.num_splits > 1 &&
-                       attn_merges_by_row(n_kv_heads, batch * n_kv_heads * (int64_t)rows, head_dim, p.num_splits))) {
+                       attn_merges_by_row(n_kv_heads, batch * n_kv_heads * (int64_t)rows, p.rows_pad, head_dim, p.num_splits))) {
         const int per_wg = 256 / (head_dim / 4);
         dim3 grid((rows + per_wg - 1) / per_wg * batch * n_kv_heads);
         if (head_dim == 128) hipLaunchKernelGGL((attn_merge_rows_kernel<128, kMergeRowPieces>), grid, dim3(256), 0, s, p);
@@ -1417,8 +1421,8 @@ static int attn_impl(
         rc = launch_status();
     } else if (p.num_splits > 1) {
         dim3 grid(rows * batch * n_kv_heads);
-        if (head_dim == 128) hipLaunchKernelGGL((attn_merge_kernel<128, 3, 384>), grid, dim3(384), 0, s, p);
-        else                 hipLaunchKernelGGL((attn_merge_kernel<64, 3, 192>), grid, dim3(192), 0, s, p);
+        if (head_dim == 128) hipLaunchKernelGGL((attn_merge_kernel<128, kMergeAhead, kMergeGroups * 32>), grid, dim3(kMergeGroups * 32), 0, s, p);
+        else                 hipLaunchKernelGGL((attn_merge_kernel<64, kMergeAhead, kMergeGroups * 16>), grid, dim3(kMergeGroups * 16), 0, s, p);
         rc = launch_status();
     }
     return rc;

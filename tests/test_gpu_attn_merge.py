@@ -1,6 +1,7 @@
 """GPU parity of the decode-attention merges where their launch changes: eight splits and nine, row counts on both sides of
 the lines from which a group of threads takes a row, rows that do not fill the last workgroup, and ragged batches in which
-requests have fewer live splits than the launch.  Bounds: those of every attention test."""
+requests have fewer live splits than the launch; partial results that 32-bit offsets do not reach.  Bounds: those of every
+attention test."""
 import numpy as np
 import pytest
 import torch
@@ -71,3 +72,27 @@ def test_ragged_batch_of_many_rows(B):
     for i, m in enumerate(q_lens):
         assert_attn_close(out[o:o + m], oracle.decode_attn(q[i], k[i], v[i], 0.088)[0], f"request {i}")
         o += m
+
+
+def test_partials_beyond_32_bit_offsets(B):
+    """480000 rows: the partial results of split 35 of 0 to 36, the last one that a workgroup requests together with the first,
+    lie 4.3e9 bytes behind those, and its keys are the ones that every query looks at."""
+    q_len, kv_len, hq, d, splits = 64, 37 * 128, 7500, 128, 37
+    g = torch.Generator(device="cuda")
+    g.manual_seed(66)
+    at = torch.randn(d, generator=g, device="cuda")
+    q = (at + 0.3 * torch.randn((q_len, hq, d), generator=g, device="cuda")).bfloat16()
+    k = torch.randn((kv_len, 1, d), generator=g, device="cuda").bfloat16()
+    v = torch.randn((kv_len, 1, d), generator=g, device="cuda").bfloat16()
+    k[35 * 128:36 * 128] = (at + 0.5 * torch.randn((128, 1, d), generator=g, device="cuda")).bfloat16()
+    scale = 1.0 / np.sqrt(d)
+    out, lse = B.decode_attn(q, k, v, scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    rows = torch.randint(q_len * hq, (64,), generator=g, device="cuda")
+    logits = (q.view(-1, d)[rows].double() @ k[:, 0].double().T) * scale
+    hidden = torch.arange(kv_len, device="cuda")[None, :] > (kv_len - q_len + rows // hq)[:, None]
+    logits.masked_fill_(hidden, float("-inf"))
+    want = (logits.softmax(-1) @ v[:, 0].double()).cpu().numpy()
+    assert np.abs(want).max() > 0.2
+    assert_attn_close(out.view(-1, d)[rows], want, "sampled rows")
+    np.testing.assert_allclose(host_f64(lse).reshape(-1)[rows.cpu().numpy()], logits.logsumexp(-1).cpu().numpy(), atol=2e-3, rtol=1e-4)
