@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "specvlm.h"
 
 namespace specvlm {
@@ -68,6 +70,23 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline int launch_status()
 {
     return hipGetLastError() == hipSuccess ? SPECVLM_OK : SPECVLM_ELAUNCH;
+}
+
+constexpr int kMaxDevices = 64;         // per-device host state (kernel attributes, scratch addresses)
+
+// Lets a kernel be launched with `bytes` of dynamic LDS, more than the 64 KB that need no leave.  The attribute belongs to
+// the kernel as loaded on one device: it is raised once per device, before the call's first launch.
+template <auto* KERNEL>
+inline int allow_lds(int bytes)
+{
+    static std::atomic<bool> raised[kMaxDevices];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
+    if (raised[dev].load(std::memory_order_acquire)) return SPECVLM_OK;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
+        return SPECVLM_ELAUNCH;
+    raised[dev].store(true, std::memory_order_release);
+    return SPECVLM_OK;
 }
 
 constexpr float kLog2e = 1.4426950408889634f;

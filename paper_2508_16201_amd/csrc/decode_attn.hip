@@ -135,7 +135,6 @@ __device__ __forceinline__ AttnBalance attn_balance(const AttnParams& p, int til
 constexpr int kMaxSplits = 256;
 constexpr float kSumRedo = 0x1p100f;     // a lane's sum of one chunk at or above this (or NaN) is redone with the maximum tracked
 constexpr int kMaxQueryBlock = 64;      // queries per request: a row's view of its block is one 64-bit mask
-constexpr int kMaxDevices = 64;         // per-device host state (kernel attributes, scratch addresses)
 constexpr int kTargetWorkgroups = 192;  // workgroups of a single-request launch
 
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.
@@ -1198,18 +1197,8 @@ static int launch_attn_s(const AttnParams& p, hipStream_t stream)
     constexpr size_t ring = (size_t)NS * 2 * TK * D * 2;
     constexpr size_t merge = KS > 1 ? sizeof(float) * (size_t)(2 * NW * 16 + NW * 16 * (D + 4)) : 0;
     constexpr size_t lds = ring > merge ? ring : merge;
-    if (lds > 64 * 1024) {
-        // the attribute belongs to the kernel as loaded on one device: raise it once per device
-        static std::atomic<bool> raised[kMaxDevices];
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
-        if (!raised[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_split_kernel<D, MB, KS, TK, NS, NLD, STREAM>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return SPECVLM_ELAUNCH;
-            raised[dev].store(true, std::memory_order_release);
-        }
-    }
+    if (lds > 64 * 1024)
+        if (const int rc = allow_lds<&attn_split_kernel<D, MB, KS, TK, NS, NLD, STREAM>>((int)lds)) return rc;
     hipLaunchKernelGGL((attn_split_kernel<D, MB, KS, TK, NS, NLD, STREAM>), dim3(p.n_work), dim3((NW + NLD) * kWave),
                        lds, stream, p);
     return launch_status();
@@ -1219,17 +1208,8 @@ template <int D, int NW, int CH, int COLS>
 static int launch_short(const AttnParams& p, hipStream_t stream)
 {
     constexpr size_t lds = (size_t)NW * (kChunkKeys * (D + COLS) * 2 + 2 * 16 * sizeof(float));
-    if (lds > 64 * 1024) {
-        static std::atomic<bool> raised[kMaxDevices];
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPECVLM_ELAUNCH;
-        if (!raised[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_short_kernel<D, NW, CH, COLS>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return SPECVLM_ELAUNCH;
-            raised[dev].store(true, std::memory_order_release);
-        }
-    }
+    if (lds > 64 * 1024)
+        if (const int rc = allow_lds<&attn_short_kernel<D, NW, CH, COLS>>((int)lds)) return rc;
     hipLaunchKernelGGL((attn_short_kernel<D, NW, CH, COLS>), dim3(p.n_work), dim3(NW * kWave), lds, stream, p);
     return launch_status();
 }

@@ -33,8 +33,6 @@
 // exponential per logit: away from the causal mask it does not track maxima at
 // all, and where it does it rescales its running sum only when a tile's maximum
 // exceeds the reference by more than 2^8.
-#include <atomic>
-
 #include "common.h"
 
 namespace specvlm {
@@ -585,7 +583,6 @@ void score_final_kernel(const ScoreParams p_launch)
 // heads: neither normalisers nor partial columns go through memory.  64 queries over 1568 + 64 keys, 4 heads of size 64: from a
 // graph 14.1 -> 8.5 us, called from Python 15.5 -> 9.7 (rows 3.3, columns 5); with the caller's normalisers 8.1 -> 3.7.
 constexpr int kSmallLds = 144 * 1024;  // of the column sums' workgroup, at most
-constexpr int kScoreMaxDevices = 64;
 constexpr int kSmallTiles = 8;         // row tiles (64 text queries of a q head), at most
 constexpr int kSmallSplits = 32;       // key ranges of the row statistics, at most (eight lanes of four)
 
@@ -857,20 +854,10 @@ static ScoreSmallPlan score_small_plan(int n_text, int domain, int n_q_heads)
 template <int D>
 static int launch_small(const ScoreSmallParams& p, hipStream_t stream)
 {
-    if (!p.row_lse) hipLaunchKernelGGL((score_small_rows_kernel<D>), dim3(p.n_tiles, p.splits), dim3(256), 0, stream, p);
-    // (more than 64 KB of LDS wants the attribute, which belongs to the kernel as loaded on one device)
     const size_t lds = (size_t)(p.n_tiles + p.n_kv_heads) * kScoreTile * D * 2;
-    static std::atomic<bool> raised[kScoreMaxDevices];
-    if (lds > 48 * 1024) {
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScoreMaxDevices) return SPECVLM_ELAUNCH;
-        if (!raised[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_small_cols_kernel<D>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds) != hipSuccess)
-                return SPECVLM_ELAUNCH;
-            raised[dev].store(true, std::memory_order_release);
-        }
-    }
+    if (lds > 60 * 1024)                                         // (the kernel declares 2.3 KB more)
+        if (const int rc = allow_lds<&score_small_cols_kernel<D>>(kSmallLds)) return rc;
+    if (!p.row_lse) hipLaunchKernelGGL((score_small_rows_kernel<D>), dim3(p.n_tiles, p.splits), dim3(256), 0, stream, p);
     hipLaunchKernelGGL((score_small_cols_kernel<D>), dim3((p.n_video + kScoreTile - 1) / kScoreTile), dim3(512), lds, stream, p);
     return launch_status();
 }

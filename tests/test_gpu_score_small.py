@@ -19,7 +19,7 @@ B = base.B
     (1568, 64, 0, 4, 1, 64, 0), (1, 1, 0, 1, 1, 64, 0), (63, 63, 0, 4, 2, 64, 1), (64, 64, 0, 8, 1, 128, 0),
     (65, 65, 3, 4, 4, 64, 0), (300, 130, 0, 2, 1, 128, 1), (700, 512, 9, 1, 1, 64, 0), (2100, 17, 0, 8, 8, 64, 0),
     (1000, 1, 2000, 3, 1, 128, 0), (17343, 64, 1, 2, 2, 64, 0), (17344, 64, 1, 2, 2, 64, 0), (500, 64, 0, 9, 1, 64, 0),
-    (430, 64, 0, 9, 1, 64, 0), (4032, 64, 0, 9, 1, 64, 0),
+    (430, 64, 0, 9, 1, 64, 0), (4032, 64, 0, 9, 1, 64, 0), (700, 64, 0, 6, 1, 64, 0),      # (the last: 58 KB of LDS)
 ])
 def test_small_layer(B, V, L, P, hq, hkv, d, mode):
     base.test_score_matches_oracle(B, V, L, P, hq, hkv, d, mode)

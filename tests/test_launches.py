@@ -1,0 +1,33 @@
+"""What calls launch, seen from the host (tests/launches.py): which kernels serve which shapes, and that a call that fails has
+launched nothing.  No GPU is touched."""
+import pytest
+
+from launches import AT, launches
+
+
+def score(hq, hkv, d, n_text, n_video, layers=None, **more):
+    n_keys = n_video + n_text
+    args = dict(q_text=AT, q_tok_stride=hq * d, q_head_stride=d, k_cache=AT, k_tok_stride=hkv * d, k_head_stride=d, batch=1,
+                n_text=n_text, n_keys=n_keys, n_video=n_video, text_pos0=-1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d,
+                softmax_scale=0.125, scores=AT, workspace=AT, workspace_bytes=1 << 40)
+    if layers:
+        args.update(n_layers=layers, q_layer_stride=n_text * hq * d, k_layer_stride=n_keys * hkv * d)
+    args.update(more)
+    return ("specvlm_score_layers" if layers else "specvlm_score", args)
+
+
+def attn(hq, hkv, d, q_len, kv_len, **more):
+    args = dict(q=AT, q_tok_stride=hq * d, q_head_stride=d, k=AT, v=AT, kv_tok_stride=hkv * d, kv_head_stride=d, batch=1, q_len=q_len,
+                kv_len=kv_len, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, softmax_scale=0.125, out=AT, workspace=AT,
+                workspace_bytes=1 << 40)
+    args.update(more)
+    return ("specvlm_decode_attn", args)
+
+
+# each with so much LDS that the kernel's attribute has to be raised first
+@pytest.mark.parametrize("call", [score(8, 4, 64, 64, 1568), score(8, 1, 128, 64, 700, row_lse=AT), attn(14, 2, 64, 1, 1511),
+                                  attn(64, 8, 128, 6, 12806), attn(64, 8, 128, 1, 1000)])
+def test_a_call_that_fails_has_launched_nothing(call, tmp_path):
+    no_device, no_attribute, good = launches([(*call, 1, 0), (*call, 0, 1), call], tmp_path)
+    assert no_device == (-4, []) and no_attribute == (-4, [])
+    assert good[0] == 0 and len(good[1]) >= 1
