@@ -314,15 +314,17 @@ __device__ __forceinline__ AcceptWeight accept_weight(const AcceptParams& p, int
 // way through LDS; the last scan by shuffles 0.3.  Chunks of 4096 for few requests and sums in whatever order is the
 // shortest were 12.0, but a uniform within rounding of a step then drew another token, and not the same in every batch.
 //
-// The last workgroup of a request goes on.  Pass 1 has cleared the arrival counter, so nothing is asked of the workspace's
-// earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release), the
-// one that finds all others counted (acquire) reads them, at device scope.
+// kWhole: the last workgroup of a request goes on.  Pass 1 has cleared the arrival counter, so nothing is asked of the
+// workspace's earlier contents, and nobody waits for anybody: every workgroup writes its masses and counts itself in (release),
+// the one that finds all others counted (acquire) reads them, at device scope.
+// kMasses, kDraw: two launches, without a counter (see accept_one_launch).
 // CHUNK = kAccShort: the only chunk, nothing to exchange.
+enum AcceptPart { kWhole, kMasses, kDraw };
 
 __device__ __forceinline__ void store_device(float* at, float x) { __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float load_device(const float* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <int CHUNK>
+template <int CHUNK, int PART>
 __global__ __launch_bounds__(kAccThreads)
 void accept_sample_kernel(const AcceptParams p)
 {
@@ -385,7 +387,7 @@ void accept_sample_kernel(const AcceptParams p)
     float* const masses = p.chunk_mass + (int64_t)b * p.n_chunks;
     float* const seg_masses = p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs;
     float mass = 0.f;
-    {
+    if (PART != kDraw) {
         segment_mass(chunk);
         const int from = chunk * CHUNK, size = min(p.vocab - from, CHUNK);
 #pragma unroll
@@ -404,11 +406,11 @@ void accept_sample_kernel(const AcceptParams p)
         mass = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
         if (!SHORT && wave == 0) {
             if (lane < kAccSegs) store_device(seg_masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
-            if (lane == 0) {
-                store_device(masses + chunk, mass);
+            if (lane == 0) store_device(masses + chunk, mass);
+            if (PART == kWhole && lane == 0)
                 s_last = __hip_atomic_fetch_add(p.arrived + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.n_chunks - 1u;
-            }
         }
+        if (PART == kMasses) return;
         if (!SHORT) {
             __syncthreads();
             if (!s_last) return;
@@ -566,6 +568,12 @@ void accept_tree_final(const AcceptParams p, const int32_t* parent, int32_t* acc
 
 static int accept_chunks(int vocab) { return (vocab + kAccChunk - 1) / kAccChunk; }
 
+// One launch behind pass 1, or two: a release and an acquire by every workgroup cost more than a launch once there are more
+// workgroups than CUs.  Us a call from a graph, rows from HBM, one / two, workgroups in brackets:  152064 tokens, gamma 7, 1
+// request [19] 15.0 / 17.0, 8 [152] 27.4 / 28.4, 12 [228] 34.4 / 34.8, 14 [266] 40.2 / 38.8, 16 [304] 43.7 / 41.8;  gamma 3, 64 [1216]
+// 96.1 / 70.6;  gamma 1, 128 [2432] 133.5 / 73.3;  32000 tokens, gamma 3, 64 [256] 24.4 / 24.1, 72 [288] 29.1 / 26.3.
+static bool accept_one_launch(int batch, int n_chunks) { return (int64_t)batch * n_chunks <= kNumCu; }
+
 // Lanes per row of the greedy final kernels: 16 where that is fewer trips.  The whole call from a graph, us, one lane /
 // 16 lanes:  152064 tokens (19 chunks): 6 rows 8.4 / 6.7, 21 rows 9.0 / 8.5, 65 rows 13.4 / 14.4;  65537 (9 chunks): 16 rows
 // 7.8 / 7.0, 21 rows 7.8 / 8.0;  32000 (4 chunks): 6 rows 6.7 / 7.0, 21 rows 6.9 / 8.0, 65 rows 7.5 / 10.7.
@@ -637,10 +645,15 @@ extern "C" int specvlm_accept(
         const dim3 rows_grid(p.n_chunks, 2 * gamma + 1, batch), grid(p.n_chunks, batch);
         if (vocab <= kAccShort) {
             hipLaunchKernelGGL(accept_softmax_partial<kAccShort>, rows_grid, dim3(256), 0, s, p);
-            hipLaunchKernelGGL(accept_sample_kernel<kAccShort>, grid, dim3(kAccThreads), 0, s, p);
+            hipLaunchKernelGGL((accept_sample_kernel<kAccShort, kWhole>), grid, dim3(kAccThreads), 0, s, p);
         } else {
             hipLaunchKernelGGL(accept_softmax_partial<kAccChunk>, rows_grid, dim3(256), 0, s, p);
-            hipLaunchKernelGGL(accept_sample_kernel<kAccChunk>, grid, dim3(kAccThreads), 0, s, p);
+            if (accept_one_launch(batch, p.n_chunks)) {
+                hipLaunchKernelGGL((accept_sample_kernel<kAccChunk, kWhole>), grid, dim3(kAccThreads), 0, s, p);
+            } else {
+                hipLaunchKernelGGL((accept_sample_kernel<kAccChunk, kMasses>), grid, dim3(kAccThreads), 0, s, p);
+                hipLaunchKernelGGL((accept_sample_kernel<kAccChunk, kDraw>), dim3(1, batch), dim3(kAccThreads), 0, s, p);
+            }
         }
     }
     return launch_status();

@@ -31,3 +31,21 @@ def test_a_call_that_fails_has_launched_nothing(call, tmp_path):
     no_device, no_attribute, good = launches([(*call, 1, 0), (*call, 0, 1), call], tmp_path)
     assert no_device == (-4, []) and no_attribute == (-4, [])
     assert good[0] == 0 and len(good[1]) >= 1
+
+
+def accept(batch, gamma, vocab, **more):
+    return ("specvlm_accept", dict(target_logits=AT, draft_logits=AT, draft_tokens=AT, uniforms=AT, batch=batch, gamma=gamma, vocab=vocab,
+                                   temperature=1, n_accepted=AT, out_tokens=AT, workspace=AT, workspace_bytes=1 << 40, **more))
+
+
+# workgroups of the second sampling pass: as many as CUs are the last that count themselves in
+@pytest.mark.parametrize("batch,vocab,one", [(1, 152064, True), (13, 152064, True), (14, 152064, False), (256, 8192, True), (257, 8192, False),
+                                             (128, 8193, True), (129, 8193, False), (5000, 1024, True)])
+def test_sampling_counts_arrivals_only_up_to_one_workgroup_per_cu(batch, vocab, one, tmp_path):
+    [(status, got)] = launches([accept(batch, 2, vocab)], tmp_path)
+    chunk = 1024 if vocab <= 1024 else 8192
+    chunks = -(-vocab // chunk)
+    assert status == 0
+    assert [(name, grid) for name, grid, _, _ in got] == [(f"accept_softmax_partial<{chunk}>", (chunks, 5, batch))] + (
+        [(f"accept_sample_kernel<{chunk}, 0>", (chunks, batch, 1))] if one else
+        [(f"accept_sample_kernel<{chunk}, 1>", (chunks, batch, 1)), (f"accept_sample_kernel<{chunk}, 2>", (1, batch, 1))])
