@@ -363,6 +363,8 @@ int specvlm_tree_attn(
  * batch, on the run or on the workspace, and the final token is the inverse
  * CDF's up to the rounding of those sums (a uniform within about 1e-6 of a step
  * of the CDF may fall on either side of it).
+ * Sampling runs with the workspace that the query asks for less its last array
+ * (64 bytes per request and 8192 tokens) too, more slowly.
  * -------------------------------------------------------------------------- */
 size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab, int sampling);
 

@@ -37,7 +37,7 @@ struct AcceptParams {
     float* part_aux;          // [batch][rows][n_chunks]   sum exp (sampling) / argmax index bits (greedy)
     float* tok_logit;         // sampling: [batch][2 * gamma + 1] logit of the drafted token in target and draft rows
     float* chunk_mass;        // sampling: [batch][n_chunks] residual (or target) mass of row n per chunk
-    float* seg_mass;          // sampling: [batch][n_chunks][kAccSegs] the same per segment
+    float* seg_mass;          // sampling: [batch][n_chunks][kAccSegs] the same per segment, or null
     uint32_t* arrived;        // sampling: [batch] chunks that are done, cleared by pass 1
 };
 
@@ -337,7 +337,7 @@ void accept_sample_kernel(const AcceptParams p)
     __shared__ float s_top[kAccWaves];
     __shared__ int s_idx[kAccWaves];
     __shared__ float s_mass;
-    __shared__ int s_last;
+    __shared__ int s_last, s_own;
     const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = 2 * p.gamma + 1;
@@ -385,7 +385,7 @@ void accept_sample_kernel(const AcceptParams p)
         if (lane == 0) s_seg[wave] = mine;
     };
     float* const masses = p.chunk_mass + (int64_t)b * p.n_chunks;
-    float* const seg_masses = p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs;
+    float* const seg_masses = p.seg_mass ? p.seg_mass + (int64_t)b * p.n_chunks * kAccSegs : nullptr;
     float mass = 0.f;
     if (PART != kDraw) {
         segment_mass(chunk);
@@ -405,7 +405,7 @@ void accept_sample_kernel(const AcceptParams p)
         __syncthreads();
         mass = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
         if (!SHORT && wave == 0) {
-            if (lane < kAccSegs) store_device(seg_masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
+            if (seg_masses && lane < kAccSegs) store_device(seg_masses + (int64_t)chunk * kAccSegs + lane, s_seg[lane]);
             if (lane == 0) store_device(masses + chunk, mass);
             if (PART == kWhole && lane == 0)
                 s_last = __hip_atomic_fetch_add(p.arrived + b, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)p.n_chunks - 1u;
@@ -426,7 +426,7 @@ void accept_sample_kernel(const AcceptParams p)
         auto walk = [&](int c0, float& sum) __attribute__((always_inline)) {
             const int c = min(c0 + lane, p.n_chunks - 1);
             m = SHORT ? mass : load_device(masses + c);
-            if (!SHORT) {
+            if (!SHORT && seg_masses) {
 #pragma unroll
                 for (int i = 0; i < kAccSegs; ++i) seg[i] = load_device(seg_masses + (int64_t)c * kAccSegs + i);
             }
@@ -447,12 +447,12 @@ void accept_sample_kernel(const AcceptParams p)
             const uint64_t fits = __ballot(m > 0.f && before <= goal);
             const int l = fits ? 63 - __builtin_clzll(fits) : 0;
             if (fits) { own1 = c0 + l; pre1 = from_lane(before, l); }
-            if (!SHORT && (fits || c0 == 0)) {
+            if (!SHORT && seg_masses && (fits || c0 == 0)) {
 #pragma unroll
                 for (int i = 0; i < kAccSegs; ++i) own_seg[i] = from_lane(seg[i], l);
             }
         }
-        if (lane == 0) s_mass = W;
+        if (lane == 0) { s_mass = W; s_own = own1; }
     }
     __syncthreads();
     W = s_mass;
@@ -479,8 +479,12 @@ void accept_sample_kernel(const AcceptParams p)
         for (int x = 1; x < kAccWaves; ++x) argmax_merge(bv, bi, s_top[x], s_idx[x]);
         y = __builtin_amdgcn_readfirstlane(bi);
     } else {
+        if (!SHORT && !seg_masses) {                             // (nobody kept the owning chunk's segments)
+            segment_mass(s_own);
+            __syncthreads();
+        }
         if (wave != 0) return;
-        if (SHORT) {
+        if (SHORT || !seg_masses) {
 #pragma unroll
             for (int i = 0; i < kAccSegs; ++i) own_seg[i] = s_seg[i];
         }
@@ -588,17 +592,24 @@ static int accept_final_lanes(int rows, int n_chunks)
 
 using namespace specvlm;
 
+// Sampling: what a call cannot do without, and what it is asked to bring, with the segments' masses.  (Without them the owning
+// chunk's are summed again; the tokens are the same.)
+static size_t accept_least_bytes(int batch, int gamma, int vocab, int sampling)
+{
+    const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
+    size_t bytes = 2 * align256((size_t)batch * rows * accept_chunks(vocab) * sizeof(float));
+    if (sampling)       // the drafted tokens' logits (room for two of each), chunk masses of the rejected row, arrivals
+        bytes += align256((size_t)batch * rows * 2 * sizeof(float)) +
+                 align256((size_t)batch * accept_chunks(vocab) * sizeof(float)) +
+                 align256((size_t)batch * sizeof(uint32_t));
+    return bytes;
+}
+
 extern "C" size_t specvlm_accept_workspace_bytes(int batch, int gamma, int vocab, int sampling)
 {
     if (batch <= 0 || gamma < 0 || vocab < 1) return 0;
-    const size_t rows = sampling ? 2 * (size_t)gamma + 1 : (size_t)gamma + 1;
-    size_t bytes = 2 * align256((size_t)batch * rows * accept_chunks(vocab) * sizeof(float));
-    if (sampling)       // the drafted tokens' logits, chunk and segment masses of the rejected row, arrivals
-        bytes += align256((size_t)batch * rows * sizeof(float)) +
-                 align256((size_t)batch * accept_chunks(vocab) * sizeof(float)) +
-                 align256((size_t)batch * accept_chunks(vocab) * kAccSegs * sizeof(float)) +
-                 align256((size_t)batch * sizeof(uint32_t));
-    return bytes;
+    const size_t segs = sampling ? align256((size_t)batch * accept_chunks(vocab) * kAccSegs * sizeof(float)) : 0;
+    return accept_least_bytes(batch, gamma, vocab, sampling) + segs;
 }
 
 extern "C" int specvlm_accept(
@@ -617,7 +628,7 @@ extern "C" int specvlm_accept(
     if (batch == 0) return SPECVLM_OK;
     if (!target_logits || !n_accepted || !out_tokens || (gamma > 0 && !draft_tokens)) return SPECVLM_EINVAL;
     if (batch > 65535) return SPECVLM_EUNSUPPORTED;
-    const size_t need = specvlm_accept_workspace_bytes(batch, gamma, vocab, sampling);
+    const size_t need = accept_least_bytes(batch, gamma, vocab, sampling);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need) return SPECVLM_EWORKSPACE;
 
     AcceptParams p;
@@ -631,9 +642,9 @@ extern "C" int specvlm_accept(
     p.part_val = (float*)ws;
     p.part_aux = (float*)(ws + part_bytes);
     p.tok_logit = (float*)(ws + 2 * part_bytes);                 // (sampling only, from here on)
-    p.chunk_mass = (float*)((char*)p.tok_logit + align256((size_t)batch * rows * sizeof(float)));
-    p.seg_mass = (float*)((char*)p.chunk_mass + align256((size_t)batch * p.n_chunks * sizeof(float)));
-    p.arrived = (uint32_t*)((char*)p.seg_mass + align256((size_t)batch * p.n_chunks * kAccSegs * sizeof(float)));
+    p.chunk_mass = (float*)((char*)p.tok_logit + align256((size_t)batch * rows * 2 * sizeof(float)));
+    p.arrived = (uint32_t*)((char*)p.chunk_mass + align256((size_t)batch * p.n_chunks * sizeof(float)));
+    p.seg_mass = workspace_bytes >= specvlm_accept_workspace_bytes(batch, gamma, vocab, sampling) ? (float*)(ws + need) : nullptr;
     hipStream_t s = (hipStream_t)stream;
     if (!sampling) {
         hipLaunchKernelGGL(accept_argmax_partial, dim3(p.n_chunks, gamma + 1, batch), dim3(256), 0, s, p);

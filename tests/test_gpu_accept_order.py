@@ -8,6 +8,7 @@ import torch
 
 import sampling_order as order
 import test_gpu_accept as base
+from test_launches import least_bytes
 
 pytestmark = pytest.mark.gpu
 B = base.B
@@ -87,3 +88,18 @@ def test_tests_at_equality_and_alone_as_in_any_batch(B, vocab, gamma):
         assert (n[0], out[0].tolist()) == want[i], (i, n[0], out[0].tolist(), want[i])
     for count in (2, 4, 16, 70):
         rows(count)
+
+
+@pytest.mark.parametrize("vocab,gamma,count", [(700, 3, 4), (8192, 3, 9), (30000, 4, 9), (30000, 4, 70), (530000, 1, 6)])
+def test_workspace_without_the_segments_masses(B, vocab, gamma, count):
+    target, draft, tokens, u = requests(vocab, gamma, vocab + 7)
+    pick = [i % len(u) for i in range(count)]
+    args = [base.cuda(np.broadcast_to(t, (count, *t.shape))) for t in (target, tokens, draft)] + [base.cuda(u[pick])]
+    least = least_bytes(count, gamma, vocab)
+    buf = torch.full((least + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    n, out = B.accept(args[0], args[1], draft_logits=args[2], uniforms=args[3], temperature=order.TEMPERATURE, workspace=buf[:least])
+    torch.cuda.synchronize()
+    assert (buf[least:] == 0x5a).all()
+    want = [order.accept(target, draft, tokens, x) for x in u]
+    for i, a, b in zip(pick, n.tolist(), out.tolist()):
+        assert (a, b) == want[i], (i, a, b, want[i])

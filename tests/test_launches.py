@@ -49,3 +49,22 @@ def test_sampling_counts_arrivals_only_up_to_one_workgroup_per_cu(batch, vocab, 
     assert [(name, grid) for name, grid, _, _ in got] == [(f"accept_softmax_partial<{chunk}>", (chunks, 5, batch))] + (
         [(f"accept_sample_kernel<{chunk}, 0>", (chunks, batch, 1))] if one else
         [(f"accept_sample_kernel<{chunk}, 1>", (chunks, batch, 1)), (f"accept_sample_kernel<{chunk}, 2>", (1, batch, 1))])
+
+
+def least_bytes(batch, gamma, vocab):
+    """What sampling needs: two statistics a row and chunk, two numbers a row, one a chunk, one a request (each 256-byte aligned)."""
+    rows, chunks = 2 * gamma + 1, -(-vocab // 8192)
+    return sum((n * 4 + 255) // 256 * 256 for n in (batch * rows * chunks, batch * rows * chunks, batch * rows * 2, batch * chunks, batch))
+
+
+# (the query asks for the segments' masses as well: 16 numbers a chunk, without which the call is slower)
+@pytest.mark.parametrize("batch,gamma,vocab", [(1, 7, 152064), (20, 3, 152064), (3, 0, 1000), (2, 64, 8193)])
+def test_sampling_does_without_the_segments_masses(batch, gamma, vocab, tmp_path):
+    least = least_bytes(batch, gamma, vocab)
+    query = ("specvlm_accept_workspace_bytes", dict(batch=batch, gamma=gamma, vocab=vocab, sampling=1))
+    calls = [accept(batch, gamma, vocab) for _ in range(3)]
+    for (_, args), n in zip(calls, (1 << 40, least, least - 1)):
+        args["workspace_bytes"] = n
+    (asked, _), full, enough, short = launches([query, *calls], tmp_path)
+    assert asked == least + (batch * -(-vocab // 8192) * 64 + 255) // 256 * 256
+    assert full[0] == 0 and enough == full and short == (-3, [])
