@@ -114,7 +114,8 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()          # (an int: the argtypes make the pointer of it)
 
 
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# (None on a torch without GPU support, which can still import this module: a call there finds no tensor on a GPU)
+_raw_stream, _current_device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
 
 
 def _stream() -> int:

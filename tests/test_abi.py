@@ -114,3 +114,23 @@ def test_short_caches_keep_their_workspace(B):
         for n in (100, 700, 1000, 1300, 1535):
             assert all(B.decode_attn_workspace_bytes(b, 1, n, hq, hkv, d) <= s for b, s in zip((1, 2, 3, 4), sizes))
         assert sizes[0] <= min(sizes)
+
+
+def test_the_binding_imports_on_a_torch_without_gpu_support():
+    """... and a call fails at its first tensor, which cannot be on a GPU."""
+    program = """
+import torch
+for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+    delattr(torch._C, name)
+from paper_2508_16201_amd import binding as B
+for call in (lambda: B.score(torch.zeros(2, 4, 64).bfloat16(), torch.zeros(9, 1, 64).bfloat16(), 0, 7, 7, 0.1),
+             lambda: B.accept(torch.zeros(1, 2, 9), torch.zeros(1, 1, dtype=torch.int32), workspace=torch.zeros(4096, dtype=torch.uint8))):
+    try:
+        call()
+    except (ValueError, RuntimeError, AssertionError) as e:
+        print(type(e).__name__)
+"""
+    import subprocess
+    import sys
+    res = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and len(res.stdout.split()) == 2, res.stdout + res.stderr
