@@ -34,13 +34,18 @@ constexpr int kSelWaves = kSelThreads / kWave;
 // 6.43 / 6.75; two 5.68 / 6.48 / 7.66); with more than 32 the last digit, where equal scores meet, takes sixteen, in the
 // place of the first one's (65536 tokens, all equal: 43.9, with four 53.7, before 45.2).
 constexpr int kSelBits[3] = {11, 11, 10}, kSelShift[3] = {21, 10, 0};
-template <int E> struct SelHist {
+// PAIR: two workgroups share a CU's LDS (see select_pairs), where three histograms of eight copies leave room for one.  With up to 4
+// tokens a thread the last digit takes the first one's place; with more all three take one place in turn, cleared between them,
+// which costs less than copies do:  four copies in two places were 15.9 us for 257 requests of 12544 tokens, eight in one 14.6.
+template <int E, bool PAIR> struct SelHist {
     static constexpr int copies(int pass) { return E <= 4 ? 4 : pass < 2 ? 8 : E <= 32 ? 4 : 16; }
     static constexpr int stride(int pass) { return (1 << kSelBits[pass]) + (pass < 2 ? 4 : 2); }   // (copies of a digit lie in different banks)
     static constexpr int words(int pass) { return copies(pass) * stride(pass); }
-    static constexpr bool kReuse = E > 32;                       // the last pass takes the first one's place
-    static constexpr int at(int pass) { return pass == 0 || (pass == 2 && kReuse) ? 0 : at(pass - 1) + words(pass - 1); }
-    static constexpr int kWords = words(0) + words(1) + (kReuse ? 0 : words(2));
+    static constexpr bool kSingle = PAIR && E > 4;               // every pass takes the same place
+    static constexpr bool kReuse = !kSingle && (E > 32 || PAIR); // the last pass takes the first one's place
+    static constexpr int at(int pass) { return kSingle || pass == 0 || (pass == 2 && kReuse) ? 0 : at(pass - 1) + words(pass - 1); }
+    static constexpr int kWords = kSingle ? words(0) : words(0) + words(1) + (kReuse ? 0 : words(2));
+    static_assert(words(1) <= words(0));
     static_assert(!kReuse || words(2) <= words(0));
 };
 
@@ -145,13 +150,13 @@ __device__ __forceinline__ void block_excl_scan2(int a, int b, int* s_wave, int*
     *b_before = __builtin_amdgcn_readlane(wb, wave) + (excl >> 16);
 }
 
-template <int E>
+template <int E, bool PAIR>
 __global__ __launch_bounds__(kSelThreads)
 void select_kernel(const SelectParams p)
 {
     using mask_t = std::conditional_t<(E <= 32), uint32_t, uint64_t>;      // a bit per key of a thread
     static_assert(kSelWaves == 16, "the waves' sums are one DPP row");
-    using H = SelHist<E>;
+    using H = SelHist<E, PAIR>;
     __shared__ __align__(16) int s_hist[H::kWords];         // a histogram for each digit
     __shared__ int s_wave[kSelWaves];
     __shared__ int s_pick[3];
@@ -194,6 +199,8 @@ void select_kernel(const SelectParams p)
         constexpr int SHIFT = kSelShift[PASS], BITS = kSelBits[PASS], BINS = 1 << BITS, COPIES = H::copies(PASS);
         constexpr int PER = BINS / kSelThreads, STRIDE = H::stride(PASS);
         int* const hist = s_hist + H::at(PASS);
+        // (every thread has read the histogram of the digit before, in front of the last barrier)
+        if (PASS > 0 && H::kSingle) { clear(H::words(PASS)); __syncthreads(); }
         // A lane may add to any copy: the lanes of an instruction are spread over the copies, the waves start at
         // different ones.  No aggregation over the wave or over a thread's keys: both were measured and cost more
         // than the additions they save.
@@ -474,6 +481,18 @@ void top_p_kernel(const TopPParams p)
     }
 }
 
+// From one request per CU on two share one.  Us a call from a graph, a twentieth kept by score and as many by stride, one to a CU /
+// two:  257 requests of 1568 tokens 9.3 / 7.4, of 12544 17.5 / 14.6, of 32768 36.9 / 36.6;  512 of 4096 12.0 / 9.5, of 12544 20.9 /
+// 17.6;  1024 of 1568 18.9 / 13.7, of 12544 41.5 / 32.9.  (More than 32 tokens a thread take too many registers for two.)
+static bool select_pairs(int batch) { return batch > kNumCu; }
+
+template <int E>
+static void launch_select(const SelectParams& p, int batch, bool pair, hipStream_t s)
+{
+    if (pair) hipLaunchKernelGGL((select_kernel<E, true>), dim3(batch), dim3(kSelThreads), 0, s, p);
+    else      hipLaunchKernelGGL((select_kernel<E, false>), dim3(batch), dim3(kSelThreads), 0, s, p);
+}
+
 }  // namespace specvlm
 
 using namespace specvlm;
@@ -510,10 +529,11 @@ extern "C" int specvlm_select(
     p.keep_idx = keep_idx; p.from_topk = from_topk; p.status = status;
     hipStream_t s = (hipStream_t)stream;
     const int per = (max_n_video + kSelThreads - 1) / kSelThreads;
-    if (per <= 4)       hipLaunchKernelGGL(select_kernel<4>, dim3(batch), dim3(kSelThreads), 0, s, p);
-    else if (per <= 16) hipLaunchKernelGGL(select_kernel<16>, dim3(batch), dim3(kSelThreads), 0, s, p);
-    else if (per <= 32) hipLaunchKernelGGL(select_kernel<32>, dim3(batch), dim3(kSelThreads), 0, s, p);
-    else                hipLaunchKernelGGL(select_kernel<64>, dim3(batch), dim3(kSelThreads), 0, s, p);
+    const bool pair = select_pairs(batch);
+    if (per <= 4)       launch_select<4>(p, batch, pair, s);
+    else if (per <= 16) launch_select<16>(p, batch, pair, s);
+    else if (per <= 32) launch_select<32>(p, batch, pair, s);
+    else                hipLaunchKernelGGL((select_kernel<64, false>), dim3(batch), dim3(kSelThreads), 0, s, p);
     return launch_status();
 }
 

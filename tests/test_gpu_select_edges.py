@@ -1,7 +1,8 @@
 """GPU parity of specvlm_select and specvlm_top_p_count at the edges of what their kernels assume: tokens that fill the
 threads' runs exactly, by one less and one more, the first and last size of every kernel (4, 16, 32 and 64 tokens a
 thread), k and budget at both ends, keys that all coincide in one digit or in all, and a selection that reaches the NaN
-keys, which the slots past the last token share.  Exact against the oracle."""
+keys, which the slots past the last token share;  batches of as many requests as there are CUs and one more, from where two share a
+CU.  Exact against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -82,3 +83,20 @@ def test_select_one_digit(B, n, shift, bits):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(keep.cpu().numpy(), want, err_msg=f"n {n} k {k} digit at {shift}")
         np.testing.assert_array_equal(flags.cpu().numpy(), want_flags, err_msg=f"n {n} k {k} digit at {shift}")
+
+
+@pytest.mark.parametrize("batch,n", [(256, 1025), (257, 4), (257, 1025), (257, 4096), (300, 4097), (257, 16384), (257, 16385), (260, 32768), (257, 32769)])
+def test_select_of_many_requests(B, batch, n):
+    r = np.random.default_rng(batch + n)
+    lens = np.minimum(r.integers(1, n + 1, batch) + np.where(r.random(batch) < 0.2, n, 0), n)
+    lens[0] = n
+    parts = [scores(("spread", "equal", "tight", "nan")[b % 4], v, b) for b, v in enumerate(lens)]
+    budget = np.array([r.integers(0, v + 1) for v in lens], np.int32)
+    k = np.array([r.integers(0, x + 1) for x in budget], np.int32)
+    cu = [torch.from_numpy(np.concatenate([[0], np.cumsum(x)]).astype(np.int32)).cuda() for x in (lens, budget)]
+    keep, flags = B.select(torch.from_numpy(np.concatenate(parts)).cuda(), torch.from_numpy(k).cuda(), torch.from_numpy(budget).cuda(),
+                           int(budget.sum()), cu_video=cu[0], cu_keep=cu[1], max_n_video=n)
+    torch.cuda.synchronize()
+    want = [oracle.select(s, int(a), int(c)) for s, a, c in zip(parts, k, budget)]
+    np.testing.assert_array_equal(keep.cpu().numpy(), np.concatenate([w[0] for w in want]))
+    np.testing.assert_array_equal(flags.cpu().numpy(), np.concatenate([w[1] for w in want]))

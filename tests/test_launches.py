@@ -68,3 +68,11 @@ def test_sampling_does_without_the_segments_masses(batch, gamma, vocab, tmp_path
     (asked, _), full, enough, short = launches([query, *calls], tmp_path)
     assert asked == least + (batch * -(-vocab // 8192) * 64 + 255) // 256 * 256
     assert full[0] == 0 and enough == full and short == (-3, [])
+
+
+@pytest.mark.parametrize("batch,n,tokens,pair", [(1, 12544, 16, False), (256, 4096, 4, False), (257, 4096, 4, True), (257, 4097, 16, True),
+                                                 (257, 16385, 32, True), (1000, 32769, 64, False)])
+def test_selections_share_a_cu_where_the_requests_are_more_than_the_cus(batch, n, tokens, pair, tmp_path):
+    args = dict(scores=AT, cu_video=AT, k_top=AT, keep_budget=AT, cu_keep=AT, batch=batch, max_n_video=n, total_keep=batch, keep_idx=AT)
+    [(status, got)] = launches([("specvlm_select", args)], tmp_path)
+    assert status == 0 and [l[:3] for l in got] == [(f"select_kernel<{tokens}, {'true' if pair else 'false'}>", (batch, 1, 1), (1024, 1, 1))]
