@@ -1,9 +1,9 @@
-"""GPU parity of specvlm_score where its merges change shape.  Key splits: one block of rows is cut into one split per
-64 keys, so 512 / 513 keys are the last launch with one lane per row and the first with eight, 4096 keys have the most
-splits a row can have, 4097 half as many; with prefix rows, hidden text keys and keyless splits.  Bounds: those of
-every score test.  Partial columns: up to sixteen of them (layers x kv heads x row splits) one thread sums a column, with
-eight or sixteen loads, then eight threads; one layer of 5, 8, 9 and 16 heads with one row split each, 2 and 17 layers of one head, columns that do not fill the last
-workgroup."""
+"""GPU parity of specvlm_score where its merges change shape.  Key counts on both sides of 8 and 64 times 64, with prefix rows
+and hidden text keys: one layer of so few rows takes the two-launch form, which cuts them into up to 32 key ranges (the sweeps'
+splits of such counts: test_gpu_score_sweeps.py).  Partial columns of the sweeps: up to sixteen of them (layers x kv heads x row
+splits) one thread sums a column, with eight or sixteen loads, then eight threads; one layer of 9 and 16 heads (5 and 8 take
+the two-launch form) with one row split each, 2 and 17 layers of one head, columns that do not fill the last workgroup.  Bounds: those of
+every score test."""
 import pytest
 
 import test_gpu_prune as base

@@ -2,6 +2,7 @@
 launched nothing.  No GPU is touched."""
 import pytest
 
+import test_gpu_score_sweeps as sweeps
 from launches import AT, launches
 
 
@@ -76,3 +77,37 @@ def test_selections_share_a_cu_where_the_requests_are_more_than_the_cus(batch, n
     args = dict(scores=AT, cu_video=AT, k_top=AT, keep_budget=AT, cu_keep=AT, batch=batch, max_n_video=n, total_keep=batch, keep_idx=AT)
     [(status, got)] = launches([("specvlm_select", args)], tmp_path)
     assert status == 0 and [l[:3] for l in got] == [(f"select_kernel<{tokens}, {'true' if pair else 'false'}>", (batch, 1, 1), (1024, 1, 1))]
+
+
+def test_the_sweeps_shapes_take_the_sweeps(tmp_path):
+    def call(layers, V, L, P, hq, hkv, d, mode, text_pos0=None):
+        more = dict(n_keys=P + V + L, video_start=P, norm_mode=mode, text_pos0=P + V if text_pos0 is None else text_pos0)
+        return score(hq, hkv, d, L, V, layers, **more)
+
+    got = launches([call(2, *shape) for shape, _ in sweeps.KEY_SPLITS], tmp_path)
+    for (shape, splits), (status, ls) in zip(sweeps.KEY_SPLITS, got):
+        d, grid = shape[5], (2 * splits + 7) // 8 * 8                 # two layers, a multiple of the XCDs
+        assert status == 0 and [l[0] for l in ls[:3]] == [f"score_sweep_kernel<{d}, 0>", f"score_lse_kernel<{1 if splits <= 8 else 8}>",
+                                                          f"score_sweep_kernel<{d}, 1>"], (shape, ls)
+        assert ls[0][1] == (grid, 1, 1), (shape, ls)
+    got = launches([call(*shape) for shape, _ in sweeps.PARTIAL_COLUMNS], tmp_path)
+    for (shape, columns), (status, ls) in zip(sweeps.PARTIAL_COLUMNS, got):
+        blocks = (shape[1] + 255) // 256
+        assert status == 0 and ls[2][1] == ((blocks * columns + 7) // 8 * 8, 1, 1), (shape, ls)
+        assert ls[3][0] == f"score_final_kernel<{'1, 8' if columns <= 8 else '1, 16' if columns <= 16 else '8, 16'}>", (shape, ls)
+    got = launches([call(None, V, L, 0, hq, hkv, d, mode, pos0) for V, L, pos0, hq, hkv, d in sweeps.INSIDE for mode in (0, 1)] +
+                   [call(None, 2200, 70, 0, 10, 2, 64, 0)], tmp_path)
+    assert all(status == 0 and [l[0].split("<")[0] for l in ls] == ["score_sweep_kernel", "score_lse_kernel", "score_sweep_kernel",
+                                                                    "score_final_kernel"] for status, ls in got)
+
+
+@pytest.mark.parametrize("hq,hkv,d,L,V,lse,small", [(4, 1, 64, 64, 1568, False, True), (8, 1, 64, 64, 17344, False, True), (8, 1, 64, 64, 17345, False, False),
+                                                    (9, 1, 64, 64, 500, False, False), (4, 4, 64, 65, 700, False, True), (8, 1, 128, 64, 300, True, True),
+                                                    (8, 2, 128, 64, 300, False, False), (1, 1, 64, 513, 300, True, False)])
+def test_one_small_layer_takes_the_two_launch_form(hq, hkv, d, L, V, lse, small, tmp_path):
+    [(status, ls)] = launches([score(hq, hkv, d, L, V, row_lse=AT if lse else None)], tmp_path)
+    assert status == 0
+    if small:
+        assert [l[0] for l in ls] == [f"score_small_rows_kernel<{d}>"] * (not lse) + [f"score_small_cols_kernel<{d}>"]
+    else:
+        assert ls[-2][0] == f"score_sweep_kernel<{d}, 1>"
