@@ -52,7 +52,7 @@ def parse():
                     help="hand the score call each row's softmax normaliser (as a prefill attention would "
                          "have saved it), so scoring is one sweep per layer")
     ap.add_argument("--score-per-layer", action="store_true",
-                    help="score with one specvlm_score call per verifier layer (4 launches each) instead of one "
+                    help="score with one specvlm_score call per verifier layer (at most 4 launches each) instead of one "
                          "specvlm_score_layers call for all layers (4 launches in all)")
     ap.add_argument("--frames", type=int, default=0, help="override the frame count (with --attn-only)")
     ap.add_argument("--attn-only", action="store_true",

@@ -128,7 +128,8 @@ int specvlm_score(
  * Everything else is as for specvlm_score, including the batch.  One set of four
  * launches serves all layers (a caller that keeps the text queries of every
  * layer until the prefill has ended pays for 4 launches instead of 4 n_layers,
- * and every launch has n_layers times the workgroups to fill the chip with).
+ * and every launch has n_layers times the workgroups to fill the chip with; one
+ * layer of one request with few rows, alone in its call, takes two).
  * n_layers = 0 only applies beta.  n_layers * batch <= 65535.
  * The workspace query takes n_layers as well; the result is deterministic (the
  * parts of all layers and kv heads are added in a fixed order that the shape

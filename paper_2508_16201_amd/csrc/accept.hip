@@ -50,11 +50,6 @@ __device__ __forceinline__ void argmax_merge(float& bv, int& bi, float v, int i)
 // Wave-wide reductions over lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2 and ^ 1, in this order: swaps of half waves and of rows, then DPP in
 // rows of 16 (rotations by 8 and 4, which reach the partner once the higher bits no longer matter).  The same bits
 // as six shuffles, each of which is an LDS round trip.
-template <int CTRL> __device__ __forceinline__ float row_move(float x)
-{
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
-}
-
 template <typename OP> __device__ __forceinline__ float wave_reduce(float x, OP op)
 {
     auto half = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);

@@ -33,6 +33,13 @@ __device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c)
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
+// Another lane's value by DPP, inside the lane's row of 16 (0xB1: lane ^ 1, 0x4E: lane ^ 2, 0x141: lane ^ 7, 0x124 and 0x128: 4 and 8
+// lanes on, around the row; 0x00, 0x55, 0xAA, 0xFF: lane 0 to 3 of the four): a VALU move, where a shuffle goes through LDS.
+template <int CTRL> __device__ __forceinline__ float row_move(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+
 // Workgroups are dealt to the XCDs round-robin by linear id.  Map the hardware
 // id to a logical id so that consecutive logical ids share an XCD (and its L2).
 // `padded` is the launch size, a multiple of kNumXcd; ids >= the real count exit.

@@ -488,7 +488,7 @@ void score_sweep_kernel(const ScoreParams p_launch)
 // lse2[g][row] from the pass-A partials, or from the caller's natural-log values.  Bound: its one round trip.  LANES
 // lanes share a row, eight splits each: one lane per row where there are at most eight splits (or none: the caller's
 // values), else eight lanes, which cover the kMaxSplitsA a row can have.  One lane walking 26 splits in four dependent
-// trips was 5.4 us of the 19 of a small layer (64 queries over 1632 keys, 4 heads); now 3.2.
+// trips was 5.4 us of the 19 of 64 queries over 1632 keys with 4 heads (which have kernels of their own now), eight lanes 3.2.
 template <int LANES>
 __global__ __launch_bounds__(256)
 void score_lse_kernel(const ScoreParams p_launch)
@@ -528,7 +528,7 @@ void score_lse_kernel(const ScoreParams p_launch)
 // The partial columns of all layers, kv heads and row splits, summed in a fixed order.  Bound: round trips.  One thread per
 // column walked 640 partials of the 80-layer shape eight at a time, in 49 workgroups: 55 us; with RUNS = 8 threads per
 // column, each with an equal run of the partials (in the order layer, head and split) and sixteen loads in flight: 9 us.
-// Up to sixteen partials are one trip for one thread, which then needs no exchange: eight loads up to eight (a small layer:
+// Up to sixteen partials are one trip for one thread, which then needs no exchange: eight loads up to eight (one block of columns:
 // 2.5 us, with sixteen 2.7, with eight threads 2.8), else sixteen (the call with given normalisers, sixteen partials of 33000
 // columns: 24.7 us, with eight threads 25.5; fourteen of 800: 9.7, 10.2).
 constexpr int kFinalRuns = 8, kFinalLoads = 16;
@@ -679,12 +679,6 @@ void score_small_rows_kernel(const ScoreSmallParams p)
     if (c == 0) p.part[(tile * kScoreTile + wave * 16 + r) * p.splits + split] = float2{m, l};
 }
 
-// Another lane's value by DPP (0xB1: lane ^ 1, 0x4E: lane ^ 2, 0x141: lane ^ 7): a VALU move, where a shuffle goes through LDS.
-template <int CTRL> __device__ __forceinline__ float lane_move(float x)
-{
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
-}
-
 template <int D>
 __global__ __launch_bounds__(512)
 void score_small_cols_kernel(const ScoreSmallParams p)
@@ -728,11 +722,11 @@ void score_small_cols_kernel(const ScoreSmallParams p)
                 float m = kNegBig, l = 0.f;
 #pragma unroll
                 for (int u = 0; u < kSmallSplits / 8; ++u) if (8 * u < p.splits) m = fmaxf(m, ml[x][u].x);
-                m = fmaxf(m, lane_move<0xB1>(m)); m = fmaxf(m, lane_move<0x4E>(m)); m = fmaxf(m, lane_move<0x141>(m));
+                m = fmaxf(m, row_move<0xB1>(m)); m = fmaxf(m, row_move<0x4E>(m)); m = fmaxf(m, row_move<0x141>(m));
 #pragma unroll
                 for (int u = 0; u < kSmallSplits / 8; ++u)
                     if (8 * u < p.splits) l += sub + 8 * u < p.splits ? ml[x][u].y * fast_exp2(ml[x][u].x - m) : 0.f;
-                l += lane_move<0xB1>(l); l += lane_move<0x4E>(l); l += lane_move<0x141>(l);
+                l += row_move<0xB1>(l); l += row_move<0x4E>(l); l += row_move<0x141>(l);
                 const int tt = t + x, h = (tt * p.tile_mul) >> 16, i = (tt - h * p.tiles_per_head) * kScoreTile + row_in;
                 if (sub == 0 && tt < p.n_tiles) s_lse[tt * kScoreTile + row_in] = i < p.n_text && l > 0.f ? m + fast_log2(l) : INFINITY;
             }
