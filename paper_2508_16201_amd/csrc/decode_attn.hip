@@ -656,9 +656,10 @@ void attn_split_kernel(const AttnParams p)
 // at most one more rounding of the size the bf16 output carries anyway, and it halves the bytes that
 // the two kernels exchange.
 // One workgroup per (kv head, query row); thread (grp, col) folds the splits grp, grp + GROUPS, ...
-// for 4 output columns.  Every load of the first PRE splits per thread is issued up front, so the
-// kernel costs one memory round trip; each group folds its splits against its own maximum and a
-// single barrier later group 0 combines the GROUPS partial results.
+// for 4 output columns.  PRE covers all of a thread's splits (launch_merge picks it) and every load is issued up front, so
+// the kernel costs one memory round trip; each group folds its splits against its own maximum and a single barrier later
+// group 0 combines the GROUPS partial results.  (Splits beyond a thread's first three were a round trip each: 192 splits of
+// 30000 keys, 4/1 heads of size 64, 11.9 us a layer, now 8.45;  96 splits of 12000, 14/2 heads, 8.4, now 6.95.)
 // Twelve groups (two loads per thread at the usual 24 splits per head) measured best: 16.3 us per 72B
 // layer against 16.7 with 8 groups, 16.35 with 16, 16.85 with 24 and 17.5 with 32; several rows per
 // workgroup are slower as well (16.9 with two, 17.2 with four).
@@ -690,12 +691,14 @@ void attn_merge_kernel(const AttnParams p)
     const int tid = threadIdx.x;
     const int grp = tid / TPR, col = (tid % TPR) * 4;
 
-    // (past the last split a group reads its first one again and leaves it out: no branch between the loads; with a branch around
-    // each and 64-bit addresses, 14/2 heads of size 64, 5000 keys were 7.2 us a layer instead of 6.7, 12000 keys 9.5 instead of 8.9)
+    // (past the last split a group reads its first one again and leaves it out: no branch between the loads;  with a branch around
+    // each and 64-bit addresses, 14/2 heads of size 64, 5000 keys were 7.2 us a layer instead of 6.7, 12000 keys 9.5 instead of 8.9.
+    // Beyond the first eight a branch between fours, the same for the whole workgroup.)
     float2 ml_i[PRE];
     bf16x4 raw[PRE];
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
+        if (i >= 8 && GROUPS * (i & ~3) >= live) break;
         const uint32_t at = (uint32_t)((grp + GROUPS * i < live ? grp + GROUPS * i : min(grp, live - 1)) * p.rows_pad);
         ml_i[i] = *reinterpret_cast<const float2*>(ml_base + at * 8u);       // the same address across the group: one transaction
         raw[i] = *reinterpret_cast<const bf16x4*>(o_base + (at * (uint32_t)D + (uint32_t)col) * 2u);
@@ -718,20 +721,10 @@ void attn_merge_kernel(const AttnParams p)
     float l_loc = 0.f;
 #pragma unroll
     for (int i = 0; i < PRE; ++i) {
+        if (i >= 8 && GROUPS * (i & ~3) >= live) break;
         const float w = fast_exp2(m_i[i] - m_ref);           // 0 for an absent or empty split
         acc += w * ov[i];
         l_loc += w * l_i[i];
-    }
-    for (int s = grp + GROUPS * PRE; s < live; s += GROUPS) {   // more splits than the prefetch covers
-        const int64_t slot = slot0 + (int64_t)s * p.rows_pad;
-        const float m_s = p.part_ml[slot * 2], l_s = p.part_ml[slot * 2 + 1];
-        const floatx4 o_s = __builtin_convertvector(*reinterpret_cast<const bf16x4*>(p.part_o + slot * D + col), floatx4);
-        const float m_new = fmaxf(m_loc, m_s);
-        const float r_new = (m_new == -INFINITY) ? 0.f : m_new;
-        const float f_old = fast_exp2(m_loc - r_new), f_s = fast_exp2(m_s - r_new);
-        acc = acc * f_old + f_s * o_s;
-        l_loc = l_loc * f_old + f_s * l_s;
-        m_loc = m_new;
     }
     *reinterpret_cast<floatx4*>(&s_acc[grp][col]) = acc;
     if (col == 0) { s_m[grp] = m_loc; s_l[grp] = l_loc; }
@@ -1180,14 +1173,28 @@ static int choose_splits(int batch, int kv_len, int n_kv_heads, int n_rgroups, i
 //     10 heads:  2560 [3000], 8 splits 18.3 / 19.0;  2 heads:  2048 [3000] 7 % slower to 3 % faster, 3072 0 to 9 % faster.
 // Where the kv heads are a multiple of the XCDs a head's partials lie in the L2 of the XCD that merges them; elsewhere more
 // rows are needed to hide the way.  With more splits the second trip costs more (16 splits 18.7 / 20.1).
-// The kernel of one row per workgroup reaches its first 36 splits, which it requests together, by 32-bit byte offsets.  Where those do
-// not get that far (480000 rows of size 128: 64 queries of a kv head's 7500 q heads) a group per row, with 64 bits, does it.
-constexpr int kMergeRowPieces = 8, kMergeGroups = 12, kMergeAhead = 3;
+// The kernel of one row per workgroup reaches its splits by 32-bit byte offsets.  Where those do not get that far (480000 rows of
+// size 128 in 36 splits: 64 queries of a kv head's 7500 q heads) a group per row, with 64 bits, does it.
+constexpr int kMergeRowPieces = 8, kMergeGroups = 12;
 static bool attn_merges_by_row(int n_kv_heads, int64_t total_rows, int rows_pad, int head_dim, int num_splits)
 {
-    const int ahead = num_splits < kMergeGroups * kMergeAhead ? num_splits : kMergeGroups * kMergeAhead;
-    if ((int64_t)ahead * rows_pad * head_dim * 2 > 0xffffffffll) return true;
+    if ((int64_t)num_splits * rows_pad * head_dim * 2 > 0xffffffffll) return true;
     return num_splits <= kMergeRowPieces && total_rows * head_dim >= (n_kv_heads % kNumXcd == 0 ? 3 : 7) * kNumCu * 128ll;
+}
+
+// A thread's splits, all requested together: the fewest of these sizes that cover them.  (A split that is not there is a load
+// of a line that is, yet eight where four do cost 0.2 us: 48 splits of 6000 keys, 28/4 heads 8.95 us a layer instead of 8.75.)
+template <int D>
+static int launch_merge(const AttnParams& p, dim3 grid, hipStream_t stream)
+{
+    constexpr int THREADS = kMergeGroups * (D / 4), MOST = (kMaxSplits + kMergeGroups - 1) / kMergeGroups;
+    const int each = (p.num_splits + kMergeGroups - 1) / kMergeGroups;
+    if (each <= 3)       hipLaunchKernelGGL((attn_merge_kernel<D, 3, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 4)  hipLaunchKernelGGL((attn_merge_kernel<D, 4, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 8)  hipLaunchKernelGGL((attn_merge_kernel<D, 8, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 16) hipLaunchKernelGGL((attn_merge_kernel<D, 16, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    else                 hipLaunchKernelGGL((attn_merge_kernel<D, MOST, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    return launch_status();
 }
 
 template <int D, int MB, int KS, int TK, int NS, int NLD, bool STREAM>
@@ -1401,9 +1408,7 @@ static int attn_impl(
         rc = launch_status();
     } else if (p.num_splits > 1) {
         dim3 grid(rows * batch * n_kv_heads);
-        if (head_dim == 128) hipLaunchKernelGGL((attn_merge_kernel<128, kMergeAhead, kMergeGroups * 32>), grid, dim3(kMergeGroups * 32), 0, s, p);
-        else                 hipLaunchKernelGGL((attn_merge_kernel<64, kMergeAhead, kMergeGroups * 16>), grid, dim3(kMergeGroups * 16), 0, s, p);
-        rc = launch_status();
+        rc = head_dim == 128 ? launch_merge<128>(p, grid, s) : launch_merge<64>(p, grid, s);
     }
     return rc;
 }

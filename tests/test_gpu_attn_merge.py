@@ -34,6 +34,13 @@ def test_uniform_splits(B, q_len, kv_len, hq, hkv, d, splits):
     np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
 
 
+# twelve groups of threads: a thread's splits are three, four, eight, sixteen and 22 at most, by the launch
+@pytest.mark.parametrize("splits", [36, 37, 48, 49, 96, 97, 192, 193, 255, 256])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 64), (6, 2, 128)])
+def test_uniform_splits_up_to_the_most(B, splits, hq, hkv, d):
+    test_uniform_splits(B, 2, 128 * splits - 1, hq, hkv, d, splits)
+
+
 def test_ragged_batch_with_named_splits(B):
     lens, q_lens, hq, hkv, d = [1500, 3, 257, 1024], [6, 3, 2, 6], 64, 4, 128
     q, k, v = [], [], []
