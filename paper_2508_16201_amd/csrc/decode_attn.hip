@@ -88,7 +88,6 @@ struct AttnParams {
     const uint64_t* block_mask;  // [sum q_len] tree masks of the block's queries, or null (chain)
     int balanced;            // batch mode: balanced pieces (see attn_balance) instead of uniform splits
     int max_wg;              // workgroups launched in balanced mode
-    int tile_keys;           // keys per tile of the split kernel that runs (the unit of balanced mode)
     int32_t* seg_table;      // balanced mode: per (request, head) {first partial slot, pieces}, written by workgroup 0
 };
 
@@ -1268,10 +1267,10 @@ template <int D>
 static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
 {
 
-    // (key-split waves, tile keys, ring depth, loader waves) per row-block count; the ring
-    // holds NS * 2 * TK * D * 2 bytes of LDS.  One row block (the single-query decode beyond the short
-    // caches) keeps its four waves, loading and computing: on a small cache the four extra waves cost more
-    // at workgroup start-up than they save (6.7 against 6.4 us per layer at 1511 keys).
+    // (key-split waves, tile keys, ring depth, loader waves) per row-block count; the ring holds NS * 2 * TK * D * 2 bytes of
+    // LDS.  Four stages at head size 64, whose tiles are half as large (us a layer, three / four):  14/2 heads, 100000 keys,
+    // 4 queries 15.05 / 14.4, 6 queries 15.55 / 15.0, 8 queries 16.1 / 15.8;  4/1 heads, 6 queries 11.8 / 11.5, but 30000 keys 9.13 / 9.2.
+    constexpr int NS = D == 64 ? 4 : 3;
     switch (mb) {
         case 1:
             // Splits of at most 128 keys: one chunk of 32 keys for each of four waves, results for the merge (a single split
@@ -1284,10 +1283,18 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
                 if (p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced && !loses)
                     return launch_short<D, kShortWaves, 1, D>(p, stream);
             }
+            // Splits of 128 keys and more are bound by the bytes that a CU has in flight: two waves compute and two load, as with more
+            // row blocks, three or four stages deep.  Shorter ones are bound by the launch, and four waves that do both take one tile in
+            // fewer steps.  Us a layer, four waves / roles:  size 128:  28/4 heads 3000 keys (splits of 125) 7.6 / 7.95, 6000 (128)
+            // 8.55 / 8.35, 8000 10.3 / 9.55, 30000 17.05 / 15.35, 120000 48.1 / 42.4;  64/8 heads 6000 10.45 / 10.0, 12000 14.55 / 13.35,
+            // 30000 26.9 / 23.85, 120000 87.6 / 77.3;  size 64:  14/2 heads 30000 9.65 / 8.8, 120000 18.9 / 15.45;  4/1 heads 30000
+            // (157) 8.45 / 8.4, 120000 13.1 / 11.4.  Balanced pieces, which are cut by tiles:  size 128, 8 requests of up to 3000 keys, 40/8
+            // heads 18.2 / 17.0, 28/4 15.4 / 14.9, 5 of 20000 the same;  size 64, 4/1 heads 12.6 / 13.7.
+            if (p.balanced ? D == 128 : p.split_keys >= 128) return launch_attn<D, 1, 2, 64, NS, 2>(p, stream);
             return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
-        case 2: return launch_attn<D, 2, 2, 64, 3, 4>(p, stream);
-        case 3: return launch_attn<D, 3, 2, 64, 3, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)
-        case 4: return launch_attn<D, 4, 2, 64, 3, 4>(p, stream);
+        case 2: return launch_attn<D, 2, 2, 64, NS, 4>(p, stream);
+        case 3: return launch_attn<D, 3, 2, 64, NS, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)
+        case 4: return launch_attn<D, 4, 2, 64, NS, 4>(p, stream);   // (four loaders: 64 rows, 12000 keys, 64/8 heads 15.2, with two 15.8)
     }
     return SPECVLM_EUNSUPPORTED;
 }
@@ -1364,7 +1371,6 @@ static int attn_impl(
     p.inv_heads = reciprocal(n_kv_heads); p.inv_all_heads = reciprocal(batch * n_kv_heads); p.inv_group = reciprocal(group);
     p.balanced = attn_is_balanced(batch, num_splits, n_kv_heads, rows) ? 1 : 0;
     p.max_wg = kNumCu;
-    p.tile_keys = mb == 1 ? 128 : 64;                 // TK of the launch shape chosen below
     p.num_splits = p.balanced ? 2 : choose_splits(batch, kv_len, n_kv_heads, n_rgroups, num_splits);
     p.split_keys = (kv_len + p.num_splits - 1) / p.num_splits;
     p.rows_pad = n_rgroups * mb * 16;

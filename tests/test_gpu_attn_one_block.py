@@ -1,0 +1,45 @@
+"""GPU parity of one block of query rows where its launch changes: splits of 127 and of 128 keys, and with fewer, as many
+and more tiles than the ring is deep; balanced pieces of it.  Bounds: those of every attention test."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev_bf16, host_f64, rnd_bits, assert_attn_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2508_16201_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kv_len,splits", [(254, 2), (255, 2), (256, 2), (257, 2), (385, 2), (511, 2), (513, 2), (640, 2), (641, 2),
+                                           (1283, 2), (128, 1), (129, 1), (1000, 1), (1537, 4)])
+def test_splits_of_one_row_block(B, kv_len, splits, d):
+    q_len, hq, hkv = 3, 10, 2                                     # 15 rows a kv head
+    q, k, v = (rnd_bits((n, h, d), 9000 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    scale = 1.0 / np.sqrt(d)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"kv{kv_len} d{d} splits {splits}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_balanced_pieces_of_one_row_block(B, d):
+    lens, hq, hkv = [3000, 1, 63, 65, 2049, 128], 32, 8
+    q, k, v = [], [], []
+    for i, n in enumerate(lens):
+        q.append(rnd_bits((1, hq, d), 9400 + i)); k.append(rnd_bits((n, hkv, d), 9500 + i)); v.append(rnd_bits((n, hkv, d), 9600 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.1,
+                        cu_q=cu([1] * len(lens)), cu_kv=cu(lens), max_q_len=1, max_kv_len=3000)
+    torch.cuda.synchronize()
+    for i in range(len(lens)):
+        assert_attn_close(out[i:i + 1], oracle.decode_attn(q[i], k[i], v[i], 0.1)[0], f"request {i}")
