@@ -2,6 +2,7 @@
 launched nothing.  No GPU is touched."""
 import pytest
 
+import test_gpu_score_packed as packed
 import test_gpu_score_sweeps as sweeps
 from launches import AT, launches
 
@@ -111,3 +112,22 @@ def test_one_small_layer_takes_the_two_launch_form(hq, hkv, d, L, V, lse, small,
         assert [l[0] for l in ls] == [f"score_small_rows_kernel<{d}>"] * (not lse) + [f"score_small_cols_kernel<{d}>"]
     else:
         assert ls[-2][0] == f"score_sweep_kernel<{d}, 1>"
+
+
+def test_the_packed_shapes_have_fewer_rows_in_the_workspace_of_before(tmp_path):
+    def call(layers, V, L, P, hq, hkv, d, mode):
+        return score(hq, hkv, d, L, V, layers, n_keys=P + V + L, video_start=P, norm_mode=mode, text_pos0=P + V)
+
+    shapes = [(s, n) for s, n in packed.PACKED] + [((1, V, L, 0, hq, hkv, d, 0), 1) for V, L, _, hq, hkv, d in packed.INSIDE]
+    for (shape, blocks), (status, ls) in zip(shapes, launches([call(*s) for s, _ in shapes], tmp_path)):
+        assert status == 0 and ls[0][0] == f"score_sweep_kernel<{shape[6]}, 0>", (shape, ls)
+        rows_a_block = 256 if ls[1][0] == "score_lse_kernel<1>" else 32
+        assert ls[1][1] == (blocks * 256 // rows_a_block, shape[5], shape[0]), (shape, ls)
+    # what the call asks for is what 64 rows a tile took: a layer's (max, sum) pairs, normalisers and columns, by the splits it had
+    layers, V, L, hq, hkv, d = 24, 12544, 85, 64, 8, 128
+    query = ("specvlm_score_layers_workspace_bytes", dict(n_layers=layers, batch=1, n_text=L, n_keys=V + L, n_video=V, n_q_heads=hq, n_kv_heads=hkv,
+                                                          head_dim=d))
+    least = layers * hkv * 4 * (1024 * 2 + 1024 + 12544)
+    (asked, _), enough, short = launches([query, score(hq, hkv, d, L, V, layers, workspace_bytes=least),
+                                          score(hq, hkv, d, L, V, layers, workspace_bytes=least - 1)], tmp_path)
+    assert asked == least and enough[0] == 0 and short == (-3, [])
