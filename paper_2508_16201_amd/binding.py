@@ -4,6 +4,10 @@ Every function has the name of the C entry point it calls (``include/specvlm.h``
 and takes torch tensors that live on the GPU; torch provides device memory and
 the current stream, nothing else.  There is no CPU fallback: if the HIP
 library is missing or a call fails, an exception is raised.
+
+The plain calls of the short functions are marshalled by ``_calls.so``
+(``csrc/calls.cpp``); what it does not take goes through the code here, which
+is also what decides what is refused.
 """
 from __future__ import annotations
 
@@ -18,6 +22,10 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # SPECVLM_LIB names another build of the same library (the host-sanitized one the CPU tests make)
 LIB_PATH = os.environ.get("SPECVLM_LIB") or os.path.join(_HERE, "libspecvlm.so")
 _lib = None
+_calls = None
+# the C functions that _calls calls, in the order its connect() takes their addresses in
+_CALLED = ("specvlm_accept", "specvlm_accept_workspace_bytes", "specvlm_score", "specvlm_score_workspace_bytes", "specvlm_select",
+           "specvlm_top_p_count", "specvlm_gather_kv", "specvlm_decode_attn", "specvlm_tree_attn", "specvlm_decode_attn_workspace_bytes")
 
 EXPORTS = (
     "specvlm_status_string", "specvlm_version",
@@ -96,6 +104,29 @@ def lib() -> C.CDLL:
             getattr(l, name).restype = C.c_int
         _lib = l
     return _lib
+
+
+class _NoCalls:
+    """Stands in for _calls on a torch without GPU support, where no tensor is one that it takes."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_calls():
+    """The native marshalling, connected to the library; the first call of a short function asks for it."""
+    global _calls
+    if _raw_stream is None:
+        _calls = _NoCalls()
+    else:
+        try:
+            from . import _calls as native
+        except ImportError as e:
+            raise FileNotFoundError(f"{os.path.join(_HERE, '_calls.so')} is missing or does not fit this torch: build it with "
+                                    "`python -m paper_2508_16201_amd.build`") from e
+        native.connect(*(C.cast(getattr(lib(), name), C.c_void_p).value for name in _CALLED))
+        _calls = native
+    return _calls
 
 
 def status_string(status: int) -> str:
@@ -244,6 +275,13 @@ def score(q_text: torch.Tensor, k_cache: torch.Tensor, video_start: int, n_video
     offsets [batch+1] on the device (host sequences are uploaded); n_video is then ignored and
     text_pos0 = -1 places every request's text queries on its last keys.  With device tensors the
     maxima over the batch and the total number of video tokens must be given."""
+    if cu_text is None:
+        got = (_calls or _load_calls()).score(q_text, k_cache, video_start, n_video, text_pos0, softmax_scale, norm_mode, row_lse, beta, scores,
+                                              workspace)
+        if got is not None:
+            if type(got) is int:
+                _check("specvlm_score", got)
+            return got
     n_text, hq, d = q_text.shape
     n_keys, hkv, _ = k_cache.shape
     if cu_text is None:
@@ -278,6 +316,12 @@ def select(scores: torch.Tensor, k_top: torch.Tensor, keep_budget: torch.Tensor,
            max_n_video: Optional[int] = None, want_flags: bool = True, want_status: bool = False,
            keep_idx: Optional[torch.Tensor] = None):
     """scores fp32 [sum V_b]; k_top/keep_budget device int32 [batch] -> keep_idx int32 [total_keep]."""
+    if not want_status:
+        got = (_calls or _load_calls()).select(scores, k_top, keep_budget, total_keep, cu_video, cu_keep, max_n_video, want_flags, keep_idx)
+        if got is not None:
+            if type(got) is int:
+                _check("specvlm_select", got)
+            return got
     batch = k_top.numel()
     if max_n_video is None:
         if cu_video is not None:
@@ -300,6 +344,11 @@ def top_p_count(scores: torch.Tensor, lam: float, *, cu_video: Optional[torch.Te
                 max_n_video: Optional[int] = None, max_count: Optional[torch.Tensor] = None,
                 count: Optional[torch.Tensor] = None) -> torch.Tensor:
     """scores fp32 [sum V_b] -> count int32 [batch]: Eq. 6's retention size per request."""
+    got = (_calls or _load_calls()).top_p_count(scores, lam, cu_video, max_n_video, max_count, count)
+    if got is not None:
+        if type(got) is int:
+            _check("specvlm_top_p_count", got)
+        return got
     batch = 1 if cu_video is None else cu_video.numel() - 1
     if max_n_video is None:
         if cu_video is not None:
@@ -323,6 +372,12 @@ def gather_kv(k_src: torch.Tensor, v_src: Optional[torch.Tensor], video_start: i
 
     A batch: requests concatenated along the token axis, cu_keys / cu_video / cu_keep device int32
     [batch+1]; n_video is then the total over the batch."""
+    if not want_status:
+        got = (_calls or _load_calls()).gather_kv(k_src, v_src, video_start, n_video, keep_idx, k_dst, v_dst, cu_keys, cu_video, cu_keep)
+        if got is not None:
+            if type(got) is int:
+                _check("specvlm_gather_kv", got)
+            return got
     if k_src.dim() != 4 or k_src.stride(3) != 1:
         raise ValueError("expected [layers, tokens, heads, d] with contiguous d")
     n_layers, n_keys, hkv, d = k_src.shape
@@ -360,6 +415,12 @@ def decode_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, softmax_scale
                 out: Optional[torch.Tensor] = None, want_lse: bool = False, num_splits: int = 0,
                 workspace: Optional[torch.Tensor] = None, ancestor_mask: Optional[torch.Tensor] = None):
     """q [sum q_len,H_q,d], k/v [sum kv_len,H_kv,d] bf16 views -> out like q (and lse fp32)."""
+    got = (_calls or _load_calls()).decode_attn(q, k, v, softmax_scale, cu_q, cu_kv, max_q_len, max_kv_len, out, want_lse, num_splits, workspace,
+                                                ancestor_mask)
+    if got is not None:
+        if type(got) is int:
+            _check("specvlm_decode_attn" if ancestor_mask is None else "specvlm_tree_attn", got)
+        return got
     tq, hq, d = q.shape
     tk, hkv, _ = k.shape
     if cu_q is None:
@@ -435,6 +496,11 @@ def accept(target_logits: torch.Tensor, draft_tokens: torch.Tensor, *,
            temperature: float = 1.0, workspace: Optional[torch.Tensor] = None,
            n_accepted: Optional[torch.Tensor] = None, out_tokens: Optional[torch.Tensor] = None):
     """target_logits fp32 [batch, gamma+1, vocab] -> (n_accepted int32 [batch], out_tokens int32 [batch, gamma+1])."""
+    got = (_calls or _load_calls()).accept(target_logits, draft_tokens, draft_logits, uniforms, temperature, workspace, n_accepted, out_tokens)
+    if got is not None:
+        if type(got) is int:
+            _check("specvlm_accept", got)
+        return got
     batch, g1, vocab = target_logits.shape
     gamma = g1 - 1
     if n_accepted is None:

@@ -1,5 +1,7 @@
 """Build step: compile the HIP sources in ``csrc/`` into ``libspecvlm.so`` for
-gfx950 with hipcc (cross-compiles without a GPU)."""
+gfx950 with hipcc (cross-compiles without a GPU), and the binding's native
+marshalling (``csrc/calls.cpp``, host code against torch's headers) into
+``_calls.so``."""
 from __future__ import annotations
 
 import glob
@@ -10,6 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libspecvlm.so")
+CALLS = os.path.join(HERE, "_calls.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -33,12 +36,7 @@ HOSTSAN_FLAGS = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsa
                  "-Xarch_host", "-fno-sanitize-recover=undefined", "-Xarch_host", "-shared-libsan"]
 
 
-def build(verbose: bool = False, host_sanitizers: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    out_lib = LIB_HOSTSAN if host_sanitizers else LIB
-    flags = [f if f != "-O3" else "-O1" for f in HIPCC_FLAGS] + HOSTSAN_FLAGS if host_sanitizers else HIPCC_FLAGS
-    cmd = [hipcc, *flags, "-I", os.path.join(ROOT, "include"),
-           "-I", os.path.join(HERE, "csrc"), "-o", out_lib, *sources()]
+def _run(cmd, verbose: bool, what: str) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -46,9 +44,33 @@ def build(verbose: bool = False, host_sanitizers: bool = False) -> str:
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
         sys.stderr.write(out + "\n")
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError(what + " failed")
     if verbose and out.strip():
         print(out)
+
+
+def build_calls(verbose: bool = False) -> str:
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    includes = [os.path.join(ROOT, "include"), *include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+          *(f"-I{i}" for i in includes), "-o", CALLS, os.path.join(HERE, "csrc", "calls.cpp"), f"-L{libs}", "-ltorch_python",
+          "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose, "g++")
+    return CALLS
+
+
+def build(verbose: bool = False, host_sanitizers: bool = False) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    out_lib = LIB_HOSTSAN if host_sanitizers else LIB
+    flags = [f if f != "-O3" else "-O1" for f in HIPCC_FLAGS] + HOSTSAN_FLAGS if host_sanitizers else HIPCC_FLAGS
+    cmd = [hipcc, *flags, "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(HERE, "csrc"), "-o", out_lib, *sources()]
+    _run(cmd, verbose, "hipcc")
+    if not host_sanitizers:
+        build_calls(verbose)
     return out_lib
 
 
