@@ -881,11 +881,11 @@ void attn_short_kernel(const AttnParams p)
     constexpr int KL = kChunkKeys / KPL, VL = kChunkKeys / VPL;   // loads per chunk
     constexpr int K_BYTES = kChunkKeys * D * 2;
     constexpr int WAVE_LDS = K_BYTES + kChunkKeys * COLS * 2;
-    static_assert(16 * COLS * 4 <= WAVE_LDS, "a wave's result takes the place of its buffers");
+    static_assert(16 * COLS * 4 + NW * 16 <= WAVE_LDS, "a wave's result takes the place of its buffers");
     // LDS: a private part per wave (its [row][column] fp32 result afterwards), then the waves' maxima and sums
     extern __shared__ __align__(16) unsigned char smem[];
-    float (*s_m)[16] = reinterpret_cast<float (*)[16]>(smem + NW * WAVE_LDS);
-    float (*s_l)[16] = s_m + NW;
+    float (*s_m)[NW] = reinterpret_cast<float (*)[NW]>(smem + NW * WAVE_LDS);
+    float (*s_l)[NW] = s_m + 16;
 
     if (DIRECT && (int)blockIdx.x >= p.n_main) { attn_prefetch_rows<D, NW * kWave>(p, blockIdx.x); return; }
     const int lane = threadIdx.x & 63;
@@ -1034,39 +1034,63 @@ void attn_short_kernel(const AttnParams p)
     // ---- the waves meet: lane (r, c) holds columns 16j + 4c .. 16j + 4c + 3 of row r ----
     // 16-byte piece q of a row goes to place q ^ r: the 16 rows of a store or a load fall on different banks
     constexpr int PIECES = COLS / 4;
+    constexpr int SKEW = DIRECT ? 16 : 0;            // (the waves' results start on different banks where lanes of one load go over the waves)
 #pragma unroll
     for (int j = 0; j < DJ; ++j)
-        reinterpret_cast<floatx4*>(k_lds)[r * PIECES + ((4 * j + c) ^ (r & (PIECES - 1)))] = o_acc[j];
-    if (c == 0) { s_m[wave][r] = m; s_l[wave][r] = l; }
+        reinterpret_cast<floatx4*>(k_lds + wave * SKEW)[r * PIECES + ((4 * j + c) ^ (r & (PIECES - 1)))] = o_acc[j];
+    if (c == 0) { s_m[r][wave] = m; s_l[r][wave] = l; }
+    if constexpr (DIRECT) {
+        // a lane per wave and piece: the waves' results are summed by DPP over NW lanes.  With a thread per piece, which is one wave's
+        // walk over all the others' results, it was the launch's last 0.5 us (us a layer, before / now:  14/2 heads of size 64, 1511 keys
+        // 6.30 / 6.11, 600 4.36 / 4.28;  4/1 heads, 1511 6.12 / 5.77;  size 128, 28/4 heads, 700 keys 6.38 / 6.25, 64/8, 1000 7.22 / 6.99)
+        static_assert(16 * PIECES == kWave && (NW == 8 || NW == 16));
+        const int w = threadIdx.x % NW, orow = threadIdx.x / NW / PIECES, piece = threadIdx.x / NW % PIECES, grow = rb * 16 + orow;
+        const QuotRem out_at = divide(grow, p.group, p.inv_group);
+        const int to = out_at.q, ho = g * p.group + out_at.r;
+        __syncthreads();
+        if (grow >= n_rows) return;
+        const float m_w = s_m[orow][w], l_w = s_l[orow][w];
+        floatx4 tot = reinterpret_cast<const floatx4*>(smem + w * (WAVE_LDS + SKEW))[orow * PIECES + (piece ^ (orow & (PIECES - 1)))];
+        const auto over_waves = [](float x, auto op) {
+            x = op(x, row_move<0xB1>(x));
+            x = op(x, row_move<0x4E>(x));
+            x = op(x, row_move<0x141>(x));
+            if constexpr (NW == 16) x = op(x, row_move<0x128>(x));
+            return x;
+        };
+        const auto sum = [](float a, float b) { return a + b; };
+        const float m_all = over_waves(m_w, [](float a, float b) { return fmaxf(a, b); });
+        const float f = fast_exp2(m_w - ((m_all == -INFINITY) ? 0.f : m_all));           // 0 for a wave without keys
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[i] = over_waves(f * tot[i], sum);
+        const float l_all = over_waves(f * l_w, sum);
+        if (w != 0) return;
+        tot *= 1.f / l_all;
+        *reinterpret_cast<bf16x4*>(p.out + (int64_t)(q0 + to) * p.q_tok + (int64_t)ho * p.q_head + part * COLS + 4 * piece) =
+            __builtin_convertvector(tot, bf16x4);
+        if (p.lse && part == 0 && piece == 0)
+            p.lse[(int64_t)(q0 + to) * p.n_q_heads + ho] = (m_all + fast_log2(l_all)) * kLn2;
+        return;
+    }
     __syncthreads();
     for (int e = threadIdx.x; e < 16 * PIECES; e += NW * kWave) {
         const int orow = e / PIECES, piece = e % PIECES, grow = rb * 16 + orow;
         if (grow >= n_rows) continue;
         float m_all = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][orow]);
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, s_m[orow][w]);
         const float ref = (m_all == -INFINITY) ? 0.f : m_all;
         floatx4 tot = {0.f, 0.f, 0.f, 0.f};
         float l_all = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float f = fast_exp2(s_m[w][orow] - ref);           // 0 for a wave without keys
+            const float f = fast_exp2(s_m[orow][w] - ref);           // 0 for a wave without keys
             tot += f * reinterpret_cast<const floatx4*>(smem + w * WAVE_LDS)[orow * PIECES + (piece ^ (orow & (PIECES - 1)))];
-            l_all += f * s_l[w][orow];
+            l_all += f * s_l[orow][w];
         }
-        if (DIRECT) {
-            const QuotRem out_at = divide(grow, p.group, p.inv_group);
-            const int to = out_at.q, ho = g * p.group + out_at.r;
-            tot *= 1.f / l_all;
-            *reinterpret_cast<bf16x4*>(p.out + (int64_t)(q0 + to) * p.q_tok + (int64_t)ho * p.q_head + part * COLS + 4 * piece) =
-                __builtin_convertvector(tot, bf16x4);
-            if (p.lse && part == 0 && piece == 0)
-                p.lse[(int64_t)(q0 + to) * p.n_q_heads + ho] = (m_all + fast_log2(l_all)) * kLn2;
-        } else {
-            const int64_t slot = ((int64_t)(b * p.n_kv_heads + g) * p.num_splits + part) * p.rows_pad + grow;
-            *reinterpret_cast<bf16x4*>(p.part_o + slot * D + 4 * piece) = __builtin_convertvector(tot, bf16x4);
-            if (piece == 0) { p.part_ml[slot * 2] = m_all; p.part_ml[slot * 2 + 1] = l_all; }
-        }
+        const int64_t slot = ((int64_t)(b * p.n_kv_heads + g) * p.num_splits + part) * p.rows_pad + grow;
+        *reinterpret_cast<bf16x4*>(p.part_o + slot * D + 4 * piece) = __builtin_convertvector(tot, bf16x4);
+        if (piece == 0) { p.part_ml[slot * 2] = m_all; p.part_ml[slot * 2 + 1] = l_all; }
     }
 }
 
