@@ -672,7 +672,7 @@ void attn_merge_kernel(const AttnParams p)
     constexpr int TPR = D / 4;                       // threads that cover one row of D columns
     constexpr int GROUPS = THREADS / TPR;            // split groups working in parallel
     __shared__ float s_m[GROUPS], s_l[GROUPS];
-    __shared__ __align__(16) float s_acc[GROUPS][D];
+    __shared__ __align__(16) float s_acc[GROUPS][D + 4];           // (the groups' rows start on different banks)
     // (request, kv head) fastest: workgroup id modulo the XCD count follows the kv head, as in the split kernel
     const int nbh = p.batch * p.n_kv_heads;
     const QuotRem at = divide(blockIdx.x, nbh, p.inv_all_heads), head = divide(at.r, p.n_kv_heads, p.inv_heads);
@@ -728,25 +728,40 @@ void attn_merge_kernel(const AttnParams p)
     *reinterpret_cast<floatx4*>(&s_acc[grp][col]) = acc;
     if (col == 0) { s_m[grp] = m_loc; s_l[grp] = l_loc; }
     __syncthreads();
-    if (grp != 0) return;
-    float m = s_m[0];
+    // four lanes a piece of four columns: three groups each, then by DPP.  (Group 0 alone walking over all
+    // twelve was 0.1 to 0.25 us longer, eight lanes were no faster and, where a CU has several workgroups, slower:  us a layer, before / four / eight
+    // lanes:  14/2 heads of size 64, 3000 keys 6.22 / 6.07 / 6.08;  40/8 heads, 12806 keys, 6 queries 14.37 / 14.20 / 14.29;  64/8 heads 14.98 / 14.94 /
+    // 15.0, a tree of 20 nodes over 3000 keys 12.25 / 12.17 / 12.33.)
+    constexpr int LANES = 4, EACH = GROUPS / LANES;
+    static_assert(GROUPS % LANES == 0 && TPR * LANES <= THREADS);
+    if (tid >= TPR * LANES) return;
+    const int w = tid % LANES, out_col = tid / LANES * 4;
+    float m_g[EACH];
 #pragma unroll
-    for (int gg = 1; gg < GROUPS; ++gg) m = fmaxf(m, s_m[gg]);
+    for (int i = 0; i < EACH; ++i) m_g[i] = s_m[w + LANES * i];
+    float m = m_g[0];
+#pragma unroll
+    for (int i = 1; i < EACH; ++i) m = fmaxf(m, m_g[i]);
+    m = fmaxf(m, row_move<0xB1>(m)); m = fmaxf(m, row_move<0x4E>(m));
     m_ref = (m == -INFINITY) ? 0.f : m;
     floatx4 tot = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll
-    for (int gg = 0; gg < GROUPS; ++gg) {
-        const float f = fast_exp2(s_m[gg] - m_ref);
-        tot += f * *reinterpret_cast<const floatx4*>(&s_acc[gg][col]);
-        l += f * s_l[gg];
+    for (int i = 0; i < EACH; ++i) {
+        const float f = fast_exp2(m_g[i] - m_ref);               // 0 for a group without splits
+        tot += f * *reinterpret_cast<const floatx4*>(&s_acc[w + LANES * i][out_col]);
+        l += f * s_l[w + LANES * i];
     }
+    l += row_move<0xB1>(l); l += row_move<0x4E>(l);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { tot[i] += row_move<0xB1>(tot[i]); tot[i] += row_move<0x4E>(tot[i]); }
+    if (w != 0) return;
     tot *= 1.f / l;
     const QuotRem out_at = divide(row, p.group, p.inv_group);
     const int t = out_at.q, h = g * p.group + out_at.r;
-    __bf16* op = p.out + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + col;
+    __bf16* op = p.out + (int64_t)(q0 + t) * p.q_tok + (int64_t)h * p.q_head + out_col;
     *reinterpret_cast<bf16x4*>(op) = __builtin_convertvector(tot, bf16x4);
-    if (p.lse && col == 0)
+    if (p.lse && out_col == 0)
         p.lse[(int64_t)(q0 + t) * p.n_q_heads + h] = (m + fast_log2(l)) * kLn2;
 }
 
