@@ -530,23 +530,22 @@ void attn_split_kernel(const AttnParams p)
         float* sm_m = reinterpret_cast<float*>(smem);            // [NW][16]
         float* sm_l = sm_m + NW * 16;                            // [NW][16]
         float* sm_o = sm_l + NW * 16;                            // [NW][16][LDS_STRIDE]
-        if (c == 0 && computes) sm_m[wave * 16 + r] = m_run;
-        __syncthreads();
-        float m_all = m_run;
-#pragma unroll
-        for (int kx = 0; kx < KS; ++kx) m_all = fmaxf(m_all, sm_m[(kx * MB + mb) * 16 + r]);
-        const float f = fast_exp2(m_run - ((m_all == -INFINITY) ? 0.f : m_all));
-        if (c == 0 && computes) sm_l[wave * 16 + r] = l_run * f;
         if (computes) {
+            if (c == 0) { sm_m[wave * 16 + r] = m_run; sm_l[wave * 16 + r] = l_run; }
             float* buf = sm_o + (wave * 16 + r) * LDS_STRIDE + 4 * c;
 #pragma unroll
-            for (int j = 0; j < DJ; ++j) *reinterpret_cast<floatx4*>(buf + 16 * j) = o_acc[j] * f;
+            for (int j = 0; j < DJ; ++j) *reinterpret_cast<floatx4*>(buf + 16 * j) = o_acc[j];
         }
         __syncthreads();
         if (!computes) return;
-        float l_all = 0.f;
+        // (brought to one reference here and not before they are written: that was a barrier and a round trip more:  us a layer, before / now:
+        // 64/8 heads, 12806 keys, 6 queries 14.97 / 14.71, one 13.79 / 13.63, 12 nodes 16.86 / 16.58;  14/2 heads of size 64, 12806 keys 8.87 / 8.66)
+        float m_x[KS], m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-        for (int kx = 0; kx < KS; ++kx) l_all += sm_l[(kx * MB + mb) * 16 + r];
+        for (int kx = 0; kx < KS; ++kx) { m_x[kx] = sm_m[(kx * MB + mb) * 16 + r]; m_all = fmaxf(m_all, m_x[kx]); }
+        const float m_ref = (m_all == -INFINITY) ? 0.f : m_all;
+#pragma unroll
+        for (int kx = 0; kx < KS; ++kx) { m_x[kx] = fast_exp2(m_x[kx] - m_ref); l_all += m_x[kx] * sm_l[(kx * MB + mb) * 16 + r]; }
         const int col0 = ks * SLICE + c * CPL;
         floatx4 acc[CPL / 4];
 #pragma unroll
@@ -555,7 +554,7 @@ void attn_split_kernel(const AttnParams p)
         for (int kx = 0; kx < KS; ++kx) {
             const float* buf = sm_o + ((kx * MB + mb) * 16 + r) * LDS_STRIDE + col0;
 #pragma unroll
-            for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] += *reinterpret_cast<const floatx4*>(buf + 4 * qd);
+            for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] += m_x[kx] * *reinterpret_cast<const floatx4*>(buf + 4 * qd);
         }
         if (direct) {
             if (row >= n_rows) return;
