@@ -655,8 +655,8 @@ void attn_split_kernel(const AttnParams p)
 // the two kernels exchange.
 // One workgroup per (kv head, query row); thread (grp, col) folds the splits grp, grp + GROUPS, ...
 // for 4 output columns.  PRE covers all of a thread's splits (launch_merge picks it) and every load is issued up front, so
-// the kernel costs one memory round trip; each group folds its splits against its own maximum and a single barrier later
-// group 0 combines the GROUPS partial results.  (Splits beyond a thread's first three were a round trip each: 192 splits of
+// the kernel costs one memory round trip; each group folds its splits against its own maximum and behind a single barrier
+// four lanes a piece combine the GROUPS partial results.  (Splits beyond a thread's first three were a round trip each: 192 splits of
 // 30000 keys, 4/1 heads of size 64, 11.9 us a layer, now 8.45;  96 splits of 12000, 14/2 heads, 8.4, now 6.95.)
 // Twelve groups (two loads per thread at the usual 24 splits per head) measured best: 16.3 us per 72B
 // layer against 16.7 with 8 groups, 16.35 with 16, 16.85 with 24 and 17.5 with 32; several rows per
