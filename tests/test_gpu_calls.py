@@ -1,13 +1,21 @@
 """The binding's native marshalling (csrc/calls.cpp) against its general code: the same call through both returns the same tensors, the
 caller's own where it gave some, and what one refuses the other refuses with the same words.  On the CPU: what it leaves to the general
 code."""
+import os
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2508_16201_amd import binding as B
+from paper_2508_16201_amd import binding as B, build
 
 gpu = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if not (os.path.exists(B.LIB_PATH) and os.path.exists(build.CALLS)):
+        build.build()
 
 
 def both(monkeypatch, call):
