@@ -106,8 +106,8 @@ __device__ __forceinline__ void attn_fetch_params(const AttnParams& p)
                      "s"(p.balanced), "s"(p.rows_pad));
 }
 
-// Tiles of request b in balanced mode; a request with nothing to do (no queries, or fewer keys
-// than queries) has none.
+// Tiles of request b in balanced mode, of the unit's size (one or more of the kernel's own tiles); a request with nothing to
+// do (no queries, or fewer keys than queries) has none.
 __device__ __forceinline__ int attn_request_tiles(const AttnParams& p, int b, int tile_keys)
 {
     const int ql = p.cu_q[b + 1] - p.cu_q[b], kvl = p.cu_kv[b + 1] - p.cu_kv[b];
@@ -598,13 +598,19 @@ void attn_split_kernel(const AttnParams p)
         return;
     }
 
-    // Balanced pieces for a batch.  The unit of work is one tile of one request (all kv heads); the
+    // Balanced pieces for a batch.  The unit of work is UNIT keys of one request (all kv heads); the
     // units are numbered request-major, then tile, and group j -- workgroups j*H .. j*H+H-1, one per
     // kv head -- takes the contiguous run [j*T/G, (j+1)*T/G).  A run that crosses from one request
     // into the next is cut into pieces there; piece (group j, request b) of head g owns partial slot
     // (j + b)*H + g, unique because from one piece to the next exactly one of j and b grows.  Every
     // workgroup derives the same numbers from the request lengths, as the merge kernel does.
-    const AttnBalance bal = attn_balance(p, TK);
+    // One row block is dealt by 128 keys whatever the tile: of 64 keys a piece is little work for what it costs to start and to merge, and with
+    // few requests a row has twice as many pieces, eight to a trip of the merge (us a layer, units of 64 / 128 keys, size 128:  2 requests of 2500
+    // keys, 28/4 heads 12.9 / 11.6;  4 of up to 6000, 7/1 heads 19.2 / 14.9;  8 of up to 600, 40/8 heads 13.1 / 10.8;  16 of 600, 12/3 heads 14.5 /
+    // 13.0;  where a group has three to six units of 64 keys the finer ones are up to 7 % faster: 2 of up to 6000, 40/8 heads 16.2 / 16.8).
+    constexpr int UNIT = MB == 1 ? 128 : TK;
+    static_assert(UNIT % TK == 0, "a unit is whole tiles");
+    const AttnBalance bal = attn_balance(p, UNIT);
     const int H = p.n_kv_heads;
     const int w = blockIdx.x;
     if (w == 0) {
@@ -614,8 +620,8 @@ void attn_split_kernel(const AttnParams p)
         for (int seg = threadIdx.x; seg < p.batch * H; seg += (MB * KS + NLD) * kWave) {
             const int sb = seg / H, sg = seg % H;
             int64_t first = 0;
-            for (int bb = 0; bb < sb; ++bb) first += attn_request_tiles(p, bb, TK);
-            const int tiles = attn_request_tiles(p, sb, TK);
+            for (int bb = 0; bb < sb; ++bb) first += attn_request_tiles(p, bb, UNIT);
+            const int tiles = attn_request_tiles(p, sb, UNIT);
             int j_first = 0, live = 0;
             if (tiles > 0) {
                 j_first = (int)(((first + 1) * bal.n_groups - 1) / bal.n_units);
@@ -633,16 +639,16 @@ void attn_split_kernel(const AttnParams p)
     int b = 0;
     int64_t base = 0;                                   // first unit of request b
     while (x < x_end) {
-        int tiles = attn_request_tiles(p, b, TK);
+        int tiles = attn_request_tiles(p, b, UNIT);
         while (x >= base + tiles) {
             base += tiles;
             ++b;
-            tiles = attn_request_tiles(p, b, TK);
+            tiles = attn_request_tiles(p, b, UNIT);
         }
         const int t = (int)(x - base);
         const int n = (int)min((int64_t)(tiles - t), x_end - x);
         const int kvl = p.cu_kv[b + 1] - p.cu_kv[b];
-        piece(b, g, 0, t * TK, min(kvl, (t + n) * TK), (int64_t)((j + b) * H + g) * p.rows_pad, false);
+        piece(b, g, 0, t * UNIT, min(kvl, (t + n) * UNIT), (int64_t)((j + b) * H + g) * p.rows_pad, false);
         x += n;
         __syncthreads();                                // the next piece reuses the ring and the exchange buffer
     }

@@ -43,3 +43,20 @@ def test_balanced_pieces_of_one_row_block(B, d):
     torch.cuda.synchronize()
     for i in range(len(lens)):
         assert_attn_close(out[i:i + 1], oracle.decode_attn(q[i], k[i], v[i], 0.1)[0], f"request {i}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv,pieces", [([2500, 2500], 28, 4, [20, 20]), ([1300, 1, 129], 40, 8, [11, 1, 2]), ([20000, 300], 12, 3, [84, 2])])
+def test_balanced_pieces_are_of_128_keys_and_more(B, lens, hq, hkv, pieces, d):
+    """Fewer units of 128 keys than groups of workgroups are a piece each; the last case has 160 for 85 groups."""
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    n = len(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(97)
+    k = torch.randn((sum(lens), hkv, d), generator=g, device="cuda").bfloat16()
+    work = B.new_workspace(B.decode_attn_workspace_bytes(n, 1, max(lens), hq, hkv, d)).zero_()
+    B.decode_attn(k[:n].repeat(1, hq // hkv, 1), k, k, 0.1, cu_q=cu([1] * n), cu_kv=cu(lens), max_q_len=1, max_kv_len=max(lens), workspace=work)
+    slots = (256 + n * hkv) * 16                                       # partial outputs, maxima and sums, then the table of pieces
+    at = (slots * d * 2 + 255) // 256 * 256 + (slots * 8 + 255) // 256 * 256
+    table = work[at:at + n * hkv * 8].view(torch.int32).view(n, hkv, 2).cpu()
+    assert table[:, :, 1].tolist() == [[x] * hkv for x in pieces]
