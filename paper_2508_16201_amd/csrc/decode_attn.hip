@@ -1298,13 +1298,35 @@ static int launch_attn_direct(const AttnParams& p, int head_dim, int chunks, hip
 // only push the split partials (which the merge re-reads) and other reusable data out of the L2.
 // Smaller caches (a draft's pruned cache, re-read at every decode step) stay cacheable.
 constexpr int64_t kStreamBytes = 8ll << 20;
+static bool attn_streams(const AttnParams& p, int head_dim) { return 4ll * p.batch * p.n_kv_heads * p.kv_len * head_dim >= kStreamBytes; }
 
 template <int D, int MB, int KS, int TK, int NS, int NLD>
 static int launch_attn(const AttnParams& p, hipStream_t stream)
 {
-    const int64_t kv_bytes = 2ll * p.batch * p.n_kv_heads * (int64_t)p.kv_len * D * 2;
-    return kv_bytes >= kStreamBytes ? launch_attn_s<D, MB, KS, TK, NS, NLD, true>(p, stream)
+    return attn_streams(p, D) ? launch_attn_s<D, MB, KS, TK, NS, NLD, true>(p, stream)
                                     : launch_attn_s<D, MB, KS, TK, NS, NLD, false>(p, stream);
+}
+
+// One block of query rows: two waves that compute and two that load, or four that do both.  The first keep more bytes in flight and win
+// where the memory is what splits of 128 keys and more wait for (us a layer, four waves / roles):  size 128:  28/4 heads 6000 keys (splits of
+// 128) 8.55 / 8.35, 8000 10.3 / 9.55, 30000 17.05 / 15.35, 120000 48.1 / 42.4;  64/8 heads 6000 10.45 / 10.0, 12000 14.55 / 13.35, 30000 26.9 / 23.85,
+// 120000 87.6 / 77.3;  size 64:  14/2 heads 30000 9.65 / 8.6, 120000 18.9 / 15.45;  balanced pieces of size 128, 16 requests of up to 2500 keys, 40/8
+// heads 26.3 / 25.1, 28/4 of up to 6000, 4 of them 18.0 / 17.3.  Left out is what loses:
+//   splits of fewer keys (28/4 heads, 3000 keys, splits of 125 7.6 / 7.95) and caches below the streamed size, which stay near and whose launches are
+//     bound by their start and their steps:  size 128, 7/1 heads, 1024 keys in 8 splits 6.45 / 7.0, 4096 in 32 7.15 / 7.5 (but 16384 in 32, 8 MB, 11.65 /
+//     10.5);  size 64, 4/1 heads, 3072 in 8 6.7 / 7.2, 14/2 heads 12288 in 32 7.5 / 7.8 (16384, 8 MB, 9.2 / 8.7);
+//   more workgroups of size 64 than CUs in one round, where two of the four waves' workgroups share a CU:  8/4 heads, 65 requests of 1500 keys 25.4 / 26.5,
+//     8 of 3200 in 16 splits 10.5 / 10.7 (in several rounds a third workgroup shares it: 16/8 heads, 40 of 1280 in 8 35.7 / 30.3, 65 of 600 23.5 / 21.1);
+//   splits of 256 keys, eight heads and more, in two rounds and more: the four waves have all of a split in flight at once, and lines of 512 KB strides:
+//     64/8 heads, 32768 keys in 128 34.3 / 35.8, 65 requests of 256 23.6 / 24.0 (splits of 250 34.4 / 33.2 and of 272 38.6 / 35.5);
+//   balanced pieces of size 64 (4/1 heads 12.6 / 13.7).
+static bool attn_has_loaders(const AttnParams& p, int head_dim)
+{
+    if (!attn_streams(p, head_dim)) return false;
+    if (p.balanced) return head_dim == 128;
+    if (p.split_keys < 128) return false;
+    if (head_dim == 64) return p.n_work <= kNumCu || p.n_work > 2 * kNumCu;
+    return !(p.split_keys == 256 && p.n_kv_heads % kNumXcd == 0 && p.n_work >= 2 * kNumCu);
 }
 
 template <int D>
@@ -1327,14 +1349,7 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
                 if (p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced && !loses)
                     return launch_short<D, kShortWaves, 1, D>(p, stream);
             }
-            // Splits of 128 keys and more are bound by the bytes that a CU has in flight: two waves compute and two load, as with more
-            // row blocks, three or four stages deep.  Shorter ones are bound by the launch, and four waves that do both take one tile in
-            // fewer steps.  Us a layer, four waves / roles:  size 128:  28/4 heads 3000 keys (splits of 125) 7.6 / 7.95, 6000 (128)
-            // 8.55 / 8.35, 8000 10.3 / 9.55, 30000 17.05 / 15.35, 120000 48.1 / 42.4;  64/8 heads 6000 10.45 / 10.0, 12000 14.55 / 13.35,
-            // 30000 26.9 / 23.85, 120000 87.6 / 77.3;  size 64:  14/2 heads 30000 9.65 / 8.8, 120000 18.9 / 15.45;  4/1 heads 30000
-            // (157) 8.45 / 8.4, 120000 13.1 / 11.4.  Balanced pieces, which are cut by tiles:  size 128, 8 requests of up to 3000 keys, 40/8
-            // heads 18.2 / 17.0, 28/4 15.4 / 14.9, 5 of 20000 the same;  size 64, 4/1 heads 12.6 / 13.7.
-            if (p.balanced ? D == 128 : p.split_keys >= 128) return launch_attn<D, 1, 2, 64, NS, 2>(p, stream);
+            if (attn_has_loaders(p, D)) return launch_attn_s<D, 1, 2, 64, NS, 2, true>(p, stream);
             return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
         case 2: return launch_attn<D, 2, 2, 64, NS, 4>(p, stream);
         case 3: return launch_attn<D, 3, 2, 64, NS, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)

@@ -1,5 +1,6 @@
 """GPU parity of one block of query rows where its launch changes: splits of 127 and of 128 keys, and with fewer, as many
-and more tiles than the ring is deep; balanced pieces of it.  Bounds: those of every attention test."""
+and more tiles than the ring is deep, of caches below the streamed size and above it; balanced pieces of it.  Bounds: those of
+every attention test."""
 import numpy as np
 import pytest
 import torch
@@ -28,6 +29,23 @@ def test_splits_of_one_row_block(B, kv_len, splits, d):
     out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
     torch.cuda.synchronize()
     assert_attn_close(out, want, f"kv{kv_len} d{d} splits {splits}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
+# (head size, kv heads, splits) with loader waves from 164 keys a split on: workgroups in one round, three of them to four CUs and one to each, and several
+STREAMED = [(128, 64, 2), (64, 100, 2), (64, 128, 2), (64, 130, 4)]
+
+
+@pytest.mark.parametrize("split_keys", [164, 192, 255, 257, 321, 641])            # 3 to 11 tiles, the last of 1 to 64 keys
+@pytest.mark.parametrize("d,hkv,splits", STREAMED)
+def test_splits_of_one_row_block_of_a_streamed_cache(B, d, hkv, splits, split_keys):
+    q_len, hq, kv_len = 3, 2 * hkv, splits * split_keys
+    q, k, v = (rnd_bits((n, h, d), 9700 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    scale = 1.0 / np.sqrt(d)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), dev_bf16(k), dev_bf16(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"{hkv} heads d{d} splits of {split_keys}")
     np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
 
 

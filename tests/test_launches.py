@@ -2,6 +2,7 @@
 launched nothing.  No GPU is touched."""
 import pytest
 
+import test_gpu_attn_one_block as one_block
 import test_gpu_score_packed as packed
 import test_gpu_score_sweeps as sweeps
 from launches import AT, launches
@@ -131,3 +132,20 @@ def test_the_packed_shapes_have_fewer_rows_in_the_workspace_of_before(tmp_path):
     (asked, _), enough, short = launches([query, score(hq, hkv, d, L, V, layers, workspace_bytes=least),
                                           score(hq, hkv, d, L, V, layers, workspace_bytes=least - 1)], tmp_path)
     assert asked == least and enough[0] == 0 and short == (-3, [])
+
+
+# one block of query rows: roles only where the cache is streamed (8 MB), the splits are of 128 keys and more and the workgroups of head size 64
+# fit one round of one to a CU or take several
+@pytest.mark.parametrize("hq,hkv,d,batch,kv_len,splits,loaders", [
+    (7, 1, 128, 1, 16383, 64, False), (7, 1, 128, 1, 16384, 64, True), (28, 4, 128, 1, 4161, 33, False), (14, 2, 64, 1, 16383, 32, False),
+    (14, 2, 64, 1, 16384, 32, True), (14, 2, 64, 1, 32768, 128, True), (14, 2, 64, 1, 33024, 129, False), (16, 8, 64, 1, 16384, 64, False),
+    (16, 8, 64, 1, 16640, 65, True), (16, 8, 64, 65, 128, 0, True), (8, 4, 64, 65, 1500, 0, False), (8, 4, 64, 100, 600, 0, False),
+    (64, 8, 128, 1, 16384, 64, False), (64, 8, 128, 1, 16128, 63, True), (64, 8, 128, 1, 16448, 64, True), (28, 4, 128, 1, 32768, 128, True),
+    (64, 8, 128, 65, 256, 0, False), (64, 8, 128, 65, 257, 0, True), (64, 8, 128, 8, 255, 0, False), (64, 8, 128, 8, 256, 0, True),
+    (40, 8, 128, 8, 1100, 0, True), (28, 4, 128, 2, 1100, 0, False), (14, 2, 64, 8, 9000, 0, False),
+    *((2 * hkv, hkv, d, 1, 164 * splits, splits, True) for d, hkv, splits in one_block.STREAMED)])
+def test_one_row_block_has_loader_waves_where_memory_is_what_it_waits_for(hq, hkv, d, batch, kv_len, splits, loaders, tmp_path):
+    more = dict(batch=batch, cu_q=AT, cu_kv=AT) if batch > 1 else {}
+    [(status, got)] = launches([attn(hq, hkv, d, 1, kv_len, num_splits=splits, **more)], tmp_path)
+    assert status == 0
+    assert got[0][0].startswith(f"attn_split_kernel<{d}, 1, " + ("2, 64, " if loaders else "4, 128, 2, 0, ")), got
