@@ -1329,14 +1329,30 @@ static bool attn_has_loaders(const AttnParams& p, int head_dim)
     return !(p.split_keys == 256 && p.n_kv_heads % kNumXcd == 0 && p.n_work >= 2 * kNumCu);
 }
 
+// Ring depth of head size 64, whose tiles are half as large: a fourth stage keeps 16 KB more in flight where a workgroup has its CU to itself
+// and tiles to come (us a layer, three stages / four, by query rows of a kv head):  14/2 heads, 100000 keys, 7 rows 14.3 / 14.1, 21 rows 14.9 / 14.5,
+// 42 rows 15.45 / 14.9, 56 rows 15.65 / 15.2;  10/5 heads, 8 rows 26.9 / 25.3.  It leaves a CU two workgroups instead of three, and it is no gain where
+// the memory is busy anyway:
+//   balanced pieces:  8/4 heads, 48 rows, 5 requests of up to 20000 keys 22.7 / 23.1;  16/8, 40 rows, 8 of up to 3000 16.1 / 16.4;
+//   eight heads in one round:  16/8, 8 rows, 100000 keys 43.9 / 45.7, 40 rows, 30000 keys 18.6 / 18.9 (row groups, which share their keys: 100 rows 23.0 / 22.6);
+//   short splits in nearly as many workgroups as CUs:  trees of 14/2 heads, 280 rows, 12000 keys (splits of 286) 11.3 / 11.5, 30000 keys 18.4 / 17.8;
+//   more workgroups than CUs:  14/2 heads, 42 rows, 65 requests of 1500 keys 18.7 / 19.6, 8 of 8000 in 32 splits 13.2 / 13.8;  8/4, 48 rows, 65 of 300
+//     9.5 / 10.4.  In several rounds of long splits it wins again: 8/4, 16 rows, 128 of up to 3000 keys 61.0 / 54.3, 64 rows 67.7 / 65.3.
+static bool attn_has_deep_ring(const AttnParams& p)
+{
+    const bool rounds = p.n_work > 2 * kNumCu;
+    if (p.balanced || (p.n_work > kNumCu && !rounds)) return false;
+    if (!rounds && p.n_kv_heads % kNumXcd == 0 && p.n_rgroups == 1) return false;
+    return 5 * p.n_work <= 4 * kNumCu || p.split_keys >= 640;
+}
+
 template <int D>
 static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
 {
 
-    // (key-split waves, tile keys, ring depth, loader waves) per row-block count; the ring holds NS * 2 * TK * D * 2 bytes of
-    // LDS.  Four stages at head size 64, whose tiles are half as large (us a layer, three / four):  14/2 heads, 100000 keys,
-    // 4 queries 15.05 / 14.4, 6 queries 15.55 / 15.0, 8 queries 16.1 / 15.8;  4/1 heads, 6 queries 11.8 / 11.5, but 30000 keys 9.13 / 9.2.
-    constexpr int NS = D == 64 ? 4 : 3;
+    // (key-split waves, tile keys, ring depth, loader waves) per row-block count; the ring holds NS * 2 * TK * D * 2 bytes of LDS
+    constexpr int DEEP = D == 64 ? 4 : 3;
+    const bool deep = D == 64 && attn_has_deep_ring(p);
     switch (mb) {
         case 1:
             // Splits of at most 128 keys: one chunk of 32 keys for each of four waves, results for the merge (a single split
@@ -1349,11 +1365,14 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
                 if (p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced && !loses)
                     return launch_short<D, kShortWaves, 1, D>(p, stream);
             }
-            if (attn_has_loaders(p, D)) return launch_attn_s<D, 1, 2, 64, NS, 2, true>(p, stream);
+            if (attn_has_loaders(p, D))
+                return deep ? launch_attn_s<D, 1, 2, 64, DEEP, 2, true>(p, stream) : launch_attn_s<D, 1, 2, 64, 3, 2, true>(p, stream);
             return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
-        case 2: return launch_attn<D, 2, 2, 64, NS, 4>(p, stream);
-        case 3: return launch_attn<D, 3, 2, 64, NS, 2>(p, stream);   // (two loaders: 16.7 against 17.0 us with four)
-        case 4: return launch_attn<D, 4, 2, 64, NS, 4>(p, stream);   // (four loaders: 64 rows, 12000 keys, 64/8 heads 15.2, with two 15.8)
+        case 2: return deep ? launch_attn<D, 2, 2, 64, DEEP, 4>(p, stream) : launch_attn<D, 2, 2, 64, 3, 4>(p, stream);
+        // (two loaders: 16.7 against 17.0 us with four)
+        case 3: return deep ? launch_attn<D, 3, 2, 64, DEEP, 2>(p, stream) : launch_attn<D, 3, 2, 64, 3, 2>(p, stream);
+        // (four loaders: 64 rows, 12000 keys, 64/8 heads 15.2, with two 15.8)
+        case 4: return deep ? launch_attn<D, 4, 2, 64, DEEP, 4>(p, stream) : launch_attn<D, 4, 2, 64, 3, 4>(p, stream);
     }
     return SPECVLM_EUNSUPPORTED;
 }

@@ -149,3 +149,17 @@ def test_one_row_block_has_loader_waves_where_memory_is_what_it_waits_for(hq, hk
     [(status, got)] = launches([attn(hq, hkv, d, 1, kv_len, num_splits=splits, **more)], tmp_path)
     assert status == 0
     assert got[0][0].startswith(f"attn_split_kernel<{d}, 1, " + ("2, 64, " if loaders else "4, 128, 2, 0, ")), got
+
+
+# head size 64: four stages where a workgroup has a CU to itself, in one round that is not full or with splits of 640 keys, and in several rounds of those
+@pytest.mark.parametrize("hq,hkv,batch,q_len,kv_len,splits,stages", [
+    (14, 2, 1, 1, 30000, 0, 4), (14, 2, 1, 4, 30000, 0, 4), (14, 2, 1, 8, 3000, 0, 4), (10, 5, 1, 4, 100000, 0, 4), (14, 2, 1, 6, 30600, 102, 4),
+    (14, 2, 1, 6, 30900, 103, 3), (14, 2, 1, 6, 65792, 103, 3), (14, 2, 1, 6, 65920, 103, 4), (14, 2, 1, 26, 12000, 0, 3), (14, 2, 1, 26, 30000, 0, 4),
+    (16, 8, 1, 20, 30000, 0, 3), (16, 8, 1, 50, 30000, 0, 4), (14, 2, 1, 6, 100000, 129, 3), (14, 2, 65, 6, 1500, 0, 3), (8, 4, 128, 8, 3000, 0, 4),
+    (8, 4, 8, 24, 20480, 32, 4), (8, 4, 8, 24, 20448, 32, 3), (14, 2, 5, 6, 20000, 0, 3)])
+def test_the_ring_of_head_size_64(hq, hkv, batch, q_len, kv_len, splits, stages, tmp_path):
+    more = dict(batch=batch, cu_q=AT, cu_kv=AT) if batch > 1 else {}
+    [(status, got)] = launches([attn(hq, hkv, 64, q_len, kv_len, num_splits=splits, **more)], tmp_path)
+    assert status == 0
+    shape = [int(x) for x in got[0][0].split("<")[1].split(",")[:6]]
+    assert shape[0] == 64 and shape[2:5] == [2, 64, stages], got
