@@ -4,7 +4,7 @@
 #include <string.h>
 
 typedef struct { unsigned x, y, z; } dim3;
-typedef struct { const char* name; dim3 grid, block; size_t lds; } launch;
+typedef struct { const char* name; dim3 grid, block; size_t lds; unsigned words[32]; } launch;   /* words: the first argument's first 128 bytes */
 
 static struct { const void* host; const char* name; } kernels[512];
 static int n_kernels, n_launches, device_error, attribute_error;
@@ -32,8 +32,9 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
 }
 int hipLaunchKernel(const void* host, dim3 grid, dim3 block, void** args, size_t lds, void* stream)
 {
-    (void)args; (void)stream;
+    (void)stream;
     launch l = {"?", grid, block, lds};
+    memcpy(l.words, args[0], sizeof(l.words));          /* (past a shorter argument lies the caller's own stack) */
     for (int i = 0; i < n_kernels; ++i) if (kernels[i].host == host) l.name = kernels[i].name;
     if (n_launches < 256) launches[n_launches++] = l;
     return 0;

@@ -1,7 +1,9 @@
 """What the library launches for a call, seen from the host: its calls into the HIP runtime are answered by
 tests/hip_recorder.c, in a process of their own.  No GPU is touched and no kernel runs.
 
-    launches(specvlm_score=dict(n_text=64, ...), device_error=0, attribute_error=0) -> [(status, [(kernel, grid, block, lds)])]
+    launches([("specvlm_score", dict(n_text=64, ...), device_error, attribute_error)], directory) -> [(status, [(kernel, grid, block, lds)])]
+
+With words=True each launch has a fifth item, the first 32 words of the kernel's first argument.
 
 Arguments go by the names of include/specvlm.h; one that is not given is 0, a pointer None.  Pointers are made-up
 addresses: nothing reads them."""
@@ -32,7 +34,7 @@ def prototypes():
 
 
 class Launch(C.Structure):
-    _fields_ = [("name", C.c_char_p), ("grid", C.c_uint * 3), ("block", C.c_uint * 3), ("lds", C.c_size_t)]
+    _fields_ = [("name", C.c_char_p), ("grid", C.c_uint * 3), ("block", C.c_uint * 3), ("lds", C.c_size_t), ("words", C.c_int * 32)]
 
 
 def _serve(recorder, library):
@@ -48,11 +50,11 @@ def _serve(recorder, library):
         rec.recorder_errors(device_error, attribute_error)
         status = f(*[args.get(n, None if t is C.c_void_p else 0) for n, t in params])
         n = rec.recorder_take(taken)
-        answers.append([status, [[l.name.decode(), list(l.grid), list(l.block), l.lds] for l in taken[:n]]])
+        answers.append([status, [[l.name.decode(), list(l.grid), list(l.block), l.lds, list(l.words)] for l in taken[:n]]])
     json.dump(answers, sys.stdout)
 
 
-def launches(calls, directory):
+def launches(calls, directory, words=False):
     """calls: [(function, arguments[, device error[, attribute error]])]"""
     recorder = os.path.join(str(directory), "recorder.so")
     subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", "-o", recorder, os.path.join(ROOT, "tests", "hip_recorder.c")], check=True)
@@ -68,7 +70,7 @@ def launches(calls, directory):
     names = sorted({l[0] for _, ls in answers for l in ls})
     plain = subprocess.run(["c++filt", *names], capture_output=True, text=True, check=True).stdout.splitlines() if names else []
     short = {n: re.sub(r"\(specvlm::.*|void |specvlm::", "", p) for n, p in zip(names, plain)}
-    return [(status, [(short[n], tuple(grid), tuple(block), lds) for n, grid, block, lds in ls]) for status, ls in answers]
+    return [(status, [(short[n], tuple(grid), tuple(block), lds, w)[:5 if words else 4] for n, grid, block, lds, w in ls]) for status, ls in answers]
 
 
 if __name__ == "__main__":

@@ -134,6 +134,23 @@ def test_the_packed_shapes_have_fewer_rows_in_the_workspace_of_before(tmp_path):
     assert asked == least and enough[0] == 0 and short == (-3, [])
 
 
+# (a q head's queries as the sweeps pad them: the word of their parameters that comes nine behind n_text, n_keys, video_start and n_video)
+def padded(launch, n_text, n_video, n_keys):
+    words = launch[4]
+    at = [i for i in range(20) if words[i:i + 4] == [n_text, n_keys, 0, n_video]]
+    assert len(at) == 1, words
+    return words[at[0] + 9]
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_text,n_video,layers,pad", [
+    (32, 32, 128, 13, 12544, None, 64), (32, 32, 128, 28, 3000, 24, 64), (16, 16, 64, 9, 3000, 24, 64), (16, 16, 64, 32, 12544, None, 64),
+    (16, 8, 128, 13, 12544, None, 16), (64, 8, 128, 28, 3000, 24, 32), (6, 3, 64, 32, 3000, 24, 32), (16, 16, 64, 130, 700, 24, 192)])
+def test_queries_are_packed_only_where_the_sweeps_have_less_to_do(hq, hkv, d, n_text, n_video, layers, pad, tmp_path):
+    [(status, ls)] = launches([score(hq, hkv, d, n_text, n_video, layers)], tmp_path, words=True)
+    assert status == 0 and [l[0] for l in ls[::2]][:2] == [f"score_sweep_kernel<{d}, 0>", f"score_sweep_kernel<{d}, 1>"]
+    assert padded(ls[0], n_text, n_video, n_text + n_video) == padded(ls[2], n_text, n_video, n_text + n_video) == pad
+
+
 # one block of query rows: roles only where the cache is streamed (8 MB), the splits are of 128 keys and more and the workgroups of head size 64
 # fit one round of one to a CU or take several
 @pytest.mark.parametrize("hq,hkv,d,batch,kv_len,splits,loaders", [
