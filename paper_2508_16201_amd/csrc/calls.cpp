@@ -69,10 +69,10 @@ struct Arg {
         if (v != (int)v) throw NotPlain();
         return (int)v;
     }
-    float real() const
+    double real() const
     {
-        if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
-        return (float)integer();
+        if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
+        return (double)integer();
     }
     bool truth() const
     {
@@ -146,7 +146,7 @@ PyObject* accept(const Arg* a)           // target, tokens, draft, uniforms, tem
     void* const tokens = a[1].contiguous();
     void* const draft = a[2].contiguous();
     void* const uniforms = a[3].contiguous();
-    const float temperature = a[4].real();
+    const float temperature = (float)a[4].real();
     const int b = as_int(batch), gamma = as_int(g1 - 1), v = as_int(vocab);
     if (!tokens) throw NotPlain();
     const Out n_accepted(a[6], [&] { return make({batch}, at::kInt, target); });
@@ -165,14 +165,15 @@ PyObject* score(const Arg* a)
     if (q.dim() != 3 || k.dim() != 3 || q.stride(2) != 1 || k.stride(2) != 1) throw NotPlain();
     const int n_text = as_int(q.size(0)), hq = as_int(q.size(1)), d = as_int(q.size(2)), n_keys = as_int(k.size(0)), hkv = as_int(k.size(1));
     const int video_start = a[2].number(), n_video = a[3].number(), text_pos0 = a[4].number(), norm_mode = a[6].number();
-    const float scale = a[5].real(), beta = a[8].real();
+    const float scale = (float)a[5].real();
+    const double beta = a[8].real();         // (one that 32 bits take for 0 needs scores too)
     const float* const row_lse = (const float*)a[7].ptr();
-    if (a[9].none() && beta != 0.f) throw NotPlain();
+    if (a[9].none() && beta != 0.) throw NotPlain();
     const Out scores(a[9], [&] { return make({n_video}, at::kFloat, q); });
     const Workspace ws(a[10], q, [&] { return c_score_bytes(1, n_text, n_keys, n_video, hq, hkv, d, !a[7].none()); });
     const int status = call(c_score, q.data_ptr(), q.stride(0), q.stride(1), k.data_ptr(), k.stride(0), k.stride(1), (const int32_t*)nullptr,
                             (const int32_t*)nullptr, (const int32_t*)nullptr, 1, n_text, n_keys, video_start, n_video, text_pos0, hq, hkv, d, scale,
-                            norm_mode, row_lse, beta, (float*)scores.at, ws.at, ws.bytes);
+                            norm_mode, row_lse, (float)beta, (float*)scores.at, ws.at, ws.bytes);
     return status ? PyLong_FromLong(status) : scores.result();
 }
 
@@ -199,7 +200,7 @@ PyObject* select(const Arg* a)           // scores, k_top, keep_budget, total_ke
 PyObject* top_p_count(const Arg* a)      // scores, lam, cu_video, max_n_video, max_count, count
 {
     const at::Tensor& scores = a[0].tensor();
-    const float lam = a[1].real();
+    const float lam = (float)a[1].real();
     if (a[3].none() && !a[2].none()) throw NotPlain();
     const int64_t batch = a[2].none() ? 1 : a[2].tensor().numel() - 1;
     const int b = as_int(batch), longest = a[3].none() ? as_int(scores.numel()) : a[3].number();
@@ -249,7 +250,7 @@ PyObject* decode_attn(const Arg* a)
     } else {
         batch = as_int(a[4].tensor().numel() - 1); q_len = a[6].number(); kv_len = a[7].number();
     }
-    const float scale = a[3].real();
+    const float scale = (float)a[3].real();
     const bool want_lse = a[9].truth();
     const int splits = a[10].number();
     void* const cu_q = a[4].ptr();

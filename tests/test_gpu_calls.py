@@ -141,7 +141,7 @@ def test_what_is_refused_is_refused_in_the_same_words(monkeypatch):
     q, k = bf16(4, 8, 128), bf16(50, 2, 128)
     calls = [lambda: B.accept(t.transpose(1, 2), x), lambda: B.accept(t.cpu(), x), lambda: B.accept(t, x, workspace=t.new_empty(8, dtype=torch.uint8)),
              lambda: B.accept(t[0], x), lambda: B.accept(t, None), lambda: B.accept(np.zeros((1, 3, 100)), x),
-             lambda: B.score(q, k, 0, 40, -1, 0.1, beta=0.5), lambda: B.score(q, k, 0, 60, -1, 0.1), lambda: B.score(q[..., ::2], k, 0, 40, -1, 0.1),
+             lambda: B.score(q, k, 0, 40, -1, 0.1, beta=0.5), lambda: B.score(q, k, 0, 40, -1, 0.1, beta=-1e-50), lambda: B.score(q, k, 0, 60, -1, 0.1), lambda: B.score(q[..., ::2], k, 0, 40, -1, 0.1),
              lambda: B.score(q, k, 0, -1, -1, 0.1), lambda: B.score(q, k, 0, 40, -1, 0.1, row_lse=torch.zeros(4, 8)),
              lambda: B.select(t[0, 0], x[0], x[0], 5, cu_video=x[0]), lambda: B.top_p_count(t[0, 0], 0.4, cu_video=x[0]),
              lambda: B.gather_kv(q, q, 0, 2, x[0]), lambda: B.gather_kv(k[None], k[None].transpose(1, 2), 0, 2, x[0]),
