@@ -120,7 +120,8 @@ def test_the_packed_shapes_have_fewer_rows_in_the_workspace_of_before(tmp_path):
         return score(hq, hkv, d, L, V, layers, n_keys=P + V + L, video_start=P, norm_mode=mode, text_pos0=P + V)
 
     shapes = [(s, n) for s, n in packed.PACKED] + [((1, V, L, 0, hq, hkv, d, 0), 1) for V, L, _, hq, hkv, d in packed.INSIDE]
-    for (shape, blocks), (status, ls) in zip(shapes, launches([call(*s) for s, _ in shapes], tmp_path)):
+    for (shape, blocks), (status, ls) in zip(shapes, launches([call(*s) for s, _ in shapes], tmp_path, words=True)):
+        assert padded(ls[2], shape[2], shape[1], sum(shape[1:4]), shape[3]) == (shape[2] + 15) // 16 * 16, (shape, ls)
         assert status == 0 and ls[0][0] == f"score_sweep_kernel<{shape[6]}, 0>", (shape, ls)
         rows_a_block = 256 if ls[1][0] == "score_lse_kernel<1>" else 32
         assert ls[1][1] == (blocks * 256 // rows_a_block, shape[5], shape[0]), (shape, ls)
@@ -135,9 +136,9 @@ def test_the_packed_shapes_have_fewer_rows_in_the_workspace_of_before(tmp_path):
 
 
 # (a q head's queries as the sweeps pad them: the word of their parameters that comes nine behind n_text, n_keys, video_start and n_video)
-def padded(launch, n_text, n_video, n_keys):
+def padded(launch, n_text, n_video, n_keys, video_start=0):
     words = launch[4]
-    at = [i for i in range(20) if words[i:i + 4] == [n_text, n_keys, 0, n_video]]
+    at = [i for i in range(20) if words[i:i + 4] == [n_text, n_keys, video_start, n_video]]
     assert len(at) == 1, words
     return words[at[0] + 9]
 
