@@ -135,6 +135,66 @@ def test_attention(monkeypatch, more):
     same(*both(monkeypatch, lambda: B.decode_attn(q, k, v, 0.1, **m).clone() if "out" in more else B.decode_attn(q, k, v, 0.1, **m)))
 
 
+# numbers as NumPy and Python programs have them (1 / np.sqrt(d) is an np.float64), parameters, flags that are not True or False
+@gpu
+@pytest.mark.parametrize("num", [np.float64, np.float32, int, bool])
+def test_plain_numbers_of_other_types(monkeypatch, num):
+    q, k = bf16(6, 8, 128), bf16(900, 2, 128)
+    same(*both(monkeypatch, lambda: B.decode_attn(q, k, k, num(1) / num(8) if num is np.float32 else num(1))))
+    same(*both(monkeypatch, lambda: B.score(q, k, 0, 800, -1, num(1), norm_mode=1, beta=num(1), scores=torch.ones(800, device="cuda"))))
+    t, x = torch.randn((2, 3, 500), generator=torch.Generator("cuda").manual_seed(5), device="cuda"), i32(3, 4, 5, 6).view(2, 2)
+    same(*both(monkeypatch, lambda: B.accept(t, x, draft_logits=t[:, :2].contiguous(), uniforms=torch.full((2, 3), 0.5, device="cuda"), temperature=num(1))))
+    same(*both(monkeypatch, lambda: B.top_p_count(torch.rand(500, generator=torch.Generator("cuda").manual_seed(6), device="cuda"), num(1))))
+
+
+@gpu
+def test_plain_sizes_flags_and_tensors_of_other_types(monkeypatch):
+    n = np.int64
+    q, k, s = bf16(6, 8, 128), bf16(3, 900, 2, 128), torch.rand(500, generator=torch.Generator("cuda").manual_seed(6), device="cuda")
+    same(*both(monkeypatch, lambda: B.score(q, k[0], n(0), n(800), n(-1), np.float64(0.1), norm_mode=n(1))))
+    same(*both(monkeypatch, lambda: B.select(s, i32(20), i32(50), n(50), want_flags=1)))
+    same(*both(monkeypatch, lambda: B.select(s, i32(20), i32(50), 50, want_flags=0)))
+    same(*both(monkeypatch, lambda: B.select(s, i32(20), i32(50), n(50), want_flags=None, max_n_video=n(500))))
+    same(*both(monkeypatch, lambda: B.decode_attn(q, k[0], k[1], 0.1, want_lse=1, num_splits=n(3), cu_q=i32(0, 2, 6), cu_kv=i32(0, 300, 900),
+                                                  max_q_len=n(4), max_kv_len=n(600))))
+    p = torch.nn.Parameter(k[0], requires_grad=False)
+    same(*both(monkeypatch, lambda: B.decode_attn(torch.nn.Parameter(q, requires_grad=False), p, p, 0.1)))
+
+
+@gpu
+def test_gather_of_keys_alone_and_into_one_destination(monkeypatch):
+    k, v = bf16(3, 120, 2, 64), bf16(3, 120, 2, 64, seed=2)
+    keep = torch.arange(0, 100, 3, dtype=torch.int32, device="cuda")
+    dst = lambda: torch.zeros((3, 54, 2, 64), dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    same(*both(monkeypatch, lambda: B.gather_kv(k, None, 0, 100, keep)))
+    same(*both(monkeypatch, lambda: B.gather_kv(k, None, 0, 100, keep, dst())))
+    same(*both(monkeypatch, lambda: B.gather_kv(k, v, 0, 100, keep, dst())))
+    same(*both(monkeypatch, lambda: B.gather_kv(k, v, 0, 100, keep, None, dst())))
+
+
+@gpu
+def test_calls_are_ordered_on_the_current_stream(monkeypatch):
+    """Inputs that a side stream writes behind a pause: a call that went elsewhere would meet what was there before."""
+    side, q, k = torch.cuda.Stream(), bf16(6, 8, 128), bf16(900, 2, 128)
+    want, s = B.decode_attn(q, k, k, 0.1), torch.rand(500, generator=torch.Generator("cuda").manual_seed(6), device="cuda")
+    kept = B.select(s, i32(20), i32(50), 50)[0]
+    torch.cuda.synchronize()
+
+    def call():
+        late_q, late_s, k_top, budget = torch.zeros_like(q), torch.zeros_like(s), i32(20), i32(50)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)
+            late_q.copy_(q)
+            late_s.copy_(s)
+            got = B.decode_attn(late_q, k, k, 0.1), B.select(late_s, k_top, budget, 50)[0]
+        side.synchronize()
+        return got
+    for route in (B._load_calls(), B._NoCalls()):
+        monkeypatch.setattr(B, "_calls", route)
+        same(call(), (want, kept))
+
+
 @gpu
 def test_what_is_refused_is_refused_in_the_same_words(monkeypatch):
     t, x = torch.randn((1, 3, 100), device="cuda"), torch.zeros((1, 2), dtype=torch.int32, device="cuda")
@@ -144,7 +204,7 @@ def test_what_is_refused_is_refused_in_the_same_words(monkeypatch):
              lambda: B.score(q, k, 0, 40, -1, 0.1, beta=0.5), lambda: B.score(q, k, 0, 40, -1, 0.1, beta=-1e-50), lambda: B.score(q, k, 0, 60, -1, 0.1), lambda: B.score(q[..., ::2], k, 0, 40, -1, 0.1),
              lambda: B.score(q, k, 0, -1, -1, 0.1), lambda: B.score(q, k, 0, 40, -1, 0.1, row_lse=torch.zeros(4, 8)),
              lambda: B.select(t[0, 0], x[0], x[0], 5, cu_video=x[0]), lambda: B.top_p_count(t[0, 0], 0.4, cu_video=x[0]),
-             lambda: B.gather_kv(q, q, 0, 2, x[0]), lambda: B.gather_kv(k[None], k[None].transpose(1, 2), 0, 2, x[0]),
+             lambda: B.gather_kv(q, q, 0, 2, x[0]), lambda: B.gather_kv(k[None], k[None].transpose(1, 2), 0, 2, x[0]), lambda: B.gather_kv(k[None], None, 0, 2, x[0], None, q[None]),
              lambda: B.decode_attn(q, k, k[::2], 0.1), lambda: B.decode_attn(q, k, k, -1.0), lambda: B.decode_attn(q, k, k, 0.1, out=q.transpose(0, 1)),
              lambda: B.decode_attn(q, k, k, 0.1, cu_q=x[0], cu_kv=x[0]), lambda: B.decode_attn(q, k, k, 0.1, workspace=t.new_empty(8), num_splits=-1)]
     native = B._load_calls()
@@ -176,3 +236,14 @@ def test_what_is_left_to_the_general_code():
         native.accept(t)
     with pytest.raises(TypeError):
         native.connect(1)
+
+
+def test_what_is_left_is_left_at_once():
+    """A call that is not plain costs it what a look at a tensor or two costs, not an exception (2.4 us, as long as a launch)."""
+    import timeit
+    native, t, x = B._load_calls(), torch.zeros(1, 3, 9), torch.zeros((1, 2), dtype=torch.int32)
+    once = lambda f: min(timeit.repeat(f, number=500, repeat=20)) / 500  # noqa: E731
+    look = once(lambda: t.stride())
+    for f in (lambda: native.accept(t, x, None, None, 1.0, None, None, None), lambda: native.gather_kv(t, None, 0, 2, x, None, None, None, None, None),
+              lambda: native.decode_attn(t, t, t, 0.1, None, None, None, None, None, False, 0, None, None)):
+        assert f() is None and once(f) < 6 * look
