@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional, Tuple
 
 import numpy as np
@@ -107,25 +108,27 @@ def lib() -> C.CDLL:
 
 
 class _NoCalls:
-    """Stands in for _calls on a torch without GPU support, where no tensor is one that it takes."""
+    """Stands in for _calls where that is not to be had: every call is left to the general code."""
 
     def __getattr__(self, name):
         return lambda *args: None
 
 
 def _load_calls():
-    """The native marshalling, connected to the library; the first call of a short function asks for it."""
+    """The native marshalling, connected to the library; the first call of a short function asks for it.  Without it (a build without it,
+    or for another torch) the general code makes every call, in more host time."""
     global _calls
     if _raw_stream is None:
         _calls = _NoCalls()
     else:
         try:
             from . import _calls as native
+            native.connect(*(C.cast(getattr(lib(), name), C.c_void_p).value for name in _CALLED))
+            _calls = native
         except ImportError as e:
-            raise FileNotFoundError(f"{os.path.join(_HERE, '_calls.so')} is missing or does not fit this torch: build it with "
-                                    "`python -m paper_2508_16201_amd.build`") from e
-        native.connect(*(C.cast(getattr(lib(), name), C.c_void_p).value for name in _CALLED))
-        _calls = native
+            warnings.warn(f"{os.path.join(_HERE, '_calls.so')} is missing or does not fit this torch, so calls take longer on the host (build it "
+                          f"with `python -m paper_2508_16201_amd.build`): {e}", RuntimeWarning, stacklevel=3)
+            _calls = _NoCalls()
     return _calls
 
 

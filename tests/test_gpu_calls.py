@@ -2,11 +2,14 @@
 caller's own where it gave some, and what one refuses the other refuses with the same words.  On the CPU: what it leaves to the general
 code."""
 import os
+import sys
+import warnings
 
 import numpy as np
 import pytest
 import torch
 
+import paper_2508_16201_amd as package
 from paper_2508_16201_amd import binding as B, build
 
 gpu = pytest.mark.gpu
@@ -247,3 +250,18 @@ def test_what_is_left_is_left_at_once():
     for f in (lambda: native.accept(t, x, None, None, 1.0, None, None, None), lambda: native.gather_kv(t, None, 0, 2, x, None, None, None, None, None),
               lambda: native.decode_attn(t, t, t, 0.1, None, None, None, None, None, False, 0, None, None)):
         assert f() is None and once(f) < 6 * look
+
+
+def test_without_the_native_code_every_call_is_left(monkeypatch):
+    """A library without _calls.so beside it serves every call, after one warning; what is missing is the faster way there."""
+    monkeypatch.setattr(B, "_calls", None)
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 0)
+    monkeypatch.delattr(package, "_calls", raising=False)
+    monkeypatch.setitem(sys.modules, package.__name__ + "._calls", None)
+    t, x = torch.zeros((1, 3, 9)), torch.zeros((1, 2), dtype=torch.int32)
+    with pytest.warns(RuntimeWarning, match="_calls.so"), pytest.raises(ValueError, match="on the GPU"):
+        B.accept(t, x, n_accepted=x[0, :1], out_tokens=x, workspace=t)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        with pytest.raises(ValueError, match="on the GPU"):
+            B.accept(t, x, n_accepted=x[0, :1], out_tokens=x, workspace=t)
