@@ -61,7 +61,8 @@ extern "C" {
 /* Static text for a return code (host pointer, never NULL). */
 const char* specvlm_status_string(int status);
 
-/* Library version as major*10000 + minor*100 + patch. */
+/* Library version as major*10000 + minor*100 + patch: that of the header it was built with. */
+#define SPECVLM_VERSION 100
 int specvlm_version(void);
 
 /* --------------------------------------------------------------------------

@@ -24,9 +24,6 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SPECVLM_LIB") or os.path.join(_HERE, "libspecvlm.so")
 _lib = None
 _calls = None
-# the C functions that _calls calls, in the order its connect() takes their addresses in
-_CALLED = ("specvlm_accept", "specvlm_accept_workspace_bytes", "specvlm_score", "specvlm_score_workspace_bytes", "specvlm_select",
-           "specvlm_top_p_count", "specvlm_gather_kv", "specvlm_decode_attn", "specvlm_tree_attn", "specvlm_decode_attn_workspace_bytes")
 
 EXPORTS = (
     "specvlm_status_string", "specvlm_version",
@@ -123,7 +120,9 @@ def _load_calls():
     else:
         try:
             from . import _calls as native
-            native.connect(*(C.cast(getattr(lib(), name), C.c_void_p).value for name in _CALLED))
+            if native.torch_version != torch.__version__.split("+")[0]:     # (it reads torch's objects in place)
+                raise ImportError(f"compiled for torch {native.torch_version}, this is {torch.__version__}")
+            native.connect(version(), {name: C.cast(getattr(lib(), name), C.c_void_p).value for name in native.functions})
             _calls = native
         except ImportError as e:
             warnings.warn(f"{os.path.join(_HERE, '_calls.so')} is missing or does not fit this torch, so calls take longer on the host (build it "

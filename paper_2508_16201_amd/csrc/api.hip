@@ -13,4 +13,4 @@ extern "C" const char* specvlm_status_string(int status)
     }
 }
 
-extern "C" int specvlm_version(void) { return 100; }
+extern "C" int specvlm_version(void) { return SPECVLM_VERSION; }

@@ -11,6 +11,7 @@
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/headeronly/version.h>
 
 #include <algorithm>
 #include <optional>
@@ -314,17 +315,30 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n)
     Py_RETURN_NONE;
 }
 
+// The functions that are called here, by the names under which connect() is handed their addresses.
+struct { const char* name; void** at; } const functions[] = {
+    {"specvlm_accept", (void**)&c_accept}, {"specvlm_accept_workspace_bytes", (void**)&c_accept_bytes}, {"specvlm_score", (void**)&c_score},
+    {"specvlm_score_workspace_bytes", (void**)&c_score_bytes}, {"specvlm_select", (void**)&c_select}, {"specvlm_top_p_count", (void**)&c_top_p_count},
+    {"specvlm_gather_kv", (void**)&c_gather_kv}, {"specvlm_decode_attn", (void**)&c_decode_attn}, {"specvlm_tree_attn", (void**)&c_tree_attn},
+    {"specvlm_decode_attn_workspace_bytes", (void**)&c_attn_bytes}};
+
+// connect(version, address of every function by its name), once, before any call: the version is the library's, which has to be the one whose
+// header this was compiled with.
 PyObject* connect(PyObject*, PyObject* const* args, Py_ssize_t n)
 {
-    void** const to[] = {(void**)&c_accept, (void**)&c_accept_bytes, (void**)&c_score, (void**)&c_score_bytes, (void**)&c_select,
-                         (void**)&c_top_p_count, (void**)&c_gather_kv, (void**)&c_decode_attn, (void**)&c_tree_attn, (void**)&c_attn_bytes};
-    if (n != (Py_ssize_t)(sizeof(to) / sizeof(to[0]))) { PyErr_SetString(PyExc_TypeError, "wrong number of addresses"); return nullptr; }
-    void* at[sizeof(to) / sizeof(to[0])];
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        at[i] = PyLong_AsVoidPtr(args[i]);
-        if (!at[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no address"); return nullptr; }
+    if (n != 2 || !PyLong_Check(args[0]) || !PyDict_Check(args[1])) { PyErr_SetString(PyExc_TypeError, "a version and a dict of addresses"); return nullptr; }
+    if (PyLong_AsLong(args[0]) != SPECVLM_VERSION) {
+        PyErr_Clear();
+        return PyErr_Format(PyExc_ImportError, "compiled for version %d of the library, which is %S", SPECVLM_VERSION, args[0]);
     }
-    for (Py_ssize_t i = 0; i < n; ++i) *to[i] = at[i];
+    constexpr size_t N = sizeof(functions) / sizeof(functions[0]);
+    void* at[N];
+    for (size_t i = 0; i < N; ++i) {
+        PyObject* const address = PyDict_GetItemString(args[1], functions[i].name);
+        at[i] = address ? PyLong_AsVoidPtr(address) : nullptr;
+        if (!at[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_KeyError, functions[i].name); return nullptr; }
+    }
+    for (size_t i = 0; i < N; ++i) *functions[i].at = at[i];
     Py_RETURN_NONE;
 }
 
@@ -338,4 +352,17 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject* PyInit__calls() { return PyModule_Create(&module); }
+extern "C" __attribute__((visibility("default"))) PyObject* PyInit__calls()
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (!m) return nullptr;
+    PyObject* const names = PyTuple_New(sizeof(functions) / sizeof(functions[0]));
+    for (Py_ssize_t i = 0; names && i < PyTuple_GET_SIZE(names); ++i) PyTuple_SET_ITEM(names, i, PyUnicode_FromString(functions[i].name));
+    if (!names || PyErr_Occurred() || PyModule_AddObjectRef(m, "functions", names) || PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION)) {
+        Py_XDECREF(names);
+        Py_DECREF(m);
+        return nullptr;
+    }
+    Py_DECREF(names);
+    return m;
+}

@@ -265,3 +265,21 @@ def test_without_the_native_code_every_call_is_left(monkeypatch):
         warnings.simplefilter("error")
         with pytest.raises(ValueError, match="on the GPU"):
             B.accept(t, x, n_accepted=x[0, :1], out_tokens=x, workspace=t)
+
+
+def test_the_native_code_is_of_the_library_and_the_torch_it_is_used_with(monkeypatch):
+    """Another interface behind the same names, or objects laid out otherwise, is noticed before a call reaches it."""
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 0)
+    native = B._load_calls()
+    at = {name: 1 for name in native.functions}
+    with pytest.raises(ImportError, match="version"):
+        native.connect(B.version() + 1, at)
+    with pytest.raises(KeyError, match=native.functions[-1]):
+        native.connect(B.version(), {name: 1 for name in native.functions[:-1]})
+    later = B.version() + 1
+    for where, name, what in ((B, "version", lambda: later), (torch, "__version__", "1.0.0+other")):
+        with monkeypatch.context() as m:
+            m.setattr(where, name, what)
+            m.setattr(B, "_calls", None)
+            with pytest.warns(RuntimeWarning, match="_calls.so"):
+                assert isinstance(B._load_calls(), B._NoCalls)
