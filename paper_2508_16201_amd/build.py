@@ -1,7 +1,7 @@
 """Build step: compile the HIP sources in ``csrc/`` into ``libspecvlm.so`` for
-gfx950 with hipcc (cross-compiles without a GPU), and the binding's native
-marshalling (``csrc/calls.cpp``, host code against torch's headers) into
-``_calls.so``."""
+gfx950 with hipcc (cross-compiles without a GPU), and where there is a torch
+for ROCm the binding's native marshalling (``csrc/calls.cpp``, host code
+against its headers) into ``_calls.so``."""
 from __future__ import annotations
 
 import glob
@@ -49,6 +49,15 @@ def _run(cmd, verbose: bool, what: str) -> None:
         print(out)
 
 
+def torch_with_gpus() -> bool:
+    """Whether there is a torch whose tensors the native marshalling could take: its headers and libraries are what that is built against."""
+    try:
+        import torch
+    except ImportError:
+        return False
+    return torch.version.hip is not None
+
+
 def build_calls(verbose: bool = False) -> str:
     import sysconfig
     import torch
@@ -70,7 +79,10 @@ def build(verbose: bool = False, host_sanitizers: bool = False) -> str:
            "-I", os.path.join(HERE, "csrc"), "-o", out_lib, *sources()]
     _run(cmd, verbose, "hipcc")
     if not host_sanitizers:
-        build_calls(verbose)
+        if torch_with_gpus():
+            build_calls(verbose)
+        else:
+            print("no torch for ROCm: _calls.so is left out, which the library does not need", flush=True)
     return out_lib
 
 

@@ -15,9 +15,12 @@ from paper_2508_16201_amd import binding as B, build
 gpu = pytest.mark.gpu
 
 
+native_code = pytest.mark.skipif(torch.version.hip is None, reason="no torch for ROCm: there is no native code")
+
+
 @pytest.fixture(scope="module", autouse=True)
 def built():
-    if not (os.path.exists(B.LIB_PATH) and os.path.exists(build.CALLS)):
+    if not os.path.exists(B.LIB_PATH) or (build.torch_with_gpus() and not os.path.exists(build.CALLS)):
         build.build()
 
 
@@ -221,6 +224,7 @@ def test_what_is_refused_is_refused_in_the_same_words(monkeypatch):
         assert said[0] == said[1], (n, said)
 
 
+@native_code
 def test_what_is_left_to_the_general_code():
     native = B._load_calls()
     t, x = torch.zeros(1, 3, 9), torch.zeros((1, 2), dtype=torch.int32)
@@ -241,6 +245,7 @@ def test_what_is_left_to_the_general_code():
         native.connect(1)
 
 
+@native_code
 def test_what_is_left_is_left_at_once():
     """A call that is not plain costs it what a look at a tensor or two costs, not an exception (2.4 us, as long as a launch)."""
     import timeit
@@ -267,6 +272,7 @@ def test_without_the_native_code_every_call_is_left(monkeypatch):
             B.accept(t, x, n_accepted=x[0, :1], out_tokens=x, workspace=t)
 
 
+@native_code
 def test_the_native_code_is_of_the_library_and_the_torch_it_is_used_with(monkeypatch):
     """Another interface behind the same names, or objects laid out otherwise, is noticed before a call reaches it."""
     monkeypatch.setattr(B, "_raw_stream", lambda device: 0)
@@ -283,3 +289,12 @@ def test_the_native_code_is_of_the_library_and_the_torch_it_is_used_with(monkeyp
             m.setattr(B, "_calls", None)
             with pytest.warns(RuntimeWarning, match="_calls.so"):
                 assert isinstance(B._load_calls(), B._NoCalls)
+
+
+@pytest.mark.parametrize("hip", [None, "7.0"])
+def test_the_native_code_is_built_where_there_is_a_torch_for_it(monkeypatch, capsys, hip):
+    made = []
+    monkeypatch.setattr(torch.version, "hip", hip)
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose, what: made.append(cmd[cmd.index("-o") + 1]))
+    assert build.build() == build.LIB and made == [build.LIB] + [build.CALLS] * (hip is not None)
+    assert ("left out" in capsys.readouterr().out) == (hip is None)
