@@ -660,14 +660,14 @@ void attn_split_kernel(const AttnParams p)
 // at most one more rounding of the size the bf16 output carries anyway, and it halves the bytes that
 // the two kernels exchange.
 // One workgroup per (kv head, query row); thread (grp, col) folds the splits grp, grp + GROUPS, ...
-// for 4 output columns.  PRE covers all of a thread's splits (launch_merge picks it) and every load is issued up front, so
-// the kernel costs one memory round trip; each group folds its splits against its own maximum and behind a single barrier
+// for 4 output columns.  PRE covers all of a thread's splits, or they go in ROUNDS of PRE (launch_merge picks it), and every load of a
+// round is issued up front, so the kernel costs one memory round trip; each group folds its splits against its own maximum and behind a single barrier
 // four lanes a piece combine the GROUPS partial results.  (Splits beyond a thread's first three were a round trip each: 192 splits of
 // 30000 keys, 4/1 heads of size 64, 11.9 us a layer, now 8.45;  96 splits of 12000, 14/2 heads, 8.4, now 6.95.)
 // Twelve groups (two loads per thread at the usual 24 splits per head) measured best: 16.3 us per 72B
 // layer against 16.7 with 8 groups, 16.35 with 16, 16.85 with 24 and 17.5 with 32; several rows per
 // workgroup are slower as well (16.9 with two, 17.2 with four).
-template <int D, int PRE, int THREADS>
+template <int D, int PRE, int THREADS, bool ROUNDS>
 __global__ __launch_bounds__(THREADS)
 void attn_merge_kernel(const AttnParams p)
 {
@@ -697,39 +697,50 @@ void attn_merge_kernel(const AttnParams p)
 
     // (past the last split a group reads its first one again and leaves it out: no branch between the loads;  with a branch around
     // each and 64-bit addresses, 14/2 heads of size 64, 5000 keys were 7.2 us a layer instead of 6.7, 12000 keys 9.5 instead of 8.9.
-    // Beyond the first eight a branch between fours, the same for the whole workgroup.)
-    float2 ml_i[PRE];
-    bf16x4 raw[PRE];
-#pragma unroll
-    for (int i = 0; i < PRE; ++i) {
-        if (i >= 8 && GROUPS * (i & ~3) >= live) break;
-        const uint32_t at = (uint32_t)((grp + GROUPS * i < live ? grp + GROUPS * i : min(grp, live - 1)) * p.rows_pad);
-        ml_i[i] = *reinterpret_cast<const float2*>(ml_base + at * 8u);       // the same address across the group: one transaction
-        raw[i] = *reinterpret_cast<const bf16x4*>(o_base + (at * (uint32_t)D + (uint32_t)col) * 2u);
-    }
-    float m_i[PRE], l_i[PRE];
-    floatx4 ov[PRE];
-#pragma unroll
-    for (int i = 0; i < PRE; ++i) {
-        const bool in = grp + GROUPS * i < live;
-        m_i[i] = in ? ml_i[i].x : -INFINITY;
-        l_i[i] = in ? ml_i[i].y : 0.f;
-        const floatx4 o = __builtin_convertvector(raw[i], floatx4);
-        ov[i] = in ? o : floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    float m_loc = m_i[0];
-#pragma unroll
-    for (int i = 1; i < PRE; ++i) m_loc = fmaxf(m_loc, m_i[i]);
-    float m_ref = (m_loc == -INFINITY) ? 0.f : m_loc;
+    // Beyond the first eight a branch between fours, the same for the whole workgroup, and in rounds one between any two.)
+    float m_loc = -INFINITY, l_loc = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    float l_loc = 0.f;
+    int s0 = 0;
+    do {
+        const auto none_left = [&](int i) { return ROUNDS ? i > 0 && s0 + GROUPS * i >= live : i >= 8 && GROUPS * (i & ~3) >= live; };
+        float2 ml_i[PRE];
+        bf16x4 raw[PRE];
 #pragma unroll
-    for (int i = 0; i < PRE; ++i) {
-        if (i >= 8 && GROUPS * (i & ~3) >= live) break;
-        const float w = fast_exp2(m_i[i] - m_ref);           // 0 for an absent or empty split
-        acc += w * ov[i];
-        l_loc += w * l_i[i];
-    }
+        for (int i = 0; i < PRE; ++i) {
+            if (none_left(i)) break;
+            const int s = s0 + grp + GROUPS * i;
+            const uint32_t at = (uint32_t)((s < live ? s : min(grp, live - 1)) * p.rows_pad);
+            ml_i[i] = *reinterpret_cast<const float2*>(ml_base + at * 8u);       // the same address across the group: one transaction
+            raw[i] = *reinterpret_cast<const bf16x4*>(o_base + (at * (uint32_t)D + (uint32_t)col) * 2u);
+        }
+        float m_i[PRE], l_i[PRE];
+        floatx4 ov[PRE];
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) {
+            const bool in = s0 + grp + GROUPS * i < live;
+            m_i[i] = in ? ml_i[i].x : -INFINITY;
+            l_i[i] = in ? ml_i[i].y : 0.f;
+            const floatx4 o = __builtin_convertvector(raw[i], floatx4);
+            ov[i] = in ? o : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        float m_new = m_loc;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) m_new = fmaxf(m_new, m_i[i]);
+        const float ref = (m_new == -INFINITY) ? 0.f : m_new;
+        if constexpr (ROUNDS) {
+            const float f_old = fast_exp2(m_loc - ref);
+            acc *= f_old; l_loc *= f_old;
+        }
+#pragma unroll
+        for (int i = 0; i < PRE; ++i) {
+            if (none_left(i)) break;
+            const float w = fast_exp2(m_i[i] - ref);             // 0 for an absent or empty split
+            acc += w * ov[i];
+            l_loc += w * l_i[i];
+        }
+        m_loc = m_new;
+        s0 += GROUPS * PRE;
+    } while (ROUNDS && s0 < live);
     *reinterpret_cast<floatx4*>(&s_acc[grp][col]) = acc;
     if (col == 0) { s_m[grp] = m_loc; s_l[grp] = l_loc; }
     __syncthreads();
@@ -748,7 +759,7 @@ void attn_merge_kernel(const AttnParams p)
 #pragma unroll
     for (int i = 1; i < EACH; ++i) m = fmaxf(m, m_g[i]);
     m = fmaxf(m, row_move<0xB1>(m)); m = fmaxf(m, row_move<0x4E>(m));
-    m_ref = (m == -INFINITY) ? 0.f : m;
+    const float m_ref = (m == -INFINITY) ? 0.f : m;
     floatx4 tot = {0.f, 0.f, 0.f, 0.f};
     float l = 0.f;
 #pragma unroll
@@ -1227,16 +1238,20 @@ static bool attn_merges_by_row(int n_kv_heads, int64_t total_rows, int rows_pad,
 
 // A thread's splits, all requested together: the fewest of these sizes that cover them.  (A split that is not there is a load
 // of a line that is, yet eight where four do cost 0.2 us: 48 splits of 6000 keys, 28/4 heads 8.95 us a layer instead of 8.75.)
+// With several workgroups to a CU it is their work that counts and not one's round trip: rounds of four, and no load for a split that is not
+// there, of which the short requests of a batch have most (us a layer, all together / this:  64/8 heads, 8 queries, 8 requests of which one has 12800
+// keys in 100 splits and the others 200 66.2 / 54.9, 8192 in 64 45.7 / 40.6, 5120 in 40 31.4 / 30.8;  28/4 heads, 12800 39.8 / 34.9;  equal requests the same).
 template <int D>
 static int launch_merge(const AttnParams& p, dim3 grid, hipStream_t stream)
 {
     constexpr int THREADS = kMergeGroups * (D / 4), MOST = (kMaxSplits + kMergeGroups - 1) / kMergeGroups;
     const int each = (p.num_splits + kMergeGroups - 1) / kMergeGroups;
-    if (each <= 3)       hipLaunchKernelGGL((attn_merge_kernel<D, 3, THREADS>), grid, dim3(THREADS), 0, stream, p);
-    else if (each <= 4)  hipLaunchKernelGGL((attn_merge_kernel<D, 4, THREADS>), grid, dim3(THREADS), 0, stream, p);
-    else if (each <= 8)  hipLaunchKernelGGL((attn_merge_kernel<D, 8, THREADS>), grid, dim3(THREADS), 0, stream, p);
-    else if (each <= 16) hipLaunchKernelGGL((attn_merge_kernel<D, 16, THREADS>), grid, dim3(THREADS), 0, stream, p);
-    else                 hipLaunchKernelGGL((attn_merge_kernel<D, MOST, THREADS>), grid, dim3(THREADS), 0, stream, p);
+    if (each <= 3)                         hipLaunchKernelGGL((attn_merge_kernel<D, 3, THREADS, false>), grid, dim3(THREADS), 0, stream, p);
+    else if (grid.x > 2u * kNumCu)         hipLaunchKernelGGL((attn_merge_kernel<D, 4, THREADS, true>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 4)                    hipLaunchKernelGGL((attn_merge_kernel<D, 4, THREADS, false>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 8)                    hipLaunchKernelGGL((attn_merge_kernel<D, 8, THREADS, false>), grid, dim3(THREADS), 0, stream, p);
+    else if (each <= 16)                   hipLaunchKernelGGL((attn_merge_kernel<D, 16, THREADS, false>), grid, dim3(THREADS), 0, stream, p);
+    else                                   hipLaunchKernelGGL((attn_merge_kernel<D, MOST, THREADS, false>), grid, dim3(THREADS), 0, stream, p);
     return launch_status();
 }
 

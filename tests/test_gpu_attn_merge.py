@@ -56,6 +56,27 @@ def test_ragged_batch_with_named_splits(B):
         o += m
 
 
+# live splits of a request: fewer than the groups, one more, a thread's first eight full, one more, all;  the last two heads make more than 512 workgroups
+FEW_LIVE = [(4, 1, 64, 2), (6, 2, 128, 2), (32, 4, 64, 4), (32, 4, 128, 4)]
+
+
+@pytest.mark.parametrize("splits", [40, 64, 100, 200])
+@pytest.mark.parametrize("hq,hkv,d,q_len", FEW_LIVE)
+def test_ragged_batch_of_few_live_splits(B, splits, hq, hkv, d, q_len):
+    lens = [q_len, 11 * 128 - 5, 13 * 128, 128 * splits] + [n * 128 - 1 for n in (37, 49, 96, 97) if n < splits]
+    q, k, v = [], [], []
+    for i, n in enumerate(lens):
+        q.append(rnd_bits((q_len, hq, d), 7300 + i)); k.append(rnd_bits((n, hkv, d), 7400 + i)); v.append(rnd_bits((n, hkv, d), 7500 + i))
+    cu = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32).cuda()  # noqa: E731
+    out, lse = B.decode_attn(dev_bf16(np.concatenate(q)), dev_bf16(np.concatenate(k)), dev_bf16(np.concatenate(v)), 0.1, cu_q=cu([q_len] * len(lens)),
+                             cu_kv=cu(lens), max_q_len=q_len, max_kv_len=max(lens), num_splits=splits, want_lse=True)
+    torch.cuda.synchronize()
+    for i, n in enumerate(lens):
+        want, want_lse = oracle.decode_attn(q[i], k[i], v[i], 0.1)
+        assert_attn_close(out[i * q_len:(i + 1) * q_len], want, f"request {i} of {n} keys")
+        np.testing.assert_allclose(host_f64(lse[i * q_len:(i + 1) * q_len]), want_lse, atol=2e-3, rtol=1e-4)
+
+
 @pytest.mark.parametrize("q_len,kv_len,hq,hkv,d,splits", [
     (12, 700, 64, 8, 128, 4), (11, 700, 64, 8, 128, 4),                    # 768 and 704 rows, a head per XCD
     (24, 1025, 64, 8, 64, 8), (24, 1100, 64, 8, 64, 9), (23, 300, 64, 8, 64, 2),      # 1536 and 1472 at head size 64

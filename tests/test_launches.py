@@ -181,3 +181,12 @@ def test_the_ring_of_head_size_64(hq, hkv, batch, q_len, kv_len, splits, stages,
     assert status == 0
     shape = [int(x) for x in got[0][0].split("<")[1].split(",")[:6]]
     assert shape[0] == 64 and shape[2:5] == [2, 64, stages], got
+
+
+@pytest.mark.parametrize("hq,hkv,d,batch,q_len,splits,kernel", [
+    (64, 8, 128, 8, 1, 64, "8, 384, false"), (64, 8, 128, 9, 1, 64, "4, 384, true"), (64, 8, 128, 8, 8, 36, "3, 384, false"),
+    (64, 8, 128, 8, 8, 37, "4, 384, true"), (14, 2, 64, 8, 4, 200, "22, 192, false"), (14, 2, 64, 8, 8, 200, "4, 192, true"),
+    (32, 4, 64, 4, 4, 40, "4, 192, false"), (32, 4, 128, 5, 4, 100, "4, 384, true"), (4, 1, 64, 8, 2, 100, "16, 192, false")])
+def test_the_merge_of_many_rows_goes_in_rounds(hq, hkv, d, batch, q_len, splits, kernel, tmp_path):
+    [(status, got)] = launches([attn(hq, hkv, d, q_len, 128 * splits, num_splits=splits, batch=batch, cu_q=AT, cu_kv=AT)], tmp_path)
+    assert status == 0 and got[1][0] == f"attn_merge_kernel<{d}, {kernel}>" and got[1][1] == (hq * q_len * batch, 1, 1), got
