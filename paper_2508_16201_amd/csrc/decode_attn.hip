@@ -912,7 +912,7 @@ void attn_short_kernel(const AttnParams p)
     constexpr int KL = kChunkKeys / KPL, VL = kChunkKeys / VPL;   // loads per chunk
     constexpr int K_BYTES = kChunkKeys * D * 2;
     constexpr int WAVE_LDS = K_BYTES + kChunkKeys * COLS * 2;
-    static_assert(16 * COLS * 4 + NW * 16 <= WAVE_LDS, "a wave's result takes the place of its buffers");
+    static_assert(16 * COLS * 4 + NW * 64 <= WAVE_LDS, "a wave's result takes the place of its buffers");
     // LDS: a private part per wave (its [row][column] fp32 result afterwards), then the waves' maxima and sums
     extern __shared__ __align__(16) unsigned char smem[];
     float (*s_m)[NW] = reinterpret_cast<float (*)[NW]>(smem + NW * WAVE_LDS);
@@ -1065,36 +1065,52 @@ void attn_short_kernel(const AttnParams p)
     // ---- the waves meet: lane (r, c) holds columns 16j + 4c .. 16j + 4c + 3 of row r ----
     // 16-byte piece q of a row goes to place q ^ r: the 16 rows of a store or a load fall on different banks
     constexpr int PIECES = COLS / 4;
-    constexpr int SKEW = DIRECT ? 16 : 0;            // (the waves' results start on different banks where lanes of one load go over the waves)
+    constexpr int LANES = 4, EACH = NW / LANES;      // (DIRECT: lanes that sum a piece, waves' results to each)
+    constexpr int SKEW = DIRECT ? 256 / LANES : 0;   // (the waves' results start on different banks where lanes of one load go over the waves)
 #pragma unroll
     for (int j = 0; j < DJ; ++j)
         reinterpret_cast<floatx4*>(k_lds + wave * SKEW)[r * PIECES + ((4 * j + c) ^ (r & (PIECES - 1)))] = o_acc[j];
     if (c == 0) { s_m[r][wave] = m; s_l[r][wave] = l; }
     if constexpr (DIRECT) {
-        // a lane per wave and piece: the waves' results are summed by DPP over NW lanes.  With a thread per piece, which is one wave's
-        // walk over all the others' results, it was the launch's last 0.5 us (us a layer, before / now:  14/2 heads of size 64, 1511 keys
-        // 6.30 / 6.11, 600 4.36 / 4.28;  4/1 heads, 1511 6.12 / 5.77;  size 128, 28/4 heads, 700 keys 6.38 / 6.25, 64/8, 1000 7.22 / 6.99)
-        static_assert(16 * PIECES == kWave && (NW == 8 || NW == 16));
-        const int w = threadIdx.x % NW, orow = threadIdx.x / NW / PIECES, piece = threadIdx.x / NW % PIECES, grow = rb * 16 + orow;
+        // four lanes a piece sum the waves' results, a quarter of them each, then by DPP: one wave of each SIMD has work.  A thread per piece is one
+        // wave's walk over all the results, and was the launch's last 0.5 us;  a lane per wave and piece has every wave reduce, which loses from eight
+        // query rows on.  Us a layer, thread / lane per wave / four lanes:  14/2 heads of size 64, 1511 keys, one query 6.37 / 6.18 / 6.04, six 6.68 /
+        // 6.90 / 6.46;  4/1 heads, 250 keys, six 3.43 / 3.48 / 3.33;  size 128, 28/4 heads, 500 keys, four 5.68 / 5.82 / 5.56;  40/8 heads, 1010 keys, twelve
+        // 8.07 / 8.25 / 7.79.  (Over 492 shapes four lanes are 3.0 % less than a thread, two as many, eight 1.6 %.)
+        static_assert(16 * PIECES == kWave && NW % LANES == 0 && NW > LANES);
+        const int w = threadIdx.x % LANES, orow = threadIdx.x / LANES / PIECES, piece = threadIdx.x / LANES % PIECES, grow = rb * 16 + orow;
         const QuotRem out_at = divide(grow, p.group, p.inv_group);
         const int to = out_at.q, ho = g * p.group + out_at.r;
         __syncthreads();
-        if (grow >= n_rows) return;
-        const float m_w = s_m[orow][w], l_w = s_l[orow][w];
-        floatx4 tot = reinterpret_cast<const floatx4*>(smem + w * (WAVE_LDS + SKEW))[orow * PIECES + (piece ^ (orow & (PIECES - 1)))];
-        const auto over_waves = [](float x, auto op) {
+        if (grow >= n_rows || threadIdx.x >= kWave * LANES) return;
+        float m_w[EACH], l_w[EACH];
+        floatx4 o_w[EACH];
+#pragma unroll
+        for (int i = 0; i < EACH; ++i) {
+            m_w[i] = s_m[orow][w + LANES * i];
+            l_w[i] = s_l[orow][w + LANES * i];
+            o_w[i] = reinterpret_cast<const floatx4*>(smem + (w + LANES * i) * (WAVE_LDS + SKEW))[orow * PIECES + (piece ^ (orow & (PIECES - 1)))];
+        }
+        const auto over_lanes = [](float x, auto op) {
             x = op(x, row_move<0xB1>(x));
-            x = op(x, row_move<0x4E>(x));
-            x = op(x, row_move<0x141>(x));
-            if constexpr (NW == 16) x = op(x, row_move<0x128>(x));
-            return x;
+            return op(x, row_move<0x4E>(x));
         };
         const auto sum = [](float a, float b) { return a + b; };
-        const float m_all = over_waves(m_w, [](float a, float b) { return fmaxf(a, b); });
-        const float f = fast_exp2(m_w - ((m_all == -INFINITY) ? 0.f : m_all));           // 0 for a wave without keys
+        float m_all = m_w[0], l_all = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tot[i] = over_waves(f * tot[i], sum);
-        const float l_all = over_waves(f * l_w, sum);
+        for (int i = 1; i < EACH; ++i) m_all = fmaxf(m_all, m_w[i]);
+        m_all = over_lanes(m_all, [](float a, float b) { return fmaxf(a, b); });
+        const float ref = (m_all == -INFINITY) ? 0.f : m_all;
+        floatx4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < EACH; ++i) {
+            const float f = fast_exp2(m_w[i] - ref);             // 0 for a wave without keys
+            tot += f * o_w[i];
+            l_all += f * l_w[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[i] = over_lanes(tot[i], sum);
+        l_all = over_lanes(l_all, sum);
         if (w != 0) return;
         tot *= 1.f / l_all;
         *reinterpret_cast<bf16x4*>(p.out + (int64_t)(q0 + to) * p.q_tok + (int64_t)ho * p.q_head + part * COLS + 4 * piece) =

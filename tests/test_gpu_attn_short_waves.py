@@ -26,3 +26,10 @@ def test_ragged_batch(B, lens, hq, hkv, d):
 @pytest.mark.parametrize("n_nodes,kv_len,hq,hkv,d", [(26, 1400, 14, 2, 64), (40, 800, 4, 1, 128)])
 def test_tree(B, n_nodes, kv_len, hq, hkv, d):
     base.test_tree_over_a_short_cache(B, n_nodes, kv_len, hq, hkv, d)
+
+
+@pytest.mark.parametrize("kv_len,d", [(40, 64), (600, 64), (1400, 64), (33, 128), (500, 128), (900, 128)])
+@pytest.mark.parametrize("q_len,hq,hkv", [(1, 1, 1), (5, 2, 2), (7, 1, 1), (4, 4, 2), (3, 3, 1), (5, 6, 2), (16, 2, 2), (17, 1, 1)])
+def test_rows_of_a_block(B, q_len, hq, hkv, kv_len, d):
+    """1 to 17 query rows a kv head: a row of a block is 16 lanes' work where the waves' results meet, the rows that are not there nobody's."""
+    base.test_edges_match_oracle(B, q_len, kv_len, hq, hkv, d, 0)
