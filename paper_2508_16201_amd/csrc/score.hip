@@ -880,14 +880,16 @@ static ScorePlan score_plan_padded(int batch, int n_text, int n_keys, int video_
 }
 
 // Padding is swept like rows: where packing the text queries of a q head to sub-blocks of 16 saves 3.5 % of what the sweeps are
-// estimated to cost, or anything of it and half the rows, they are packed (in arrays and a workspace that are no larger than with whole tiles of
+// estimated to cost (9 % with given normalisers), or anything of it and half the rows, they are packed (in arrays and a workspace that are no larger than with whole tiles of
 // 64, so that what was enough for a call stays enough).  Us a layer, tiles / packed:  24 layers over 12544 keys, 64/8 heads:  16 queries
 // 24.3 / 11.7, 28 25.5 / 16.3, 85 49.4 / 42.6, 142 71.0 / 61.2, 200 93.4 / 85.8, 401 164.9 / 159.5;  14/2 heads of size 64:  16 4.9 / 2.5,
 // 85 8.55 / 7.1, 142 12.45 / 9.6;  one layer, 64/8 heads:  16 46.0 / 28.6, 85 73.8 / 62.8, over 3000 keys 16 25.0 / 19.2.  What the rule
 // leaves out, 300 and 401 queries above all, gains or loses 3 %: 14/2 heads, one layer, 401 queries 52.1 / 53.7, over 3000 keys, 64/8
 // heads, 85 queries 32.5 / 34.9 (three blocks of rows for four, and no fewer tiles for any workgroup).  With as many tiles as before (one q
 // head a kv head, 32 queries and fewer) only the loads' own heads are left to pay: 32/32 heads, one layer 50.0 / 51.3, 24 layers over 3000 keys 11.1 /
-// 11.25, with given normalisers 6.3 / 6.5.
+// 11.25, with given normalisers 6.3 / 6.5.  With these there is pass B alone, whose loads work out the heads, and less than 9 % does not pay for
+// that: 7/1 heads, 24 layers, 104 queries over 8343 keys 56.7 / 62.2 us in all, 14/2 heads of size 64, 2 layers, 327 over 17529 43.3 / 46.9 (by what is
+// saved, medians of 40 to 90 shapes each: 4 to 5 % 0.8 % slower, 5 to 9 % 1 to 2 % faster and in one of eight slower by up to 8 %, 9 to 10 % 4.5 % faster).
 static ScorePlan score_plan(int batch, int n_text, int n_keys, int video_start, int n_video, int n_q_heads,
                             int n_kv_heads, int head_dim, int norm_mode, int have_row_lse)
 {
@@ -896,7 +898,7 @@ static ScorePlan score_plan(int batch, int n_text, int n_keys, int video_start, 
     if (round_up(n_text, kScoreSub) % kScoreTile == 0) return tiles;
     ScorePlan s = score_plan_padded(batch, n_text, n_keys, video_start, n_video, n_q_heads, n_kv_heads, head_dim, norm_mode, have_row_lse,
                                     kScoreSub, &tiles);
-    if (s.cost >= tiles.cost || (2 * s.rows > tiles.rows && 1000 * s.cost > 965 * tiles.cost)) return tiles;
+    if (s.cost >= tiles.cost || (2 * s.rows > tiles.rows && 1000 * s.cost > (have_row_lse ? 910 : 965) * tiles.cost)) return tiles;
     s.total = tiles.total;
     return s;
 }

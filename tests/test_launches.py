@@ -152,6 +152,16 @@ def test_queries_are_packed_only_where_the_sweeps_have_less_to_do(hq, hkv, d, n_
     assert padded(ls[0], n_text, n_video, n_text + n_video) == padded(ls[2], n_text, n_video, n_text + n_video) == pad
 
 
+# (given normalisers: pass B alone)
+@pytest.mark.parametrize("hq,hkv,d,n_text,n_video,layers,pad", [
+    (7, 1, 128, 104, 8343, 24, 128), (14, 2, 64, 327, 17529, 2, 384), (40, 8, 128, 303, 9187, None, 320), (4, 1, 64, 458, 16508, 24, 512),
+    (64, 8, 128, 85, 12544, 24, 96), (28, 4, 128, 200, 25088, 28, 208), (4, 1, 64, 263, 28130, 8, 272)])
+def test_with_given_normalisers_queries_are_packed_for_more(hq, hkv, d, n_text, n_video, layers, pad, tmp_path):
+    [(status, ls)] = launches([score(hq, hkv, d, n_text, n_video, layers, row_lse=AT)], tmp_path, words=True)
+    assert status == 0 and ls[1][0] == f"score_sweep_kernel<{d}, 1>"
+    assert padded(ls[1], n_text, n_video, n_text + n_video) == pad
+
+
 # one block of query rows: roles only where the cache is streamed (8 MB), the splits are of 128 keys and more and the workgroups of head size 64
 # fit one round of one to a CU or take several
 @pytest.mark.parametrize("hq,hkv,d,batch,kv_len,splits,loaders", [
