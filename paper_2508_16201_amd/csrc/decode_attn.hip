@@ -496,81 +496,60 @@ void attn_split_kernel(const AttnParams p)
     }
 
     // ---- epilogue (the loader waves only keep the barriers of the exchange) ----
-    if constexpr (KS == 1) { if (!computes) return; }
     l_run = quad_sum(l_run);
     const int row = row0 + mb * 16 + r;
     const QuotRem out_at = divide(row, p.group, p.inv_group);
     const int t_row = out_at.q, h_row = g * p.group + out_at.r;
     const int64_t slot = slot0 + row;
-    if constexpr (KS == 1) {
-        // lane (r, c) holds columns 16j + 4c .. 16j + 4c + 3 of its row in o_acc[j]: write them out directly
-        if (direct) {
-            if (row >= n_rows) return;
-            const float inv = 1.f / l_run;
-            __bf16* op = p.out + (int64_t)(q0 + t_row) * p.q_tok + (int64_t)h_row * p.q_head + 4 * c;
+    // The KS waves of a row block exchange their accumulators through LDS;
+    // afterwards wave ks owns the column slice [ks*D/KS, (ks+1)*D/KS) of all
+    // 16 rows, so every wave takes part in the final add and store.
+    constexpr int SLICE = D / KS;                // columns per wave after the exchange
+    constexpr int CPL = SLICE / 4;               // columns per lane (lane (r, c): c-th quarter)
+    __syncthreads();                             // every wave is done with the ring
+    float* sm_m = reinterpret_cast<float*>(smem);            // [NW][16]
+    float* sm_l = sm_m + NW * 16;                            // [NW][16]
+    float* sm_o = sm_l + NW * 16;                            // [NW][16][LDS_STRIDE]
+    if (computes) {
+        if (c == 0) { sm_m[wave * 16 + r] = m_run; sm_l[wave * 16 + r] = l_run; }
+        float* buf = sm_o + (wave * 16 + r) * LDS_STRIDE + 4 * c;
 #pragma unroll
-            for (int j = 0; j < DJ; ++j)
-                *reinterpret_cast<bf16x4*>(op + 16 * j) = __builtin_convertvector(o_acc[j] * inv, bf16x4);
-            if (p.lse && c == 0)
-                p.lse[(int64_t)(q0 + t_row) * p.n_q_heads + h_row] = (m_run + fast_log2(l_run)) * kLn2;
-        } else {
-            __bf16* po = p.part_o + slot * D + 4 * c;
+        for (int j = 0; j < DJ; ++j) *reinterpret_cast<floatx4*>(buf + 16 * j) = o_acc[j];
+    }
+    __syncthreads();
+    if (!computes) return;
+    // (brought to one reference here and not before they are written: that was a barrier and a round trip more:  us a layer, before / now:
+    // 64/8 heads, 12806 keys, 6 queries 14.97 / 14.71, one 13.79 / 13.63, 12 nodes 16.86 / 16.58;  14/2 heads of size 64, 12806 keys 8.87 / 8.66)
+    float m_x[KS], m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
-            for (int j = 0; j < DJ; ++j)
-                *reinterpret_cast<bf16x4*>(po + 16 * j) = __builtin_convertvector(o_acc[j], bf16x4);
-            if (c == 0) { p.part_ml[slot * 2] = m_run; p.part_ml[slot * 2 + 1] = l_run; }
-        }
+    for (int kx = 0; kx < KS; ++kx) { m_x[kx] = sm_m[(kx * MB + mb) * 16 + r]; m_all = fmaxf(m_all, m_x[kx]); }
+    const float m_ref = (m_all == -INFINITY) ? 0.f : m_all;
+#pragma unroll
+    for (int kx = 0; kx < KS; ++kx) { m_x[kx] = fast_exp2(m_x[kx] - m_ref); l_all += m_x[kx] * sm_l[(kx * MB + mb) * 16 + r]; }
+    const int col0 = ks * SLICE + c * CPL;
+    floatx4 acc[CPL / 4];
+#pragma unroll
+    for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kx = 0; kx < KS; ++kx) {
+        const float* buf = sm_o + ((kx * MB + mb) * 16 + r) * LDS_STRIDE + col0;
+#pragma unroll
+        for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] += m_x[kx] * *reinterpret_cast<const floatx4*>(buf + 4 * qd);
+    }
+    if (direct) {
+        if (row >= n_rows) return;
+        const float inv = 1.f / l_all;
+        __bf16* op = p.out + (int64_t)(q0 + t_row) * p.q_tok + (int64_t)h_row * p.q_head + col0;
+#pragma unroll
+        for (int qd = 0; qd < CPL / 4; ++qd)
+            *reinterpret_cast<bf16x4*>(op + 4 * qd) = __builtin_convertvector(acc[qd] * inv, bf16x4);
+        if (p.lse && c == 0 && ks == 0)
+            p.lse[(int64_t)(q0 + t_row) * p.n_q_heads + h_row] = (m_all + fast_log2(l_all)) * kLn2;
     } else {
-        // The KS waves of a row block exchange their accumulators through LDS;
-        // afterwards wave ks owns the column slice [ks*D/KS, (ks+1)*D/KS) of all
-        // 16 rows, so every wave takes part in the final add and store.
-        constexpr int SLICE = D / KS;                // columns per wave after the exchange
-        constexpr int CPL = SLICE / 4;               // columns per lane (lane (r, c): c-th quarter)
-        __syncthreads();                             // every wave is done with the ring
-        float* sm_m = reinterpret_cast<float*>(smem);            // [NW][16]
-        float* sm_l = sm_m + NW * 16;                            // [NW][16]
-        float* sm_o = sm_l + NW * 16;                            // [NW][16][LDS_STRIDE]
-        if (computes) {
-            if (c == 0) { sm_m[wave * 16 + r] = m_run; sm_l[wave * 16 + r] = l_run; }
-            float* buf = sm_o + (wave * 16 + r) * LDS_STRIDE + 4 * c;
+        __bf16* po = p.part_o + slot * D + col0;
 #pragma unroll
-            for (int j = 0; j < DJ; ++j) *reinterpret_cast<floatx4*>(buf + 16 * j) = o_acc[j];
-        }
-        __syncthreads();
-        if (!computes) return;
-        // (brought to one reference here and not before they are written: that was a barrier and a round trip more:  us a layer, before / now:
-        // 64/8 heads, 12806 keys, 6 queries 14.97 / 14.71, one 13.79 / 13.63, 12 nodes 16.86 / 16.58;  14/2 heads of size 64, 12806 keys 8.87 / 8.66)
-        float m_x[KS], m_all = -INFINITY, l_all = 0.f;
-#pragma unroll
-        for (int kx = 0; kx < KS; ++kx) { m_x[kx] = sm_m[(kx * MB + mb) * 16 + r]; m_all = fmaxf(m_all, m_x[kx]); }
-        const float m_ref = (m_all == -INFINITY) ? 0.f : m_all;
-#pragma unroll
-        for (int kx = 0; kx < KS; ++kx) { m_x[kx] = fast_exp2(m_x[kx] - m_ref); l_all += m_x[kx] * sm_l[(kx * MB + mb) * 16 + r]; }
-        const int col0 = ks * SLICE + c * CPL;
-        floatx4 acc[CPL / 4];
-#pragma unroll
-        for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kx = 0; kx < KS; ++kx) {
-            const float* buf = sm_o + ((kx * MB + mb) * 16 + r) * LDS_STRIDE + col0;
-#pragma unroll
-            for (int qd = 0; qd < CPL / 4; ++qd) acc[qd] += m_x[kx] * *reinterpret_cast<const floatx4*>(buf + 4 * qd);
-        }
-        if (direct) {
-            if (row >= n_rows) return;
-            const float inv = 1.f / l_all;
-            __bf16* op = p.out + (int64_t)(q0 + t_row) * p.q_tok + (int64_t)h_row * p.q_head + col0;
-#pragma unroll
-            for (int qd = 0; qd < CPL / 4; ++qd)
-                *reinterpret_cast<bf16x4*>(op + 4 * qd) = __builtin_convertvector(acc[qd] * inv, bf16x4);
-            if (p.lse && c == 0 && ks == 0)
-                p.lse[(int64_t)(q0 + t_row) * p.n_q_heads + h_row] = (m_all + fast_log2(l_all)) * kLn2;
-        } else {
-            __bf16* po = p.part_o + slot * D + col0;
-#pragma unroll
-            for (int qd = 0; qd < CPL / 4; ++qd) *reinterpret_cast<bf16x4*>(po + 4 * qd) = __builtin_convertvector(acc[qd], bf16x4);
-            if (c == 0 && ks == 0) { p.part_ml[slot * 2] = m_all; p.part_ml[slot * 2 + 1] = l_all; }
-        }
+        for (int qd = 0; qd < CPL / 4; ++qd) *reinterpret_cast<bf16x4*>(po + 4 * qd) = __builtin_convertvector(acc[qd], bf16x4);
+        if (c == 0 && ks == 0) { p.part_ml[slot * 2] = m_all; p.part_ml[slot * 2 + 1] = l_all; }
     }
     };   // piece
 
@@ -1276,7 +1255,7 @@ static int launch_attn_s(const AttnParams& p, hipStream_t stream)
 {
     constexpr int NW = MB * KS;
     constexpr size_t ring = (size_t)NS * 2 * TK * D * 2;
-    constexpr size_t merge = KS > 1 ? sizeof(float) * (size_t)(2 * NW * 16 + NW * 16 * (D + 4)) : 0;
+    constexpr size_t merge = sizeof(float) * (size_t)(2 * NW * 16 + NW * 16 * (D + 4));
     constexpr size_t lds = ring > merge ? ring : merge;
     if (lds > 64 * 1024)
         if (const int rc = allow_lds<&attn_split_kernel<D, MB, KS, TK, NS, NLD, STREAM>>((int)lds)) return rc;
