@@ -152,8 +152,8 @@ _raw_stream, _current_device = (getattr(torch._C, name, None) for name in ("_cud
 
 
 def _stream() -> int:
-    """The hipStream_t of torch's current stream on the current device, without a Stream object around it: the
-    short calls (acceptance, pruning, the scores of one layer) are bound by the host, and every call asks."""
+    """The hipStream_t of torch's current stream on the current device, without a Stream object around it: what is
+    not marshalled by _calls.so takes its host time here, and every call asks."""
     return _raw_stream(_current_device())
 
 

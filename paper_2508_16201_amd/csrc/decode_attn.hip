@@ -723,10 +723,10 @@ void attn_merge_kernel(const AttnParams p)
     *reinterpret_cast<floatx4*>(&s_acc[grp][col]) = acc;
     if (col == 0) { s_m[grp] = m_loc; s_l[grp] = l_loc; }
     __syncthreads();
-    // four lanes a piece of four columns: three groups each, then by DPP.  (Group 0 alone walking over all
-    // twelve was 0.1 to 0.25 us longer, eight lanes were no faster and, where a CU has several workgroups, slower:  us a layer, before / four / eight
-    // lanes:  14/2 heads of size 64, 3000 keys 6.22 / 6.07 / 6.08;  40/8 heads, 12806 keys, 6 queries 14.37 / 14.20 / 14.29;  64/8 heads 14.98 / 14.94 /
-    // 15.0, a tree of 20 nodes over 3000 keys 12.25 / 12.17 / 12.33.)
+    // four lanes a piece of four columns: three groups each, then by DPP.  (Group 0 alone walking over all twelve was 0.1 to 0.2 us longer, eight
+    // lanes were no faster than four and, where a CU has several workgroups, slower:  us a layer, group 0 / four lanes:  14/2 heads of size 64, 3000 keys, one
+    // query 6.28 / 6.12, six 7.68 / 7.49;  size 128, 12806 keys:  28/4 heads, six 11.9 / 11.74, 40/8 14.36 / 14.21, 64/8, one 13.75 / 13.64, but six the same
+    // within the noise.)
     constexpr int LANES = 4, EACH = GROUPS / LANES;
     static_assert(GROUPS % LANES == 0 && TPR * LANES <= THREADS);
     if (tid >= TPR * LANES) return;
