@@ -1324,7 +1324,9 @@ static int launch_attn(const AttnParams& p, hipStream_t stream)
 // heads 26.3 / 25.1, 28/4 of up to 6000, 4 of them 18.0 / 17.3.  Left out is what loses:
 //   splits of fewer keys (28/4 heads, 3000 keys, splits of 125 7.6 / 7.95) and caches below the streamed size, which stay near and whose launches are
 //     bound by their start and their steps:  size 128, 7/1 heads, 1024 keys in 8 splits 6.45 / 7.0, 4096 in 32 7.15 / 7.5 (but 16384 in 32, 8 MB, 11.65 /
-//     10.5);  size 64, 4/1 heads, 3072 in 8 6.7 / 7.2, 14/2 heads 12288 in 32 7.5 / 7.8 (16384, 8 MB, 9.2 / 8.7);
+//     10.5);  size 64, 4/1 heads, 3072 in 8 6.7 / 7.2, 14/2 heads 12288 in 32 7.5 / 7.8 (16384, 8 MB, 9.2 / 8.7).  Splits of 700 keys of size 128 and
+//     more, which a caller can name, are no start any more: 7/1 heads, 3590 in 3 14.9 / 14.0, 15719 in 5 43.8 / 34.3, from near caches 2 to 5 %
+//     faster;  of size 64 they are from far ones (4/1 heads, 30637 in 20 17.9 / 13.9) and 11 to 16 % slower from near ones, and stay with four waves;
 //   more workgroups of size 64 than CUs in one round, where two of the four waves' workgroups share a CU:  8/4 heads, 65 requests of 1500 keys 25.4 / 26.5,
 //     8 of 3200 in 16 splits 10.5 / 10.7 (in several rounds a third workgroup shares it: 16/8 heads, 40 of 1280 in 8 35.7 / 30.3, 65 of 600 23.5 / 21.1);
 //   splits of 256 keys, eight heads and more, in two rounds and more: the four waves have all of a split in flight at once, and lines of 512 KB strides:
@@ -1332,7 +1334,7 @@ static int launch_attn(const AttnParams& p, hipStream_t stream)
 //   balanced pieces of size 64 (4/1 heads 12.6 / 13.7).
 static bool attn_has_loaders(const AttnParams& p, int head_dim)
 {
-    if (!attn_streams(p, head_dim)) return false;
+    if (!attn_streams(p, head_dim)) return head_dim == 128 && !p.balanced && p.split_keys >= 700;
     if (p.balanced) return head_dim == 128;
     if (p.split_keys < 128) return false;
     if (head_dim == 64) return p.n_work <= kNumCu || p.n_work > 2 * kNumCu;
@@ -1344,7 +1346,9 @@ static bool attn_has_loaders(const AttnParams& p, int head_dim)
 // 42 rows 15.45 / 14.9, 56 rows 15.65 / 15.2;  10/5 heads, 8 rows 26.9 / 25.3.  It leaves a CU two workgroups instead of three, and it is no gain where
 // the memory is busy anyway:
 //   balanced pieces:  8/4 heads, 48 rows, 5 requests of up to 20000 keys 22.7 / 23.1;  16/8, 40 rows, 8 of up to 3000 16.1 / 16.4;
-//   eight heads in one round:  16/8, 8 rows, 100000 keys 43.9 / 45.7, 40 rows, 30000 keys 18.6 / 18.9 (row groups, which share their keys: 100 rows 23.0 / 22.6);
+//   eight heads in one round whose keys lie side by side for all of them, where the heads' workgroups walk the same pages at once:  16/8 heads, 2 rows, 20012
+//     keys 13.2 / 13.6, 42214 22.4 / 23.1 (a head's keys side by side: 17329 11.7 / 11.3, 37883 18.6 / 17.8, 50652 in 6 splits 56.3 / 47.6;  row groups,
+//     which share their keys, either way: 100 rows 23.0 / 22.6);
 //   short splits in nearly as many workgroups as CUs:  trees of 14/2 heads, 280 rows, 12000 keys (splits of 286) 11.3 / 11.5, 30000 keys 18.4 / 17.8;
 //   more workgroups than CUs:  14/2 heads, 42 rows, 65 requests of 1500 keys 18.7 / 19.6, 8 of 8000 in 32 splits 13.2 / 13.8;  8/4, 48 rows, 65 of 300
 //     9.5 / 10.4.  In several rounds of long splits it wins again: 8/4, 16 rows, 128 of up to 3000 keys 61.0 / 54.3, 64 rows 67.7 / 65.3.
@@ -1352,7 +1356,7 @@ static bool attn_has_deep_ring(const AttnParams& p)
 {
     const bool rounds = p.n_work > 2 * kNumCu;
     if (p.balanced || (p.n_work > kNumCu && !rounds)) return false;
-    if (!rounds && p.n_kv_heads % kNumXcd == 0 && p.n_rgroups == 1) return false;
+    if (!rounds && p.n_kv_heads % kNumXcd == 0 && p.n_rgroups == 1 && p.kv_head < p.kv_tok) return false;
     return 5 * p.n_work <= 4 * kNumCu || p.split_keys >= 640;
 }
 
@@ -1375,8 +1379,10 @@ static int launch_attn_d(const AttnParams& p, int mb, hipStream_t stream)
                 if (p.num_splits > 1 && p.split_keys <= kShortWaves * kChunkKeys && !p.balanced && !loses)
                     return launch_short<D, kShortWaves, 1, D>(p, stream);
             }
-            if (attn_has_loaders(p, D))
+            if (attn_has_loaders(p, D)) {
+                if constexpr (D == 128) return launch_attn<D, 1, 2, 64, 3, 2>(p, stream);
                 return deep ? launch_attn_s<D, 1, 2, 64, DEEP, 2, true>(p, stream) : launch_attn_s<D, 1, 2, 64, 3, 2, true>(p, stream);
+            }
             return launch_attn<D, 1, 4, 128, 2, 0>(p, stream);
         case 2: return deep ? launch_attn<D, 2, 2, 64, DEEP, 4>(p, stream) : launch_attn<D, 2, 2, 64, 3, 4>(p, stream);
         // (two loaders: 16.7 against 17.0 us with four)

@@ -49,6 +49,22 @@ def test_splits_of_one_row_block_of_a_streamed_cache(B, d, hkv, splits, split_ke
     np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
 
 
+# long splits of a cache below the streamed size, which size 128 has loader waves for, and eight heads whose keys lie side by side a head, which has size 64
+# four ring stages for one block of rows and for two
+@pytest.mark.parametrize("q_len,hq,hkv,d,splits,split_keys", [
+    (1, 7, 1, 128, 3, 699), (1, 7, 1, 128, 3, 700), (3, 4, 1, 128, 2, 767), (2, 6, 3, 128, 2, 833), (2, 16, 8, 64, 3, 1400), (1, 16, 16, 64, 2, 1153), (20, 16, 8, 64, 4, 1100)])
+def test_long_splits_of_heads_apart(B, q_len, hq, hkv, d, splits, split_keys):
+    kv_len = splits * split_keys
+    q, k, v = (rnd_bits((n, h, d), 9900 + kv_len + i) for i, (n, h) in enumerate(((q_len, hq), (kv_len, hkv), (kv_len, hkv))))
+    apart = lambda x: dev_bf16(x).transpose(0, 1).contiguous().transpose(0, 1)  # noqa: E731
+    scale = 1.0 / np.sqrt(d)
+    want, want_lse = oracle.decode_attn(q, k, v, scale)
+    out, lse = B.decode_attn(dev_bf16(q), apart(k), apart(v), scale, want_lse=True, num_splits=splits)
+    torch.cuda.synchronize()
+    assert_attn_close(out, want, f"{hkv} heads d{d} splits of {split_keys}")
+    np.testing.assert_allclose(host_f64(lse), want_lse, atol=2e-3, rtol=1e-4)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_balanced_pieces_of_one_row_block(B, d):
     lens, hq, hkv = [3000, 1, 63, 65, 2049, 128], 32, 8

@@ -171,6 +171,7 @@ def test_with_given_normalisers_queries_are_packed_for_more(hq, hkv, d, n_text, 
     (64, 8, 128, 1, 16384, 64, False), (64, 8, 128, 1, 16128, 63, True), (64, 8, 128, 1, 16448, 64, True), (28, 4, 128, 1, 32768, 128, True),
     (64, 8, 128, 65, 256, 0, False), (64, 8, 128, 65, 257, 0, True), (64, 8, 128, 8, 255, 0, False), (64, 8, 128, 8, 256, 0, True),
     (40, 8, 128, 8, 1100, 0, True), (28, 4, 128, 2, 1100, 0, False), (14, 2, 64, 8, 9000, 0, False),
+    (7, 1, 128, 1, 2097, 3, False), (7, 1, 128, 1, 2098, 3, True), (12, 3, 128, 1, 1399, 2, True), (4, 1, 64, 1, 30000, 8, False),
     *((2 * hkv, hkv, d, 1, 164 * splits, splits, True) for d, hkv, splits in one_block.STREAMED)])
 def test_one_row_block_has_loader_waves_where_memory_is_what_it_waits_for(hq, hkv, d, batch, kv_len, splits, loaders, tmp_path):
     more = dict(batch=batch, cu_q=AT, cu_kv=AT) if batch > 1 else {}
@@ -191,6 +192,13 @@ def test_the_ring_of_head_size_64(hq, hkv, batch, q_len, kv_len, splits, stages,
     assert status == 0
     shape = [int(x) for x in got[0][0].split("<")[1].split(",")[:6]]
     assert shape[0] == 64 and shape[2:5] == [2, 64, stages], got
+
+
+@pytest.mark.parametrize("hq,hkv,q_len,kv_len,splits", [(16, 8, 1, 30000, 0), (16, 8, 20, 30000, 0), (16, 16, 4, 50000, 6), (16, 8, 1, 8400, 3)])
+def test_the_ring_of_eight_heads_of_size_64_is_deep_where_a_heads_keys_lie_together(hq, hkv, q_len, kv_len, splits, tmp_path):
+    apart = dict(kv_tok_stride=64, kv_head_stride=64 * kv_len)
+    both = launches([attn(hq, hkv, 64, q_len, kv_len, num_splits=splits, **more) for more in ({}, apart)], tmp_path)
+    assert [got[0][0].split(",")[4].strip() for _, got in both] == ["3", "4"], both
 
 
 @pytest.mark.parametrize("hq,hkv,d,batch,q_len,splits,kernel", [
