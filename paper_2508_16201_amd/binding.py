@@ -120,8 +120,9 @@ def _load_calls():
     else:
         try:
             from . import _calls as native
-            if native.torch_version != torch.__version__.split("+")[0]:     # (it reads torch's objects in place)
-                raise ImportError(f"compiled for torch {native.torch_version}, this is {torch.__version__}")
+            compiled_for = getattr(native, "torch_version", None)             # (an older _calls.so does not say)
+            if compiled_for != torch.__version__.split("+")[0]:             # (it reads torch's objects in place)
+                raise ImportError(f"compiled for torch {compiled_for}, this is {torch.__version__}")
             native.connect(version(), {name: C.cast(getattr(lib(), name), C.c_void_p).value for name in native.functions})
             _calls = native
         except ImportError as e:

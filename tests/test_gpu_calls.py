@@ -283,7 +283,9 @@ def test_the_native_code_is_of_the_library_and_the_torch_it_is_used_with(monkeyp
     with pytest.raises(KeyError, match=native.functions[-1]):
         native.connect(B.version(), {name: 1 for name in native.functions[:-1]})
     later = B.version() + 1
-    for where, name, what in ((B, "version", lambda: later), (torch, "__version__", "1.0.0+other")):
+    class Older:                                               # (what was compiled before it said what for)
+        connect = native.connect
+    for where, name, what in ((B, "version", lambda: later), (torch, "__version__", "1.0.0+other"), (package, "_calls", Older)):
         with monkeypatch.context() as m:
             m.setattr(where, name, what)
             m.setattr(B, "_calls", None)
